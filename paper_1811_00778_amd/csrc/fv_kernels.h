@@ -5,6 +5,7 @@
 // unit-stride across the lanes of a wavefront.
 #pragma once
 #include "modarith.h"
+#include "ntt_kernels.h"
 
 namespace hcnn {
 
@@ -212,11 +213,7 @@ struct ExtKernelT {
       if constexpr (bconv_use_mont(K, 0)) {
 #pragma unroll
         for (int i = 0; i < K; ++i) acc += (uint64_t)z[i] * ldc(bt, i);
-        // The forward transform that reads these rows takes any value below 4p.  A sum of K products leaves the
-        // Montgomery step below K*2^28 + p; for K <= 9 one conditional subtraction of 2p brings that under
-        // max(2p, 9*2^28 - p) < 4p for every p > 2^29.
-        if constexpr (K <= 9) dst[(size_t)(K + j) * n] = csub(mont_step(acc, dm.p, ldc(a.bc.dst_pinv, j)), 2 * dm.p);
-        else                  dst[(size_t)(K + j) * n] = mont_reduce(acc, dm, ldc(a.bc.dst_pinv, j));
+        dst[(size_t)(K + j) * n] = mont_reduce(acc, dm, ldc(a.bc.dst_pinv, j));
       } else {
 #pragma unroll
         for (int i = 0; i < K; ++i) {
@@ -386,7 +383,7 @@ struct RelinMacArgs {
   const uint32_t* dig;   // [n_ct][k][k][n]
   const uint32_t* evk;   // [k][2][k][n]
   uint32_t* acc;         // [n_ct][2][k][n]
-  const Mod* mods;
+  const NttLimb* limbs;
   uint32_t k, n;
   uint32_t n_grp;        // groups of CT ciphertexts in this launch
   uint32_t ct_base;      // first ciphertext of the launch
@@ -396,6 +393,7 @@ struct RelinMacArgs {
 // is loaded once and multiplied with the digits of all CT ciphertexts from registers.  (The key is read from
 // L2; with one ciphertext per workgroup it makes up two thirds of what flows from L2 into the compute units,
 // and that flow, not HBM, then bounds the kernel.)
+HCNN_HD int64_t mul_s32(uint32_t a, uint32_t b) { return (int64_t)(int32_t)a * (int32_t)b; }
 template <int CT>
 struct RelinMacKernel {
   static constexpr int kThreads = kEwThreads;
@@ -423,16 +421,22 @@ struct RelinMacKernel {
     }
     const size_t ct0 = a.ct_base + grp * CT;
     const uint32_t c = (tile * kThreads + tid) * kEwVec;
-    const Mod m = ldc(a.mods, j);
+    const NttLimb L = ldc(a.limbs, j);
     const size_t rn = a.n;
-    uint64_t s0[CT][4], s1[CT][4];
+    // signed digits in [-p, p), centred key values: 16 products stay below 8 p^2 < 2^63, 13 after a fold (whose
+    // result takes the room of two); inside a run the loop is unrolled so that the loads of several digits are in
+    // flight together
+    int64_t s0[CT][4], s1[CT][4];
 #pragma unroll
     for (int t = 0; t < CT; ++t)
       for (int q = 0; q < 4; ++q) { s0[t][q] = 0; s1[t][q] = 0; }
-    // 15 products below 2^60 (+ a residue) fit 64 bits; inside a run of 15 the loop is unrolled so that the
-    // loads of several digits are in flight together
-    for (uint32_t i0 = 0; i0 < a.k; i0 += 15) {
-      const uint32_t i1 = i0 + 15 < a.k ? i0 + 15 : a.k;
+    for (uint32_t i0 = 0, run = 16; i0 < a.k; i0 += run, run = 13) {
+      if (i0 > 0) {
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+          for (int q = 0; q < 4; ++q) { s0[t][q] = sfold(s0[t][q], L.rc); s1[t][q] = sfold(s1[t][q], L.rc); }
+      }
+      const uint32_t i1 = i0 + run < a.k ? i0 + run : a.k;
 #pragma unroll 2
       for (uint32_t i = i0; i < i1; ++i) {
         const U4 e0 = *reinterpret_cast<const U4*>(a.evk + (((size_t)i * 2 + 0) * a.k + j) * rn + c);
@@ -443,23 +447,20 @@ struct RelinMacKernel {
           d[t] = *reinterpret_cast<const U4*>(a.dig + (((ct0 + t) * a.k + i) * a.k + j) * rn + c);
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
-          s0[t][0] += (uint64_t)d[t].x * e0.x; s0[t][1] += (uint64_t)d[t].y * e0.y;
-          s0[t][2] += (uint64_t)d[t].z * e0.z; s0[t][3] += (uint64_t)d[t].w * e0.w;
-          s1[t][0] += (uint64_t)d[t].x * e1.x; s1[t][1] += (uint64_t)d[t].y * e1.y;
-          s1[t][2] += (uint64_t)d[t].z * e1.z; s1[t][3] += (uint64_t)d[t].w * e1.w;
+          s0[t][0] += mul_s32(d[t].x, e0.x); s0[t][1] += mul_s32(d[t].y, e0.y);
+          s0[t][2] += mul_s32(d[t].z, e0.z); s0[t][3] += mul_s32(d[t].w, e0.w);
+          s1[t][0] += mul_s32(d[t].x, e1.x); s1[t][1] += mul_s32(d[t].y, e1.y);
+          s1[t][2] += mul_s32(d[t].z, e1.z); s1[t][3] += mul_s32(d[t].w, e1.w);
         }
       }
-      if (i1 < a.k) {
-#pragma unroll
-        for (int t = 0; t < CT; ++t)
-          for (int q = 0; q < 4; ++q) { s0[t][q] = reduce64(s0[t][q], m); s1[t][q] = reduce64(s1[t][q], m); }
-      }
     }
+    // (the sums are left signed in (-p, p): the inverse transform that reads them takes them as they are)
+    auto out = [&](int64_t s) { return (uint32_t)sredc(sfold(s, L.rc), L.m.p, L.pinv); };
 #pragma unroll
     for (int t = 0; t < CT; ++t) {
       U4 r0, r1;
-      r0.x = reduce64(s0[t][0], m); r0.y = reduce64(s0[t][1], m); r0.z = reduce64(s0[t][2], m); r0.w = reduce64(s0[t][3], m);
-      r1.x = reduce64(s1[t][0], m); r1.y = reduce64(s1[t][1], m); r1.z = reduce64(s1[t][2], m); r1.w = reduce64(s1[t][3], m);
+      r0.x = out(s0[t][0]); r0.y = out(s0[t][1]); r0.z = out(s0[t][2]); r0.w = out(s0[t][3]);
+      r1.x = out(s1[t][0]); r1.y = out(s1[t][1]); r1.z = out(s1[t][2]); r1.w = out(s1[t][3]);
       *reinterpret_cast<U4*>(a.acc + (((ct0 + t) * 2 + 0) * a.k + j) * rn + c) = r0;
       *reinterpret_cast<U4*>(a.acc + (((ct0 + t) * 2 + 1) * a.k + j) * rn + c) = r1;
     }

@@ -273,8 +273,7 @@ struct hcnn_ctx {
 
   Mod* d_mods = nullptr;            // [k + kp]
   NttLimb* d_limbs = nullptr;       // [k + kp]
-  ShoupConst* d_tw_fwd = nullptr;   // [k + kp][n]
-  ShoupConst* d_tw_inv = nullptr;
+  TwTable d_tw_fwd{}, d_tw_inv{};   // [k + kp][n/2]
   ShoupConst* d_delta = nullptr;    // [k] floor(q/t) mod q_l
   uint32_t* d_tq_inv = nullptr;     // [kp] t * q^-1 mod p_j
   BConvDev ext{}, to_p{}, to_q{}, dec{};
@@ -464,42 +463,63 @@ int build_tables(hcnn_ctx* c) {
 
   std::vector<Mod> mods;
   std::vector<NttLimb> limbs;
-  std::vector<ShoupConst> twf((size_t)L * n), twi((size_t)L * n);
+  // radix-4 butterflies sit at the stages s, s + 1 with s = log2(n) mod 2; their constants carry 2^32 and are centred
+  const uint32_t odd = c->logn & 1u;
+  std::vector<R4Twiddle> quad[2];
+  std::vector<int32_t> nuw[2];
+  for (int d = 0; d < 2; ++d) {
+    quad[d].assign((size_t)L * (n / 2), R4Twiddle{0, 0, 0, 0});
+    nuw[d].assign((size_t)L * (n / 2), 0);
+  }
   std::vector<uint32_t> pw(2 * (size_t)n);
   for (uint32_t l = 0; l < L; ++l) {
     const uint32_t p = all[l];
     const uint32_t psi = h_root_of_unity(n, p);
     uint64_t v = 1;
     for (uint32_t e = 0; e < 2 * n; ++e) { pw[e] = (uint32_t)v; v = v * psi % p; }
-    twf[(size_t)l * n] = h_shoup(0, p);
-    twi[(size_t)l * n] = h_shoup(0, p);
-    for (uint32_t node = 1; node < n; ++node) {
+    const uint32_t r32 = (uint32_t)((1ull << 32) % p);
+    auto centred = [&](uint32_t x) { return x > p / 2 ? (int32_t)x - (int32_t)p : (int32_t)x; };
+    auto mont = [&](uint32_t x) { return centred(h_mulmod(x, r32, p)); };
+    // twiddle of a node: psi^brev(node) forward, its inverse backward
+    auto tw = [&](int dir, uint32_t node) {
       const uint32_t e = h_brev(node, (int)c->logn);
-      twf[(size_t)l * n + node] = h_shoup(pw[e], p);
-      // the forward butterflies use the twiddle negated modulo 2^32 (their product is kept negated)
-      twf[(size_t)l * n + node].w = 0u - twf[(size_t)l * n + node].w;
-      twi[(size_t)l * n + node] = h_shoup(pw[2 * n - e], p);
-    }
-    NttLimb nl;
+      return pw[dir ? 2 * n - e : e];
+    };
+    for (int d = 0; d < 2; ++d)
+      for (uint32_t s = odd; s + 2 <= c->logn; s += 2)
+        for (uint32_t node = 1u << s; node < 2u << s; ++node) {
+          const uint32_t w = tw(d, node), tv = tw(d, 2 * node), u = tw(d, 2 * node + 1);
+          quad[d][(size_t)l * (n / 2) + node] = R4Twiddle{mont(w), mont(tv), mont(h_mulmod(tv, w, p)), mont(u)};
+          nuw[d][(size_t)l * (n / 2) + node] = mont(p - h_mulmod(u, w, p));
+        }
+    NttLimb nl{};
     nl.m = h_mod(p);
-    const uint32_t ninv = h_inv(n % p, p);
-    nl.ninv = h_shoup(ninv, p);
-    nl.w1ninv = h_shoup(h_mulmod(twi[(size_t)l * n + 1].w, ninv, p), p);
-    const uint32_t ninv_r = h_mulmod(ninv, nl.m.c32, p);                     // c32 = 2^32 mod p
-    nl.ninv_r = h_shoup(ninv_r, p);
-    nl.w1ninv_r = h_shoup(h_mulmod(twi[(size_t)l * n + 1].w, ninv_r, p), p);
+    nl.rc = centred(r32);
     nl.pinv = h_neg_inv32(p);
-    nl.pneg = 0u - p;
     nl.zero = 0;
-    nl.pad = 0;
+    nl.w1 = mont(tw(0, 1));
+    nl.key_scale = mont(r32);
+    auto inv_root = [&](uint32_t scale) {
+      auto sc = [&](uint32_t x) { return mont(h_mulmod(x, scale, p)); };
+      const uint32_t w = tw(1, 1), v2 = tw(1, 2), u2 = tw(1, 3);
+      return InvRoot{mont(scale), sc(w), sc(v2), sc(u2), sc(h_mulmod(v2, w, p)), sc(p - h_mulmod(u2, w, p))};
+    };
+    const uint32_t ninv = h_inv(n % p, p);
+    nl.inv = inv_root(ninv);
+    nl.inv_r = inv_root(h_mulmod(ninv, r32, p));
     mods.push_back(nl.m);
     limbs.push_back(nl);
   }
   int e;
   if ((e = upload(c, mods, &c->d_mods))) return e;
   if ((e = upload(c, limbs, &c->d_limbs))) return e;
-  if ((e = upload(c, twf, &c->d_tw_fwd))) return e;
-  if ((e = upload(c, twi, &c->d_tw_inv))) return e;
+  R4Twiddle* dq;
+  int32_t* dn;
+  for (int d = 0; d < 2; ++d) {
+    if ((e = upload(c, quad[d], &dq))) return e;
+    if ((e = upload(c, nuw[d], &dn))) return e;
+    (d ? c->d_tw_inv : c->d_tw_fwd) = TwTable{dq, dn};
+  }
 
   // floor(q/t) mod q_l = -(q mod t) * t^-1 mod q_l   (q = 0 mod q_l)
   const uint64_t q_mod_t = h_prod_mod64(c->q, -1, c->t);
@@ -584,7 +604,7 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   a.in = r.in; a.out = r.out; a.aux = r.aux;
   a.tw = inverse ? c->d_tw_inv : c->d_tw_fwd;
   a.limbs = c->d_limbs;
-  a.limb_cycle = r.cycle; a.limb_base = r.limb_base;
+  a.cycle = fast_div(r.cycle); a.limb_base = r.limb_base;
   a.in_group_rows = r.in_group_rows; a.in_row0 = r.in_row0;
   a.out_group_rows = r.out_group_rows; a.out_row0 = r.out_row0;
   a.n_rows = (uint32_t)r.rows;
@@ -611,6 +631,10 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
         using K = NttFwd<LOGN, LOGR, kNttStoreLazy, 1>;
         return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
       }
+      if (io == kNttStoreKey) {
+        using K = NttFwd<LOGN, LOGR, kNttStoreKey, 1>;
+        return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
+      }
       using K = NttFwd<LOGN, LOGR, kNttPlain, 1>;
       return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
     }
@@ -618,6 +642,7 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   if (io == kNttLoadDigit)
     return run<NttFwd<LOGN, LOGR, kNttLoadDigit>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
   if (io == kNttStoreLazy) return run<NttFwd<LOGN, LOGR, kNttStoreLazy>>(c, r.rows, lds, a);
+  if (io == kNttStoreKey) return run<NttFwd<LOGN, LOGR, kNttStoreKey>>(c, r.rows, lds, a);
   return run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a);
 }
 
@@ -626,9 +651,10 @@ int ntt_rows(hcnn_ctx* c, const NttRows& r, bool inverse, int io = kNttPlain) {
     case 10: return ntt_launch<10, 4>(c, r, inverse, io);
     case 11: return ntt_launch<11, 4>(c, r, inverse, io);
     case 12: return ntt_launch<12, 4>(c, r, inverse, io);
-    case 13: return ntt_launch<13, 5>(c, r, inverse, io);
-    // n = 2^14: 16 residues per thread (1024 threads, four passes) give twice the waves per compute unit of the
-    // 32-residue shape, whose 66 KiB of LDS per row allow only two workgroups; measured 8-10 % faster per row
+    // 16 residues per thread wherever 1024 threads hold the row: twice the waves of the 32-residue shapes (at n = 8192,
+    // 1024 rows: forward 20.4 us with 32 residues and passes 5 + 4 + 2 + 2, 18.6 with 16 and 3 + 4 + 4 + 2; inverse
+    // 20.4 and 16.8; n = 16384 8-10 % faster per row)
+    case 13: return ntt_launch<13, 4>(c, r, inverse, io);
     case 14: return ntt_launch<14, 4>(c, r, inverse, io);
     case 15: return ntt_launch<15, 5>(c, r, inverse, io);
   }
@@ -722,7 +748,7 @@ int query_fused_occupancy(hcnn_ctx* c) {
     case 10: HCNN_OCC(10, 4) break;
     case 11: HCNN_OCC(11, 4) break;
     case 12: HCNN_OCC(12, 4) break;
-    case 13: HCNN_OCC(13, 5) break;
+    case 13: HCNN_OCC(13, 4) break;
     case 14: HCNN_OCC(14, 4) break;
   }
 #undef HCNN_OCC
@@ -873,7 +899,7 @@ int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
     if (e) return e;
     c->d_evk_hat = (uint32_t*)ptr;
   }
-  int e = ntt_dense(c, evk_dev, c->d_evk_hat, rows, c->k, false);
+  int e = ntt_dense(c, evk_dev, c->d_evk_hat, rows, c->k, false, kNttStoreKey);
   if (e) return e;
   c->has_key = true;
   return HCNN_OK;
@@ -1004,11 +1030,13 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     }
     return nf;
   };
-  // Steps 2+3 in one kernel for squarings: its workgroups are long (five transforms) and two fit a compute unit at
-  // n = 8192 (one at n = 16384), so it pays from several rounds of workgroups on (measured: +3-5 % from 6 rounds,
-  // nothing below).
+  // Steps 2+3 in one kernel for squarings: its workgroups are long (five transforms), so it pays when they fill their
+  // rounds.  Measured at n = 8192, k = 8: 1.06 us per ciphertext in full rounds against 1.25 of the two separate kernels
+  // (64 to 512 ciphertexts), a ratio of 0.85.
   auto takes_tensor_fused = [&](size_t cc) {
-    return !in_b && c->logn <= 14 && c->fusion != 1 && (c->fusion == 2 || cc * L >= 6 * tensor_fused_slots(c));
+    if (in_b || c->logn > 14 || c->fusion == 1) return false;
+    const size_t slots = tensor_fused_slots(c), rounds = (cc * L + slots - 1) / slots;
+    return c->fusion == 2 || cc * L * 8 >= rounds * slots * 7;
   };
 
   // One internal batch: ciphertexts [c0, c0 + cc) of the call, kept in slots [s0, s0 + cc) of the work arrays, nf of
@@ -1032,14 +1060,12 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     if ((e = ext_dispatch(c, cc * 2 * bpp, ea))) return e;
     const bool tensor_fused = takes_tensor_fused(cc);
     if (tensor_fused) {
-      TensorFusedArgs ta{in + c0 * ct_words, b_ext, b_d, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, L, (uint32_t)(cc * L)};
+      TensorFusedArgs ta{in + c0 * ct_words, b_ext, b_d, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, L, (uint32_t)(cc * L), fast_div(L)};
       const size_t rows = cc * L * 5;
       switch (c->logn) {
         case 10: e = run<TensorFused<10, 4>>(c, cc * L, NttGeom<10, 4>::kLdsBytes, ta, rows); break;
         case 11: e = run<TensorFused<11, 4>>(c, cc * L, NttGeom<11, 4>::kLdsBytes, ta, rows); break;
         case 12: e = run<TensorFused<12, 4>>(c, cc * L, NttGeom<12, 4>::kLdsBytes, ta, rows); break;
-        // 16 residues per thread also at n = 8192: with the two transformed operands (2 x 16 registers) the kernel
-        // needs 120 registers; at 32 residues per thread it spills
         case 13: e = run<TensorFused<13, 4>>(c, cc * L, NttGeom<13, 4>::kLdsBytes, ta, rows); break;
         case 14: e = run<TensorFused<14, 4>>(c, cc * L, NttGeom<14, 4>::kLdsBytes, ta, rows); break;
         default: e = HCNN_ERR_N; break;
@@ -1067,7 +1093,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     if ((e = scale_dispatch(c, cc * 3 * bpp, sa))) return e;
     // 6-8 in one kernel
     if (nf) {
-      RelinFusedArgs fa{b_y, c->d_evk_hat, out + c0 * ct_words, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, (uint32_t)(nf * k)};
+      RelinFusedArgs fa{b_y, c->d_evk_hat, out + c0 * ct_words, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, (uint32_t)(nf * k), fast_div(k)};
       const size_t grid = ntt_grouped_grid(nf * k, k), rows = nf * k * (k + 2);
 #define HCNN_FUSED(LOGN, LOGR)                                                                                      \
   (k <= 8 ? run<RelinFused<LOGN, LOGR, kNttFusedMac>>(c, grid, NttGeom<LOGN, LOGR>::kLdsBytes, fa, rows)             \
@@ -1077,10 +1103,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
         case 10: e = HCNN_FUSED(10, 4); break;
         case 11: e = HCNN_FUSED(11, 4); break;
         case 12: e = HCNN_FUSED(12, 4); break;
-        // n = 8192: 32 residues per thread (three passes, 8 waves per compute unit) when the launch holds several
-        // rounds of workgroups; a single round runs 5 % shorter at 16 residues per thread (four passes, 16 waves per
-        // compute unit hide more of what no other round overlaps).  Both forms hold two workgroups per compute unit.
-        case 13: e = nf > std::max<size_t>(fused_round, 1) ? HCNN_FUSED(13, 5) : HCNN_FUSED(13, 4); break;
+        case 13: e = HCNN_FUSED(13, 4); break;
         case 14: e = HCNN_FUSED(14, 4); break;
         default: e = HCNN_ERR_N; break;
       }
@@ -1095,7 +1118,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     if ((e = ntt_dense(c, y_s, b_dig, ns * k * k, k, false, kNttLoadDigit))) return e;
     // 7. inner product with the evaluation key
     RelinMacArgs ra;
-    ra.dig = b_dig; ra.evk = c->d_evk_hat; ra.acc = b_acc; ra.mods = c->d_mods; ra.k = k; ra.n = n;
+    ra.dig = b_dig; ra.evk = c->d_evk_hat; ra.acc = b_acc; ra.limbs = c->d_limbs; ra.k = k; ra.n = n;
     // in the plain (ciphertext-major) order every die touches the key tiles of all limbs: 2*k*k*(tiles/8) * 4 KiB
     ra.key_major = (bpr % kXcds == 0 && (size_t)2 * k * k * (bpr / kXcds) * 4096 > ((size_t)1 << 20)) ? 1u : 0u;
     if (c->relin_order == 1) ra.key_major = 0;

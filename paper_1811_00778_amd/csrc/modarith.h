@@ -51,19 +51,30 @@ HCNN_HD uint32_t reduce64(uint64_t x, const Mod& m) {
   return csub(s, m.p);
 }
 
-// x mod p up to one extra p: result in [0, 2p) for any x < 2^64.
-HCNN_HD uint32_t reduce64_2p(uint64_t x, const Mod& m) {
-  uint32_t hi = (uint32_t)(x >> 32), lo = (uint32_t)x;
-  uint32_t y = shoup_lazy(hi, m.c32, m.c32s, m.p);
-  uint32_t qb = mulhi32(lo, m.mu) >> 29;
-  return csub(y + (lo - qb * m.p), 2 * m.p);
+// Signed Montgomery reduction: x * 2^-32 mod p with |result| <= |x| / 2^32 + p/2, for |x| < 2^63 - 2^61.
+// pinv = -p^-1 mod 2^32.
+HCNN_HD int32_t sredc(int64_t x, uint32_t p, uint32_t pinv) {
+  const int32_t mm = (int32_t)((uint32_t)x * pinv);                 // x + mm*p = 0 mod 2^32
+  return (int32_t)((x + (int64_t)mm * (int32_t)p) >> 32);
 }
-
-// Montgomery reduction: x * 2^-32 mod p up to one extra p, for x < p * 2^32 (in particular for the
-// product of two values below 2p).  pinv = -p^-1 mod 2^32; result in [0, 2p).
-HCNN_HD uint32_t redc_2p(uint64_t x, uint32_t p, uint32_t pinv) {
-  const uint32_t mm = (uint32_t)x * pinv;              // x + mm*p = 0 mod 2^32
-  return (uint32_t)((x + (uint64_t)mm * p) >> 32);     // below 2^62 + 2^62: no overflow
+// A value congruent to x mod p of magnitude at most 2^60 + 2^32, for any signed 64-bit x (rc: 2^32 mod p, centred).
+HCNN_HD int64_t sfold(int64_t x, int32_t rc) {
+  return (int64_t)(int32_t)(x >> 32) * rc + (int64_t)(uint64_t)(uint32_t)x;
+}
+// x in [-2p, 2p) -> [-p, p)
+HCNN_HD int32_t half_range(int32_t x, uint32_t p) {
+  const uint32_t a = (uint32_t)x, b = a + 2 * p;
+  return (int32_t)((a < b ? a : b) - p);
+}
+// x in [-2p, 2p) -> [0, p)
+HCNN_HD uint32_t canon_2p(int32_t x, uint32_t p) {
+  const uint32_t a = (uint32_t)x, b = a + 2 * p, u = a < b ? a : b;
+  return csub(u, p);
+}
+// x in [-p, p) -> [0, p)
+HCNN_HD uint32_t canon_p(int32_t x, uint32_t p) {
+  const uint32_t a = (uint32_t)x, b = a + p;
+  return a < b ? a : b;
 }
 
 // x mod p for x < 2^32, canonical.

@@ -7,54 +7,76 @@
 //
 // The log2(n) stages are cut into passes of at most LOGR stages.  In a pass every
 // thread keeps R = 2^LOGR residues in registers and runs complete radix-2^NS
-// butterfly networks on them; between passes the row lives in LDS (one barrier per
-// pass).  The first pass reads HBM with unit stride across lanes, the last pass
-// writes HBM.  Residues stay lazily reduced (forward: [0,4p), inverse: [0,2p)) and
-// are made canonical only on the way out.
+// networks on them; between passes the row lives in LDS (one barrier per pass).
+// The first pass reads HBM with unit stride across lanes, the last pass writes HBM.
 //
-// Twiddle table layout: tw[limb][node], node in [1, n): the butterflies of the stage
-// with m groups use nodes m .. 2m-1 (node m+i = psi^brev_{log n}(m+i)); a radix-2^NS
-// network rooted at node r uses the sub-tree r, 2r, 2r+1, 4r, ...
+// Residues are SIGNED inside a transform and the stages are taken two at a time, as one
+// radix-4 butterfly whose products are summed in 64 bits before a shared Montgomery
+// reduction (sredc).  What bounds these kernels is VALU issue, and on this device a
+// multiplication, a 64-bit multiply-add, v_min_u32 and v_add3_u32 all issue at 34-36 T
+// lane-instructions/s, a plain 32-bit addition or subtraction at 57-61 T.  Counted in
+// multiplications, four residues through two stages cost 17 (7 multiply-adds, 4 reductions
+// of 2, 4 additions at one half) against 24 of four lazy Shoup butterflies (each 3 for the
+// product, 1.5 for the conditional subtraction, 1.5 for sum and difference).  There is no
+// conditional subtraction: with |x| < 2^31 on entry every output of a forward radix-4
+// butterfly lies in (-2p, 2p), and with |x| <= p on entry every output of an inverse one
+// lies in (-p, p), whatever the number of stages (see r4_fwd, r4_inv).  An odd log2(n) adds
+// one radix-2 stage at the root of the tree: first in the forward transform, where the
+// inputs are still small enough to need no reduction, last in the inverse.
+//
+// Twiddle tables: the radix-4 butterfly rooted at node m+i of the stage with m groups
+// (node m+i = psi^brev_{log n}(m+i)) needs five constants, all centred and carrying the
+// factor 2^32 of the reduction: W = tw[node], V = tw[2 node], V*W, U = tw[2 node + 1] (one
+// 16-byte word) and -U*W.  A network rooted at node r uses the sub-tree r, 4r.., 16r.., ...
 #pragma once
 #include "modarith.h"
 
 namespace hcnn {
 
-struct NttLimb {
-  Mod m;
-  ShoupConst ninv;    // n^-1 mod p
-  ShoupConst w1ninv;  // (inverse twiddle of node 1) * n^-1 mod p
-  // the tensor-forming loads multiply with a Montgomery reduction, which leaves a factor 2^-32 on every
-  // product; their transforms scale by n^-1 * 2^32 at the end instead of n^-1
-  ShoupConst ninv_r;    // n^-1 * 2^32 mod p
-  ShoupConst w1ninv_r;  // (inverse twiddle of node 1) * n^-1 * 2^32 mod p
-  uint32_t pinv;        // -p^-1 mod 2^32
-  uint32_t pneg;        // -p mod 2^32.  The compiler folds a 32-bit product into a following addition (one multiply-add)
-                        // but not into a subtraction: written x*w + q*pneg, the lazy product x*w - q*p is a
-                        // multiplication and a multiply-add.  The word has to come from memory for that: a negation
-                        // the compiler can see is turned back into the subtraction.
-  uint32_t zero;        // 0, unknown to the compiler: zero - w is the negated twiddle and stays one (see the inverse butterfly)
-  uint32_t pad;
+struct alignas(16) R4Twiddle {
+  int32_t w, v, vw, u;
+};
+struct TwTable {
+  const R4Twiddle* quad;    // [L][n/2], index = node
+  const int32_t* nuw;       // [L][n/2], -u*w
+};
+// Constants of the outermost butterfly of an inverse transform (node 1), with the output scaling folded in:
+// odd log2(n): c0 = scale, w = tw^-1 * scale; even: all six of a radix-4 butterfly
+struct InvRoot {
+  int32_t c0, w, v, u, vw, nuw;
 };
 
-// Row r (= workgroup index) belongs to group r / limb_cycle and limb limb_base + r % limb_cycle.
-// Its data sits at row (group * group_rows + row0 + r % limb_cycle) of the in / out arrays, so a
+struct NttLimb {
+  Mod m;
+  int32_t rc;           // 2^32 mod p, centred: 1 in the form of the twiddles
+  uint32_t pinv;        // -p^-1 mod 2^32
+  int32_t zero;         // 0, unknown to the compiler: zero - w is a negated constant and stays one (it would turn a visible
+                        // negation into a product and a 64-bit subtraction)
+  int32_t w1;           // forward twiddle of node 1 (the radix-2 stage of an odd log2(n))
+  int32_t key_scale;    // 2^64 mod p, centred: sredc(x * key_scale) = x * 2^32
+  InvRoot inv;          // scale = n^-1
+  InvRoot inv_r;        // scale = n^-1 * 2^32: the tensor-forming loads leave a factor 2^-32 on every product
+};
+
+// Row r (= workgroup index) belongs to group r / cycle and limb limb_base + r % cycle.
+// Its data sits at row (group * group_rows + row0 + r % cycle) of the in / out arrays, so a
 // launch can pick one polynomial out of every ciphertext of a batch.
 // Fused input / output stages (template parameter IO of the kernels):
 //   kNttPlain       rows are read and written as they are
 //   kNttLoadDigit   forward only: row (ct, i, j) reads digit i of y2, i.e. row (ct*3+2)*k + i of `in`
 //                   = y[n_ct][3][k][n], taken as it is (every prime lies in (2^29, 2^30), so a digit is below
-//                   2*q_j, which the lazy butterflies accept); output rows dense [ct][i][j]
+//                   2*q_j); output rows dense [ct][i][j], left signed in [-p, p)
 //   kNttLoadTensor  inverse only: row (ct, b, l) reads c0^ = in[(ct*2)*L + l], c1^ = in[(ct*2+1)*L + l]
 //                   and transforms c0^*c0^, 2*c0^*c1^ or c1^*c1^ for b = 0, 1, 2 (HMult step 1, c = c')
 //   kNttLoadTensorMul  inverse only: the general tensor of HMult step 1 for two different operands;
 //                   `in` holds the first, `aux` the second (same [ct][2][L][n] layout):
 //                   c0^*c0'^, c0^*c1'^ + c1^*c0'^, c1^*c1'^
 //   kNttStoreAdd    inverse only: row (ct, b, j) adds aux row (ct*3+b)*k + j (aux = y) on the way out
-//   kNttStoreLazy   forward only: the output is left lazily reduced in [0, 2p) (for rows whose only reader is
-//                   the tensor-forming load: products of two such values are below p * 2^32, the range of
-//                   its Montgomery reduction)
-// The tensor-forming loads also leave their output lazily reduced, in [0, 2p): its only reader multiplies it
+//   kNttStoreLazy   forward only: the output is left signed, in [-p, p) (for rows whose only reader is the
+//                   tensor-forming load)
+//   kNttStoreKey    forward only: the output is multiplied by 2^32 and centred (evaluation-key rows: the sums of their
+//                   products with the digits go through one Montgomery reduction, and |key| <= p/2 leaves room for more)
+// The tensor-forming loads leave their output lazily reduced, in [0, 2p): its only reader multiplies it
 // by a constant with Shoup's method, which takes any 32-bit operand.
 //   kNttFusedMac    forward only, inside RelinFused: workgroup (ct, j) transforms digit `iter` of y2 modulo q_j
 //                   (loaded like kNttLoadDigit) and, instead of storing, adds its products with the two key
@@ -65,14 +87,15 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              kNttStoreLazy = 5, kNttFusedMac = 6, kNttFromRegs0 = 7, kNttFromRegs1 = 8,
              kNttFusedMac16 = 9, kNttFusedMacAny = 10,     // the fused inner product for k <= 8, k <= 16, any k
              kNttToRegs0 = 11, kNttToRegs1 = 12,           // forward, inside TensorFused: c0 / c1 of workgroup (ct, limb); the
-                                                           // transformed row stays in registers, lazily reduced in [0, 2p)
-             kNttTensorRegs0 = 13, kNttTensorRegs1 = 14, kNttTensorRegs2 = 15 };   // inverse, inside TensorFused: component
+                                                           // transformed row stays in registers, signed in [-p, p)
+             kNttTensorRegs0 = 13, kNttTensorRegs1 = 14, kNttTensorRegs2 = 15,
+             kNttStoreKey = 16 };   // inverse, inside TensorFused: component
                                                            // b of the tensor formed from those registers (as kNttLoadTensor)
 
 // Per-thread state of TensorFused: the two transformed polynomials of the ciphertext, one limb.
 template <int R>
 struct TensorRegs {
-  uint32_t c0[R], c1[R];
+  int32_t c0[R], c1[R];
 };
 
 // Per-thread state of RelinFused: the iteration (digit) and the two inner-product sums of every residue the
@@ -80,7 +103,7 @@ struct TensorRegs {
 template <int R>
 struct RelinRegs {
   uint32_t iter;
-  uint64_t s0[R], s1[R];
+  int64_t s0[R], s1[R];
 };
 struct NoRegs {};
 
@@ -88,9 +111,9 @@ struct NttArgs {
   const uint32_t* in;
   uint32_t* out;            // may equal `in`
   const uint32_t* aux;      // kNttStoreAdd: the addend; kNttLoadTensorMul: the second operand
-  const ShoupConst* tw;     // [L][n] node table (forward: {-w mod 2^32, w'}; inverse: {w, w'})
+  TwTable tw;
   const NttLimb* limbs;     // [L]
-  uint32_t limb_cycle;
+  FastDiv cycle;            // limbs per group of rows
   uint32_t limb_base;
   uint32_t in_group_rows, in_row0;
   uint32_t out_group_rows, out_row0;
@@ -106,17 +129,24 @@ struct NttArgs {
 // Rows are numbered unit*share + within for the digit load (within = j) and the caller converts
 // for the tensor load.  Returns n_rows or more for the padding workgroups of the last round.
 constexpr uint32_t kNttXcds = 8;
-HCNN_HD uint32_t ntt_grouped_index(uint32_t bid, uint32_t share) {
-  const uint32_t xcd = bid % kNttXcds, local = bid / kNttXcds;
-  return ((local / share) * kNttXcds + xcd) * share + local % share;
+HCNN_HD uint32_t ntt_grouped_index(uint32_t bid, FastDiv share) {
+  const uint32_t xcd = bid % kNttXcds, local = bid / kNttXcds, q = quot(local, share);
+  return (q * kNttXcds + xcd) * share.d + (local - q * share.d);
 }
 inline size_t ntt_grouped_grid(size_t rows, size_t share) {
   const size_t units = rows / share;
   return (units + kNttXcds - 1) / kNttXcds * kNttXcds * share;
 }
 
-HCNN_HD size_t ntt_row(uint32_t r, uint32_t cycle, uint32_t group_rows, uint32_t row0) {
-  return (size_t)(r / cycle) * group_rows + row0 + r % cycle;
+// NET consecutive words of a row from word `first`, 16 bytes at a time (rows and networks are 16-byte aligned)
+template <int NET>
+HCNN_HD void load_row(int32_t (&v)[NET], const uint32_t* src, uint32_t first) {
+  static_assert(NET % 4 == 0, "whole 16-byte words");
+#pragma unroll
+  for (int e = 0; e < NET; e += 4) {
+    const U4 t = ld4_at(src, (first + (uint32_t)e) * 4);
+    v[e] = (int32_t)t.x; v[e + 1] = (int32_t)t.y; v[e + 2] = (int32_t)t.z; v[e + 3] = (int32_t)t.w;
+  }
 }
 
 // LDS layout: one unused word after every 32, which spreads the power-of-two strides of the passes
@@ -129,27 +159,12 @@ HCNN_HD constexpr uint32_t lds_elem(uint32_t sbase, int e) {
   return sbase + lds_swz((uint32_t)e << LOG_TLAST);
 }
 
+// Stages per pass of every ring and thread shape.  The first pass takes the odd stage of an odd log2(n); every other
+// pass is a whole number of radix-4 levels.  The last forward pass (the first inverse one) has every thread store (load)
+// 2^ns consecutive residues: two stages there make it one 16-byte word per lane, so that the lanes of a wave touch
+// consecutive words.
 template <int LOGN, int LOGR>
-struct NttGeom {
-  static constexpr int N = 1 << LOGN;
-  static constexpr int R = 1 << LOGR;
-  static constexpr int kThreads = N / R;
-  static constexpr int kPhases = (LOGN + LOGR - 1) / LOGR;
-  static constexpr size_t kLdsBytes = (size_t)(N + N / 32) * 4;
-  // forward pass PH covers stages [s0(PH), s0(PH)+ns(PH))
-  static constexpr int s0(int ph) { return ph * LOGR; }
-  static constexpr int ns(int ph) { return ph < kPhases - 1 ? LOGR : LOGN - LOGR * (kPhases - 1); }
-};
-
-// n = 32768: four passes of 5 + 4 + 4 + 2 stages.  The last forward pass (the first inverse one) has every thread store
-// (load) 2^ns consecutive residues; with five stages there that is 128 bytes per lane, one cache line per lane and
-// access, eight times the line accesses the bytes need.  Two stages there make it one 16-byte word per lane: the lanes of
-// a wave touch consecutive words.  Measured against 5 + 5 + 5: whole-row forward 119 -> 98 ns per row, the inverse
-// transforms of a squaring 123 -> 103, although the row makes one more trip through the LDS (5 + 5 + 3 + 2 and
-// 4 + 5 + 4 + 2 are within 2 % of it; 5 + 5 + 4 + 1, eight bytes per lane, gains nothing).  The half-row network of
-// that ring's two-workgroup forward transform (14 stages, 32 residues per thread) takes 5 + 4 + 3 + 2 for the same
-// reason (2 % faster than 5 + 5 + 4).  At n = 8192 the three passes 5 + 5 + 3 (32 bytes per lane) stay: 5 + 4 + 2 + 2,
-// 5 + 3 + 3 + 2 and 5 + 4 + 4 were each 3-5 % slower.
+struct NttGeom;
 #define HCNN_GEOM_SPEC(LOGN_, LOGR_, NP_, ...)                                                        \
   template <>                                                                                          \
   struct NttGeom<LOGN_, LOGR_> {                                                                       \
@@ -162,10 +177,43 @@ struct NttGeom {
     static constexpr int s0(int ph) { int s = 0; for (int i = 0; i < ph; ++i) s += kNs[i]; return s; } \
     static constexpr int ns(int ph) { return kNs[ph]; }                                                \
   };
+HCNN_GEOM_SPEC(10, 4, 3, 4, 4, 2)
+HCNN_GEOM_SPEC(11, 4, 4, 3, 4, 2, 2)
+HCNN_GEOM_SPEC(12, 4, 4, 4, 4, 2, 2)
+HCNN_GEOM_SPEC(13, 4, 4, 3, 4, 4, 2)
+HCNN_GEOM_SPEC(14, 4, 4, 4, 4, 4, 2)
+HCNN_GEOM_SPEC(14, 5, 4, 4, 4, 4, 2)      // the half rows of n = 32768's two-workgroup forward transform
 HCNN_GEOM_SPEC(15, 5, 4, 5, 4, 4, 2)
-HCNN_GEOM_SPEC(14, 5, 4, 5, 4, 3, 2)
-HCNN_GEOM_SPEC(13, 4, 4, 4, 3, 4, 2)
 #undef HCNN_GEOM_SPEC
+
+// Two Cooley-Tukey stages on (x0, x1, x2, x3): pairs (0,2), (1,3) with W, then (0,1) with V and (2,3) with U.
+// Twiddles c are centred and carry 2^32, so sredc(c * x) is the product: |sum of two products| <= p |x|max, which the
+// reduction brings to p |x|max / 2^32 + p/2 <= p for any 32-bit x; every output is a sum or difference of two: in (-2p, 2p).
+HCNN_HD void r4_fwd(int32_t& x0, int32_t& x1, int32_t& x2, int32_t& x3, const R4Twiddle& t, int32_t nuw, const NttLimb& L) {
+  const uint32_t p = L.m.p;
+  const int64_t e = (int64_t)x0 * L.rc;
+  const int32_t A = sredc(e + (int64_t)x2 * t.w, p, L.pinv);
+  const int32_t C = sredc(e + (int64_t)x2 * (L.zero - t.w), p, L.pinv);
+  const int32_t P = sredc((int64_t)x1 * t.v + (int64_t)x3 * t.vw, p, L.pinv);
+  const int32_t Q = sredc((int64_t)x1 * t.u + (int64_t)x3 * nuw, p, L.pinv);
+  x0 = A + P;
+  x1 = A - P;
+  x2 = C + Q;
+  x3 = C - Q;
+}
+
+// Two Gentleman-Sande stages: pairs (0,1) with V and (2,3) with U, then (0,2), (1,3) with W (inverse twiddles).
+// c0 is the constant of the untwisted output (2^32, or the scaling of the last level).  With |x| <= p the sums and differences
+// fit 32 bits, two products of them stay below 2 p^2 and every output in (-p, p).
+HCNN_HD void r4_inv(int32_t& x0, int32_t& x1, int32_t& x2, int32_t& x3, int32_t c0, const R4Twiddle& t, int32_t nuw, const NttLimb& L) {
+  const uint32_t p = L.m.p;
+  const int32_t s1 = x0 + x1, d1 = x0 - x1, s2 = x2 + x3, d2 = x2 - x3;
+  // (untraced: the compiler would factor c0 out, into a 64-bit sum and a 64-bit product)
+  x0 = sredc(untraced((int64_t)s1 * c0) + (int64_t)s2 * c0, p, L.pinv);
+  x1 = sredc((int64_t)d1 * t.v + (int64_t)d2 * t.u, p, L.pinv);
+  x2 = sredc((int64_t)s1 * t.w + (int64_t)s2 * (L.zero - t.w), p, L.pinv);
+  x3 = sredc((int64_t)d1 * t.vw + (int64_t)d2 * nuw, p, L.pinv);
+}
 
 // ------------------------------------------------------------------------- forward
 // SPLIT = 1: two workgroups per row.  The first stage of the forward transform pairs element i with element
@@ -177,9 +225,9 @@ template <int LOGN, int LOGR, int IO = kNttPlain, int SPLIT = 0>
 struct NttFwd {
   static constexpr bool kFused = IO == kNttFusedMac || IO == kNttFusedMac16 || IO == kNttFusedMacAny;
   static constexpr bool kToRegs = IO == kNttToRegs0 || IO == kNttToRegs1;
-  static_assert(IO == kNttPlain || IO == kNttLoadDigit || IO == kNttStoreLazy || kFused || kToRegs,
-                "forward NTT: plain, digit load, lazy store, fused inner product or register output");
-  static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kToRegs), "the split form stores its rows");
+  static_assert(IO == kNttPlain || IO == kNttLoadDigit || IO == kNttStoreLazy || IO == kNttStoreKey || kFused || kToRegs,
+                "forward NTT: plain, digit load, lazy or key store, fused inner product or register output");
+  static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kToRegs && LOGN % 2 == 1), "the split form stores its rows");
   using G = NttGeom<LOGN - SPLIT, LOGR>;      // the stages after the split one
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
@@ -195,6 +243,8 @@ struct NttFwd {
     constexpr int S0 = G::s0(PH), NS = G::ns(PH), NET = 1 << NS, C = R / NET;
     constexpr int LOG_TLAST = LOGM - S0 - NS, TLAST = 1 << LOG_TLAST;
     constexpr bool kFirst = PH == 0, kLast = PH == kPhases - 1;
+    constexpr bool kOdd = NS % 2 == 1;                     // one radix-2 stage, at the root of the whole tree
+    static_assert(!kOdd || (kFirst && !SPLIT), "only the root stage is taken alone");
     if constexpr (kFused || kToRegs) tid = opaque(tid);
 
     uint32_t half = 0;
@@ -207,141 +257,142 @@ struct NttFwd {
       }
     }
     if constexpr (kDigitIn) {
-      bid = ntt_grouped_index(bid, a.limb_cycle);      // the k transforms of one digit row share a die
+      bid = ntt_grouped_index(bid, a.cycle);      // the k transforms of one digit row share a die
       if (bid >= a.n_rows) return;
     }
-    const uint32_t limb = a.limb_base + bid % a.limb_cycle;
+    const uint32_t group = quot(bid, a.cycle), within = bid - group * a.cycle.d, limb = a.limb_base + within;
     const NttLimb L = ldc(a.limbs, limb);
-    const uint32_t p = L.m.p, two_p = 2 * L.m.p;
-    const ShoupConst* tw = a.tw + (size_t)limb * N;
+    const uint32_t p = L.m.p;
+    const R4Twiddle* tq = a.tw.quad + (size_t)limb * (N / 2);
+    const int32_t* tn = a.tw.nuw + (size_t)limb * (N / 2);
     const uint32_t* gin;
     uint32_t* gout = nullptr;
     const uint32_t* key0 = nullptr;       // kNttFusedMac: evk^[iter][0][j]; component 1 lies k rows further
     if constexpr (kFused) {
-      const uint32_t kk = a.limb_cycle;                // rows are (ct, j)
-      gin = a.in + ((size_t)(bid / kk) * 3 * kk + 2 * kk + regs.iter) * N;
+      const uint32_t kk = a.cycle.d;                   // rows are (ct, j)
+      gin = a.in + ((size_t)group * 3 * kk + 2 * kk + regs.iter) * N;
       key0 = a.aux + ((size_t)regs.iter * 2 * kk + limb) * N;
       if (kFirst && regs.iter == 0) {
 #pragma unroll
         for (int r = 0; r < R; ++r) { regs.s0[r] = 0; regs.s1[r] = 0; }
       }
     } else if constexpr (IO == kNttLoadDigit) {
-      const uint32_t kk = a.limb_cycle;
-      gin = a.in + ((size_t)(bid / (kk * kk)) * 3 * kk + 2 * kk + (bid / kk) % kk) * N;
+      const uint32_t kk = a.cycle.d, ct = quot(group, a.cycle);      // group = (ct, digit)
+      gin = a.in + ((size_t)ct * 3 * kk + 2 * kk + (group - ct * kk)) * N;
     } else if constexpr (kToRegs) {
       // workgroup (ct, l): polynomial c0 or c1 of the ciphertext; its own limbs come from the ciphertext (`aux`,
       // [ct][2][own_limbs][n]), the auxiliary limbs from the extension buffer (`in`, [ct][2][L][n])
-      const uint32_t LL = a.limb_cycle, poly = IO == kNttToRegs1 ? 1u : 0u;
-      const size_t grp = (size_t)(bid / LL) * 2 + poly;
+      const uint32_t LL = a.cycle.d, poly = IO == kNttToRegs1 ? 1u : 0u;
+      const size_t grp = (size_t)group * 2 + poly;
       if (bid >= a.n_rows) return;
       gin = limb < a.own_limbs ? a.aux + (grp * a.own_limbs + limb) * N : a.in + (grp * LL + limb) * N;
     } else {
-      gin = a.in + ntt_row(bid, a.limb_cycle, a.in_group_rows, a.in_row0) * N;
+      gin = a.in + ((size_t)group * a.in_group_rows + a.in_row0 + within) * N;
       if constexpr (IO == kNttStoreLazy) {
-        if (a.aux != nullptr && bid % a.limb_cycle < a.own_limbs)
-          gin = a.aux + ((size_t)(bid / a.limb_cycle) * a.own_limbs + bid % a.limb_cycle) * N;
+        if (a.aux != nullptr && within < a.own_limbs) gin = a.aux + ((size_t)group * a.own_limbs + within) * N;
       }
     }
     if constexpr (!kFused && !kToRegs)
-      gout = a.out + ntt_row(bid, a.limb_cycle, a.out_group_rows, a.out_row0) * N + (size_t)half * (N / 2);
-    // split form: the butterfly of the first stage (node 1) on the way in -- this half's output of the pair
-    // (i, i + n/2).  X is brought below 2p first (rows may arrive lazily reduced below 4p), the product T lies in
-    // [0, 2p): X + T and X - T + 2p are valid inputs of the stages that follow.
-    [[maybe_unused]] const ShoupConst w_split = SPLIT ? ldc(tw, 1) : ShoupConst{0, 0};
-    auto load_first = [&](uint32_t idx) -> uint32_t {
+      gout = a.out + ((size_t)group * a.out_group_rows + a.out_row0 + within) * N + (size_t)half * (N / 2);
+
+    // The radix-2 stage of node 1 on rows with residues in [0, 2p) (canonical ones, or digits of another prime):
+    // with X brought below p, X + T and X - T lie in (-0.75 p, 1.75 p) and the stage needs no other reduction.
+    // split form: this half's output of the pair (i, i + n/2), on the way in.
+    auto load_first = [&](uint32_t at, uint32_t e_off) -> int32_t {      // element at + e_off, e_off uniform
       if constexpr (SPLIT) {
-        const uint32_t X = csub(gin[idx], two_p), Y = gin[idx + N / 2];
-        const uint32_t negT = mulhi32(Y, w_split.ws) * p + Y * w_split.w;
-        return half ? X + two_p + negT : X - negT;
+        const int32_t X = (int32_t)csub(ld_at(gin + e_off, at * 4), p);
+        const int32_t T = sredc((int64_t)(int32_t)ld_at(gin + e_off + N / 2, at * 4) * L.w1, p, L.pinv);
+        return half ? X - T : X + T;
       } else {
-        return gin[idx];
+        return (int32_t)ld_at(gin + e_off, at * 4);
       }
     };
 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       const uint32_t nu = (uint32_t)tid + (uint32_t)kThreads * c;   // network id
-      const uint32_t o = nu & (TLAST - 1), i = nu >> LOG_TLAST;
+      const uint32_t o = nu & (TLAST - 1);
+      uint32_t i = nu >> LOG_TLAST;
+      if constexpr (TLAST >= 64) i = wave_uniform(i);               // (scalar twiddle loads)
       const uint32_t base = i * (uint32_t)(NET * TLAST) + o;        // element e at base + e*TLAST
       const uint32_t sbase = lds_swz(base);
-      uint32_t v[NET];
+      int32_t v[NET];
 #pragma unroll
       for (int e = 0; e < NET; ++e)
-        v[e] = kFirst ? load_first(base + (uint32_t)e * TLAST) : lds[lds_elem<LOG_TLAST>(sbase, e)];
-      // (kNttLoadDigit: a digit lies in [0, q_i) and every prime in (2^29, 2^30), so it is below 2p for this
-      // row's prime p: a valid lazily reduced input of the butterflies as it stands)
+        v[e] = kFirst ? load_first(base, (uint32_t)e * TLAST) : (int32_t)lds[lds_elem<LOG_TLAST>(sbase, e)];
       // node of the twiddle tree over the whole row: the half's own sub-tree in the split form
       const uint32_t root = SPLIT ? ((2u + half) << S0) + i : (1u << S0) + i;
+      if constexpr (kOdd) {
 #pragma unroll
-      for (int l = 0; l < NS; ++l) {
-        const int half = NET >> (l + 1);
+        for (int x = 0; x < NET / 2; ++x) {
+          const int32_t X = (int32_t)csub((uint32_t)v[x], p), T = sredc((int64_t)v[x + NET / 2] * L.w1, p, L.pinv);
+          v[x] = X + T;
+          v[x + NET / 2] = X - T;
+        }
+      }
+#pragma unroll
+      for (int l = kOdd ? 1 : 0; l < NS; l += 2) {
+        const int q = NET >> (l + 2);
 #pragma unroll
         for (int h = 0; h < (1 << l); ++h) {
-          const ShoupConst w = ldc(tw, (root << l) + h);
+          const R4Twiddle t = ldc_at(tq + h, (root << l) * 16);
+          const int32_t nuw = ldc_at(tn + h, (root << l) * 4);
 #pragma unroll
-          for (int x = 0; x < half; ++x) {
-            const int ia = h * 2 * half + x, ib = ia + half;
-            const uint32_t X = csub(v[ia], two_p);                          // [0, 2p)
-            // the forward table holds -w (mod 2^32): q*p - y*w is then a multiplication and a multiply-add
-            const uint32_t negT = mulhi32(v[ib], w.ws) * p + v[ib] * w.w;   // -(y*w mod p) - {0,p}  (mod 2^32)
-            v[ia] = X - negT;                                              // X + T        in [0, 4p)
-            v[ib] = X + two_p + negT;                                      // X - T + 2p   in (0, 4p)
+          for (int x = 0; x < q; ++x) {
+            const int b = h * 4 * q + x;
+            r4_fwd(v[b], v[b + q], v[b + 2 * q], v[b + 3 * q], t, nuw, L);
           }
         }
       }
       if constexpr (kLast && kFused) {
-        // The transformed digit times the key rows (below p < 2^30), added to the 64-bit sums.  With the digit only
-        // brought into [0, 2p), 8 products stay below 16 p^2 < 2^64 (kNttFusedMac, k <= 8); with the digit made
-        // canonical, 16 products do, or 15 and a residue (kNttFusedMac16, k <= 16), and
-        // kNttFusedMacAny folds the sums before digits 16, 31, 46, ...
-        const uint32_t* key1 = key0 + (size_t)a.limb_cycle * N;
-        uint32_t e0[NET], e1[NET];
-#pragma unroll
-        for (int e = 0; e < NET; ++e) { e0[e] = key0[base + (uint32_t)e]; e1[e] = key1[base + (uint32_t)e]; }
+        // The transformed digit times the key rows (|key| <= p/2), added to the 64-bit sums.  With the digit as it is, in
+        // (-2p, 2p), 8 products stay below 8 p^2 < 2^63 (kNttFusedMac, k <= 8); brought into [-p, p), 16 products do
+        // (kNttFusedMac16, k <= 16), and kNttFusedMacAny folds the sums to 2^60 (two products) before digits 16, 29, 42, ...
+        const uint32_t* key1 = key0 + (size_t)a.cycle.d * N;
+        int32_t e0[NET], e1[NET];
+        load_row<NET>(e0, key0, base);
+        load_row<NET>(e1, key1, base);
         if constexpr (IO == kNttFusedMacAny) {
-          if (regs.iter >= 16 && (regs.iter - 16) % 15 == 0) {
+          if (regs.iter >= 16 && (regs.iter - 16) % 13 == 0) {
 #pragma unroll
             for (int e = 0; e < NET; ++e) {
-              regs.s0[c * NET + e] = reduce64(regs.s0[c * NET + e], L.m);
-              regs.s1[c * NET + e] = reduce64(regs.s1[c * NET + e], L.m);
+              regs.s0[c * NET + e] = sfold(regs.s0[c * NET + e], L.rc);
+              regs.s1[c * NET + e] = sfold(regs.s1[c * NET + e], L.rc);
             }
           }
         }
 #pragma unroll
         for (int e = 0; e < NET; ++e) {
-          uint32_t d = csub(v[e], two_p);
-          if constexpr (IO != kNttFusedMac) d = csub(d, p);
-          regs.s0[c * NET + e] += (uint64_t)d * e0[e];
-          regs.s1[c * NET + e] += (uint64_t)d * e1[e];
+          const int32_t d = IO == kNttFusedMac ? v[e] : half_range(v[e], p);
+          regs.s0[c * NET + e] += (int64_t)d * e0[e];
+          regs.s1[c * NET + e] += (int64_t)d * e1[e];
         }
       } else if constexpr (kLast && kToRegs) {
 #pragma unroll
         for (int e = 0; e < NET; ++e) {
-          if constexpr (IO == kNttToRegs1) regs.c1[c * NET + e] = csub(v[e], two_p);
-          else                             regs.c0[c * NET + e] = csub(v[e], two_p);
+          if constexpr (IO == kNttToRegs1) regs.c1[c * NET + e] = half_range(v[e], p);
+          else                             regs.c0[c * NET + e] = half_range(v[e], p);
         }
-      } else if constexpr (kLast && NET >= 4) {
-        // TLAST == 1: the network is NET consecutive coefficients -> 16-byte stores
-        U4* g4 = reinterpret_cast<U4*>(gout + base);
+      } else if constexpr (kLast) {
+        static_assert(!kLast || TLAST == 1, "the last pass holds consecutive residues");
+        uint32_t r[NET];
+#pragma unroll
+        for (int e = 0; e < NET; ++e) {
+          if constexpr (IO == kNttStoreLazy || IO == kNttLoadDigit) r[e] = (uint32_t)half_range(v[e], p);
+          else if constexpr (IO == kNttStoreKey) {
+            const uint32_t x = canon_p(sredc((int64_t)v[e] * L.key_scale, p, L.pinv), p);
+            r[e] = x > p / 2 ? x - p : x;
+          } else r[e] = canon_2p(v[e], p);
+        }
 #pragma unroll
         for (int e = 0; e < NET; e += 4) {
           U4 t;
-          if constexpr (IO == kNttStoreLazy) {
-            t.x = csub(v[e + 0], two_p); t.y = csub(v[e + 1], two_p); t.z = csub(v[e + 2], two_p); t.w = csub(v[e + 3], two_p);
-          } else {
-            t.x = csub(csub(v[e + 0], two_p), p);
-            t.y = csub(csub(v[e + 1], two_p), p);
-            t.z = csub(csub(v[e + 2], two_p), p);
-            t.w = csub(csub(v[e + 3], two_p), p);
-          }
-          g4[e / 4] = t;
+          t.x = r[e]; t.y = r[e + 1]; t.z = r[e + 2]; t.w = r[e + 3];
+          st4_at(gout, (base + (uint32_t)e) * 4, t);
         }
       } else {
 #pragma unroll
-        for (int e = 0; e < NET; ++e) {
-          if (kLast) gout[base + (uint32_t)e * TLAST] = IO == kNttStoreLazy ? csub(v[e], two_p) : csub(csub(v[e], two_p), p);
-          else       lds[lds_elem<LOG_TLAST>(sbase, e)] = v[e];
-        }
+        for (int e = 0; e < NET; ++e) lds[lds_elem<LOG_TLAST>(sbase, e)] = (uint32_t)v[e];
       }
     }
   }
@@ -370,190 +421,169 @@ struct NttInv {
     constexpr int S0 = G::s0(PH), NS = G::ns(PH), NET = 1 << NS, C = R / NET;
     constexpr int LOG_TLAST = LOGN - S0 - NS, TLAST = 1 << LOG_TLAST;
     constexpr bool kFirst = PHI == 0, kLast = PHI == kPhases - 1;   // kLast <=> S0 == 0
+    constexpr bool kOdd = NS % 2 == 1;
 
     if constexpr (IO == kNttLoadTensor || IO == kNttLoadTensorMul) {
       // the three components of one (ciphertext, limb) pair read the same c0^ / c1^ rows: same die
-      const uint32_t LL = a.limb_cycle;
-      const uint32_t g = ntt_grouped_index(bid, 3);            // unit = ct*L + l, within = component
-      const uint32_t unit = g / 3, b = g % 3;
-      bid = ((unit / LL) * 3 + b) * LL + unit % LL;            // row (ct, b, l)
+      const uint32_t LL = a.cycle.d;
+      const uint32_t xcd = bid % kNttXcds, local = bid / kNttXcds;
+      const uint32_t unit = local / 3 * kNttXcds + xcd, b = local % 3, ct = quot(unit, a.cycle);   // unit = ct*L + l
+      bid = (ct * 3 + b) * LL + (unit - ct * LL);               // row (ct, b, l)
       if (unit >= a.n_rows / 3) return;
     }
     if constexpr (kFromRegs) {
-      bid = ntt_grouped_index(bid, a.limb_cycle);      // the same workgroup -> (ct, j) map as kNttFusedMac
+      bid = ntt_grouped_index(bid, a.cycle);      // the same workgroup -> (ct, j) map as kNttFusedMac
       if (bid >= a.n_rows) return;
     }
     if constexpr (kTensorRegs) {
       tid = opaque(tid);
       if (bid >= a.n_rows) return;
     }
-    const uint32_t limb = a.limb_base + bid % a.limb_cycle;
+    const uint32_t group = quot(bid, a.cycle), within = bid - group * a.cycle.d, limb = a.limb_base + within;
     const NttLimb L = ldc(a.limbs, limb);
-    const uint32_t p = L.m.p, two_p = 2 * L.m.p;
-    const ShoupConst* tw = a.tw + (size_t)limb * N;
+    const uint32_t p = L.m.p;
+    const R4Twiddle* tq = a.tw.quad + (size_t)limb * (N / 2);
+    const int32_t* tn = a.tw.nuw + (size_t)limb * (N / 2);
     const uint32_t* gin = nullptr;
     const uint32_t* gin2 = nullptr;       // kNttLoadTensor: the c1^ row
     uint32_t comp = 0;                    // kNttLoadTensor: tensor component b
     const uint32_t* gmul0 = nullptr;      // kNttLoadTensorMul: rows c0^, c1^ of the first operand and
     const uint32_t* gmul1 = nullptr;      // c0'^, c1'^ of the second
     if constexpr (IO == kNttLoadTensor) {
-      const uint32_t LL = a.limb_cycle;
-      const uint32_t ct = bid / (3 * LL);
-      comp = (bid / LL) % 3;
-      gin2 = a.in + ((size_t)(ct * 2 + 1) * LL + bid % LL) * N;     // c1^
+      const uint32_t LL = a.cycle.d, ct = group / 3;
+      comp = group % 3;
+      gin2 = a.in + ((size_t)(ct * 2 + 1) * LL + within) * N;       // c1^
       gin = comp == 2 ? gin2 : gin2 - (size_t)LL * N;                 // c0^ unless b = 2
     } else if constexpr (IO == kNttLoadTensorMul) {
-      const uint32_t LL = a.limb_cycle;
-      const uint32_t ct = bid / (3 * LL);
-      comp = (bid / LL) % 3;
-      const size_t row0 = ((size_t)ct * 2 * LL + bid % LL) * N;        // component 0 of this limb
+      const uint32_t LL = a.cycle.d, ct = group / 3;
+      comp = group % 3;
+      const size_t row0 = ((size_t)ct * 2 * LL + within) * N;        // component 0 of this limb
       gmul0 = a.in + row0;
       gmul1 = a.aux + row0;
       // b = 0: c0*c0' ; b = 2: c1*c1' ; b = 1: c0*c1' + c1*c0'
       gin = gmul0 + (comp == 2 ? (size_t)LL * N : 0);
       gin2 = gmul1 + (comp == 0 ? 0 : (size_t)LL * N);
     } else if constexpr (!kFromRegs && !kTensorRegs) {
-      gin = a.in + ntt_row(bid, a.limb_cycle, a.in_group_rows, a.in_row0) * N;
+      gin = a.in + ((size_t)group * a.in_group_rows + a.in_row0 + within) * N;
     }
     uint32_t* gout;
     const uint32_t* gaux = nullptr;
     if constexpr (kFromRegs) {
-      const uint32_t kk = a.limb_cycle, ct = bid / kk, b = IO == kNttFromRegs1 ? 1u : 0u;
-      gout = a.out + ((size_t)(ct * 2 + b) * kk + bid % kk) * N;
-      gaux = a.aux + ((size_t)(ct * 3 + b) * kk + bid % kk) * N;
+      const uint32_t kk = a.cycle.d, b = IO == kNttFromRegs1 ? 1u : 0u;
+      gout = a.out + ((size_t)(group * 2 + b) * kk + within) * N;
+      gaux = a.aux + ((size_t)(group * 3 + b) * kk + within) * N;
     } else if constexpr (kTensorRegs) {
-      const uint32_t LL = a.limb_cycle, b = IO == kNttTensorRegs0 ? 0u : (IO == kNttTensorRegs1 ? 1u : 2u);
-      gout = a.out + ((size_t)((bid / LL) * 3 + b) * LL + bid % LL) * N;       // d row (ct, b, l)
+      const uint32_t LL = a.cycle.d, b = IO == kNttTensorRegs0 ? 0u : (IO == kNttTensorRegs1 ? 1u : 2u);
+      gout = a.out + ((size_t)(group * 3 + b) * LL + within) * N;       // d row (ct, b, l)
     } else {
-      gout = a.out + ntt_row(bid, a.limb_cycle, a.out_group_rows, a.out_row0) * N;
+      gout = a.out + ((size_t)group * a.out_group_rows + a.out_row0 + within) * N;
     }
     if constexpr (IO == kNttStoreAdd) {
-      const uint32_t kk = a.limb_cycle, grp = bid / kk;
-      gaux = a.aux + ((size_t)(grp / 2) * 3 * kk + (size_t)(grp % 2) * kk + bid % kk) * N;
+      const uint32_t kk = a.cycle.d;
+      gaux = a.aux + ((size_t)(group / 2) * 3 * kk + (size_t)(group % 2) * kk + within) * N;
     }
 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       const uint32_t nu = (uint32_t)tid + (uint32_t)kThreads * c;
-      const uint32_t o = nu & (TLAST - 1), i = nu >> LOG_TLAST;
+      const uint32_t o = nu & (TLAST - 1);
+      uint32_t i = nu >> LOG_TLAST;
+      if constexpr (TLAST >= 64) i = wave_uniform(i);
       const uint32_t base = i * (uint32_t)(NET * TLAST) + o;
       const uint32_t sbase = lds_swz(base);
-      uint32_t v[NET];
+      int32_t v[NET];
+      static_assert(!kFirst || TLAST == 1, "the first pass holds consecutive residues");
       if constexpr (kFirst && kFromRegs) {
-        // the sums sit where the last forward pass left its residues, which is where this pass takes them
+        // the sums sit where the last forward pass left its residues, which is where this pass takes them; the key
+        // carries the factor 2^32 of the reduction.  |sfold| / 2^32 + p/2 <= p
 #pragma unroll
         for (int e = 0; e < NET; ++e)
-          v[e] = reduce64(IO == kNttFromRegs1 ? regs.s1[c * NET + e] : regs.s0[c * NET + e], L.m);
+          v[e] = sredc(sfold(IO == kNttFromRegs1 ? regs.s1[c * NET + e] : regs.s0[c * NET + e], L.rc), p, L.pinv);
       } else if constexpr (kFirst && kTensorRegs) {
-        // c0^*c0^, 2*c0^*c1^ or c1^*c1^ from the registers of the two forward transforms (values in [0, 2p)); products
-        // carry the factor 2^-32 of the reduction and stay in [0, 2p)
+        // c0^*c0^, 2*c0^*c1^ or c1^*c1^ from the registers of the two forward transforms (values in [-p, p)); products
+        // carry the factor 2^-32 of the reduction and stay in (-p, p)
 #pragma unroll
         for (int e = 0; e < NET; ++e) {
-          const uint32_t x = IO == kNttTensorRegs2 ? regs.c1[c * NET + e] : regs.c0[c * NET + e];
-          const uint32_t y = IO == kNttTensorRegs0 ? regs.c0[c * NET + e] : regs.c1[c * NET + e];
-          uint32_t t = redc_2p((uint64_t)x * y, p, L.pinv);
-          if constexpr (IO == kNttTensorRegs1) t = csub(2 * t, two_p);
-          v[e] = t;
+          const int32_t x = untraced(IO == kNttTensorRegs2 ? regs.c1[c * NET + e] : regs.c0[c * NET + e]);
+          const int32_t y = IO == kNttTensorRegs1 ? untraced(regs.c1[c * NET + e]) : x;
+          v[e] = sredc((int64_t)(IO == kNttTensorRegs1 ? untraced(x + x) : x) * y, p, L.pinv);
         }
-      } else if constexpr (kFirst && NET >= 4) {
-        // TLAST == 1: NET consecutive coefficients -> 16-byte loads
-        const U4* g4 = reinterpret_cast<const U4*>(gin + base);
+      } else if constexpr (kFirst) {
+        load_row<NET>(v, gin, base);
+        if constexpr (IO == kNttLoadTensorMul) {
+          // v = c0^ (b = 0, 1) or c1^ (b = 2);  y = c0'^ (b = 0) or c1'^ (b = 1, 2); all in [-p, p).  The cross term is
+          // summed in 64 bits
+          int32_t y[NET];
+          load_row<NET>(y, gin2, base);
+          if (comp == 1) {                 // + c1^ * c0'^
+            int32_t u[NET], w[NET];
+            load_row<NET>(u, gmul0 + (size_t)a.cycle.d * N, base);
+            load_row<NET>(w, gmul1, base);
 #pragma unroll
-        for (int e = 0; e < NET; e += 4) {
-          U4 t = g4[e / 4];
-          if constexpr (IO == kNttLoadTensorMul) {
-            // t = c0^ (b = 0, 1) or c1^ (b = 2);  y = c0'^ (b = 0) or c1'^ (b = 1, 2); all in [0, 2p)
-            const U4 y = reinterpret_cast<const U4*>(gin2 + base)[e / 4];
-            t.x = redc_2p((uint64_t)t.x * y.x, p, L.pinv); t.y = redc_2p((uint64_t)t.y * y.y, p, L.pinv);
-            t.z = redc_2p((uint64_t)t.z * y.z, p, L.pinv); t.w = redc_2p((uint64_t)t.w * y.w, p, L.pinv);
-            if (comp == 1) {                 // + c1^ * c0'^
-              const U4 u = reinterpret_cast<const U4*>(gmul0 + (size_t)a.limb_cycle * N + base)[e / 4];
-              const U4 w = reinterpret_cast<const U4*>(gmul1 + base)[e / 4];
-              t.x = csub(t.x + redc_2p((uint64_t)u.x * w.x, p, L.pinv), two_p);
-              t.y = csub(t.y + redc_2p((uint64_t)u.y * w.y, p, L.pinv), two_p);
-              t.z = csub(t.z + redc_2p((uint64_t)u.z * w.z, p, L.pinv), two_p);
-              t.w = csub(t.w + redc_2p((uint64_t)u.w * w.w, p, L.pinv), two_p);
-            }
+            for (int e = 0; e < NET; ++e) v[e] = sredc((int64_t)v[e] * y[e] + (int64_t)u[e] * w[e], p, L.pinv);
+          } else {
+#pragma unroll
+            for (int e = 0; e < NET; ++e) v[e] = sredc((int64_t)v[e] * y[e], p, L.pinv);
           }
-          if constexpr (IO == kNttLoadTensor) {
-            // gin was pointed at c0^ (b = 0, 1) or c1^ (b = 2); only b = 1 needs the second row.  Products (with
-            // the factor 2^-32 of the reduction) and the doubled cross term stay in [0, 2p), which is what the
-            // first butterflies of the inverse transform take
-            U4 y = t;
-            if (comp == 1) y = reinterpret_cast<const U4*>(gin2 + base)[e / 4];
-            t.x = redc_2p((uint64_t)t.x * y.x, p, L.pinv); t.y = redc_2p((uint64_t)t.y * y.y, p, L.pinv);
-            t.z = redc_2p((uint64_t)t.z * y.z, p, L.pinv); t.w = redc_2p((uint64_t)t.w * y.w, p, L.pinv);
-            if (comp == 1) { t.x = csub(2 * t.x, two_p); t.y = csub(2 * t.y, two_p); t.z = csub(2 * t.z, two_p); t.w = csub(2 * t.w, two_p); }
+        }
+        if constexpr (IO == kNttLoadTensor) {
+          // gin was pointed at c0^ (b = 0, 1) or c1^ (b = 2); only b = 1 needs the second row.  Products carry the
+          // factor 2^-32 of the reduction
+          if (comp == 1) {
+            int32_t y[NET];
+            load_row<NET>(y, gin2, base);
+#pragma unroll
+            for (int e = 0; e < NET; ++e) v[e] = sredc((int64_t)(v[e] + v[e]) * y[e], p, L.pinv);
+          } else {
+#pragma unroll
+            for (int e = 0; e < NET; ++e) v[e] = sredc((int64_t)v[e] * v[e], p, L.pinv);
           }
-          v[e + 0] = t.x; v[e + 1] = t.y; v[e + 2] = t.z; v[e + 3] = t.w;
         }
       } else {
 #pragma unroll
-        for (int e = 0; e < NET; ++e) {
-          if constexpr (kFirst) {
-            uint32_t t = gin[base + (uint32_t)e * TLAST];
-            if constexpr (IO == kNttLoadTensorMul) {
-              const uint32_t idx = base + (uint32_t)e * TLAST;
-              t = redc_2p((uint64_t)t * gin2[idx], p, L.pinv);
-              if (comp == 1)
-                t = csub(t + redc_2p((uint64_t)gmul0[(size_t)a.limb_cycle * N + idx] * gmul1[idx], p, L.pinv), two_p);
-            }
-            if constexpr (IO == kNttLoadTensor) {
-              const uint32_t u = comp == 1 ? gin2[base + (uint32_t)e * TLAST] : t;
-              t = redc_2p((uint64_t)t * u, p, L.pinv);
-              if (comp == 1) t = csub(2 * t, two_p);
-            }
-            v[e] = t;
-          } else {
-            v[e] = lds[lds_elem<LOG_TLAST>(sbase, e)];   // [0, 2p)
+        for (int e = 0; e < NET; ++e) v[e] = (int32_t)lds[lds_elem<LOG_TLAST>(sbase, e)];
+      }
+      const uint32_t root = (1u << S0) + i;
+      constexpr bool kMont = IO == kNttLoadTensor || IO == kNttLoadTensorMul || kTensorRegs;
+      const InvRoot& top = kMont ? L.inv_r : L.inv;       // node 1: the output scaling folded in
+#pragma unroll
+      for (int l = NS - 2; l >= (kOdd ? 1 : 0); l -= 2) {
+        const int q = NET >> (l + 2);
+#pragma unroll
+        for (int h = 0; h < (1 << l); ++h) {
+          const bool outer = kLast && l == 0;
+          const R4Twiddle t = outer ? R4Twiddle{top.w, top.v, top.vw, top.u} : ldc_at(tq + h, (root << l) * 16);
+          const int32_t nuw = outer ? top.nuw : ldc_at(tn + h, (root << l) * 4), c0 = outer ? top.c0 : L.rc;
+#pragma unroll
+          for (int x = 0; x < q; ++x) {
+            const int b = h * 4 * q + x;
+            r4_inv(v[b], v[b + q], v[b + 2 * q], v[b + 3 * q], c0, t, nuw, L);
           }
         }
       }
-      const uint32_t root = (1u << S0) + i;
-      const uint32_t pn = L.pneg;
+      if constexpr (kOdd) {
+        static_assert(!kOdd || kLast, "only the root stage is taken alone");
 #pragma unroll
-      for (int l = NS - 1; l >= 0; --l) {
-        const int half = NET >> (l + 1);
-        const bool top = kLast && l == 0;                 // node 1: fold in n^-1
-#pragma unroll
-        for (int h = 0; h < (1 << l); ++h) {
-          constexpr bool kMont = IO == kNttLoadTensor || IO == kNttLoadTensorMul || kTensorRegs;
-          const ShoupConst w = top ? (kMont ? L.w1ninv_r : L.w1ninv) : ldc(tw, (root << l) + h);
-          const ShoupConst nv = kMont ? L.ninv_r : L.ninv;
-          // Both forms of the lazy product are a multiplication and a multiply-add: x*w + q*(-p), and negated
-          // x*(-w) + q*p.  -p and the zero that -w is taken from come out of the table, so that the compiler
-          // keeps the sums (it would turn a visible negation back into two multiplications and a subtraction).
-          const uint32_t wn = L.zero - w.w;
-#pragma unroll
-          for (int x = 0; x < half; ++x) {
-            const int ia = h * 2 * half + x, ib = ia + half;
-            // A product that the next level subtracts (its position is a right operand there) is kept
-            // negated mod 2^32: the difference then is one three-operand addition.
-            const bool y_neg = l < NS - 1 && (x & (half >> 1)) != 0;    // v[ib] was stored negated by level l + 1
-            const bool out_neg = l > 0 && (h & 1) != 0;                 // v[ib] is a right operand of level l - 1
-            const uint32_t X = v[ia], Y = v[ib];
-            const uint32_t S = y_neg ? X - Y : X + Y;                   // [0, 4p)
-            const uint32_t D = y_neg ? X + two_p + Y : X + two_p - Y;   // (0, 4p)
-            v[ia] = top ? S * nv.w + mulhi32(S, nv.ws) * pn : csub(S, two_p);
-            v[ib] = out_neg ? D * wn + mulhi32(D, w.ws) * p             // -(D * w mod p) - {0, p}  (mod 2^32)
-                            : D * w.w + mulhi32(D, w.ws) * pn;          // D * w mod p + {0, p}: [0, 2p)
-          }
+        for (int x = 0; x < NET / 2; ++x) {
+          const int32_t X = v[x], Y = v[x + NET / 2];
+          v[x] = sredc((int64_t)(X + Y) * top.c0, p, L.pinv);
+          v[x + NET / 2] = sredc((int64_t)(X - Y) * top.w, p, L.pinv);
         }
       }
       if constexpr (kLast && (IO == kNttStoreAdd || kFromRegs)) {
         // all loads of the addend before the first store (the compiler must assume the buffers alias)
         uint32_t addend[NET];
 #pragma unroll
-        for (int e = 0; e < NET; ++e) addend[e] = gaux[base + (uint32_t)e * TLAST];
+        for (int e = 0; e < NET; ++e) addend[e] = ld_at(gaux + e * TLAST, base * 4);
 #pragma unroll
-        for (int e = 0; e < NET; ++e) gout[base + (uint32_t)e * TLAST] = add_mod(csub(v[e], p), addend[e], p);
+        for (int e = 0; e < NET; ++e) st_at(gout + e * TLAST, base * 4, add_mod(canon_p(v[e], p), addend[e], p));
       } else if constexpr (kLast) {
         constexpr bool kLazyOut = IO == kNttLoadTensor || IO == kNttLoadTensorMul || kTensorRegs;
 #pragma unroll
-        for (int e = 0; e < NET; ++e) gout[base + (uint32_t)e * TLAST] = kLazyOut ? v[e] : csub(v[e], p);
+        for (int e = 0; e < NET; ++e) st_at(gout + e * TLAST, base * 4, kLazyOut ? (uint32_t)v[e] + p : canon_p(v[e], p));
       } else {
 #pragma unroll
-        for (int e = 0; e < NET; ++e) lds[lds_elem<LOG_TLAST>(sbase, e)] = v[e];
+        for (int e = 0; e < NET; ++e) lds[lds_elem<LOG_TLAST>(sbase, e)] = (uint32_t)v[e];
       }
     }
   }
@@ -567,11 +597,12 @@ struct RelinFusedArgs {
   const uint32_t* y;        // [n_ct][3][k][n]
   const uint32_t* evk;      // [k][2][k][n], transformed
   uint32_t* out;            // [n_ct][2][k][n]
-  const ShoupConst* tw_fwd;
-  const ShoupConst* tw_inv;
+  TwTable tw_fwd;
+  TwTable tw_inv;
   const NttLimb* limbs;
   uint32_t k;
   uint32_t n_rows;          // n_ct * k
+  FastDiv cycle;            // k
 };
 
 template <int LOGN, int LOGR, int MAC = kNttFusedMacAny>
@@ -592,7 +623,7 @@ struct RelinFused {
   template <int PH>
   HCNN_HD static void phase(const RelinFusedArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
     NttArgs na{};
-    na.limbs = a.limbs; na.limb_cycle = a.k; na.limb_base = 0; na.n_rows = a.n_rows;
+    na.limbs = a.limbs; na.cycle = a.cycle; na.limb_base = 0; na.n_rows = a.n_rows;
     if constexpr (PH < P) {
       na.in = a.y; na.aux = a.evk; na.tw = a.tw_fwd;
       Fwd::template phase<PH>(na, bid, tid, lds, regs);
@@ -612,11 +643,12 @@ struct TensorFusedArgs {
   const uint32_t* cts;      // [n_ct][2][k][n]
   const uint32_t* ext;      // [n_ct][2][L][n], rows k..L-1 of every polynomial valid
   uint32_t* d;              // [n_ct][3][L][n]
-  const ShoupConst* tw_fwd;
-  const ShoupConst* tw_inv;
+  TwTable tw_fwd;
+  TwTable tw_inv;
   const NttLimb* limbs;
   uint32_t k, L;
   uint32_t n_rows;          // n_ct * L
+  FastDiv cycle;            // L
 };
 
 template <int LOGN, int LOGR>
@@ -631,7 +663,7 @@ struct TensorFused {
   template <int PH>
   HCNN_HD static void phase(const TensorFusedArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
     NttArgs na{};
-    na.limbs = a.limbs; na.limb_cycle = a.L; na.limb_base = 0; na.n_rows = a.n_rows;
+    na.limbs = a.limbs; na.cycle = a.cycle; na.limb_base = 0; na.n_rows = a.n_rows;
     if constexpr (PH < 2 * P) {
       na.in = a.ext; na.aux = a.cts; na.own_limbs = a.k; na.tw = a.tw_fwd;
       if constexpr (PH < P) NttFwd<LOGN, LOGR, kNttToRegs0>::template phase<PH>(na, bid, tid, lds, regs);

@@ -80,6 +80,93 @@ template <class T> inline T ldc(const T* table, size_t i) { return table[i]; }
 template <class T> __device__ __forceinline__ T ldc(const T* table, size_t i) { return table[i]; }
 #endif
 
+// Accesses of the form uniform base + 32-bit byte offset per lane.  On the device the base is pinned to scalar registers,
+// so that the access takes it as it is: written as an array index, the compiler moves compile-time parts of the offset
+// behind the per-lane part and spends a 64-bit vector addition on every access.
+// ldc_at: from a read-only table, by scalar loads where the offset is wave-uniform.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef uint32_t hcnn_word4 __attribute__((ext_vector_type(4)));
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wold-style-cast"
+template <class T>
+__device__ __forceinline__ T ldc_at(const T* table, uint32_t byte_off) {
+  static_assert(sizeof(T) == 4 || (sizeof(T) == 16 && alignof(T) == 16), "one word or one aligned 16-byte word");
+  typedef std::conditional_t<sizeof(T) == 4, uint32_t, hcnn_word4> word;
+  typedef const word __attribute__((address_space(4))) * cptr;
+  typedef const char __attribute__((address_space(4))) * bptr;
+  return __builtin_bit_cast(T, *(cptr)((bptr)table + byte_off));
+}
+__device__ __forceinline__ uint32_t ld_at(const uint32_t* base, uint32_t byte_off) {
+  typedef const uint32_t __attribute__((address_space(1))) * gptr;
+  typedef const char __attribute__((address_space(1))) * bptr;
+  bptr b = (bptr)base;
+  asm("" : "+s"(b));
+  return *(gptr)(b + byte_off);
+}
+__device__ __forceinline__ U4 ld4_at(const uint32_t* base, uint32_t byte_off) {
+  typedef const hcnn_word4 __attribute__((address_space(1))) * gptr;
+  typedef const char __attribute__((address_space(1))) * bptr;
+  bptr b = (bptr)base;
+  asm("" : "+s"(b));
+  const hcnn_word4 w = *(gptr)(b + byte_off);
+  U4 r; r.x = w.x; r.y = w.y; r.z = w.z; r.w = w.w;
+  return r;
+}
+__device__ __forceinline__ void st_at(uint32_t* base, uint32_t byte_off, uint32_t v) {
+  typedef uint32_t __attribute__((address_space(1))) * gptr;
+  typedef char __attribute__((address_space(1))) * bptr;
+  bptr b = (bptr)base;
+  asm("" : "+s"(b));
+  *(gptr)(b + byte_off) = v;
+}
+__device__ __forceinline__ void st4_at(uint32_t* base, uint32_t byte_off, U4 v) {
+  typedef hcnn_word4 __attribute__((address_space(1))) * gptr;
+  typedef char __attribute__((address_space(1))) * bptr;
+  bptr b = (bptr)base;
+  asm("" : "+s"(b));
+  *(gptr)(b + byte_off) = hcnn_word4{v.x, v.y, v.z, v.w};
+}
+#pragma clang diagnostic pop
+#else
+template <class T> HCNN_HD T ldc_at(const T* table, uint32_t byte_off) { return table[byte_off / sizeof(T)]; }
+HCNN_HD uint32_t ld_at(const uint32_t* base, uint32_t byte_off) { return base[byte_off / 4]; }
+HCNN_HD U4 ld4_at(const uint32_t* base, uint32_t byte_off) { return *reinterpret_cast<const U4*>(base + byte_off / 4); }
+HCNN_HD void st_at(uint32_t* base, uint32_t byte_off, uint32_t v) { base[byte_off / 4] = v; }
+HCNN_HD void st4_at(uint32_t* base, uint32_t byte_off, U4 v) { *reinterpret_cast<U4*>(base + byte_off / 4) = v; }
+#endif
+
+// Division of a workgroup index by a launch constant: m = floor(2^32 / d), or 2^32 - 1 for d = 1 (the estimate is the
+// quotient or one less).  (A run-time divisor otherwise costs a floating-point reciprocal and its corrections in every phase.)
+struct FastDiv { uint32_t d, m; };
+inline FastDiv fast_div(uint32_t d) { return FastDiv{d, d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / d)}; }
+HCNN_HD uint32_t quot(uint32_t x, FastDiv f) {
+#if defined(HCNN_HOSTEMU)
+  const uint32_t q = (uint32_t)(((uint64_t)x * f.m) >> 32);
+#else
+  const uint32_t q = __umulhi(x, f.m);
+#endif
+  return x - q * f.d >= f.d ? q + 1 : q;
+}
+HCNN_HD uint32_t rem(uint32_t x, FastDiv f) { return x - quot(x, f) * f.d; }
+
+// The value as it is, but not one the compiler can trace back to where it came from.
+template <class T>
+HCNN_HD T untraced(T x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(x));
+#endif
+  return x;
+}
+
+// x, known to be the same in all lanes of a wave, as a scalar
+HCNN_HD uint32_t wave_uniform(uint32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+#else
+  return x;
+#endif
+}
+
 // kMinWavesPerSimd (optional): occupancy the register allocation of the kernel must allow
 template <class K, class = void> struct MinWavesPerSimd { static constexpr int value = 1; };
 template <class K> struct MinWavesPerSimd<K, std::void_t<decltype(K::kMinWavesPerSimd)>> { static constexpr int value = K::kMinWavesPerSimd; };

@@ -232,6 +232,46 @@ def check_square_relin(backend, n, k, n_random=2, n_genuine=1, seed_id=1, chunk=
     s.ctx.close()
 
 
+def check_transform_ranges(backend, n, t=65537):
+    """The lazily reduced signed ranges of the transforms at their ends: ciphertext primes from both ends of
+    (2^29, 2^30) (a digit of the largest is close to twice the smallest), rows of p - 1 and of alternating 0 and
+    p - 1; transforms, squaring in every form and the general product against the oracle."""
+    step = 2 * n
+    small = []
+    v = (1 << 29) // step * step + step + 1
+    while len(small) < 2:
+        if fv.is_prime(v):
+            small.append(v)
+        v += step
+    large = fv.ntt_primes(n, 8)
+    q = [large[0], small[0], large[1], small[1]]
+    p = large[2:2 + _capi.min_aux_count(backend.lib, n, q, t, large[2:])]
+    octx, ctx = fv.Context(n, q, t), backend.make_ctx(n, q, p, t)
+    rng = gen.rng_for(1, 17)
+    x = gen.uniform_residues(rng, q, n, lead=(3, 2))
+    for l, m in enumerate(q):
+        x[0, :, l] = m - 1
+        x[1, 0, l, 0::2], x[1, 0, l, 1::2], x[1, 1, l] = 0, m - 1, m - 1
+    buf = backend.dev(x.reshape(6, len(q), n))
+    ctx.ntt_fwd(buf)
+    hat = backend.host(buf).copy()
+    for r in (0, 2, 4):
+        for l, m in enumerate(q):
+            assert np.array_equal(hat[r, l], fv.ntt_forward(x.reshape(6, len(q), n)[r, l], m)), ("forward", n, r, l)
+    ctx.ntt_inv(buf)
+    assert np.array_equal(backend.host(buf).reshape(x.shape), x), ("round trip", n)
+    kr = gen.key_randomness(rng, q, n)
+    evk = fv.keygen(octx, kr["s"], kr["a"], kr["e"], kr["a_evk"], kr["e_evk"])[1]
+    ctx.set_relin_key(backend.dev(evk))
+    want = np.stack([fv.square_relin(octx, c, evk) for c in x])
+    for mode in (0, 2, 1):
+        ctx.set_fusion(mode)
+        assert np.array_equal(backend.host(ctx.ct_square_relin(backend.dev(x))), want), ("square", n, mode)
+    got = backend.host(ctx.ct_mul_relin(backend.dev(x[:1]), backend.dev(x[1:2])))
+    assert np.array_equal(got[0], fv.hmult(octx, x[0], x[1], evk)), ("product", n)
+    ctx.close()
+
+
 def check_mul_relin(backend, n, k, seed_id=1, force_exact=False, check_decrypt=True):
     """General HMult on genuine and on uniformly random ciphertext pairs."""
     s = Setup(backend, n, k, seed_id=seed_id, stream=3)

@@ -48,6 +48,12 @@ def test_ntt_all_sizes(backend, n, k, n_polys, rows):
     pc.check_ntt(backend, n, k, n_polys, rows)
 
 
+@pytest.mark.parametrize("n", [1024, 2048])
+def test_transform_ranges_at_both_ends_of_the_prime_interval(backend, n):
+    say("transform ranges n=%d" % n)
+    pc.check_transform_ranges(backend, n)
+
+
 @pytest.mark.parametrize("n,k", [(1024, 2), (2048, 3)])
 def test_keygen_encrypt_decrypt(backend, n, k):
     say("keygen/encrypt/decrypt n=%d k=%d" % (n, k))
