@@ -475,10 +475,12 @@ struct MacArgs {
   const int32_t* w;       // [G][F][T]
   uint32_t* out;          // [F][G][2][k][n]
   const Mod* mods;        // [k]
+  const NttLimb* limbs;   // [k]
   uint32_t k, n;
   uint32_t n_in, G, F, T;
   int32_t w_abs_max;
   uint32_t chunk;         // terms between reductions of the signed 64-bit accumulators
+  uint32_t steps;         // MacMfma: tiles per wave
   unsigned long long* bad_counter;
 };
 // Fallback for gather rows too long to stage in LDS: indices and weights are read from global
@@ -673,6 +675,205 @@ struct MacKernel {
       }
     }
   }
+};
+
+// Many filters: the sums as matrix products on the byte planes of the residues (v_mfma_i32_16x16x64_i8).
+// With F filters every gathered residue feeds F multiply-adds; at 16 filters the kernel above is bound by their rate (576 terms:
+// 28 T multiply-adds/s of 34).  Here a residue is split into four bytes; a matrix instruction multiplies 16 filters x 64 terms
+// of 8-bit weights with 64 terms x 16 coefficients of one byte plane, and the vector unit is left with the 4 x 4 byte
+// transposition that brings four terms of a coefficient into one operand word (8 v_perm_b32 per four residues) and with
+// the recombination of the four 32-bit sums of an output.
+//   wave            one group g, tiles of 64 consecutive coefficients; a lane holds 4 of them (one 16-byte load per term)
+//   lane            lg = lane / 16, ln = lane % 16: coefficients 4 ln .. 4 ln + 3; of every 16 terms those 4 lg .. 4 lg + 3
+//   operand word    quad step q of a chunk of 64 terms: terms 16 q + 4 lg .. + 3 of filter ln (weights) or of coefficient
+//                   4 ln + s (data, s = 0..3); weights and data use the same order of terms
+//   result          sums of filters 4 lg .. 4 lg + 3 at coefficient 4 ln + s
+// Bytes 0..2 of a residue are taken less 128 (byte 3 is below 64); the sums start at 128 * (sum of the weights) instead of 0.
+// The GB groups of a workgroup are neighbours (kernel placements that share most of their inputs): their waves run through
+// the terms together and find each other's inputs in the compute unit's cache.  The XCD order of the tiles is that of MacKernel.
+// A term row is padded to a multiple of 16 with zero-weight terms on its last input.
+// Bound: the gather.  576 terms x 16 filters over 64 groups at n = 8192, k = 10: 3.54 -> 1.95 ms, 24 GB gathered at 23
+// bytes per clock and compute unit, vector unit 44 % used, matrix unit 9 %.  Measured and left out: a second register
+// buffer of inputs (spills: 2.6 ms); the waves kept in step by a barrier per chunk (L2 requests halved, 2.0 ms: the
+// waits it adds cost what it saves); eight groups on eight waves (2.0 ms).
+constexpr uint32_t kMfmaMaxSum = 1u << 20;     // T * |w| <= 2^20: sums of weight * byte stay below 2^28, and 4 * 2^28 * p/2
+                                               // leaves the Montgomery step within (-p, p)
+template <int GB>
+struct MacMfma {
+  // (one group: the workgroup's waves take tiles, and eight of them share the staged tables)
+  static constexpr int kThreads = GB == 1 ? 512 : 256;
+  static constexpr int kPhases = 2;
+  static constexpr int kMinWavesPerSimd = 2;     // 64 registers of inputs in flight, 64 of sums
+  struct Regs {};
+  static constexpr uint32_t kTile = 64, kStreams = kThreads / 64 / GB;      // coefficients per wave and step; waves on one group
+  HCNN_HOSTDEV static uint32_t terms(uint32_t T) { return (T + 15) / 16 * 16; }
+  HCNN_HOSTDEV static uint32_t chunks(uint32_t T) { return (T + 63) / 64; }
+  HCNN_HOSTDEV static uint32_t group_words(uint32_t T) { return chunks(T) * (64 + 256); }   // offsets and weights of one group
+  static size_t lds_bytes(size_t T) { return (size_t)GB * group_words((uint32_t)T) * 4; }
+  static uint32_t tile_blocks(const MacArgs& a) {
+    const uint32_t per = a.steps * kStreams, tiles = 2 * a.k * a.n / kTile;
+    return (tiles + per - 1) / per;
+  }
+  static size_t grid(const MacArgs& a) {
+    return (size_t)kXcds * ((tile_blocks(a) + kXcds - 1) / kXcds) * ((a.G + GB - 1) / GB);
+  }
+
+  template <int PH>
+  HCNN_HD static void phase(const MacArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
+    const uint32_t g_blocks = (a.G + GB - 1) / GB;
+    const uint32_t xcd = bid % kXcds, local = bid / kXcds;
+    const uint32_t tb = (local / g_blocks) * kXcds + xcd, g0 = local % g_blocks * GB;
+    const uint32_t tiles = 2 * a.k * a.n / kTile;
+    const uint32_t tile0 = tb * a.steps * kStreams;
+    if (tile0 >= tiles) return;                                       // padding blocks (whole block)
+    const uint32_t words = group_words(a.T), T16 = terms(a.T);
+    if constexpr (PH == 0) {
+      for (uint32_t gi = 0; gi < GB && g0 + gi < a.G; ++gi) {
+        const uint32_t* idx = a.idx + (size_t)(g0 + gi) * a.T;
+        const int32_t* w = a.w + (size_t)(g0 + gi) * a.F * a.T;
+        uint32_t* l_off = lds + gi * words;
+        uint32_t* l_w = l_off + chunks(a.T) * 64;
+        for (uint32_t t = tid; t < T16; t += kThreads) {
+          const bool pad = t >= a.T;
+          uint32_t src = idx[pad ? a.T - 1 : t];
+          if (src >= a.n_in) {
+            src = 0;
+            if (tb == 0 && !pad) atomic_inc64(a.bad_counter);
+          }
+          l_off[t] = src * (2u * a.k * a.n / 4);       // in 16-byte units (the host checked that it fits)
+        }
+        for (uint32_t x = tid; x < chunks(a.T) * 256; x += kThreads) {
+          const uint32_t q = x % 4, lane = x / 4 % 64, f = lane % 16;
+          const uint32_t t0 = x / 256 * 64 + q * 16 + lane / 16 * 4;
+          uint32_t packed = 0;
+          for (uint32_t b = 0; b < 4; ++b) {
+            const uint32_t t = t0 + b;
+            if (t >= a.T || f >= a.F) continue;
+            int32_t wf = w[(size_t)f * a.T + t];
+            if (wf > a.w_abs_max || wf < -a.w_abs_max) {
+              wf = 0;
+              if (tb == 0) atomic_inc64(a.bad_counter);
+            }
+            if (idx[t] >= a.n_in) wf = 0;
+            packed |= (uint32_t)(wf & 0xff) << (8 * b);
+          }
+          l_w[x] = packed;
+        }
+      }
+    } else {
+      const uint32_t wave = wave_uniform((uint32_t)tid / 64), lane = (uint32_t)tid % 64;
+      const uint32_t gi = wave % GB, g = g0 + gi, lg = lane / 16, ln = lane % 16;
+      if (g >= a.G) return;
+      const uint32_t* l_off = lds + gi * words;
+      const uint32_t* l_w = l_off + chunks(a.T) * 64;
+      const size_t ct_words = (size_t)2 * a.k * a.n;
+      const uint32_t n_chunks = chunks(a.T);
+      Sums wsum;                                                      // 128 * sum of the weights, per filter
+      weight_sums(l_w, n_chunks, lane, wsum);
+      for (uint32_t st = 0; st < a.steps; ++st) {
+        const uint32_t tile = tile0 + st * kStreams + wave / GB;
+        if (tile >= tiles) break;
+        const uint32_t limb = tile / (a.n / kTile) % a.k;
+        const NttLimb L = ldc(a.limbs, limb);
+        const uint32_t pos = tile * kTile + ln * 4;                   // word inside a ciphertext
+        Sums acc[4][4];                                               // [s][byte]
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[s][j] = j < 3 ? wsum : Sums{};
+        for (uint32_t c = 0; c < n_chunks; ++c) {
+          if (c * 64 + 64 <= T16) chunk<4>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
+          else if (c * 64 + 48 <= T16) chunk<3>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
+          else if (c * 64 + 32 <= T16) chunk<2>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
+          else chunk<1>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const uint32_t f = lg * 4 + r;
+          if (f >= a.F) break;
+          uint32_t o[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            int64_t t = (int64_t)acc[s][0].v[r] * L.rc;
+            t += (int64_t)acc[s][1].v[r] * L.byte_c[0];
+            t += (int64_t)acc[s][2].v[r] * L.byte_c[1];
+            t += (int64_t)acc[s][3].v[r] * L.byte_c[2];
+            o[s] = canon_p(sredc(t, L.m.p, L.pinv), L.m.p);
+          }
+          U4 u;
+          u.x = o[0]; u.y = o[1]; u.z = o[2]; u.w = o[3];
+          *reinterpret_cast<U4*>(a.out + ((size_t)f * a.G + g) * ct_words + pos) = u;
+        }
+      }
+    }
+  }
+
+#if defined(HCNN_HOSTEMU)
+  // The checker runs lane by lane: every lane forms its own 4 filters x 4 coefficients from the staged tables.
+  struct Sums { int32_t v[4] = {0, 0, 0, 0}; };
+  static int32_t weight(const uint32_t* l_w, uint32_t f, uint32_t t) {          // term t of a chunk
+    return (int8_t)(l_w[((t / 4 % 4 * 16 + f) * 4) + t / 16] >> (8 * (t % 4)));
+  }
+  static void weight_sums(const uint32_t* l_w, uint32_t n_chunks, uint32_t lane, Sums& out) {
+    for (int r = 0; r < 4; ++r)
+      for (uint32_t t = 0; t < n_chunks * 64; ++t) out.v[r] += 128 * weight(l_w + t / 64 * 256, lane / 16 * 4 + r, t % 64);
+  }
+  template <int Q>
+  static void chunk(const uint32_t* in, const uint32_t* l_off, const uint32_t* l_w, uint32_t lane, Sums (&acc)[4][4]) {
+    for (uint32_t t = 0; t < 16 * Q; ++t)
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t x = in[(size_t)l_off[t] * 4 + s];
+        for (int r = 0; r < 4; ++r)
+          for (int j = 0; j < 4; ++j)
+            acc[s][j].v[r] += weight(l_w, lane / 16 * 4 + r, t) * ((int32_t)(x >> (8 * j) & 0xff) - (j < 3 ? 128 : 0));
+      }
+  }
+#elif !defined(__HIP_DEVICE_COMPILE__)
+  // (the host pass of the device build only parses the callers)
+  struct Sums { int32_t v[4] = {0, 0, 0, 0}; };
+  __device__ static void weight_sums(const uint32_t*, uint32_t, uint32_t, Sums&);
+  template <int Q> __device__ static void chunk(const uint32_t*, const uint32_t*, const uint32_t*, uint32_t, Sums (&)[4][4]);
+#else
+  typedef int32_t Vec __attribute__((ext_vector_type(4)));
+  struct Sums { Vec v = {0, 0, 0, 0}; };
+  __device__ __forceinline__ static void weight_sums(const uint32_t* l_w, uint32_t n_chunks, uint32_t lane, Sums& out) {
+    const Vec ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    for (uint32_t c = 0; c < n_chunks; ++c)
+      out.v = __builtin_amdgcn_mfma_i32_16x16x64_i8(reinterpret_cast<const Vec*>(l_w + c * 256)[lane], ones, out.v, 0, 0, 0);
+    out.v *= 128;
+  }
+  // Q quad steps of 16 terms; operand words beyond them are zero
+  template <int Q>
+  __device__ __forceinline__ static void chunk(const uint32_t* in, const uint32_t* l_off, const uint32_t* l_w, uint32_t lane,
+                                               Sums (&acc)[4][4]) {
+    typedef const hcnn_word4 __attribute__((address_space(1))) * gptr;
+    const gptr g = (gptr)(const hcnn_word4*)in;
+    hcnn_word4 x[Q][4];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const hcnn_word4 off = *reinterpret_cast<const hcnn_word4*>(l_off + q * 16 + lane / 16 * 4);
+      x[q][0] = g[off.x]; x[q][1] = g[off.y]; x[q][2] = g[off.z]; x[q][3] = g[off.w];
+    }
+    const Vec w = reinterpret_cast<const Vec*>(l_w)[lane];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      Vec b[4] = {};
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const uint32_t lo01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x05010400u);    // a0 b0 a1 b1
+        const uint32_t hi01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x07030602u);    // a2 b2 a3 b3
+        const uint32_t lo23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x05010400u);
+        const uint32_t hi23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x07030602u);
+        b[0][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u);
+        b[1][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u);
+        b[2][q] = (int32_t)(__builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u);
+        b[3][q] = (int32_t)__builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[s][j].v = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, b[j], acc[s][j].v, 0, 0, 0);
+    }
+  }
+#endif
 };
 
 // ---------------------------------------------------------------- helpers for KeyGen / Encrypt / Decrypt

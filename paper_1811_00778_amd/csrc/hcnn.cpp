@@ -334,6 +334,7 @@ template <int A> struct KernelClass<RelinMacKernel<A>> { static constexpr int id
 template <int A, int B, int C> struct KernelClass<RelinFused<A, B, C>> { static constexpr int id = HCNN_PROF_RELIN_FUSED; };
 template <int A, int B> struct KernelClass<TensorFused<A, B>> { static constexpr int id = HCNN_PROF_TENSOR; };
 template <int F, bool S> struct KernelClass<MacKernel<F, S>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
+template <int B> struct KernelClass<MacMfma<B>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <int F> struct KernelClass<MacKernelDirect<F>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 
 int take_event(hcnn_ctx* c, hcnn_event_t* ev) {
@@ -499,6 +500,7 @@ int build_tables(hcnn_ctx* c) {
     nl.zero = 0;
     nl.w1 = mont(tw(0, 1));
     nl.key_scale = mont(r32);
+    for (int j = 0; j < 3; ++j) nl.byte_c[j] = mont(1u << (8 * (j + 1)));
     auto inv_root = [&](uint32_t scale) {
       auto sc = [&](uint32_t x) { return mont(h_mulmod(x, scale, p)); };
       const uint32_t w = tw(1, 1), v2 = tw(1, 2), u2 = tw(1, 3);
@@ -710,7 +712,32 @@ int mac_launch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
   return run<MacKernelDirect<FT>>(c, grid, 0, a);
 }
 
+template <int GB>
+int mac_mfma_launch(hcnn_ctx* c, const MacArgs& a) {
+  // tiles per wave: up to 8, so that staging the group's tables is spread over many coefficients, fewer while the
+  // launch would not hold several rounds of workgroups
+  MacArgs b = a;
+  b.steps = 8;
+  while (b.steps > 1 && MacMfma<GB>::grid(b) < 4 * (size_t)c->compute_units) b.steps /= 2;
+  return run<MacMfma<GB>>(c, MacMfma<GB>::grid(b), MacMfma<GB>::lds_bytes(a.T), b);
+}
+
 int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
+  const bool offsets_fit = (uint64_t)a.n_in * 2 * a.k * a.n / 4 <= 0xffffffffull;   // 16-byte offsets kept in 32 bits
+  const size_t lds_max = std::min<size_t>(64 * 1024, c->max_lds);
+  // The matrix form: where the multiply-adds weigh more than the byte transposition (measured, matrix against vector form,
+  // us: 16 filters x 25 terms 600 / 666, x 32 553 / 638, x 144 543 / 884, x 576 1950 / 3540; 8 x 144 490 / 497, 8 x 32
+  // 464 / 347); where the vector form's workgroups (1024 coefficients of one group) do not fill the chip (one group, 845
+  // terms x 10 filters at n = 8192, k = 8: 87 / 141; 1536 workgroups at n = 32768, k = 24 do: 1235 / 1188); and where the
+  // vector form could not stage its row (1600 x 16: 1.42 / 20.2 ms).
+  const bool many = (a.F >= 10 && a.T >= 96) || (a.F >= 14 && a.T >= 25), few_blocks = grid < 4 * (size_t)c->compute_units;
+  const bool long_row = MacKernel<1>::lds_bytes(a.F, a.T) > lds_max;
+  if ((a.G > 1 ? many : a.F >= 8 && a.T >= 64 && few_blocks) || long_row)
+  if (a.w_abs_max <= 127 && (uint64_t)a.T * (uint32_t)a.w_abs_max <= kMfmaMaxSum && offsets_fit) {
+    if (a.G >= 4 && MacMfma<4>::lds_bytes(a.T) <= lds_max) return mac_mfma_launch<4>(c, a);
+    if (a.G >= 2 && MacMfma<2>::lds_bytes(a.T) <= lds_max) return mac_mfma_launch<2>(c, a);
+    if (MacMfma<1>::lds_bytes(a.T) <= lds_max) return mac_mfma_launch<1>(c, a);
+  }
   switch (a.F) {
     case 1: return mac_launch<1>(c, grid, a);
     case 2: return mac_launch<2>(c, grid, a);
@@ -938,7 +965,7 @@ int hcnn_ct_scalar_mac(hcnn_ctx* c, const uint32_t* in, size_t n_in, const uint3
   if (G > (size_t)0x7fffffff / tiles) return HCNN_ERR_ARG;
   MacArgs a;
   a.in = in; a.idx = idx; a.w = w; a.out = out;
-  a.mods = c->d_mods; a.k = c->k; a.n = c->n;
+  a.mods = c->d_mods; a.limbs = c->d_limbs; a.k = c->k; a.n = c->n; a.steps = 0;
   a.n_in = (uint32_t)n_in; a.G = (uint32_t)G; a.F = (uint32_t)F; a.T = (uint32_t)T;
   a.w_abs_max = w_abs_max;
   // partial sums stay below 2^62 in magnitude: chunk * w_abs_max * 2^30 + 2^30 <= 2^62

@@ -54,6 +54,7 @@ struct NttLimb {
                         // negation into a product and a 64-bit subtraction)
   int32_t w1;           // forward twiddle of node 1 (the radix-2 stage of an odd log2(n))
   int32_t key_scale;    // 2^64 mod p, centred: sredc(x * key_scale) = x * 2^32
+  int32_t byte_c[3];    // 2^40, 2^48, 2^56 mod p, centred (byte planes of MacMfma)
   InvRoot inv;          // scale = n^-1
   InvRoot inv_r;        // scale = n^-1 * 2^32: the tensor-forming loads leave a factor 2^-32 on every product
 };

@@ -163,6 +163,39 @@ def check_scalar_mac(backend, n, k, seed_id=1):
     s.ctx.close()
 
 
+def check_scalar_mac_matrix_form(backend, G, F, T, bound, n=1024, k=2):
+    """Rows and filter counts that take the matrix form of the scalar MAC (edges of its chunks of 64 terms and of its
+    groups of workgroup neighbours), extreme residues and weights, then out-of-range table entries."""
+    s = Setup(backend, n, k, with_keys=False)
+    n_in = 11
+    cts = gen.uniform_residues(s.rng, s.q, n, lead=(n_in, 2))
+    for l, p in enumerate(s.q):
+        cts[0, :, l] = p - 1
+        cts[1, :, l] = 0
+    dcts = backend.dev(cts)
+    idx = s.rng.integers(0, n_in, size=(G, T)).astype(np.uint32)
+    idx[0] = 0
+    w = gen.int_weights(s.rng, (G, F, T), bound)
+    w[0, 0], w[0, F - 1], w[G - 1, F // 2] = bound, -bound, 0
+
+    def want(g, f, skip=()):
+        keep = [t for t in range(T) if t not in skip]
+        return fv.scalar_mac(s.octx, cts, idx[g, keep], w[g, f, keep])
+
+    out = backend.host(s.ctx.ct_scalar_mac(dcts, backend.dev(idx), backend.dev(w), bound))
+    for g in range(G):
+        for f in range(F):
+            assert np.array_equal(out[f, g], want(g, f)), ("matrix form", G, F, T, g, f)
+    assert s.ctx.bad_inputs() == 0
+    bad_idx, bad_w = idx.copy(), w.copy()
+    bad_idx[G - 1, T - 1], bad_w[G - 1, F - 1, 0] = n_in, bound + 1
+    out = backend.host(s.ctx.ct_scalar_mac(dcts, backend.dev(bad_idx), backend.dev(bad_w), bound))
+    assert np.array_equal(out[F - 1, G - 1], want(G - 1, F - 1, (0, T - 1)))
+    assert np.array_equal(out[0, G - 1], want(G - 1, 0, (T - 1,)))
+    assert s.ctx.bad_inputs() == 2
+    s.ctx.close()
+
+
 def check_mac_linear_in_ntt_domain(backend, n, k, seed_id=1):
     """MAC of transformed inputs equals the transform of the MAC."""
     s = Setup(backend, n, k, seed_id=seed_id, with_keys=False)

@@ -51,6 +51,12 @@ def test_scalar_mac(backend, n, k):
     pc.check_mac_linear_in_ntt_domain(backend, n, k)
 
 
+@pytest.mark.parametrize("G,F,T,bound", [(5, 16, 25, 7), (4, 14, 31, 127), (6, 10, 96, 127), (3, 11, 97, 15), (2, 16, 130, 31),
+                                         (1, 8, 64, 127), (1, 13, 81, 7), (1, 16, 1000, 127), (9, 16, 48, 1)])
+def test_scalar_mac_matrix_form(backend, G, F, T, bound):
+    pc.check_scalar_mac_matrix_form(backend, G, F, T, bound)
+
+
 def test_square_relin_tiny_config(backend):
     pc.check_square_relin(backend, 1024, 2)
 
