@@ -927,13 +927,10 @@ struct PointMulKernel {
   }
 };
 
-// out[row] = x[row] + small[poly(row)] (+ scale_l * msg[poly(row)]) ; rows are [count][k][n]
+// out[row] = x[row] + small[poly(row)] ; rows are [count][k][n]
 struct AddSmallArgs {
   const uint32_t* x;
   const int32_t* small;        // [count][n]
-  const uint32_t* msg;         // [count][n] or null
-  const uint64_t* msg64;       // [count][n] or null: the plaintext in 64-bit words (plaintext modulus above 2^32)
-  const ShoupConst* scale;     // [k] (floor(q/t) mod q_l) or null
   uint32_t* out;
   const Mod* mods;
   uint32_t k, n;
@@ -953,9 +950,7 @@ struct AddSmallKernel {
     const uint32_t l = (uint32_t)(row % a.k);
     const Mod m = ldc(a.mods, l);
     const uint32_t sv = small_to_res(a.small[poly * a.n + c], m);
-    uint32_t r = a.subtract_small ? sub_mod(a.x[row * a.n + c], sv, m.p) : add_mod(a.x[row * a.n + c], sv, m.p);
-    if (a.msg) r = add_mod(r, shoup_mul(reduce32(a.msg[poly * a.n + c], m), ldc(a.scale, l), m.p), m.p);
-    if (a.msg64) r = add_mod(r, shoup_mul(reduce64(a.msg64[poly * a.n + c], m), ldc(a.scale, l), m.p), m.p);
+    const uint32_t r = a.subtract_small ? sub_mod(a.x[row * a.n + c], sv, m.p) : add_mod(a.x[row * a.n + c], sv, m.p);
     a.out[(poly * a.out_poly_rows + a.out_row0 + l) * a.n + c] = r;
   }
 };
@@ -981,38 +976,17 @@ struct AddDiagKernel {
   }
 };
 
-// c = a + b over `rows` rows [..][k][n]
-struct AddRowsArgs {
-  const uint32_t* a;
-  const uint32_t* b;
-  uint32_t* c;
-  const Mod* mods;
-  uint32_t k, n;
-  uint32_t a_poly_rows, a_row0;   // a row = (poly*a_poly_rows + a_row0 + l); b and c are dense [poly][k]
-};
-struct AddRowsKernel {
-  static constexpr int kThreads = kEwThreads;
-  static constexpr int kPhases = 1;
-  struct Regs {};
-  template <int PH>
-  HCNN_HD static void phase(const AddRowsArgs& a, unsigned bid, int tid, uint32_t*, Regs&) {
-    const uint32_t per_row = a.n / kThreads;
-    const size_t row = bid / per_row;
-    const uint32_t c = (bid % per_row) * kThreads + tid;
-    const size_t poly = row / a.k;
-    const uint32_t l = (uint32_t)(row % a.k);
-    const uint32_t p = ldc(a.mods, l).p;
-    a.c[row * a.n + c] = add_mod(a.a[(poly * a.a_poly_rows + a.a_row0 + l) * a.n + c], a.b[row * a.n + c], p);
-  }
-};
-
-// Decrypt rounding: x [count][k][n] (c0 + c1*s mod q) -> m = round(t*x/q) mod t.
-// r = [t*x]_q centred is converted to the single modulus t; m = -r * q^-1 mod t.
+// Decrypt rounding: x [count][k][n] (c0 + c1*s mod q) -> m = round(t*x/q) mod t, t of up to 47 bits.
+// r = [t*x]_q centred is converted to the single modulus t; m = -r * q^-1 mod t = sum_i z_i * b_i + v * b_k with
+// b_i = -(q/q_i) q^-1 and b_k = (q mod t) q^-1 = 1 mod t.  The constants are cut into 16-bit pieces: every piece's sum stays
+// below (k + 1) 2^46, and three 64-bit remainders put an output together, whatever k is.
 struct DecRoundArgs {
   const uint32_t* x;
-  uint32_t* m_out;
-  BConvDev bc;             // src q (zmul = t*(q/q_i)^-1, xmul = t), dst {t}: Bp = q/q_i mod t, Vp = t - (q mod t)
-  uint32_t t, neg_qinv_t;  // -q^-1 mod t
+  uint32_t* m_out;         // 32-bit plaintext words, or null:
+  uint64_t* m_out64;       // 64-bit ones
+  BConvDev bc;             // source side only (zmul = t*(q/q_i)^-1, xmul = t)
+  const uint32_t* tab;     // [k][3]: 16-bit pieces of b_i, least significant first
+  uint64_t t;
   uint32_t n;
   uint32_t band;
   unsigned long long* fallback_counter;
@@ -1033,56 +1007,18 @@ struct DecRoundKernel {
     uint32_t* gcol = lds + (size_t)ks * kThreads + tid;
     auto in = [&](uint32_t i) { return src[(size_t)i * n]; };
     const uint32_t v = bconv_prepare(a.bc, in, zcol, gcol, kThreads, a.band, a.fallback_counter);
-    // the destination modulus t is small: plain 64-bit remainder (test helper, not tuned)
-    uint64_t acc = ((uint64_t)v * ldc(a.bc.Vp, 0)) % a.t;
-    for (uint32_t i = 0; i < ks; ++i) acc = (acc + (uint64_t)zcol[i * kThreads] * ldc(a.bc.Bp, i)) % a.t;
-    a.m_out[poly * n + c] = (uint32_t)((acc * a.neg_qinv_t) % a.t);
-  }
-};
-
-// Decrypt rounding for a plaintext modulus of up to 47 bits (64-bit plaintext words).  Same conversion as above
-// with the destination arithmetic done modulo t in 64-bit words: a 32-bit by 47-bit product is formed from
-// two 16-bit halves, each partial product below 2^63.
-struct DecRoundWideArgs {
-  const uint32_t* x;
-  uint64_t* m_out;
-  BConvDev bc;             // source side only (zmul = t*(q/q_i)^-1, xmul = t)
-  const uint64_t* tab;     // [ks + 2]: (q/q_i) mod t for i < ks, then t - (q mod t), then -q^-1 mod t
-  uint64_t t;
-  uint32_t n;
-  uint32_t band;
-  unsigned long long* fallback_counter;
-};
-HCNN_HD uint64_t mul32_mod_wide(uint32_t a, uint64_t b, uint64_t t) {     // a*b mod t for b < t < 2^47
-  uint64_t r = ((uint64_t)(a >> 16) * b) % t;
-  r = (r << 16) % t;
-  return (r + ((uint64_t)(a & 0xffffu) * b) % t) % t;
-}
-HCNN_HD uint64_t mul_mod_wide(uint64_t a, uint64_t b, uint64_t t) {       // a*b mod t for a, b < t < 2^47
-  uint64_t r = mul32_mod_wide((uint32_t)(a >> 32), b, t);                  // a = hi*2^32 + lo
-  r = (r << 16) % t;
-  r = (r << 16) % t;
-  return (r + mul32_mod_wide((uint32_t)a, b, t)) % t;
-}
-struct DecRoundWideKernel {
-  static constexpr int kThreads = kEwThreads;
-  static constexpr int kPhases = 1;
-  struct Regs {};
-  static size_t lds_bytes(uint32_t ks) { return (size_t)2 * ks * kThreads * 4; }
-  template <int PH>
-  HCNN_HD static void phase(const DecRoundWideArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
-    const uint32_t ks = a.bc.ks, n = a.n;
-    const uint32_t per_poly = n / kThreads;
-    const size_t poly = bid / per_poly;
-    const uint32_t c = (bid % per_poly) * kThreads + tid;
-    const uint32_t* src = a.x + poly * ks * n + c;
-    uint32_t* zcol = lds + tid;
-    uint32_t* gcol = lds + (size_t)ks * kThreads + tid;
-    auto in = [&](uint32_t i) { return src[(size_t)i * n]; };
-    const uint32_t v = bconv_prepare(a.bc, in, zcol, gcol, kThreads, a.band, a.fallback_counter);
-    uint64_t acc = mul32_mod_wide(v, a.tab[ks], a.t);
-    for (uint32_t i = 0; i < ks; ++i) acc = (acc + mul32_mod_wide(zcol[i * kThreads], a.tab[i], a.t)) % a.t;
-    a.m_out[poly * n + c] = mul_mod_wide(acc, a.tab[ks + 1], a.t);
+    uint64_t s0 = v, s1 = 0, s2 = 0;
+    for (uint32_t i = 0; i < ks; ++i) {
+      const uint64_t z = zcol[i * kThreads];
+      s0 += z * ldc(a.tab, 3 * i);
+      s1 += z * ldc(a.tab, 3 * i + 1);
+      s2 += z * ldc(a.tab, 3 * i + 2);
+    }
+    uint64_t r = s2 % a.t;                       // below 2^47: the shifted sums stay below 2^63 + 2^52
+    r = ((r << 16) + s1) % a.t;
+    r = ((r << 16) + s0) % a.t;
+    if (a.m_out) a.m_out[poly * n + c] = (uint32_t)r;
+    else         a.m_out64[poly * n + c] = r;
   }
 };
 

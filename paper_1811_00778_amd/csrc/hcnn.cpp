@@ -277,9 +277,8 @@ struct hcnn_ctx {
   ShoupConst* d_delta = nullptr;    // [k] floor(q/t) mod q_l
   uint32_t* d_tq_inv = nullptr;     // [kp] t * q^-1 mod p_j
   BConvDev ext{}, to_p{}, to_q{}, dec{};
-  uint32_t neg_qinv_t = 0;
   uint32_t* d_gauss_t = nullptr;    // thresholds of the Gaussian sampler (uploaded on first use)
-  uint64_t* d_dec_wide = nullptr;   // plaintext modulus above 2^32: [k + 2] constants of the decrypt rounding
+  uint32_t* d_dec_tab = nullptr;    // [k][3] constants of the decrypt rounding
   unsigned long long* d_counters = nullptr;   // [2]
 
   uint32_t* d_evk_hat = nullptr;
@@ -472,39 +471,51 @@ int build_tables(hcnn_ctx* c) {
     quad[d].assign((size_t)L * (n / 2), R4Twiddle{0, 0, 0, 0});
     nuw[d].assign((size_t)L * (n / 2), 0);
   }
-  std::vector<uint32_t> pw(2 * (size_t)n);
+  // every constant is +-psi^e * 2^32 (a product of twiddles adds exponents, a sign is psi^n): one table of powers per prime
+  std::vector<int32_t> pw(2 * (size_t)n);
   for (uint32_t l = 0; l < L; ++l) {
     const uint32_t p = all[l];
-    const uint32_t psi = h_root_of_unity(n, p);
-    uint64_t v = 1;
-    for (uint32_t e = 0; e < 2 * n; ++e) { pw[e] = (uint32_t)v; v = v * psi % p; }
-    const uint32_t r32 = (uint32_t)((1ull << 32) % p);
+    const uint32_t psi = h_root_of_unity(n, p), r32 = (uint32_t)((1ull << 32) % p);
+    const uint32_t psi_s = h_shoup(psi, p).ws;
     auto centred = [&](uint32_t x) { return x > p / 2 ? (int32_t)x - (int32_t)p : (int32_t)x; };
     auto mont = [&](uint32_t x) { return centred(h_mulmod(x, r32, p)); };
-    // twiddle of a node: psi^brev(node) forward, its inverse backward
-    auto tw = [&](int dir, uint32_t node) {
-      const uint32_t e = h_brev(node, (int)c->logn);
-      return pw[dir ? 2 * n - e : e];
+    uint32_t v = r32;
+    for (uint32_t e = 0; e < n; ++e) {
+      pw[e] = centred(v);
+      pw[e + n] = -pw[e];
+      const uint32_t y = v * psi - (uint32_t)(((uint64_t)v * psi_s) >> 32) * p;
+      v = y >= p ? y - p : y;
+    }
+    // exponent of a node's twiddle: brev(node) forward, its negative backward
+    auto ex = [&](int dir, uint32_t node) {
+      const uint32_t x = h_brev(node, (int)c->logn);
+      return dir ? 2 * n - x : x;
     };
-    for (int d = 0; d < 2; ++d)
+    for (int d = 0; d < 2; ++d) {
+      R4Twiddle* q4 = quad[d].data() + (size_t)l * (n / 2);
+      int32_t* q1 = nuw[d].data() + (size_t)l * (n / 2);
       for (uint32_t s = odd; s + 2 <= c->logn; s += 2)
         for (uint32_t node = 1u << s; node < 2u << s; ++node) {
-          const uint32_t w = tw(d, node), tv = tw(d, 2 * node), u = tw(d, 2 * node + 1);
-          quad[d][(size_t)l * (n / 2) + node] = R4Twiddle{mont(w), mont(tv), mont(h_mulmod(tv, w, p)), mont(u)};
-          nuw[d][(size_t)l * (n / 2) + node] = mont(p - h_mulmod(u, w, p));
+          const uint32_t w = ex(d, node), ev = ex(d, 2 * node), u = ex(d, 2 * node + 1), m = 2 * n - 1;
+          q4[node] = R4Twiddle{pw[w & m], pw[ev & m], pw[(ev + w) & m], pw[u & m]};
+          q1[node] = pw[(u + w + n) & m];
         }
+    }
     NttLimb nl{};
     nl.m = h_mod(p);
     nl.rc = centred(r32);
     nl.pinv = h_neg_inv32(p);
     nl.zero = 0;
-    nl.w1 = mont(tw(0, 1));
+    nl.w1 = pw[ex(0, 1)];
     nl.key_scale = mont(r32);
     for (int j = 0; j < 3; ++j) nl.byte_c[j] = mont(1u << (8 * (j + 1)));
     auto inv_root = [&](uint32_t scale) {
-      auto sc = [&](uint32_t x) { return mont(h_mulmod(x, scale, p)); };
-      const uint32_t w = tw(1, 1), v2 = tw(1, 2), u2 = tw(1, 3);
-      return InvRoot{mont(scale), sc(w), sc(v2), sc(u2), sc(h_mulmod(v2, w, p)), sc(p - h_mulmod(u2, w, p))};
+      auto sc = [&](uint32_t e) {           // psi^e * scale * 2^32
+        const int32_t x = pw[e & (2 * n - 1)];
+        return centred(h_mulmod(x < 0 ? (uint32_t)(x + (int32_t)p) : (uint32_t)x, scale, p));
+      };
+      const uint32_t w = ex(1, 1), v2 = ex(1, 2), u2 = ex(1, 3);
+      return InvRoot{mont(scale), sc(w), sc(v2), sc(u2), sc(v2 + w), sc(u2 + w + n)};
     };
     const uint32_t ninv = h_inv(n % p, p);
     nl.inv = inv_root(ninv);
@@ -533,22 +544,17 @@ int build_tables(hcnn_ctx* c) {
   }
   if ((e = upload(c, delta, &c->d_delta))) return e;
 
-  // decryption: r = [t*x]_q converted to the modulus t
-  if (c->t < (1ull << 32)) {
-    const uint32_t t32 = (uint32_t)c->t;
-    BConvHost h = make_bconv(c->q, std::vector<uint32_t>{t32}, c->t, false, false);
-    if ((e = upload_bconv(c, h, &c->dec))) return e;
-    const uint32_t qinv_t = h_inv((uint32_t)q_mod_t, t32);
-    c->neg_qinv_t = (t32 - qinv_t) % t32;
-  } else {
-    // source side of the same conversion; the destination constants modulo the wide t live in 64-bit words
+  // decryption: r = [t*x]_q converted to the modulus t; the table carries the factor -q^-1 (DecRoundKernel)
+  {
     BConvHost h = make_bconv(c->q, std::vector<uint32_t>{}, c->t, false, false);
     if ((e = upload_bconv(c, h, &c->dec))) return e;
-    std::vector<uint64_t> tab;
-    for (uint32_t i = 0; i < c->k; ++i) tab.push_back(h_prod_mod64(c->q, (int)i, c->t));
-    tab.push_back((c->t - q_mod_t) % c->t);
-    tab.push_back((c->t - h_powmod64(q_mod_t, c->t - 2, c->t)) % c->t);
-    if ((e = upload(c, tab, &c->d_dec_wide))) return e;
+    const uint64_t qinv_t = h_powmod64(q_mod_t, c->t - 2, c->t);
+    std::vector<uint32_t> tab;
+    for (uint32_t i = 0; i < c->k; ++i) {
+      const uint64_t b = (c->t - h_mulmod64(h_prod_mod64(c->q, (int)i, c->t), qinv_t, c->t)) % c->t;
+      for (int piece = 0; piece < 3; ++piece) tab.push_back((uint32_t)(b >> (16 * piece)) & 0xffffu);
+    }
+    if ((e = upload(c, tab, &c->d_dec_tab))) return e;
   }
   if (c->kp) {
     BConvHost h_ext = make_bconv(c->q, c->p, 1, false, true);
@@ -598,12 +604,13 @@ struct NttRows {
   uint32_t in_group_rows, in_row0, out_group_rows, out_row0;
   const uint32_t* aux = nullptr;
   uint32_t own_limbs = 0;
+  const int32_t* small = nullptr;
 };
 
 template <int LOGN, int LOGR>
 int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
-  NttArgs a;
-  a.in = r.in; a.out = r.out; a.aux = r.aux;
+  NttArgs a{};
+  a.in = r.in; a.out = r.out; a.aux = r.aux; a.small = r.small;
   a.tw = inverse ? c->d_tw_inv : c->d_tw_fwd;
   a.limbs = c->d_limbs;
   a.cycle = fast_div(r.cycle); a.limb_base = r.limb_base;
@@ -633,6 +640,10 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
         using K = NttFwd<LOGN, LOGR, kNttStoreLazy, 1>;
         return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
       }
+      if (io == kNttSmallKey) {
+        using K = NttFwd<LOGN, LOGR, kNttSmallKey, 1>;
+        return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
+      }
       if (io == kNttStoreKey) {
         using K = NttFwd<LOGN, LOGR, kNttStoreKey, 1>;
         return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
@@ -644,6 +655,7 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   if (io == kNttLoadDigit)
     return run<NttFwd<LOGN, LOGR, kNttLoadDigit>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
   if (io == kNttStoreLazy) return run<NttFwd<LOGN, LOGR, kNttStoreLazy>>(c, r.rows, lds, a);
+  if (io == kNttSmallKey) return run<NttFwd<LOGN, LOGR, kNttSmallKey>>(c, r.rows, lds, a);
   if (io == kNttStoreKey) return run<NttFwd<LOGN, LOGR, kNttStoreKey>>(c, r.rows, lds, a);
   return run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a);
 }
@@ -791,6 +803,39 @@ int query_fused_occupancy(hcnn_ctx* c) {
   c->relin_fused_wgs = (uint32_t)r;
   c->tensor_fused_wgs = (uint32_t)t;
   return 0;
+}
+
+// Encryption and decryption rows: launches of CryptFused
+constexpr size_t kCryptRows = (size_t)1 << 26;     // rows of one launch
+template <int LOGN, int LOGR>
+int crypt_fused(hcnn_ctx* c, const CryptArgs& a, bool enc) {
+  const size_t grid = ntt_grouped_grid(a.n_rows, c->k), lds = NttGeom<LOGN, LOGR>::kLdsBytes;
+  if (enc) return run<CryptFused<LOGN, LOGR, true>>(c, grid, lds, a);
+  return run<CryptFused<LOGN, LOGR, false>>(c, grid, lds, a);
+}
+int crypt_rows(hcnn_ctx* c, CryptArgs a, size_t n_ct, bool enc) {
+  a.tw_fwd = c->d_tw_fwd; a.tw_inv = c->d_tw_inv; a.limbs = c->d_limbs; a.cycle = fast_div(c->k);
+  a.n_rows = (uint32_t)(n_ct * c->k);
+  switch (c->logn) {
+    case 10: return crypt_fused<10, 4>(c, a, enc);
+    case 11: return crypt_fused<11, 4>(c, a, enc);
+    case 12: return crypt_fused<12, 4>(c, a, enc);
+    case 13: return crypt_fused<13, 4>(c, a, enc);
+    case 14: return crypt_fused<14, 4>(c, a, enc);
+    case 15: return crypt_fused<15, 5>(c, a, enc);
+  }
+  return HCNN_ERR_N;
+}
+int secret_hat(hcnn_ctx* c, const int32_t* s, uint32_t* s_hat) {
+  NttRows r{nullptr, s_hat, c->k, c->k, 0, c->k, 0, c->k, 0};
+  r.small = s;
+  return ntt_rows(c, r, false, kNttSmallKey);
+}
+// x = c0 + c1*s mod q of cc ciphertexts
+int decrypt_rows(hcnn_ctx* c, const uint32_t* cts, size_t cc, const uint32_t* s_hat, uint32_t* x) {
+  CryptArgs a{};
+  a.key = s_hat; a.cts = cts; a.out = x;
+  return crypt_rows(c, a, cc, false);
 }
 
 // Median duration in milliseconds of `reps` launches of one kernel on the context's stream, one event pair each.
@@ -1217,7 +1262,7 @@ int hcnn_keygen(hcnn_ctx* c, const int32_t* s, const uint32_t* a, const int32_t*
   PointMulArgs pm{tmp, s_hat, tmp, c->d_mods, k, n, k, k, 1u};
   if ((e = run<PointMulKernel>(c, (size_t)k * bpp, 0, pm))) return e;
   if ((e = ntt_dense(c, tmp, tmp, k, k, true))) return e;
-  AddSmallArgs as{tmp, e_small, nullptr, nullptr, nullptr, pk_out, c->d_mods, k, n, 0u, 2 * k, 0u};
+  AddSmallArgs as{tmp, e_small, pk_out, c->d_mods, k, n, 0u, 2 * k, 0u};
   if ((e = run<AddSmallKernel>(c, (size_t)k * bpp, 0, as))) return e;
   if ((e = copy_d2d(pk_out + poly, a, poly * 4, c->stream))) return e;
   if (!evk_out) return HCNN_OK;
@@ -1231,7 +1276,7 @@ int hcnn_keygen(hcnn_ctx* c, const int32_t* s, const uint32_t* a, const int32_t*
   PointMulArgs pe{tmp, s_hat, tmp, c->d_mods, k, n, k * k, k, 1u};
   if ((e = run<PointMulKernel>(c, (size_t)k * k * bpp, 0, pe))) return e;
   if ((e = ntt_dense(c, tmp, tmp, (size_t)k * k, k, true))) return e;
-  AddSmallArgs ae{tmp, e_evk, nullptr, nullptr, nullptr, evk_out, c->d_mods, k, n, 1u, 2 * k, 0u};
+  AddSmallArgs ae{tmp, e_evk, evk_out, c->d_mods, k, n, 1u, 2 * k, 0u};
   if ((e = run<AddSmallKernel>(c, (size_t)k * k * bpp, 0, ae))) return e;
   AddDiagArgs ad{evk_out, s2, c->d_mods, k, n};
   if ((e = run<AddDiagKernel>(c, (size_t)k * bpp, 0, ad))) return e;
@@ -1248,29 +1293,17 @@ static int encrypt_impl(hcnn_ctx* c, const uint32_t* pk, const uint32_t* m, cons
   if (n_ct == 0) return HCNN_OK;
   const uint32_t k = c->k, n = c->n;
   const size_t rn = n, poly = (size_t)k * rn;
-  const size_t bpp = n / kEwThreads;
-  const size_t C = std::min<size_t>(n_ct, 64);
-  // scratch: pk_hat [2][k][n] | u_hat [C][k][n] | prod [C][k][n]
-  int e = ensure_work(c, (2 * poly + 2 * C * poly) * 4);
+  // scratch: pk_hat [2][k][n]
+  int e = ensure_work(c, 2 * poly * 4);
   if (e) return e;
-  uint32_t* pk_hat = c->work;
-  uint32_t* u_hat = pk_hat + 2 * poly;
-  uint32_t* prod = u_hat + C * poly;
-  if ((e = ntt_dense(c, pk, pk_hat, 2 * (size_t)k, k, false))) return e;
+  if ((e = ntt_dense(c, pk, c->work, 2 * (size_t)k, k, false, kNttStoreKey))) return e;
+  const size_t C = kCryptRows / k;               // rows of a launch fit its 32-bit indices
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
-    const size_t cc = std::min(C, n_ct - c0);
-    SmallToRnsArgs sr{u + c0 * rn, u_hat, c->d_mods, k, n};
-    if ((e = run<SmallToRnsKernel>(c, cc * bpp, 0, sr))) return e;
-    if ((e = ntt_dense(c, u_hat, u_hat, cc * k, k, false))) return e;
-    for (uint32_t b = 0; b < 2; ++b) {
-      PointMulArgs pm{u_hat, pk_hat + b * poly, prod, c->d_mods, k, n, (uint32_t)(cc * k), k, 0u};
-      if ((e = run<PointMulKernel>(c, cc * k * bpp, 0, pm))) return e;
-      if ((e = ntt_dense(c, prod, prod, cc * k, k, true))) return e;
-      AddSmallArgs as{prod, (b == 0 ? e1 : e2) + c0 * rn, (b == 0 && m) ? m + c0 * rn : nullptr,
-                      (b == 0 && m64) ? m64 + c0 * rn : nullptr,
-                      b == 0 ? c->d_delta : nullptr, ct_out + c0 * 2 * poly, c->d_mods, k, n, 0u, 2 * k, b * k};
-      if ((e = run<AddSmallKernel>(c, cc * k * bpp, 0, as))) return e;
-    }
+    CryptArgs a{};
+    a.key = c->work; a.u = u + c0 * rn; a.e1 = e1 + c0 * rn; a.e2 = e2 + c0 * rn;
+    a.msg = m ? m + c0 * rn : nullptr; a.msg64 = m64 ? m64 + c0 * rn : nullptr; a.scale = c->d_delta;
+    a.out = ct_out + c0 * 2 * poly;
+    if ((e = crypt_rows(c, a, std::min(C, n_ct - c0), true))) return e;
   }
   return HCNN_OK;
 }
@@ -1296,37 +1329,21 @@ static int decrypt_impl(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size
   const uint32_t k = c->k, n = c->n;
   const size_t rn = n, poly = (size_t)k * rn;
   const size_t bpp = n / kEwThreads;
-  const size_t C = std::min<size_t>(n_ct, 64);
-  // scratch: s_hat [k][n] | x [C][k][n]
+  const size_t C = std::min<size_t>(n_ct, std::max<size_t>(64, ((size_t)256 << 20) / (poly * 4)));
+  // scratch: s_hat [k][n] | x [C][k][n], up to 256 MiB
   int e = ensure_work(c, (poly + C * poly) * 4);
   if (e) return e;
   uint32_t* s_hat = c->work;
   uint32_t* x = s_hat + poly;
-  SmallToRnsArgs sr{sk, s_hat, c->d_mods, k, n};
-  if ((e = run<SmallToRnsKernel>(c, bpp, 0, sr))) return e;
-  if ((e = ntt_dense(c, s_hat, s_hat, k, k, false))) return e;
+  if ((e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);
-    const uint32_t* cts = ct + c0 * 2 * poly;
-    // x = NTT(c1) picked out of every ciphertext
-    NttRows r{cts, x, cc * k, k, 0, 2 * k, k, k, 0};
-    if ((e = ntt_rows(c, r, false))) return e;
-    PointMulArgs pm{x, s_hat, x, c->d_mods, k, n, (uint32_t)(cc * k), k, 0u};
-    if ((e = run<PointMulKernel>(c, cc * k * bpp, 0, pm))) return e;
-    if ((e = ntt_dense(c, x, x, cc * k, k, true))) return e;
-    AddRowsArgs ar{cts, x, x, c->d_mods, k, n, 2 * k, 0u};
-    if ((e = run<AddRowsKernel>(c, cc * k * bpp, 0, ar))) return e;
-    if (m_out) {
-      DecRoundArgs da;
-      da.x = x; da.m_out = m_out + c0 * rn; da.bc = c->dec; da.t = (uint32_t)c->t; da.neg_qinv_t = c->neg_qinv_t; da.n = n;
-      da.band = c->band; da.fallback_counter = c->d_counters;
-      if ((e = run<DecRoundKernel>(c, cc * bpp, DecRoundKernel::lds_bytes(k), da))) return e;
-    } else {
-      DecRoundWideArgs da;
-      da.x = x; da.m_out = m_out64 + c0 * rn; da.bc = c->dec; da.tab = c->d_dec_wide; da.t = c->t; da.n = n;
-      da.band = c->band; da.fallback_counter = c->d_counters;
-      if ((e = run<DecRoundWideKernel>(c, cc * bpp, DecRoundWideKernel::lds_bytes(k), da))) return e;
-    }
+    if ((e = decrypt_rows(c, ct + c0 * 2 * poly, cc, s_hat, x))) return e;
+    DecRoundArgs da;
+    da.x = x; da.m_out = m_out ? m_out + c0 * rn : nullptr; da.m_out64 = m_out64 ? m_out64 + c0 * rn : nullptr;
+    da.bc = c->dec; da.tab = c->d_dec_tab; da.t = c->t; da.n = n;
+    da.band = c->band; da.fallback_counter = c->d_counters;
+    if ((e = run<DecRoundKernel>(c, cc * bpp, DecRoundKernel::lds_bytes(k), da))) return e;
   }
   return HCNN_OK;
 }
@@ -1348,26 +1365,17 @@ int hcnn_noise_bits(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size_t n
   const uint32_t k = c->k, n = c->n;
   const size_t rn = n, poly = (size_t)k * rn;
   const size_t bpp = n / kEwThreads;
-  const size_t C = std::min<size_t>(n_ct, 64);
-  // scratch: s_hat [k][n] | x [C][k][n]
+  const size_t C = std::min<size_t>(n_ct, std::max<size_t>(64, ((size_t)256 << 20) / (poly * 4)));
+  // scratch: s_hat [k][n] | x [C][k][n], up to 256 MiB
   int e = ensure_work(c, (poly + C * poly) * 4);
   if (e) return e;
   uint32_t* s_hat = c->work;
   uint32_t* x = s_hat + poly;
   if ((e = dev_memset(bits_out, 0, n_ct * sizeof(uint32_t), c->stream))) return e;
-  SmallToRnsArgs sr{sk, s_hat, c->d_mods, k, n};
-  if ((e = run<SmallToRnsKernel>(c, bpp, 0, sr))) return e;
-  if ((e = ntt_dense(c, s_hat, s_hat, k, k, false))) return e;
+  if ((e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);
-    const uint32_t* cts = ct + c0 * 2 * poly;
-    NttRows r{cts, x, cc * k, k, 0, 2 * k, k, k, 0};            // x = NTT(c1) of every ciphertext
-    if ((e = ntt_rows(c, r, false))) return e;
-    PointMulArgs pm{x, s_hat, x, c->d_mods, k, n, (uint32_t)(cc * k), k, 0u};
-    if ((e = run<PointMulKernel>(c, cc * k * bpp, 0, pm))) return e;
-    if ((e = ntt_dense(c, x, x, cc * k, k, true))) return e;
-    AddRowsArgs ar{cts, x, x, c->d_mods, k, n, 2 * k, 0u};
-    if ((e = run<AddRowsKernel>(c, cc * k * bpp, 0, ar))) return e;
+    if ((e = decrypt_rows(c, ct + c0 * 2 * poly, cc, s_hat, x))) return e;
     NoiseArgs na;
     na.x = x; na.bits = bits_out + c0; na.bc = c->dec; na.n = n;
     if ((e = run<NoiseKernel>(c, cc * bpp, NoiseKernel::lds_bytes(k), na))) return e;

@@ -90,7 +90,12 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              kNttToRegs0 = 11, kNttToRegs1 = 12,           // forward, inside TensorFused: c0 / c1 of workgroup (ct, limb); the
                                                            // transformed row stays in registers, signed in [-p, p)
              kNttTensorRegs0 = 13, kNttTensorRegs1 = 14, kNttTensorRegs2 = 15,
-             kNttStoreKey = 16 };   // inverse, inside TensorFused: component
+             kNttStoreKey = 16,
+             // forward, inside CryptFused: the encryption's u (small signed values, [ct][n], limb by limb) or the
+             // decryption's c1 into registers; kNttSmallKey: the secret's rows, stored like kNttStoreKey
+             kNttSmallToRegs = 17, kNttSmallKey = 18, kNttCtToRegs = 19,
+             // inverse, inside CryptFused: the registers times a key row, plus what Encrypt / Decrypt add
+             kNttEncOut0 = 20, kNttEncOut1 = 21, kNttDecOut = 22 };   // inverse, inside TensorFused: component
                                                            // b of the tensor formed from those registers (as kNttLoadTensor)
 
 // Per-thread state of TensorFused: the two transformed polynomials of the ciphertext, one limb.
@@ -107,6 +112,11 @@ struct RelinRegs {
   int64_t s0[R], s1[R];
 };
 struct NoRegs {};
+// Per-thread state of CryptFused: one transformed polynomial.
+template <int R>
+struct RowRegs {
+  int32_t c0[R];
+};
 
 struct NttArgs {
   const uint32_t* in;
@@ -119,6 +129,10 @@ struct NttArgs {
   uint32_t in_group_rows, in_row0;
   uint32_t out_group_rows, out_row0;
   uint32_t n_rows;          // rows of this launch (the grid may be padded, see ntt_logical_row)
+  const int32_t* small;     // kNttSmallToRegs, kNttSmallKey: the signed polynomials; kNttEncOut0/1: the errors
+  const uint32_t* msg;      // kNttEncOut0: the plaintexts in 32-bit or
+  const uint64_t* msg64;    // 64-bit words (the other pointer is null), and
+  const ShoupConst* scale;  // [L] floor(q/t) mod q_l
   uint32_t own_limbs;       // kNttStoreLazy with `aux` set: rows of the first own_limbs limbs of every group are read from
                             // aux, laid out [group][own_limbs][n] (a ciphertext's own limbs), the others from `in`
 };
@@ -164,11 +178,16 @@ HCNN_HD constexpr uint32_t lds_elem(uint32_t sbase, int e) {
 // pass is a whole number of radix-4 levels.  The last forward pass (the first inverse one) has every thread store (load)
 // 2^ns consecutive residues: two stages there make it one 16-byte word per lane, so that the lanes of a wave touch
 // consecutive words.
-template <int LOGN, int LOGR>
+// PLAIN: the transforms of the public entry points, which only move rows.  At n = 2048 and 4096 they keep that rule;
+// inside the squaring, the encryption and the decryption a pass less counts for more (n = 4096: 4000 x 4 rows forward and
+// back 403 us with four passes, 457 with three; 1000 squarings 621 and 593, one squaring 29.2 and 27.0).
+template <int LOGN, int LOGR, bool PLAIN = false>
 struct NttGeom;
-#define HCNN_GEOM_SPEC(LOGN_, LOGR_, NP_, ...)                                                        \
+template <int LOGN, int LOGR>
+struct NttGeom<LOGN, LOGR, true> : NttGeom<LOGN, LOGR, false> {};
+#define HCNN_GEOM_SPEC(LOGN_, LOGR_, PLAIN_, NP_, ...)                                                \
   template <>                                                                                          \
-  struct NttGeom<LOGN_, LOGR_> {                                                                       \
+  struct NttGeom<LOGN_, LOGR_, PLAIN_> {                                                               \
     static constexpr int N = 1 << LOGN_;                                                               \
     static constexpr int R = 1 << LOGR_;                                                               \
     static constexpr int kThreads = N / R;                                                             \
@@ -178,13 +197,15 @@ struct NttGeom;
     static constexpr int s0(int ph) { int s = 0; for (int i = 0; i < ph; ++i) s += kNs[i]; return s; } \
     static constexpr int ns(int ph) { return kNs[ph]; }                                                \
   };
-HCNN_GEOM_SPEC(10, 4, 3, 4, 4, 2)
-HCNN_GEOM_SPEC(11, 4, 4, 3, 4, 2, 2)
-HCNN_GEOM_SPEC(12, 4, 4, 4, 4, 2, 2)
-HCNN_GEOM_SPEC(13, 4, 4, 3, 4, 4, 2)
-HCNN_GEOM_SPEC(14, 4, 4, 4, 4, 4, 2)
-HCNN_GEOM_SPEC(14, 5, 4, 4, 4, 4, 2)      // the half rows of n = 32768's two-workgroup forward transform
-HCNN_GEOM_SPEC(15, 5, 4, 5, 4, 4, 2)
+HCNN_GEOM_SPEC(10, 4, false, 3, 4, 4, 2)
+HCNN_GEOM_SPEC(11, 4, false, 3, 3, 4, 4)
+HCNN_GEOM_SPEC(11, 4, true, 4, 3, 4, 2, 2)
+HCNN_GEOM_SPEC(12, 4, false, 3, 4, 4, 4)
+HCNN_GEOM_SPEC(12, 4, true, 4, 4, 4, 2, 2)
+HCNN_GEOM_SPEC(13, 4, false, 4, 3, 4, 4, 2)
+HCNN_GEOM_SPEC(14, 4, false, 4, 4, 4, 4, 2)
+HCNN_GEOM_SPEC(14, 5, false, 4, 4, 4, 4, 2)      // the half rows of n = 32768's two-workgroup forward transform
+HCNN_GEOM_SPEC(15, 5, false, 4, 5, 4, 4, 2)
 #undef HCNN_GEOM_SPEC
 
 // Two Cooley-Tukey stages on (x0, x1, x2, x3): pairs (0,2), (1,3) with W, then (0,1) with V and (2,3) with U.
@@ -225,15 +246,18 @@ HCNN_HD void r4_inv(int32_t& x0, int32_t& x1, int32_t& x2, int32_t& x3, int32_t 
 template <int LOGN, int LOGR, int IO = kNttPlain, int SPLIT = 0>
 struct NttFwd {
   static constexpr bool kFused = IO == kNttFusedMac || IO == kNttFusedMac16 || IO == kNttFusedMacAny;
-  static constexpr bool kToRegs = IO == kNttToRegs0 || IO == kNttToRegs1;
-  static_assert(IO == kNttPlain || IO == kNttLoadDigit || IO == kNttStoreLazy || IO == kNttStoreKey || kFused || kToRegs,
+  static constexpr bool kRowToRegs = IO == kNttSmallToRegs || IO == kNttCtToRegs;
+  static constexpr bool kToRegs = IO == kNttToRegs0 || IO == kNttToRegs1 || kRowToRegs;
+  static constexpr bool kSmallIn = IO == kNttSmallToRegs || IO == kNttSmallKey;
+  static constexpr bool kKeyOut = IO == kNttStoreKey || IO == kNttSmallKey;
+  static_assert(IO == kNttPlain || IO == kNttLoadDigit || IO == kNttStoreLazy || kKeyOut || kFused || kToRegs,
                 "forward NTT: plain, digit load, lazy or key store, fused inner product or register output");
   static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kToRegs && LOGN % 2 == 1), "the split form stores its rows");
-  using G = NttGeom<LOGN - SPLIT, LOGR>;      // the stages after the split one
+  using G = NttGeom<LOGN - SPLIT, LOGR, IO == kNttPlain>;      // the stages after the split one
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
   static constexpr bool kDigitIn = IO == kNttLoadDigit || kFused;
-  using Regs = std::conditional_t<kFused, RelinRegs<G::R>, std::conditional_t<kToRegs, TensorRegs<G::R>, NoRegs>>;
+  using Regs = std::conditional_t<kFused, RelinRegs<G::R>, std::conditional_t<kRowToRegs, RowRegs<G::R>, std::conditional_t<kToRegs, TensorRegs<G::R>, NoRegs>>>;
   // workgroups of a launch over `slots` row positions (a multiple of the die count for the split form)
   static size_t grid(size_t slots) { return SPLIT ? 2 * ((slots + kNttXcds - 1) / kNttXcds * kNttXcds) : slots; }
 
@@ -257,8 +281,8 @@ struct NttFwd {
         if (bid >= a.n_rows) return;                       // padding workgroups of the last round
       }
     }
-    if constexpr (kDigitIn) {
-      bid = ntt_grouped_index(bid, a.cycle);      // the k transforms of one digit row share a die
+    if constexpr (kDigitIn || kRowToRegs) {
+      bid = ntt_grouped_index(bid, a.cycle);      // the k transforms of one digit row (or small row) share a die
       if (bid >= a.n_rows) return;
     }
     const uint32_t group = quot(bid, a.cycle), within = bid - group * a.cycle.d, limb = a.limb_base + within;
@@ -280,6 +304,10 @@ struct NttFwd {
     } else if constexpr (IO == kNttLoadDigit) {
       const uint32_t kk = a.cycle.d, ct = quot(group, a.cycle);      // group = (ct, digit)
       gin = a.in + ((size_t)ct * 3 * kk + 2 * kk + (group - ct * kk)) * N;
+    } else if constexpr (kSmallIn) {
+      gin = reinterpret_cast<const uint32_t*>(a.small) + (size_t)group * N;
+    } else if constexpr (IO == kNttCtToRegs) {
+      gin = a.in + ((size_t)(group * 2 + 1) * a.cycle.d + within) * N;
     } else if constexpr (kToRegs) {
       // workgroup (ct, l): polynomial c0 or c1 of the ciphertext; its own limbs come from the ciphertext (`aux`,
       // [ct][2][own_limbs][n]), the auxiliary limbs from the extension buffer (`in`, [ct][2][L][n])
@@ -299,13 +327,17 @@ struct NttFwd {
     // The radix-2 stage of node 1 on rows with residues in [0, 2p) (canonical ones, or digits of another prime):
     // with X brought below p, X + T and X - T lie in (-0.75 p, 1.75 p) and the stage needs no other reduction.
     // split form: this half's output of the pair (i, i + n/2), on the way in.
-    auto load_first = [&](uint32_t at, uint32_t e_off) -> int32_t {      // element at + e_off, e_off uniform
+    auto element = [&](uint32_t at, uint32_t e_off) -> uint32_t {        // element at + e_off, e_off uniform
+      const uint32_t x = ld_at(gin + e_off, at * 4);
+      return kSmallIn ? small_to_res((int32_t)x, L.m) : x;
+    };
+    auto load_first = [&](uint32_t at, uint32_t e_off) -> int32_t {
       if constexpr (SPLIT) {
-        const int32_t X = (int32_t)csub(ld_at(gin + e_off, at * 4), p);
-        const int32_t T = sredc((int64_t)(int32_t)ld_at(gin + e_off + N / 2, at * 4) * L.w1, p, L.pinv);
+        const int32_t X = (int32_t)csub(element(at, e_off), p);
+        const int32_t T = sredc((int64_t)(int32_t)element(at, e_off + N / 2) * L.w1, p, L.pinv);
         return half ? X - T : X + T;
       } else {
-        return (int32_t)ld_at(gin + e_off, at * 4);
+        return (int32_t)element(at, e_off);
       }
     };
 
@@ -372,7 +404,7 @@ struct NttFwd {
 #pragma unroll
         for (int e = 0; e < NET; ++e) {
           if constexpr (IO == kNttToRegs1) regs.c1[c * NET + e] = half_range(v[e], p);
-          else                             regs.c0[c * NET + e] = half_range(v[e], p);
+          else                             regs.c0[c * NET + e] = half_range(v[e], p);      // (the only row of RowRegs)
         }
       } else if constexpr (kLast) {
         static_assert(!kLast || TLAST == 1, "the last pass holds consecutive residues");
@@ -380,7 +412,7 @@ struct NttFwd {
 #pragma unroll
         for (int e = 0; e < NET; ++e) {
           if constexpr (IO == kNttStoreLazy || IO == kNttLoadDigit) r[e] = (uint32_t)half_range(v[e], p);
-          else if constexpr (IO == kNttStoreKey) {
+          else if constexpr (kKeyOut) {
             const uint32_t x = canon_p(sredc((int64_t)v[e] * L.key_scale, p, L.pinv), p);
             r[e] = x > p / 2 ? x - p : x;
           } else r[e] = canon_2p(v[e], p);
@@ -404,8 +436,8 @@ template <int LOGN, int LOGR, int IO = kNttPlain>
 struct NttInv {
   static_assert(IO == kNttPlain || IO == kNttLoadTensor || IO == kNttStoreAdd || IO == kNttLoadTensorMul ||
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
-                IO == kNttTensorRegs2, "inverse NTT io mode");
-  using G = NttGeom<LOGN, LOGR>;
+                IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut, "inverse NTT io mode");
+  using G = NttGeom<LOGN, LOGR, IO == kNttPlain>;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
   // a 1024-thread workgroup whose row leaves LDS for a second one: keep the registers within what two of them need
@@ -413,7 +445,9 @@ struct NttInv {
   static constexpr int kMinWavesPerSimd = (G::kThreads == 1024 && 2 * G::kLdsBytes <= 160 * 1024) ? 8 : 1;
   static constexpr bool kFromRegs = IO == kNttFromRegs0 || IO == kNttFromRegs1;
   static constexpr bool kTensorRegs = IO == kNttTensorRegs0 || IO == kNttTensorRegs1 || IO == kNttTensorRegs2;
-  using Regs = std::conditional_t<kFromRegs, RelinRegs<G::R>, std::conditional_t<kTensorRegs, TensorRegs<G::R>, NoRegs>>;
+  static constexpr bool kEncOut = IO == kNttEncOut0 || IO == kNttEncOut1, kKeyRegs = kEncOut || IO == kNttDecOut;
+  using Regs = std::conditional_t<kFromRegs, RelinRegs<G::R>, std::conditional_t<kTensorRegs, TensorRegs<G::R>,
+               std::conditional_t<kKeyRegs, RowRegs<G::R>, NoRegs>>>;
 
   template <int PHI>
   HCNN_HD static void phase(const NttArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
@@ -432,8 +466,9 @@ struct NttInv {
       bid = (ct * 3 + b) * LL + (unit - ct * LL);               // row (ct, b, l)
       if (unit >= a.n_rows / 3) return;
     }
-    if constexpr (kFromRegs) {
-      bid = ntt_grouped_index(bid, a.cycle);      // the same workgroup -> (ct, j) map as kNttFusedMac
+    if constexpr (kFromRegs || kKeyRegs) {
+      if constexpr (kKeyRegs) tid = opaque(tid);
+      bid = ntt_grouped_index(bid, a.cycle);      // the same workgroup -> (ct, j) map as the forward transforms
       if (bid >= a.n_rows) return;
     }
     if constexpr (kTensorRegs) {
@@ -464,6 +499,8 @@ struct NttInv {
       // b = 0: c0*c0' ; b = 2: c1*c1' ; b = 1: c0*c1' + c1*c0'
       gin = gmul0 + (comp == 2 ? (size_t)LL * N : 0);
       gin2 = gmul1 + (comp == 0 ? 0 : (size_t)LL * N);
+    } else if constexpr (kKeyRegs) {
+      gin = a.in + ((IO == kNttEncOut1 ? (size_t)a.cycle.d : 0) + within) * N;      // key row of this limb
     } else if constexpr (!kFromRegs && !kTensorRegs) {
       gin = a.in + ((size_t)group * a.in_group_rows + a.in_row0 + within) * N;
     }
@@ -476,6 +513,11 @@ struct NttInv {
     } else if constexpr (kTensorRegs) {
       const uint32_t LL = a.cycle.d, b = IO == kNttTensorRegs0 ? 0u : (IO == kNttTensorRegs1 ? 1u : 2u);
       gout = a.out + ((size_t)(group * 3 + b) * LL + within) * N;       // d row (ct, b, l)
+    } else if constexpr (kEncOut) {
+      gout = a.out + ((size_t)(group * 2 + (IO == kNttEncOut1 ? 1 : 0)) * a.cycle.d + within) * N;
+    } else if constexpr (IO == kNttDecOut) {
+      gout = a.out + (size_t)bid * N;
+      gaux = a.aux + ((size_t)group * 2 * a.cycle.d + within) * N;                   // c0
     } else {
       gout = a.out + ((size_t)group * a.out_group_rows + a.out_row0 + within) * N;
     }
@@ -509,6 +551,12 @@ struct NttInv {
           const int32_t y = IO == kNttTensorRegs1 ? untraced(regs.c1[c * NET + e]) : x;
           v[e] = sredc((int64_t)(IO == kNttTensorRegs1 ? untraced(x + x) : x) * y, p, L.pinv);
         }
+      } else if constexpr (kFirst && kKeyRegs) {
+        // |row| <= p, |key| <= p/2: products stay within (-p, p)
+        int32_t y[NET];
+        load_row<NET>(y, gin, base);
+#pragma unroll
+        for (int e = 0; e < NET; ++e) v[e] = sredc((int64_t)untraced(regs.c0[c * NET + e]) * y[e], p, L.pinv);
       } else if constexpr (kFirst) {
         load_row<NET>(v, gin, base);
         if constexpr (IO == kNttLoadTensorMul) {
@@ -571,7 +619,32 @@ struct NttInv {
           v[x + NET / 2] = sredc((int64_t)(X - Y) * top.w, p, L.pinv);
         }
       }
-      if constexpr (kLast && (IO == kNttStoreAdd || kFromRegs)) {
+      if constexpr (kLast && kEncOut) {
+        // + e (+ floor(q/t) * m)
+        const uint32_t* ge = reinterpret_cast<const uint32_t*>(a.small) + (size_t)group * N;
+        int32_t err[NET];
+        uint32_t dm[NET];
+#pragma unroll
+        for (int e = 0; e < NET; ++e) err[e] = (int32_t)ld_at(ge + e * TLAST, base * 4);
+        if constexpr (IO == kNttEncOut0) {
+          const ShoupConst delta = ldc(a.scale, within);
+          if (a.msg != nullptr) {
+#pragma unroll
+            for (int e = 0; e < NET; ++e) dm[e] = reduce32(ld_at(a.msg + (size_t)group * N + e * TLAST, base * 4), L.m);
+          } else {
+#pragma unroll
+            for (int e = 0; e < NET; ++e) dm[e] = reduce64(a.msg64[(size_t)group * N + e * TLAST + base], L.m);
+          }
+#pragma unroll
+          for (int e = 0; e < NET; ++e) dm[e] = shoup_mul(dm[e], delta, p);
+        }
+#pragma unroll
+        for (int e = 0; e < NET; ++e) {
+          uint32_t r = add_mod(canon_p(v[e], p), small_to_res(err[e], L.m), p);
+          if constexpr (IO == kNttEncOut0) r = add_mod(r, dm[e], p);
+          st_at(gout + e * TLAST, base * 4, r);
+        }
+      } else if constexpr (kLast && (IO == kNttStoreAdd || kFromRegs || IO == kNttDecOut)) {
         // all loads of the addend before the first store (the compiler must assume the buffers alias)
         uint32_t addend[NET];
 #pragma unroll
@@ -674,6 +747,56 @@ struct TensorFused {
       if constexpr (PH < 3 * P) NttInv<LOGN, LOGR, kNttTensorRegs0>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
       else if constexpr (PH < 4 * P) NttInv<LOGN, LOGR, kNttTensorRegs1>::template phase<PH - 3 * P>(na, bid, tid, lds, regs);
       else NttInv<LOGN, LOGR, kNttTensorRegs2>::template phase<PH - 4 * P>(na, bid, tid, lds, regs);
+    }
+  }
+};
+
+// ------------------------------------------------------------------------- encryption and decryption
+// Workgroup (ct, l), one row in registers from the forward transform to the last store:
+//   encryption  u -> forward; times pk0^, back, + e1 + floor(q/t) m -> c0; times pk1^, back, + e2 -> c1
+//   decryption  c1 -> forward; times s^, back, + c0 -> x
+// As separate launches the same work moves every row through memory five times in between (and was cut into batches of 64
+// for its buffers): 784 encryptions at n = 8192, k = 8 took 1312 us.
+struct CryptArgs {
+  const uint32_t* key;      // [2][k][n] (encryption) or [k][n]: transformed, as kNttStoreKey leaves it
+  const int32_t* u;         // encryption: [n_ct][n]
+  const int32_t* e1;
+  const int32_t* e2;
+  const uint32_t* msg;      // as in NttArgs
+  const uint64_t* msg64;
+  const ShoupConst* scale;
+  const uint32_t* cts;      // decryption: [n_ct][2][k][n]
+  uint32_t* out;            // [n_ct][2][k][n] or [n_ct][k][n]
+  TwTable tw_fwd;
+  TwTable tw_inv;
+  const NttLimb* limbs;
+  uint32_t n_rows;          // n_ct * k
+  FastDiv cycle;            // k
+};
+
+template <int LOGN, int LOGR, bool ENC>
+struct CryptFused {
+  using G = NttGeom<LOGN, LOGR>;
+  static constexpr int P = G::kPhases;
+  static constexpr int kThreads = G::kThreads;
+  static constexpr int kPhases = (ENC ? 3 : 2) * P;
+  static constexpr int kMinWavesPerSimd = 4;
+  using Regs = RowRegs<G::R>;
+
+  template <int PH>
+  HCNN_HD static void phase(const CryptArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
+    NttArgs na{};
+    na.limbs = a.limbs; na.cycle = a.cycle; na.n_rows = a.n_rows;
+    if constexpr (PH < P) {
+      na.tw = a.tw_fwd; na.small = a.u; na.in = a.cts;
+      NttFwd<LOGN, LOGR, ENC ? kNttSmallToRegs : kNttCtToRegs>::template phase<PH>(na, bid, tid, lds, regs);
+    } else {
+      na.tw = a.tw_inv; na.in = a.key; na.out = a.out; na.aux = a.cts;
+      na.msg = a.msg; na.msg64 = a.msg64; na.scale = a.scale;
+      na.small = PH < 2 * P ? a.e1 : a.e2;
+      if constexpr (!ENC) NttInv<LOGN, LOGR, kNttDecOut>::template phase<PH - P>(na, bid, tid, lds, regs);
+      else if constexpr (PH < 2 * P) NttInv<LOGN, LOGR, kNttEncOut0>::template phase<PH - P>(na, bid, tid, lds, regs);
+      else NttInv<LOGN, LOGR, kNttEncOut1>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
     }
   }
 };

@@ -60,6 +60,12 @@ def test_keygen_encrypt_decrypt(backend, n, k):
     pc.check_keygen_encrypt_decrypt(backend, n, k)
 
 
+@pytest.mark.parametrize("n,k", [(4096, 3), (8192, 2), (16384, 2), (32768, 2)])
+def test_encrypt_decrypt_of_every_ring(backend, n, k):
+    say("keygen/encrypt/decrypt n=%d k=%d" % (n, k))
+    pc.check_keygen_encrypt_decrypt(backend, n, k, count=1)
+
+
 @pytest.mark.parametrize("n,k", [(1024, 2), (2048, 5)])
 def test_scalar_mac(backend, n, k):
     say("scalar_mac n=%d k=%d" % (n, k))
