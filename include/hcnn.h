@@ -235,8 +235,9 @@ enum {
                                     (compute units x the occupancy the runtime reports for the compiled kernel);
                                     the default policy of HCNN_OPT_FUSION sizes its rounds from it: a round is
                                     8 * floor(this / 8 / k) ciphertexts                         */
-  HCNN_STAT_TENSOR_FUSED_WGS = 4 /* the same for the one-kernel squaring tensor, taken for internal batches of
-                                    at least 6 * this (ciphertext, limb) pairs                  */
+  HCNN_STAT_TENSOR_FUSED_WGS = 4 /* the same for the one-kernel squaring tensor, taken for internal batches whose
+                                    (ciphertext, limb) pairs fill their rounds of compute units *
+                                    this to at least 7/8                                        */
 };
 /* Synchronises the context's stream, then reads the counter. */
 int hcnn_get_stat(hcnn_ctx* ctx, int which, uint64_t* out);
@@ -261,7 +262,8 @@ enum {
                                    primes).  0 (default) = chosen per internal batch: the tensor kernel for
                                    batches of several rounds of its workgroups, the relinearisation kernel for
                                    as many ciphertexts as fill whole rounds, the separate kernels for the rest
-                                   and for small batches; 1 = always the separate kernels; 2 = always the
+                                   and for small batches; the largest rings with many primes relinearise through
+                                   three auxiliary primes shared by all digits instead; 1 = always the separate kernels; 2 = always the
                                    one-kernel forms where the ring allows them.  Same results either way; for
                                    tests and tuning. */
 };

@@ -467,6 +467,126 @@ struct RelinMacKernel {
   }
 };
 
+// ---------------------------------------------------------------- shared-basis relinearisation
+// The inner product over the integers instead of modulo every q_j: digits and key coefficients are below 2^30, so
+// sum_i D_i * evk[i][b][j] is below k n 2^60 <= 2^80 in magnitude and three auxiliary primes (product above 2^87) hold it.
+// 3k digit transforms and 6k inverse ones replace k^2 and 2k; the inner product has three times the terms:
+//   acc[ct][o][r] = sum_i dig[ct][i][r] * key[i][o][r],   o = (b, j) of 2k, r < 3      (NTT domain, modulo p_r)
+// A workgroup takes 64 coefficients of one r for CT ciphertexts: their digits go to LDS once, its eight waves share out
+// the 2k outputs (O each) and load every key word once for the CT ciphertexts.
+struct RelinSharedArgs {
+  const uint32_t* dig;   // [n_ct][3][n/64][k][64], signed in [-p, p)
+  const uint32_t* key;   // [3][n/64][k][2k][64], as kNttStoreKey leaves it
+  uint32_t* acc;         // [n_ct][3][n/64][2k][64], signed in (-p, p)
+  const NttLimb* limbs;  // of the three primes
+  uint32_t k, n, n_ct, n_grp;
+};
+template <int O>
+struct RelinSharedMac {
+  static constexpr int kThreads = 512;
+  static constexpr int kPhases = 2;
+  static constexpr int kMinWavesPerSimd = O <= 4 ? 4 : 2;
+  static constexpr int CT = 8;
+  struct Regs {};
+  static size_t lds_bytes(uint32_t k) { return (size_t)CT * k * 64 * 4; }
+  template <int PH>
+  HCNN_HD static void phase(const RelinSharedArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
+    // the ciphertext groups of one (r, tile) follow each other on one die: its key words stay in that L2
+    const uint32_t xcd = bid % kXcds, local = bid / kXcds;
+    const uint32_t grp = local % a.n_grp, unit = local / a.n_grp * kXcds + xcd;
+    const uint32_t tiles = a.n / 64, r = unit / tiles, tile = unit % tiles;
+    const uint32_t wave = wave_uniform((uint32_t)tid / 64), lane = (uint32_t)tid % 64;
+    const uint32_t ct0 = grp * CT;
+    if constexpr (PH == 0) {
+      const uint32_t words = a.k * 16;                // 16-byte words of one ciphertext's tile
+      for (uint32_t x = tid; x < CT * words; x += kThreads) {
+        const uint32_t t = x / words, ct = ct0 + t < a.n_ct ? ct0 + t : a.n_ct - 1;
+        reinterpret_cast<U4*>(lds)[x] =
+            *reinterpret_cast<const U4*>(a.dig + (((size_t)ct * 3 + r) * tiles + tile) * a.k * 64 + (x - t * words) * 4);
+      }
+    } else {
+      const uint32_t o0 = wave * O, outs = 2 * a.k;
+      if (o0 >= outs) return;
+      const NttLimb L = ldc(a.limbs, r);
+      const uint32_t* key = a.key + ((size_t)r * tiles + tile) * a.k * outs * 64;
+      int64_t s[CT][O];
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+#pragma unroll
+        for (int o = 0; o < O; ++o) s[t][o] = 0;
+      // (fold rule of RelinMacKernel)
+      for (uint32_t i0 = 0, run = 16; i0 < a.k; i0 += run, run = 13) {
+        if (i0 > 0) {
+#pragma unroll
+          for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int o = 0; o < O; ++o) s[t][o] = sfold(s[t][o], L.rc);
+        }
+        const uint32_t i1 = i0 + run < a.k ? i0 + run : a.k;
+#pragma unroll 4
+        for (uint32_t i = i0; i < i1; ++i) {
+          int32_t e[O];
+#pragma unroll
+          for (int o = 0; o < O; ++o) {
+            const uint32_t oo = o0 + o < outs ? o0 + o : outs - 1;
+            e[o] = (int32_t)ld_at(key + ((size_t)i * outs + oo) * 64, lane * 4);
+          }
+#pragma unroll
+          for (int t = 0; t < CT; ++t) {
+            const int32_t d = (int32_t)lds[(t * a.k + i) * 64 + lane];
+#pragma unroll
+            for (int o = 0; o < O; ++o) s[t][o] += (int64_t)d * e[o];
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < CT; ++t) {
+        if (ct0 + t >= a.n_ct) break;
+#pragma unroll
+        for (int o = 0; o < O; ++o)
+          if (o0 + o < outs)
+            st_at(a.acc + ((((size_t)(ct0 + t) * 3 + r) * tiles + tile) * outs + o0 + o) * 64, lane * 4,
+                  (uint32_t)sredc(sfold(s[t][o], L.rc), L.m.p, L.pinv));
+      }
+    }
+  }
+};
+
+// Largest ring: the three rows of an output, back in coefficients (kNttBackRow), to modulo q_j, plus y_b.
+struct RelinCombineArgs {
+  const uint32_t* z;     // [n_ct][2k][3][n], dense rows
+  const uint32_t* y;     // [n_ct][3][k][n]
+  uint32_t* out;         // [n_ct][2][k][n]
+  const NttLimb* limbs;
+  const RelinCrt* crt;   // [k]
+  RelinCrtInv crt_inv;
+  FastDiv outputs;       // 2k
+  uint32_t n;
+};
+struct RelinCombine {
+  static constexpr int kThreads = kEwThreads;
+  static constexpr int kPhases = 1;
+  struct Regs {};
+  template <int PH>
+  HCNN_HD static void phase(const RelinCombineArgs& a, unsigned bid, int tid, uint32_t*, Regs&) {
+    const uint32_t per_row = a.n / (kThreads * kEwVec);
+    const uint32_t row = bid / per_row, c = (bid % per_row * kThreads + tid) * kEwVec;
+    const uint32_t ct = quot(row, a.outputs), o = row - ct * a.outputs.d, k = a.outputs.d / 2, j = o >= k ? o - k : o;
+    const NttLimb L = ldc(a.limbs, j);
+    const RelinCrt kc = ldc(a.crt, j);
+    const uint32_t* z = a.z + (size_t)row * 3 * a.n;
+    const U4 z0 = ld4_at(z, c * 4), z1 = ld4_at(z + a.n, c * 4), z2 = ld4_at(z + 2 * (size_t)a.n, c * 4);
+    const U4 y = ld4_at(a.y + ((size_t)ct * 3 * k + o) * a.n, c * 4);
+    auto one = [&](uint32_t x0, uint32_t x1, uint32_t x2, uint32_t add) {
+      return add_mod(relin_crt((int32_t)x0, (int32_t)x1, (int32_t)x2, kc, a.crt_inv, L.m.p, L.pinv), add, L.m.p);
+    };
+    U4 r;
+    r.x = one(z0.x, z1.x, z2.x, y.x); r.y = one(z0.y, z1.y, z2.y, y.y);
+    r.z = one(z0.z, z1.z, z2.z, y.z); r.w = one(z0.w, z1.w, z2.w, y.w);
+    st4_at(a.out + (size_t)row * a.n, c * 4, r);
+  }
+};
+
 // ---------------------------------------------------------------- scalar multiply-accumulate
 // out[f][g] = sum_tau w[g][f][tau] * in[idx[g][tau]]  per residue (HMultPlain by an integer + HAdd).
 struct MacArgs {

@@ -282,6 +282,9 @@ struct hcnn_ctx {
   unsigned long long* d_counters = nullptr;   // [2]
 
   uint32_t* d_evk_hat = nullptr;
+  uint32_t* d_evk_shared = nullptr;  // [3][n/64][k][2k][64], where the shared-basis relinearisation is in use
+  RelinCrt* d_crt = nullptr;         // [k]
+  RelinCrtInv crt_inv{};
   bool has_key = false;
 
   uint32_t* work = nullptr;       // device work buffer of the entry points that may allocate (grown on demand)
@@ -328,6 +331,8 @@ template <int A, int B, int C> struct KernelClass<NttInv<A, B, C>> { static cons
 template <> struct KernelClass<ExtKernel> { static constexpr int id = HCNN_PROF_BASE_EXT; };
 template <int A, int B> struct KernelClass<ExtKernelT<A, B>> { static constexpr int id = HCNN_PROF_BASE_EXT; };
 template <int A, int B> struct KernelClass<ScaleKernelR<A, B>> { static constexpr int id = HCNN_PROF_SCALE; };
+template <int O> struct KernelClass<RelinSharedMac<O>> { static constexpr int id = HCNN_PROF_RELIN_MAC; };
+template <int A, int B> struct KernelClass<RelinBack<A, B>> { static constexpr int id = HCNN_PROF_NTT_INV; };
 template <> struct KernelClass<ScaleKernel> { static constexpr int id = HCNN_PROF_SCALE; };
 template <int A> struct KernelClass<RelinMacKernel<A>> { static constexpr int id = HCNN_PROF_RELIN_MAC; };
 template <int A, int B, int C> struct KernelClass<RelinFused<A, B, C>> { static constexpr int id = HCNN_PROF_RELIN_FUSED; };
@@ -520,6 +525,10 @@ int build_tables(hcnn_ctx* c) {
     const uint32_t ninv = h_inv(n % p, p);
     nl.inv = inv_root(ninv);
     nl.inv_r = inv_root(h_mulmod(ninv, r32, p));
+    if (l >= c->k && l < c->k + 3 && c->kp >= 3) {
+      const std::vector<uint32_t> three(c->p.begin(), c->p.begin() + 3);
+      nl.inv_z = inv_root(h_mulmod(ninv, h_inv(h_prod_mod(three, (int)(l - c->k), p), p), p));
+    }
     mods.push_back(nl.m);
     limbs.push_back(nl);
   }
@@ -555,6 +564,20 @@ int build_tables(hcnn_ctx* c) {
       for (int piece = 0; piece < 3; ++piece) tab.push_back((uint32_t)(b >> (16 * piece)) & 0xffffu);
     }
     if ((e = upload(c, tab, &c->d_dec_tab))) return e;
+  }
+  if (c->kp >= 3) {
+    const std::vector<uint32_t> three(c->p.begin(), c->p.begin() + 3);
+    std::vector<RelinCrt> crt;
+    for (uint32_t j = 0; j < c->k; ++j) {
+      const uint32_t qj = c->q[j], r32 = (uint32_t)((1ull << 32) % qj);
+      auto centred = [&](uint32_t x) { return x > qj / 2 ? (int32_t)x - (int32_t)qj : (int32_t)x; };
+      RelinCrt kc;
+      for (int r = 0; r < 3; ++r) kc.c[r] = centred(h_mulmod(h_prod_mod(three, r, qj), r32, qj));
+      kc.cv = -centred(h_mulmod(h_prod_mod(three, -1, qj), r32, qj));
+      crt.push_back(kc);
+    }
+    for (int r = 0; r < 3; ++r) c->crt_inv.f[r] = 1.0f / (float)three[r];
+    if ((e = upload(c, crt, &c->d_crt))) return e;
   }
   if (c->kp) {
     BConvHost h_ext = make_bconv(c->q, c->p, 1, false, true);
@@ -605,6 +628,7 @@ struct NttRows {
   const uint32_t* aux = nullptr;
   uint32_t own_limbs = 0;
   const int32_t* small = nullptr;
+  uint32_t digits = 0, tile_words = 0;      // 0 digits: k
 };
 
 template <int LOGN, int LOGR>
@@ -618,12 +642,17 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   a.out_group_rows = r.out_group_rows; a.out_row0 = r.out_row0;
   a.n_rows = (uint32_t)r.rows;
   a.own_limbs = r.own_limbs;
+  a.digits = fast_div(r.digits ? r.digits : c->k);
+  a.tile_words = r.tile_words;
   const size_t lds = NttGeom<LOGN, LOGR>::kLdsBytes;
   if (inverse) {
     const size_t g3 = ntt_grouped_grid(r.rows, 3);
     if (io == kNttLoadTensor) return run<NttInv<LOGN, LOGR, kNttLoadTensor>>(c, g3, lds, a, r.rows);
     if (io == kNttLoadTensorMul) return run<NttInv<LOGN, LOGR, kNttLoadTensorMul>>(c, g3, lds, a, r.rows);
     if (io == kNttStoreAdd) return run<NttInv<LOGN, LOGR, kNttStoreAdd>>(c, r.rows, lds, a);
+    if constexpr (LOGN == 15) {
+      if (io == kNttBackRow) return run<NttInv<LOGN, LOGR, kNttBackRow>>(c, r.rows, lds, a);
+    }
     return run<NttInv<LOGN, LOGR>>(c, r.rows, lds, a);
   }
   // The largest ring runs its forward transforms as two workgroups per row (first stage folded into the load):
@@ -635,6 +664,14 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
       if (io == kNttLoadDigit) {
         using K = NttFwd<LOGN, LOGR, kNttLoadDigit, 1>;
         return run<K>(c, K::grid(ntt_grouped_grid(r.rows, r.cycle)), lds_h, a, r.rows);
+      }
+      if (io == kNttDigitTile) {
+        using K = NttFwd<LOGN, LOGR, kNttDigitTile, 1>;
+        return run<K>(c, K::grid(ntt_grouped_grid(r.rows, r.cycle)), lds_h, a, r.rows);
+      }
+      if (io == kNttKeyTile) {
+        using K = NttFwd<LOGN, LOGR, kNttKeyTile, 1>;
+        return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
       }
       if (io == kNttStoreLazy) {
         using K = NttFwd<LOGN, LOGR, kNttStoreLazy, 1>;
@@ -654,6 +691,9 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   }
   if (io == kNttLoadDigit)
     return run<NttFwd<LOGN, LOGR, kNttLoadDigit>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
+  if (io == kNttDigitTile)
+    return run<NttFwd<LOGN, LOGR, kNttDigitTile>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
+  if (io == kNttKeyTile) return run<NttFwd<LOGN, LOGR, kNttKeyTile>>(c, r.rows, lds, a);
   if (io == kNttStoreLazy) return run<NttFwd<LOGN, LOGR, kNttStoreLazy>>(c, r.rows, lds, a);
   if (io == kNttSmallKey) return run<NttFwd<LOGN, LOGR, kNttSmallKey>>(c, r.rows, lds, a);
   if (io == kNttStoreKey) return run<NttFwd<LOGN, LOGR, kNttStoreKey>>(c, r.rows, lds, a);
@@ -948,6 +988,7 @@ int hcnn_ctx_destroy(hcnn_ctx* c) {
   for (auto ev : c->free_events) event_destroy(ev);
   for (void* p : c->owned) dev_free(p);
   if (c->d_evk_hat) dev_free(c->d_evk_hat);
+  if (c->d_evk_shared) dev_free(c->d_evk_shared);
   if (c->work) dev_free(c->work);
   delete c;
   return HCNN_OK;
@@ -959,6 +1000,20 @@ int hcnn_set_stream(hcnn_ctx* c, void* hip_stream) {
   if (e) return e;
   c->stream = (hcnn_stream_t)hip_stream;
   return HCNN_OK;
+}
+
+// Smallest internal batch that takes the shared-basis relinearisation, 0: none does.  It saves k^2 - 7k transforms per
+// ciphertext and pays with three times the key products and a base change.  Measured against the other forms, us:
+// n = 32768  k = 24  32 ciphertexts 2277 / 3070, 6: 530 / 690, 1: 251 / 193;  k = 18  32: 3194 / 3552;
+//            k = 12  32: 1049 / 1100, 6: 250 / 257, 1: 110 / 100
+// n = 16384  k = 16  225: 3907 / 4110, 16: 334 / 333;  k = 11  225: 2547 / 2329;  n = 8192  k = 12  700: 3949 / 3592.
+static size_t shared_basis_min(const hcnn_ctx* c) {
+#ifdef HCNN_SHARED_ALL
+  return c->kp >= 3 ? 2 : 0;            // (checker builds: every ring and basis)
+#else
+  if (c->kp < 3) return 0;
+  return c->logn == 15 && c->k >= 12 ? 4 : c->logn == 14 && c->k >= 16 ? 64 : 0;
+#endif
 }
 
 int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
@@ -973,6 +1028,18 @@ int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
   }
   int e = ntt_dense(c, evk_dev, c->d_evk_hat, rows, c->k, false, kNttStoreKey);
   if (e) return e;
+  if (shared_basis_min(c)) {
+    if (!c->d_evk_shared) {
+      void* ptr = nullptr;
+      if ((e = dev_malloc(&ptr, rows * 3 * c->n * 4))) return e;
+      c->d_evk_shared = (uint32_t*)ptr;
+    }
+    for (uint32_t r = 0; r < 3; ++r) {
+      NttRows kr{evk_dev, c->d_evk_shared, rows, 1, c->k + r, 1, 0, 1, r};
+      kr.tile_words = (uint32_t)(rows * 64);
+      if ((e = ntt_rows(c, kr, false, kNttKeyTile))) return e;
+    }
+  }
   c->has_key = true;
   return HCNN_OK;
 }
@@ -1028,6 +1095,42 @@ int hcnn_ct_scalar_mac(hcnn_ctx* c, const uint32_t* in, size_t n_in, const uint3
 static size_t relin_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_units * c->relin_fused_wgs; }
 static size_t tensor_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_units * c->tensor_fused_wgs; }
 
+// Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 3k, acc 6k and (largest ring only) z 6k rows
+// per ciphertext.
+static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* dig, uint32_t* acc, uint32_t* z, uint32_t* out) {
+  const uint32_t k = c->k, n = c->n;
+  int e;
+  NttRows r{y, dig, n_ct * k * 3, 3, k, 3, 0, 3, 0};
+  r.tile_words = k * 64;
+  if ((e = ntt_rows(c, r, false, kNttDigitTile))) return e;
+  RelinSharedArgs sa{dig, c->d_evk_shared, acc, c->d_limbs + k, k, n, (uint32_t)n_ct, (uint32_t)((n_ct + 7) / 8)};
+  const size_t grid = (size_t)3 * (n / 64) * sa.n_grp;
+  switch ((2 * k + 7) / 8) {
+#define HCNN_SHARED_MAC(O) case O: e = run<RelinSharedMac<O>>(c, grid, RelinSharedMac<O>::lds_bytes(k), sa); break;
+    HCNN_SHARED_MAC(1) HCNN_SHARED_MAC(2) HCNN_SHARED_MAC(3) HCNN_SHARED_MAC(4)
+    HCNN_SHARED_MAC(5) HCNN_SHARED_MAC(6) HCNN_SHARED_MAC(7) HCNN_SHARED_MAC(8)
+#undef HCNN_SHARED_MAC
+    default: e = HCNN_ERR_ARG; break;
+  }
+  if (e) return e;
+  const size_t rows = n_ct * 2 * k;
+  if (c->logn == 15) {
+    NttRows b{acc, z, rows * 3, 3, k, 3, 0, 3, 0};
+    b.digits = 2 * k;
+    b.tile_words = 2 * k * 64;
+    if ((e = ntt_rows(c, b, true, kNttBackRow))) return e;
+    RelinCombineArgs ca{z, y, out, c->d_limbs, c->d_crt, c->crt_inv, fast_div(2 * k), n};
+    return run<RelinCombine>(c, rows * (n / (kEwThreads * kEwVec)), 0, ca);
+  }
+  RelinBackArgs ba{acc, y, out, c->d_tw_inv, c->d_limbs, c->d_crt, c->crt_inv, k, fast_div(2 * k)};
+  switch (c->logn) {
+#define HCNN_BACK(LOGN) case LOGN: return run<RelinBack<LOGN, 4>>(c, rows, NttGeom<LOGN, 4>::kLdsBytes, ba, 3 * rows);
+    HCNN_BACK(10) HCNN_BACK(11) HCNN_BACK(12) HCNN_BACK(13) HCNN_BACK(14)
+#undef HCNN_BACK
+  }
+  return HCNN_ERR_N;
+}
+
 // HMult of Sec. 2.1 on n_ct pairs (a_i, b_i); b == nullptr squares a (HSquare).
 // static_ws: the intermediate polynomials go to this device's copy of the file-scope array `scratch` and nothing is
 // allocated; a parameter set whose single ciphertext does not fit that array is refused.
@@ -1051,12 +1154,13 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   // Its workgroups are long (k + 2 transforms each), so it only takes whole rounds of resident workgroups; what is
   // left of a batch (all of a small batch) goes through the three separate kernels, which spread k^2 rows per
   // ciphertext over the chip.
+  const size_t shared_min = c->fusion == 0 && !static_ws ? shared_basis_min(c) : 0;
   const bool fused = c->fusion != 1 && (c->logn <= 13 || (c->logn == 14 && k <= 16));
   // (the k workgroups of a ciphertext share a die, for its L2: a round is counted per die)
   const size_t fused_round = fused ? relin_fused_slots(c) / kXcds / k * kXcds : 0;   // ciphertexts per round (0: never)
   const size_t words_main = (ext_rows + 3 * L + 3 * k) * rn;
-  const size_t words_split = ((size_t)k * k + 2 * k) * rn;
-  const size_t words_per_ct = words_main + words_split;
+  const size_t words_split = ((size_t)k * k + 2 * k) * rn, words_shared = 9 * (size_t)k * rn;
+  const size_t words_per_ct = words_main + (shared_min ? words_shared : words_split);
   size_t C = c->square_chunk;
   // 6 GiB of work buffer (of 288 GB): enough rows per launch at every n
   const size_t budget = static_ws ? kStaticScratchBytes : (size_t)6 << 30;
@@ -1068,23 +1172,22 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     // ciphertexts to fill the chip at all
     const size_t cap = std::max<size_t>(c->logn <= 13 ? 512 : 256, fused_round);
     if (C > cap) C = cap;
-    if (fused_round && C > fused_round) C = C / fused_round * fused_round;   // whole rounds of the one-kernel relinearisation
+    if (!shared_min && fused_round && C > fused_round) C = C / fused_round * fused_round;   // whole rounds of the one-kernel relinearisation
   }
   if (C < 1) C = 1;
   if (C > n_ct) C = n_ct;
   const size_t need_lds_scale = ScaleKernel::lds_bytes(k, kp);
   if (need_lds_scale > c->max_lds) return HCNN_ERR_NODEVICE;
   // ciphertexts of one internal batch that can take the separate kernels
-  const size_t C_split = (fused && fused_round) ? std::min(C, fused_round) : C;
+  const size_t C_split = shared_min ? std::min(C, shared_min - 1) : (fused && fused_round) ? std::min(C, fused_round) : C;
   int e;
-  e = static_ws ? 0 : ensure_work(c, (C * words_main + C_split * words_split) * 4);
+  e = static_ws ? 0 : ensure_work(c, (C * words_main + std::max(C_split * words_split, shared_min ? C * words_shared : 0)) * 4);
   if (e) return e;
   uint32_t* ext = static_ws ? c->static_scratch : c->work;
   uint32_t* ext_b = ext + C * 2 * L * rn;                 // used only by the two-operand product
   uint32_t* d = ext + C * ext_rows * rn;
   uint32_t* y = d + C * 3 * L * rn;
   uint32_t* dig = y + C * 3 * k * rn;
-  uint32_t* acc = dig + C_split * k * k * rn;
   const size_t ct_words = (size_t)2 * k * rn;
   const size_t bpp = n / kEwThreads;                 // blocks per polynomial, 1 coefficient / thread
   const size_t bpr = n / (kEwThreads * kEwVec);      // blocks per row, 4 coefficients / thread
@@ -1111,16 +1214,17 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     return c->fusion == 2 || cc * L * 8 >= rounds * slots * 7;
   };
 
-  // One internal batch: ciphertexts [c0, c0 + cc) of the call, kept in slots [s0, s0 + cc) of the work arrays, nf of
+  // One internal batch: ciphertexts [c0, c0 + cc) of the call, nf of
   // them through the one-kernel relinearisation.
-  auto one_batch = [&](size_t c0, size_t cc, size_t s0, size_t nf) -> int {
+  auto one_batch = [&](size_t c0, size_t cc, size_t nf) -> int {
     int e;
-    uint32_t* const b_ext = ext + s0 * 2 * L * rn;
-    uint32_t* const b_ext_b = ext_b + s0 * 2 * L * rn;
-    uint32_t* const b_d = d + s0 * 3 * L * rn;
-    uint32_t* const b_y = y + s0 * 3 * k * rn;
-    uint32_t* const b_dig = dig + s0 * k * k * rn;
-    uint32_t* const b_acc = acc + s0 * 2 * k * rn;
+    uint32_t* const b_ext = ext;
+    uint32_t* const b_ext_b = ext_b;
+    uint32_t* const b_d = d;
+    uint32_t* const b_y = y;
+    const bool shared = shared_min && cc >= shared_min;
+    uint32_t* const b_dig = dig;
+    uint32_t* const b_acc = dig + (shared ? cc * 3 : (cc - nf) * k) * k * rn;
     // 1. centred lift of c0, c1 extended to the auxiliary primes (only the new rows are written);
     // 2. forward NTT over all k + k' limbs, the first k read from the ciphertext itself
     // (n = 32768: the new rows are staged in the array of the tensor, free until step 3, because the two-workgroup
@@ -1163,6 +1267,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     sa.d = b_d; sa.y = b_y; sa.to_p = c->to_p; sa.to_q = c->to_q; sa.tq_inv = c->d_tq_inv; sa.n = n;
     sa.band = c->band; sa.fallback_counter = c->d_counters;
     if ((e = scale_dispatch(c, cc * 3 * bpp, sa))) return e;
+    if (shared) return relin_shared(c, b_y, cc, b_dig, b_acc, b_d, out + c0 * ct_words);     // (the tensor's rows, 3L > 6k, are free by now)
     // 6-8 in one kernel
     if (nf) {
       RelinFusedArgs fa{b_y, c->d_evk_hat, out + c0 * ct_words, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, (uint32_t)(nf * k), fast_div(k)};
@@ -1213,7 +1318,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);
     const size_t nf = fused_count(cc);
-    if ((e = one_batch(c0, cc, 0, nf))) return e;
+    if ((e = one_batch(c0, cc, nf))) return e;
   }
   return HCNN_OK;
 }
@@ -1524,8 +1629,6 @@ int hcnn_set_option(hcnn_ctx* c, int which, uint64_t value) {
     case HCNN_OPT_FUSION:
       if (value > 2) return HCNN_ERR_ARG;
       c->fusion = value;
-      return HCNN_OK;
-      if (value > 2) return HCNN_ERR_ARG;
       return HCNN_OK;
   }
   return HCNN_ERR_ARG;

@@ -57,7 +57,23 @@ struct NttLimb {
   int32_t byte_c[3];    // 2^40, 2^48, 2^56 mod p, centred (byte planes of MacMfma)
   InvRoot inv;          // scale = n^-1
   InvRoot inv_r;        // scale = n^-1 * 2^32: the tensor-forming loads leave a factor 2^-32 on every product
+  InvRoot inv_z;        // scale = n^-1 * (R/p)^-1: the three primes of the shared-basis relinearisation (product R)
 };
+// Shared-basis relinearisation: from the residues of a key product modulo the three primes p_0, p_1, p_2 to modulo q_j.
+// With z_r = [x_r (R/p_r)^-1] in (-p_r, p_r) and |X| < R/64, sum_r z_r R/p_r = X + v R with v = round(sum_r z_r/p_r), and
+// that sum lies within 1/64 of an integer: fp32 decides it.
+struct RelinCrt {
+  int32_t c[3];         // R/p_r * 2^32 mod q_j, centred
+  int32_t cv;           // -R * 2^32 mod q_j, centred
+};
+struct RelinCrtInv { float f[3]; };      // 1 / p_r
+HCNN_HD uint32_t relin_crt(int32_t z0, int32_t z1, int32_t z2, const RelinCrt& k, const RelinCrtInv& f, uint32_t q, uint32_t qinv) {
+  const float v = (float)z0 * f.f[0] + (float)z1 * f.f[1] + (float)z2 * f.f[2];
+  const int32_t iv = (int32_t)(v < 0.0f ? v - 0.5f : v + 0.5f);
+  // |z| < 2^30, |c| <= q/2: the reduced value lies within 3 q/8 + q/2 + 1
+  const int64_t s = (int64_t)z0 * k.c[0] + (int64_t)z1 * k.c[1] + (int64_t)z2 * k.c[2] + (int64_t)iv * k.cv;
+  return canon_p(sredc(s, q, qinv), q);
+}
 
 // Row r (= workgroup index) belongs to group r / cycle and limb limb_base + r % cycle.
 // Its data sits at row (group * group_rows + row0 + r % cycle) of the in / out arrays, so a
@@ -95,7 +111,14 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              // decryption's c1 into registers; kNttSmallKey: the secret's rows, stored like kNttStoreKey
              kNttSmallToRegs = 17, kNttSmallKey = 18, kNttCtToRegs = 19,
              // inverse, inside CryptFused: the registers times a key row, plus what Encrypt / Decrypt add
-             kNttEncOut0 = 20, kNttEncOut1 = 21, kNttDecOut = 22 };   // inverse, inside TensorFused: component
+             kNttEncOut0 = 20, kNttEncOut1 = 21, kNttDecOut = 22,
+             // inverse, shared-basis relinearisation: row (ct, o, r) with the scaling of inv_z, output signed in (-p, p):
+             // to memory, or (inside RelinBack) to registers and, from the third, through the base change to the output
+             kNttBackRow = 23, kNttBack0 = 24, kNttBack1 = 25, kNttBack2 = 26,
+             // forward, shared-basis relinearisation: digit rows and key rows, stored in tiles of 64 coefficients (the key
+             // product reads all rows of a tile: whole kilobytes in one place instead of 256 bytes from every row):
+             // digits [ct][r][tile][i][64], key [r][tile][i][o][64]; the sums lie in [ct][r][tile][o][64]
+             kNttDigitTile = 27, kNttKeyTile = 28 };   // inverse, inside TensorFused: component
                                                            // b of the tensor formed from those registers (as kNttLoadTensor)
 
 // Per-thread state of TensorFused: the two transformed polynomials of the ciphertext, one limb.
@@ -112,6 +135,11 @@ struct RelinRegs {
   int64_t s0[R], s1[R];
 };
 struct NoRegs {};
+// Per-thread state of RelinBack: the first two residues of every coefficient.
+template <int R>
+struct BackRegs {
+  int32_t z0[R], z1[R];
+};
 // Per-thread state of CryptFused: one transformed polynomial.
 template <int R>
 struct RowRegs {
@@ -126,6 +154,10 @@ struct NttArgs {
   const NttLimb* limbs;     // [L]
   FastDiv cycle;            // limbs per group of rows
   uint32_t limb_base;
+  FastDiv digits;           // digit loads: digits per ciphertext; kNttBackRow: 2k
+  uint32_t tile_words;      // tiled rows: words from one tile of a row to its next
+  const RelinCrt* crt;      // kNttBack2: [k]
+  RelinCrtInv crt_inv;
   uint32_t in_group_rows, in_row0;
   uint32_t out_group_rows, out_row0;
   uint32_t n_rows;          // rows of this launch (the grid may be padded, see ntt_logical_row)
@@ -249,14 +281,16 @@ struct NttFwd {
   static constexpr bool kRowToRegs = IO == kNttSmallToRegs || IO == kNttCtToRegs;
   static constexpr bool kToRegs = IO == kNttToRegs0 || IO == kNttToRegs1 || kRowToRegs;
   static constexpr bool kSmallIn = IO == kNttSmallToRegs || IO == kNttSmallKey;
-  static constexpr bool kKeyOut = IO == kNttStoreKey || IO == kNttSmallKey;
-  static_assert(IO == kNttPlain || IO == kNttLoadDigit || IO == kNttStoreLazy || kKeyOut || kFused || kToRegs,
+  static constexpr bool kKeyOut = IO == kNttStoreKey || IO == kNttSmallKey || IO == kNttKeyTile;
+  static constexpr bool kTileOut = IO == kNttDigitTile || IO == kNttKeyTile;
+  static constexpr bool kDigitRow = IO == kNttLoadDigit || IO == kNttDigitTile;
+  static_assert(IO == kNttPlain || kDigitRow || IO == kNttStoreLazy || kKeyOut || kFused || kToRegs,
                 "forward NTT: plain, digit load, lazy or key store, fused inner product or register output");
   static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kToRegs && LOGN % 2 == 1), "the split form stores its rows");
   using G = NttGeom<LOGN - SPLIT, LOGR, IO == kNttPlain>;      // the stages after the split one
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
-  static constexpr bool kDigitIn = IO == kNttLoadDigit || kFused;
+  static constexpr bool kDigitIn = kDigitRow || kFused;
   using Regs = std::conditional_t<kFused, RelinRegs<G::R>, std::conditional_t<kRowToRegs, RowRegs<G::R>, std::conditional_t<kToRegs, TensorRegs<G::R>, NoRegs>>>;
   // workgroups of a launch over `slots` row positions (a multiple of the die count for the split form)
   static size_t grid(size_t slots) { return SPLIT ? 2 * ((slots + kNttXcds - 1) / kNttXcds * kNttXcds) : slots; }
@@ -301,8 +335,8 @@ struct NttFwd {
 #pragma unroll
         for (int r = 0; r < R; ++r) { regs.s0[r] = 0; regs.s1[r] = 0; }
       }
-    } else if constexpr (IO == kNttLoadDigit) {
-      const uint32_t kk = a.cycle.d, ct = quot(group, a.cycle);      // group = (ct, digit)
+    } else if constexpr (kDigitRow) {
+      const uint32_t kk = a.digits.d, ct = quot(group, a.digits);     // group = (ct, digit)
       gin = a.in + ((size_t)ct * 3 * kk + 2 * kk + (group - ct * kk)) * N;
     } else if constexpr (kSmallIn) {
       gin = reinterpret_cast<const uint32_t*>(a.small) + (size_t)group * N;
@@ -321,7 +355,12 @@ struct NttFwd {
         if (a.aux != nullptr && within < a.own_limbs) gin = a.aux + ((size_t)group * a.own_limbs + within) * N;
       }
     }
-    if constexpr (!kFused && !kToRegs)
+    if constexpr (IO == kNttDigitTile) {
+      const uint32_t kk = a.digits.d, ct = quot(group, a.digits);
+      gout = a.out + (size_t)(ct * 3 + within) * (N / 64) * a.tile_words + (group - ct * kk) * 64;
+    } else if constexpr (IO == kNttKeyTile) {
+      gout = a.out + (size_t)a.out_row0 * (N / 64) * a.tile_words + (size_t)group * 64;
+    } else if constexpr (!kFused && !kToRegs)
       gout = a.out + ((size_t)group * a.out_group_rows + a.out_row0 + within) * N + (size_t)half * (N / 2);
 
     // The radix-2 stage of node 1 on rows with residues in [0, 2p) (canonical ones, or digits of another prime):
@@ -411,7 +450,7 @@ struct NttFwd {
         uint32_t r[NET];
 #pragma unroll
         for (int e = 0; e < NET; ++e) {
-          if constexpr (IO == kNttStoreLazy || IO == kNttLoadDigit) r[e] = (uint32_t)half_range(v[e], p);
+          if constexpr (IO == kNttStoreLazy || kDigitRow) r[e] = (uint32_t)half_range(v[e], p);
           else if constexpr (kKeyOut) {
             const uint32_t x = canon_p(sredc((int64_t)v[e] * L.key_scale, p, L.pinv), p);
             r[e] = x > p / 2 ? x - p : x;
@@ -421,7 +460,9 @@ struct NttFwd {
         for (int e = 0; e < NET; e += 4) {
           U4 t;
           t.x = r[e]; t.y = r[e + 1]; t.z = r[e + 2]; t.w = r[e + 3];
-          st4_at(gout, (base + (uint32_t)e) * 4, t);
+          const uint32_t at = base + (uint32_t)e, row_at = at + (SPLIT ? half * (N / 2) : 0);
+          if constexpr (kTileOut) st4_at(gout, ((row_at >> 6) * a.tile_words + (row_at & 63u)) * 4, t);
+          else                    st4_at(gout, at * 4, t);
         }
       } else {
 #pragma unroll
@@ -436,7 +477,8 @@ template <int LOGN, int LOGR, int IO = kNttPlain>
 struct NttInv {
   static_assert(IO == kNttPlain || IO == kNttLoadTensor || IO == kNttStoreAdd || IO == kNttLoadTensorMul ||
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
-                IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut, "inverse NTT io mode");
+                IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut || IO == kNttBackRow || IO == kNttBack0 ||
+                IO == kNttBack1 || IO == kNttBack2, "inverse NTT io mode");
   using G = NttGeom<LOGN, LOGR, IO == kNttPlain>;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
@@ -445,9 +487,10 @@ struct NttInv {
   static constexpr int kMinWavesPerSimd = (G::kThreads == 1024 && 2 * G::kLdsBytes <= 160 * 1024) ? 8 : 1;
   static constexpr bool kFromRegs = IO == kNttFromRegs0 || IO == kNttFromRegs1;
   static constexpr bool kTensorRegs = IO == kNttTensorRegs0 || IO == kNttTensorRegs1 || IO == kNttTensorRegs2;
+  static constexpr bool kBack = IO == kNttBack0 || IO == kNttBack1 || IO == kNttBack2;
   static constexpr bool kEncOut = IO == kNttEncOut0 || IO == kNttEncOut1, kKeyRegs = kEncOut || IO == kNttDecOut;
   using Regs = std::conditional_t<kFromRegs, RelinRegs<G::R>, std::conditional_t<kTensorRegs, TensorRegs<G::R>,
-               std::conditional_t<kKeyRegs, RowRegs<G::R>, NoRegs>>>;
+               std::conditional_t<kKeyRegs, RowRegs<G::R>, std::conditional_t<kBack, BackRegs<G::R>, NoRegs>>>>;
 
   template <int PHI>
   HCNN_HD static void phase(const NttArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
@@ -475,6 +518,11 @@ struct NttInv {
       tid = opaque(tid);
       if (bid >= a.n_rows) return;
     }
+    const uint32_t unit_ct = kBack ? quot(bid, a.digits) : 0, unit_o = bid - unit_ct * a.digits.d;     // RelinBack: (ct, o)
+    if constexpr (kBack) {
+      tid = opaque(tid);
+      bid = bid * 3 + (IO - kNttBack0);                // row (ct, o, r)
+    }
     const uint32_t group = quot(bid, a.cycle), within = bid - group * a.cycle.d, limb = a.limb_base + within;
     const NttLimb L = ldc(a.limbs, limb);
     const uint32_t p = L.m.p;
@@ -501,6 +549,9 @@ struct NttInv {
       gin2 = gmul1 + (comp == 0 ? 0 : (size_t)LL * N);
     } else if constexpr (kKeyRegs) {
       gin = a.in + ((IO == kNttEncOut1 ? (size_t)a.cycle.d : 0) + within) * N;      // key row of this limb
+    } else if constexpr (IO == kNttBackRow || kBack) {
+      const uint32_t ct = kBack ? unit_ct : quot(group, a.digits), o = group - ct * a.digits.d;
+      gin = a.in + (size_t)(ct * 3 + within) * (N / 64) * a.tile_words + o * 64;
     } else if constexpr (!kFromRegs && !kTensorRegs) {
       gin = a.in + ((size_t)group * a.in_group_rows + a.in_row0 + within) * N;
     }
@@ -515,6 +566,10 @@ struct NttInv {
       gout = a.out + ((size_t)(group * 3 + b) * LL + within) * N;       // d row (ct, b, l)
     } else if constexpr (kEncOut) {
       gout = a.out + ((size_t)(group * 2 + (IO == kNttEncOut1 ? 1 : 0)) * a.cycle.d + within) * N;
+    } else if constexpr (kBack) {
+      // o = (b, j), 2k = a.digits of them
+      gout = a.out + ((size_t)unit_ct * a.digits.d + unit_o) * N;
+      gaux = a.aux + ((size_t)unit_ct * (a.digits.d / 2 * 3) + unit_o) * N;            // y row (ct, b, j)
     } else if constexpr (IO == kNttDecOut) {
       gout = a.out + (size_t)bid * N;
       gaux = a.aux + ((size_t)group * 2 * a.cycle.d + within) * N;                   // c0
@@ -557,6 +612,8 @@ struct NttInv {
         load_row<NET>(y, gin, base);
 #pragma unroll
         for (int e = 0; e < NET; ++e) v[e] = sredc((int64_t)untraced(regs.c0[c * NET + e]) * y[e], p, L.pinv);
+      } else if constexpr (kFirst && (IO == kNttBackRow || kBack)) {
+        load_row<NET>(v, gin, (base >> 6) * a.tile_words + (base & 63u));
       } else if constexpr (kFirst) {
         load_row<NET>(v, gin, base);
         if constexpr (IO == kNttLoadTensorMul) {
@@ -594,7 +651,8 @@ struct NttInv {
       }
       const uint32_t root = (1u << S0) + i;
       constexpr bool kMont = IO == kNttLoadTensor || IO == kNttLoadTensorMul || kTensorRegs;
-      const InvRoot& top = kMont ? L.inv_r : L.inv;       // node 1: the output scaling folded in
+      constexpr bool kZ = IO == kNttBackRow || kBack;
+      const InvRoot& top = kMont ? L.inv_r : kZ ? L.inv_z : L.inv;       // node 1: the output scaling folded in
 #pragma unroll
       for (int l = NS - 2; l >= (kOdd ? 1 : 0); l -= 2) {
         const int q = NET >> (l + 2);
@@ -619,7 +677,27 @@ struct NttInv {
           v[x + NET / 2] = sredc((int64_t)(X - Y) * top.w, p, L.pinv);
         }
       }
-      if constexpr (kLast && kEncOut) {
+      if constexpr (kLast && (IO == kNttBack0 || IO == kNttBack1)) {
+#pragma unroll
+        for (int e = 0; e < NET; ++e) {
+          if constexpr (IO == kNttBack0) regs.z0[c * NET + e] = v[e];
+          else                           regs.z1[c * NET + e] = v[e];
+        }
+      } else if constexpr (kLast && IO == kNttBack2) {
+        const uint32_t j = unit_o >= a.digits.d / 2 ? unit_o - a.digits.d / 2 : unit_o;
+        const NttLimb Q = ldc(a.limbs, j);
+        const RelinCrt kc = ldc(a.crt, j);
+        uint32_t addend[NET];
+#pragma unroll
+        for (int e = 0; e < NET; ++e) addend[e] = ld_at(gaux + e * TLAST, base * 4);
+#pragma unroll
+        for (int e = 0; e < NET; ++e)
+          st_at(gout + e * TLAST, base * 4,
+                add_mod(relin_crt(regs.z0[c * NET + e], regs.z1[c * NET + e], v[e], kc, a.crt_inv, Q.m.p, Q.pinv), addend[e], Q.m.p));
+      } else if constexpr (kLast && IO == kNttBackRow) {
+#pragma unroll
+        for (int e = 0; e < NET; ++e) st_at(gout + e * TLAST, base * 4, (uint32_t)v[e]);
+      } else if constexpr (kLast && kEncOut) {
         // + e (+ floor(q/t) * m)
         const uint32_t* ge = reinterpret_cast<const uint32_t*>(a.small) + (size_t)group * N;
         int32_t err[NET];
@@ -748,6 +826,41 @@ struct TensorFused {
       else if constexpr (PH < 4 * P) NttInv<LOGN, LOGR, kNttTensorRegs1>::template phase<PH - 3 * P>(na, bid, tid, lds, regs);
       else NttInv<LOGN, LOGR, kNttTensorRegs2>::template phase<PH - 4 * P>(na, bid, tid, lds, regs);
     }
+  }
+};
+
+// ------------------------------------------------------------------------- shared-basis relinearisation, last part
+// Workgroup (ct, o = (b, j)): the three rows acc[ct][o][r] back to coefficients, from modulo p_0, p_1, p_2 to modulo q_j,
+// plus y_b: one read of the sums, one write of the result.  (The largest ring does not hold two rows beside the one in
+// work in its registers: kNttBackRow and RelinCombine.)
+struct RelinBackArgs {
+  const uint32_t* acc;      // [n_ct][3][n/64][2k][64]
+  const uint32_t* y;        // [n_ct][3][k][n]
+  uint32_t* out;            // [n_ct][2][k][n]
+  TwTable tw_inv;
+  const NttLimb* limbs;
+  const RelinCrt* crt;
+  RelinCrtInv crt_inv;
+  uint32_t limb_base;       // of the three primes
+  FastDiv outputs;          // 2k
+};
+template <int LOGN, int LOGR>
+struct RelinBack {
+  using G = NttGeom<LOGN, LOGR>;
+  static constexpr int P = G::kPhases;
+  static constexpr int kThreads = G::kThreads;
+  static constexpr int kPhases = 3 * P;
+  static constexpr int kMinWavesPerSimd = 4;
+  using Regs = BackRegs<G::R>;
+  template <int PH>
+  HCNN_HD static void phase(const RelinBackArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
+    NttArgs na{};
+    na.in = a.acc; na.aux = a.y; na.out = a.out; na.tw = a.tw_inv; na.limbs = a.limbs; na.limb_base = a.limb_base;
+    na.cycle = FastDiv{3, 0x55555555u}; na.tile_words = a.outputs.d * 64;
+    na.digits = a.outputs; na.crt = a.crt; na.crt_inv = a.crt_inv;
+    if constexpr (PH < P) NttInv<LOGN, LOGR, kNttBack0>::template phase<PH>(na, bid, tid, lds, regs);
+    else if constexpr (PH < 2 * P) NttInv<LOGN, LOGR, kNttBack1>::template phase<PH - P>(na, bid, tid, lds, regs);
+    else NttInv<LOGN, LOGR, kNttBack2>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
   }
 };
 

@@ -25,22 +25,22 @@ _OUT_DIR = os.path.join(_ROOT, "tests", "_build")
 #         python -m pytest tests/test_emu_parity.py -q
 SANITIZE = os.environ.get("HCNN_EMU_SANITIZE", "") not in ("", "0")
 _OUT = os.path.join(_OUT_DIR, "libhcnn_emu_san.so" if SANITIZE else "libhcnn_emu.so")
-_lib = None
+_lib = _lib_shared = None
 
 
-def build() -> str:
+def build(defines=(), out=_OUT) -> str:
     os.makedirs(_OUT_DIR, exist_ok=True)
     srcs = [os.path.join(_SRC_DIR, f) for f in os.listdir(_SRC_DIR)] + [os.path.join(_ROOT, "include", "hcnn.h")]
-    if os.path.exists(_OUT) and all(os.path.getmtime(s) <= os.path.getmtime(_OUT) for s in srcs):
-        return _OUT
-    tmp = _OUT + ".tmp.%d" % os.getpid()
+    if os.path.exists(out) and all(os.path.getmtime(s) <= os.path.getmtime(out) for s in srcs):
+        return out
+    tmp = out + ".tmp.%d" % os.getpid()
     extra = ["-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"] \
         if SANITIZE else ["-O2"]
-    subprocess.check_call(["g++", "-std=c++17"] + extra + ["-DHCNN_HOSTEMU", "-fPIC", "-shared", "-Wall", "-Wextra",
+    subprocess.check_call(["g++", "-std=c++17"] + extra + ["-DHCNN_HOSTEMU", *defines, "-fPIC", "-shared", "-Wall", "-Wextra",
                            "-Wno-unused-parameter", "-Wno-unknown-pragmas", "-o", tmp,
                            os.path.join(_SRC_DIR, "hcnn.cpp")])
-    os.replace(tmp, _OUT)
-    return _OUT
+    os.replace(tmp, out)
+    return out
 
 
 def lib():
@@ -50,9 +50,18 @@ def lib():
     return _lib
 
 
+def lib_shared_basis():
+    """The checker with the shared-basis relinearisation taken by every ring and basis (the rule of the product waits
+    for parameter sets that the oracle is slow at)."""
+    global _lib_shared
+    if _lib_shared is None:
+        _lib_shared = _capi.declare(ctypes.CDLL(build(["-DHCNN_SHARED_ALL"], _OUT.replace(".so", "_shared.so"))))
+    return _lib_shared
+
+
 class EmuContext(OpsMixin):
-    def __init__(self, n, q, p, t):
-        self.raw = _capi.RawContext(lib(), n, q, p, t, 0)
+    def __init__(self, n, q, p, t, library=None):
+        self.raw = _capi.RawContext(library or lib(), n, q, p, t, 0)
 
     def _ptr(self, x):
         return ctypes.c_void_p(x.ctypes.data)

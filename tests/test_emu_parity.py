@@ -29,6 +29,21 @@ def backend():
     return EmuBackend()
 
 
+class SharedBasisBackend(EmuBackend):
+    def make_ctx(self, n, q, p, t):
+        return emu.EmuContext(n, q, p, t, emu.lib_shared_basis())
+
+
+@pytest.mark.parametrize("n,k,count", [(1024, 2, 3), (1024, 17, 9), (2048, 5, 8), (4096, 3, 2), (16384, 2, 2), (32768, 2, 2)])
+def test_square_relin_shared_basis(n, k, count):
+    """The shared-basis relinearisation: both of its last parts, groups of eight ciphertexts and a remainder, bases on
+    both sides of its folds; residues at the ends of the transforms' ranges."""
+    backend = SharedBasisBackend()
+    pc.check_square_relin(backend, n, k, n_random=count, n_genuine=0, check_decrypt=False)
+    if n <= 2048:
+        pc.check_transform_ranges(backend, n)
+
+
 @pytest.mark.parametrize("n,k,n_polys,rows", [(1024, 2, 3, None), (2048, 3, 2, 3), (4096, 2, 1, 2),
                                              (8192, 2, 1, 1), (16384, 1, 1, 1), (32768, 1, 10, 1)])
 def test_ntt_all_sizes(backend, n, k, n_polys, rows):

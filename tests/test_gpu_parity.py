@@ -8,6 +8,7 @@ import pytest
 
 import parity_cases as pc
 from oracle import fv
+from paper_1811_00778_amd import _capi
 from workloads import generators as gen
 
 pytestmark = pytest.mark.gpu
@@ -91,6 +92,25 @@ def test_square_relin_chunked_ragged(backend):
     pc.check_square_relin(backend, 1024, 3, n_random=5, n_genuine=1)      # one group of four sharing key loads + two singles
     pc.check_square_relin(backend, 1024, 3, n_random=2, n_genuine=0, chunk=2, relin_order=1)   # ciphertext-major order forced
     pc.check_square_relin(backend, 8192, 2, n_random=6, n_genuine=0, relin_order=2)            # key-major order
+
+
+@pytest.mark.parametrize("n,k,cts", [(32768, 12, 5), (32768, 13, 12), (16384, 16, 65)])
+def test_square_relin_shared_basis_equals_the_separate_kernels(backend, n, k, cts):
+    """Batches that take the shared-basis relinearisation by default, against the separate kernels (the deep-modulus
+    configuration below compares the same path with the oracle)."""
+    say("square_relin shared basis n=%d k=%d cts=%d" % (n, k, cts))
+    cand = _capi.gen_primes(backend.lib, n, 2 * k + 4)
+    q, rest = cand[:k], cand[k:]
+    ctx = backend.make_ctx(n, q, rest[:_capi.min_aux_count(backend.lib, n, q, 65537, rest)], 65537)
+    ctx.set_relin_key(ctx.sample_uniform(5, 1, 2 * k).reshape((k, 2, k, n)))
+    x = ctx.sample_uniform(5, 2, 2 * cts).reshape((cts, 2, k, n))
+    x[0, 0, :, :] = x[0, 0, :, :1]
+    out = ctx.ct_square_relin(x)
+    prod = ctx.ct_mul_relin(x, x)
+    ctx.set_fusion(1)
+    want = ctx.ct_square_relin(x)
+    assert (out == want).all() and (prod == want).all()
+    ctx.close()
 
 
 def test_square_relin_largest_rings_residue_exact(backend):
