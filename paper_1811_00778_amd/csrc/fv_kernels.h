@@ -21,10 +21,10 @@ constexpr uint32_t kXcds = 8;     // accelerator dies (each with its own L2); wo
 //     z_i = [x_i * (M/m_i)^-1]_{m_i},   sum_i z_i * (M/m_i) = x + v*M,
 //     v   = round(sum_i z_i / m_i)                      (because |x|/M < 1/2),
 //     x mod m'_j = sum_i z_i * [(M/m_i)]_{m'_j} - v * [M]_{m'_j}.
-// The tables hold the destination constants in "positive form", Bp and Vp, so that
-//     out_j = ( sum_i z_i * Bp[i][j] + v * Vp[j] (+ caller's extra term) ) mod m'_j
-// is one lazy 64-bit accumulation and one reduction (Vp = m' - [M]_{m'}; callers may fold
-// further constant factors into zmul, Bp and Vp).
+// The tables hold the destination constants centred and with the factor 2^32 of the signed Montgomery reduction, so that
+//     out_j = ( sum_i z_i * B[i][j] + v * V[j] (+ caller's extra term) ) * 2^-32 mod m'_j
+// is one 64-bit accumulation and one reduction (V = -[M]_{m'}; callers may fold further constant factors into zmul, B
+// and V).  A product is below 2^30 * 2^29 in magnitude; the reduction takes 12 of them, a fold (sfold) leaves room for 9 more.
 //
 // sum_i z_i/m_i is estimated in fixed point with 26 fractional bits: every term
 // floor(4 z_i * floor(2^56/m_i) / 2^32) is low by less than 2 units, so the estimate S
@@ -34,6 +34,14 @@ constexpr uint32_t kXcds = 8;     // accelerator dies (each with its own L2); wo
 // with those of (M-1)/2.  With the default band (128) that happens for about one
 // coefficient in 2^19.
 // ===================================================================================
+struct alignas(16) BConvDst {
+  uint32_t p, pinv;          // m'_j, -m'_j^-1 mod 2^32
+  int32_t rc, v;             // 2^32 mod m'_j centred, V[j]
+};
+struct alignas(16) BConvSrc {
+  uint32_t p, pinv;
+  int32_t rc, zm;            // zm: zmul_i * 2^32 centred, sredc(x * zm) = x * zmul_i
+};
 struct BConvDev {
   uint32_t ks, kd;
   const Mod* src_mod;        // [ks]
@@ -41,19 +49,12 @@ struct BConvDev {
   const ShoupConst* xmul;    // [ks]   residue of the converted integer = in_i * xmul_i mod m_i
   const uint32_t* ginv;      // [ks][ks] ginv[i*ks + l] = m_l^-1 mod m_i, l < i
   const uint32_t* half;      // [ks]   mixed-radix digits of (M-1)/2
-  const Mod* dst_mod;        // [kd]
-  const uint32_t* dst_pinv;  // [kd]   -m'_j^-1 mod 2^32 (destinations that are RNS primes)
-  uint32_t mont;             // 1: the destination constants carry an extra factor 2^32 (Montgomery form), which the
-                             // reduction of the accumulated sum takes out again (mont_reduce); see bconv_use_mont
-  const uint32_t* Bp;        // [ks][kd]
-  const uint32_t* BpT;       // [kd][ks]  the same constants, transposed
-  const uint32_t* Vp;        // [kd]
+  const BConvDst* dst;       // [kd]
+  const int32_t* B;          // [ks][kd]
+  const int32_t* BT;         // [kd][ks]  the same constants, transposed
+  const BConvSrc* src;       // [ks]   signed form of the source side (intermediate residues of the scaling step)
 };
-
-// Montgomery form is used where the whole sum of a destination residue (ks products plus `extra` more of the same
-// size) fits the 64-bit accumulator without an intermediate fold; longer sums keep plain constants and the
-// two-word Barrett reduction, which leaves room for 15 products between folds.
-HCNN_HOSTDEV constexpr bool bconv_use_mont(uint32_t ks, uint32_t extra) { return ks + extra <= kMontRoom; }
+constexpr int kSumRoom = 12, kSumAfterFold = 9;
 
 constexpr uint32_t kFracBits = 26;
 constexpr uint32_t kFracOne = 1u << kFracBits;
@@ -120,21 +121,20 @@ HCNN_HD uint32_t bconv_prepare(const BConvDev& bc, In in, uint32_t* zcol, uint32
   return bconv_round(S, band, exact, fallback_counter);
 }
 
-// Residue of the converted integer modulo destination j; `extra` (below 2^60, in the form of the table's constants)
-// is added before reducing.
-HCNN_HD uint32_t bconv_output(const BConvDev& bc, const uint32_t* zcol, int stride, uint32_t v, uint32_t j,
-                              uint64_t extra = 0) {
-  const Mod dm = ldc(bc.dst_mod, j);
-  uint64_t acc = extra + (uint64_t)v * ldc(bc.Vp, j);
-  if (bc.mont) {
-    for (uint32_t i = 0; i < bc.ks; ++i) acc += (uint64_t)zcol[i * stride] * ldc(bc.Bp, i * bc.kd + j);
-    return mont_reduce(acc, dm, ldc(bc.dst_pinv, j));
+// Canonical residue of a sum in the form of the tables.
+HCNN_HD uint32_t bconv_reduce(int64_t acc, const BConvDst& d) { return canon_p(sredc(sfold(acc, d.rc), d.p, d.pinv), d.p); }
+// acc + sum_i z[i] * b[i], folded where the room ends; `used`: products' worth of room that acc takes
+// (z: untraced, here and below -- a factor that the compiler knows to be non-negative it extends with zeros, and the signed
+// 32 x 32 product is lost to a 64-bit one: three instructions instead of one)
+template <int K>
+HCNN_HD int64_t bconv_sum(int64_t acc, const int32_t (&z)[K], const int32_t* b, int used, int32_t rc) {
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    if (used == kSumRoom) { acc = sfold(acc, rc); used = kSumRoom - kSumAfterFold; }
+    acc += (int64_t)z[i] * ldc(b, i);
+    ++used;
   }
-  for (uint32_t i = 0; i < bc.ks; ++i) {
-    acc += (uint64_t)zcol[i * stride] * ldc(bc.Bp, i * bc.kd + j);
-    if ((i & 7u) == 7u) acc = reduce64(acc, dm);
-  }
-  return reduce64(acc, dm);
+  return acc;
 }
 
 // ---------------------------------------------------------------- q -> q u p extension
@@ -148,32 +148,10 @@ struct ExtArgs {
   uint32_t band;
   unsigned long long* fallback_counter;
 };
-struct ExtKernel {
-  static constexpr int kThreads = kEwThreads;
-  static constexpr int kPhases = 1;
-  struct Regs {};
-  static size_t lds_bytes(uint32_t ks) { return (size_t)2 * ks * kThreads * 4; }
-  template <int PH>
-  HCNN_HD static void phase(const ExtArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
-    const uint32_t ks = a.bc.ks, kd = a.bc.kd, n = a.n;
-    const uint32_t blocks_per_poly = n / kThreads;
-    const size_t poly = bid / blocks_per_poly;
-    const uint32_t c = (bid % blocks_per_poly) * kThreads + tid;
-    const uint32_t* src = a.in + poly * ks * n + c;
-    uint32_t* dst = a.out + poly * (size_t)(ks + kd) * n + c;
-    uint32_t* zcol = lds + tid;
-    uint32_t* gcol = lds + (size_t)ks * kThreads + tid;
-    auto in = [&](uint32_t i) { return src[(size_t)i * n]; };
-    const uint32_t v = bconv_prepare(a.bc, in, zcol, gcol, kThreads, a.band, a.fallback_counter);
-    // (rows 0..ks-1 of `out` are not written: the forward transform reads those limbs from the ciphertext itself)
-    for (uint32_t j = 0; j < kd; ++j) dst[(size_t)(ks + j) * n] = bconv_output(a.bc, zcol, kThreads, v, j);
-  }
-};
-
-// Register-resident variant for compile-time basis sizes: z_i stay in VGPRs, every table index is a
+// The number of source primes is a compile-time constant (every k is instantiated): z_i stay in VGPRs, every table index is a
 // compile-time constant (scalar loads), the LDS column is touched only by the exact path.
-template <int K, int KP>
-struct ExtKernelT {
+template <int K>
+struct ExtKernel {
   static constexpr int kThreads = kEwThreads;
   static constexpr int kPhases = 1;
   struct Regs {};
@@ -185,16 +163,19 @@ struct ExtKernelT {
     const size_t poly = bid / blocks_per_poly;
     const uint32_t c = (bid % blocks_per_poly) * kThreads + tid;
     const uint32_t* src = a.in + poly * K * n + c;
-    uint32_t* dst = a.out + poly * (size_t)(K + KP) * n + c;
-    uint32_t x[K], z[K];
+    const uint32_t kp = a.bc.kd;
+    uint32_t* dst = a.out + poly * (size_t)(K + kp) * n + c;
+    uint32_t x[K];
+    int32_t z[K];
     uint32_t S = 0;
 #pragma unroll
     for (int i = 0; i < K; ++i) x[i] = src[(size_t)i * n];
 #pragma unroll
     for (int i = 0; i < K; ++i) {
       const Mod m = ldc(a.bc.src_mod, i);
-      z[i] = shoup_mul(x[i], ldc(a.bc.zmul, i), m.p);
-      S += frac_est(z[i], m);
+      const uint32_t zi = shoup_mul(x[i], ldc(a.bc.zmul, i), m.p);
+      S += frac_est(zi, m);
+      z[i] = untraced((int32_t)zi);
     }
     auto exact = [&]() {
       uint32_t* col = lds + tid;
@@ -202,26 +183,13 @@ struct ExtKernelT {
       for (int i = 0; i < K; ++i) col[i * kThreads] = shoup_mul(x[i], ldc(a.bc.xmul, i), ldc(a.bc.src_mod, i).p);
       return garner_gt_half(a.bc, col, kThreads);
     };
-    const uint32_t v = bconv_round(S, a.band, exact, a.fallback_counter);
+    const int32_t v = untraced((int32_t)bconv_round(S, a.band, exact, a.fallback_counter));
     // (rows 0..K-1 of `out` are not written: the forward transform reads those limbs from the ciphertext itself)
     // rolled loop over the destination primes: row j of the transposed table is one contiguous scalar load
 #pragma unroll 1
-    for (uint32_t j = 0; j < (uint32_t)KP; ++j) {
-      const Mod dm = ldc(a.bc.dst_mod, j);
-      const uint32_t* bt = a.bc.BpT + (size_t)j * K;
-      uint64_t acc = (uint64_t)v * ldc(a.bc.Vp, j);
-      if constexpr (bconv_use_mont(K, 0)) {
-#pragma unroll
-        for (int i = 0; i < K; ++i) acc += (uint64_t)z[i] * ldc(bt, i);
-        dst[(size_t)(K + j) * n] = mont_reduce(acc, dm, ldc(a.bc.dst_pinv, j));
-      } else {
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-          acc += (uint64_t)z[i] * ldc(bt, i);
-          if ((i % 14) == 12 && i + 1 < K) acc = reduce64(acc, dm);
-        }
-        dst[(size_t)(K + j) * n] = reduce64(acc, dm);
-      }
+    for (uint32_t j = 0; j < kp; ++j) {
+      const BConvDst d = ldc_at(a.bc.dst + j, 0u);
+      dst[(size_t)(K + j) * n] = bconv_reduce(bconv_sum<K>((int64_t)v * d.v, z, a.bc.BT + (size_t)j * K, 1, d.rc), d);
     }
   }
 };
@@ -231,62 +199,32 @@ struct ExtKernelT {
 //   -> y [n_ct][3][k][n],  y = round(t*d/q) mod q.
 // With r = [t*d]_q (centred): y = (t*d - r)/q exactly.  Modulo p_j:
 //     y = d'_j * (t q^-1) - sum_i z_i * q_i^-1 + v          (z_i = [t d_i (q/q_i)^-1]_{q_i})
-// (table to_p: Bp = p_j - q_i^-1, Vp = 1, extra term d'_j * tq_inv_j), then y, which satisfies
+// (table to_p: B = -q_i^-1, V = 1, extra term d'_j * tq_inv_j), then y, which satisfies
 // |y| < p/2 by the choice of the auxiliary basis, is converted p -> q (table to_q).
 struct ScaleArgs {
   const uint32_t* d;
   uint32_t* y;
   BConvDev to_p;              // src q (zmul = t*(q/q_i)^-1, xmul = t), dst p
   BConvDev to_q;              // src p (zmul = (p/p_j)^-1, xmul = 1), dst q
-  const uint32_t* tq_inv;     // [kp]  t * q^-1 mod p_j
+  const int32_t* tq_inv;      // [kp]  t * q^-1 mod p_j, in the form of the tables
   uint32_t n;
   uint32_t band;
   unsigned long long* fallback_counter;
 };
+// The number of ciphertext primes is a compile-time constant (see ExtKernel), the loop over the auxiliary primes is rolled:
+// y_j is produced, used at once for the p -> q conversion (k running 64-bit sums) and parked in the LDS column for the exact
+// path, so the register footprint is 3k + O(1) and the code size does not grow with k*k'.
+// Bound: memory up to k = 8 (3 L rows read, 3 k written: 4.7 TB/s), the multiply-adds and reductions beyond.
+template <int K>
 struct ScaleKernel {
   static constexpr int kThreads = kEwThreads;
   static constexpr int kPhases = 1;
   struct Regs {};
-  static size_t lds_bytes(uint32_t k, uint32_t kp) { return (size_t)(2 * (k > kp ? k : kp) + kp) * kThreads * 4; }
+  static size_t lds_bytes(uint32_t kp) { return (size_t)((uint32_t)K > kp ? (uint32_t)K : kp) * kThreads * 4; }
   template <int PH>
   HCNN_HD static void phase(const ScaleArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
-    const uint32_t k = a.to_p.ks, kp = a.to_p.kd, n = a.n, L = k + kp;
-    const uint32_t kmax = k > kp ? k : kp;
-    const uint32_t blocks_per_poly = n / kThreads;
-    const size_t poly = bid / blocks_per_poly;             // (ct, component)
-    const uint32_t c = (bid % blocks_per_poly) * kThreads + tid;
-    const uint32_t* src = a.d + poly * (size_t)L * n + c;
-    uint32_t* dst = a.y + poly * (size_t)k * n + c;
-    uint32_t* zcol = lds + tid;
-    uint32_t* gcol = lds + (size_t)kmax * kThreads + tid;
-    uint32_t* ycol = lds + (size_t)2 * kmax * kThreads + tid;
-
-    auto in_q = [&](uint32_t i) { return src[(size_t)i * n]; };
-    const uint32_t v = bconv_prepare(a.to_p, in_q, zcol, gcol, kThreads, a.band, a.fallback_counter);
-    for (uint32_t j = 0; j < kp; ++j) {
-      // d'_j arrives in [0, 2p): made canonical so that its product takes the room of one
-      const uint64_t extra = (uint64_t)csub(src[(size_t)(k + j) * n], ldc(a.to_p.dst_mod, j).p) * ldc(a.tq_inv, j);
-      ycol[j * kThreads] = bconv_output(a.to_p, zcol, kThreads, v, j, extra);
-    }
-    auto in_p = [&](uint32_t j) { return ycol[j * kThreads]; };
-    const uint32_t v2 = bconv_prepare(a.to_q, in_p, zcol, gcol, kThreads, a.band, a.fallback_counter);
-    for (uint32_t i = 0; i < k; ++i) dst[(size_t)i * n] = bconv_output(a.to_q, zcol, kThreads, v2, i);
-  }
-};
-
-// Register-resident variant (see ExtKernelT) with a rolled loop over the auxiliary primes: y_j is produced, used at once for the
-// p -> q conversion (k running 64-bit sums) and parked in the LDS column for the exact path, so
-// the register footprint is 3k + O(1) and the code size does not grow with k*k'.
-template <int K, int KP>
-struct ScaleKernelR {
-  static constexpr int kThreads = kEwThreads;
-  static constexpr int kPhases = 1;
-  struct Regs {};
-  static size_t lds_bytes() { return (size_t)(K > KP ? K : KP) * kThreads * 4; }
-  template <int PH>
-  HCNN_HD static void phase(const ScaleArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
-    const uint32_t n = a.n;
-    constexpr int L = K + KP;
+    const uint32_t n = a.n, kp = a.to_p.kd;
+    const uint32_t L = K + kp;
     const uint32_t blocks_per_poly = n / kThreads;
     const size_t poly = bid / blocks_per_poly;             // (ct, component)
     const uint32_t c = (bid % blocks_per_poly) * kThreads + tid;
@@ -294,7 +232,7 @@ struct ScaleKernelR {
     uint32_t* dst = a.y + poly * (size_t)K * n + c;
     uint32_t* col = lds + tid;
 
-    uint32_t z[K];
+    int32_t z[K];
     uint32_t S = 0;
     {
       uint32_t dq[K];
@@ -303,8 +241,9 @@ struct ScaleKernelR {
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         const Mod m = ldc(a.to_p.src_mod, i);
-        z[i] = shoup_mul(dq[i], ldc(a.to_p.zmul, i), m.p);
-        S += frac_est(z[i], m);
+        const uint32_t zi = shoup_mul(dq[i], ldc(a.to_p.zmul, i), m.p);
+        S += frac_est(zi, m);
+        z[i] = untraced((int32_t)zi);
       }
     }
     auto exact_q = [&]() {
@@ -312,66 +251,48 @@ struct ScaleKernelR {
         col[i * kThreads] = shoup_mul(src[(size_t)i * n], ldc(a.to_p.xmul, i), ldc(a.to_p.src_mod, i).p);
       return garner_gt_half(a.to_p, col, kThreads);
     };
-    const uint32_t v = bconv_round(S, a.band, exact_q, a.fallback_counter);
+    const int32_t v = untraced((int32_t)bconv_round(S, a.band, exact_q, a.fallback_counter));
 
-    // to_p sums K products and the term of d'_j (which arrives in [0, 2p): it takes the room of two unless it is made
-    // canonical first); to_q sums KP products.  Each uses Montgomery-form constants iff the host built them so.
-    constexpr bool kMontP = bconv_use_mont(K, 1), kCanonDp = !bconv_use_mont(K, 2);
-    constexpr bool kMontQ = bconv_use_mont(KP, 0);
-    constexpr int kCadence = 14;             // plain form: products below 2^60 between two-word reductions
-    uint64_t out_acc[K];
+    int64_t out_acc[K];
 #pragma unroll
     for (int i = 0; i < K; ++i) out_acc[i] = 0;
-    uint32_t S2 = 0;
+    uint32_t S2 = 0, room = kSumRoom;
     uint32_t dp_next = src[(size_t)K * n];
 #pragma unroll 1
-    for (uint32_t j = 0; j < (uint32_t)KP; ++j) {
+    for (uint32_t j = 0; j < kp; ++j) {
       uint32_t dpj = dp_next;
-      if (j + 1 < (uint32_t)KP) dp_next = src[(size_t)(K + j + 1) * n];
-      const Mod dm = ldc(a.to_p.dst_mod, j);
-      if constexpr (kCanonDp) dpj = csub(dpj, dm.p);
-      uint64_t acc = (uint64_t)dpj * ldc(a.tq_inv, j) + (uint64_t)v * ldc(a.to_p.Vp, j);
-      const uint32_t* bt = a.to_p.BpT + (size_t)j * K;
-      uint32_t yj;
-      if constexpr (kMontP) {
+      if (j + 1 < kp) dp_next = src[(size_t)(K + j + 1) * n];
+      const BConvDst d = ldc_at(a.to_p.dst + j, 0u);
+      dpj = csub(dpj, d.p);                                       // arrives in [0, 2p)
+      const int64_t first = (int64_t)untraced((int32_t)dpj) * ldc(a.tq_inv, j) + (int64_t)v * d.v;
+      const int32_t yj = sredc(bconv_sum<K>(first, z, a.to_p.BT + (size_t)j * K, 2, d.rc), d.p, d.pinv);
+      col[j * kThreads] = (uint32_t)yj;                           // made canonical by the exact path if it runs
+      const BConvSrc q = ldc_at(a.to_q.src + j, 0u);
+      const uint32_t z2 = canon_p(sredc((int64_t)yj * q.zm, q.p, q.pinv), q.p);
+      S2 += frac_est(z2, ldc(a.to_q.src_mod, j));
+      const int32_t* b2 = a.to_q.B + (size_t)j * K;
+      const int32_t zs = untraced((int32_t)z2);
+      if (room == 0) {
+        room = kSumAfterFold;
 #pragma unroll
-        for (int i = 0; i < K; ++i) acc += (uint64_t)z[i] * ldc(bt, i);
-        yj = mont_step(acc, dm.p, ldc(a.to_p.dst_pinv, j));     // any 32-bit value is a valid operand of the Shoup product below
-      } else {
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-          acc += (uint64_t)z[i] * ldc(bt, i);
-          if ((i % kCadence) == kCadence - 2 && i + 1 < K) acc = reduce64(acc, dm);   // the term of d'_j came first
-        }
-        yj = reduce64_lazy(acc, dm);
+        for (int i = 0; i < K; ++i) out_acc[i] = sfold(out_acc[i], ldc(a.to_q.dst, i).rc);
       }
-      col[j * kThreads] = yj;                                     // made canonical by the exact path if it runs
-      const Mod sm = ldc(a.to_q.src_mod, j);
-      const uint32_t z2 = shoup_mul(yj, ldc(a.to_q.zmul, j), sm.p);
-      S2 += frac_est(z2, sm);
-      const uint32_t* b2 = a.to_q.Bp + (size_t)j * K;
+      --room;
 #pragma unroll
-      for (int i = 0; i < K; ++i) out_acc[i] += (uint64_t)z2 * ldc(b2, i);
-      if constexpr (!kMontQ) {
-        if ((j % kCadence) == kCadence - 1) {
-#pragma unroll
-          for (int i = 0; i < K; ++i) out_acc[i] = reduce64(out_acc[i], ldc(a.to_q.dst_mod, i));
-        }
-      }
+      for (int i = 0; i < K; ++i) out_acc[i] += (int64_t)zs * ldc(b2, i);
     }
     auto exact_p = [&]() {
-      for (uint32_t j = 0; j < (uint32_t)KP; ++j) {
-        const Mod sm = ldc(a.to_q.src_mod, j);
-        col[j * kThreads] = reduce32(col[j * kThreads], sm);
+      for (uint32_t j = 0; j < kp; ++j) {
+        const BConvSrc q = ldc_at(a.to_q.src + j, 0u);
+        col[j * kThreads] = canon_p(sredc((int64_t)(int32_t)col[j * kThreads] * q.rc, q.p, q.pinv), q.p);
       }
       return garner_gt_half(a.to_q, col, kThreads);
     };
-    const uint32_t v2 = bconv_round(S2, a.band, exact_p, a.fallback_counter);
+    const int32_t v2 = untraced((int32_t)bconv_round(S2, a.band, exact_p, a.fallback_counter));
 #pragma unroll
     for (int i = 0; i < K; ++i) {
-      const Mod dm = ldc(a.to_q.dst_mod, i);
-      const uint64_t sum = out_acc[i] + (uint64_t)v2 * ldc(a.to_q.Vp, i);      // v2*Vp < 2^36
-      dst[(size_t)i * n] = kMontQ ? mont_reduce(sum, dm, ldc(a.to_q.dst_pinv, i)) : reduce64(sum, dm);
+      const BConvDst d = ldc_at(a.to_q.dst + i, 0u);
+      dst[(size_t)i * n] = bconv_reduce(out_acc[i] + (int64_t)v2 * d.v, d);      // v2 * V < 2^36
     }
   }
 };

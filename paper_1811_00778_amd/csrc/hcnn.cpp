@@ -258,10 +258,12 @@ int static_scratch_of_current_device(uint32_t** out) {
 // ---------------------------------------------------------------- context
 struct BConvHost {
   uint32_t ks = 0, kd = 0;
-  std::vector<Mod> src_mod, dst_mod;
+  std::vector<Mod> src_mod;
   std::vector<ShoupConst> zmul, xmul;
-  std::vector<uint32_t> ginv, half, Bp, BpT, Vp, dst_pinv;
-  uint32_t mont = 0;
+  std::vector<uint32_t> ginv, half;
+  std::vector<BConvDst> dst;
+  std::vector<BConvSrc> src;
+  std::vector<int32_t> B, BT;
 };
 
 struct hcnn_ctx {
@@ -275,7 +277,7 @@ struct hcnn_ctx {
   NttLimb* d_limbs = nullptr;       // [k + kp]
   TwTable d_tw_fwd{}, d_tw_inv{};   // [k + kp][n/2]
   ShoupConst* d_delta = nullptr;    // [k] floor(q/t) mod q_l
-  uint32_t* d_tq_inv = nullptr;     // [kp] t * q^-1 mod p_j
+  int32_t* d_tq_inv = nullptr;      // [kp] t * q^-1 mod p_j
   BConvDev ext{}, to_p{}, to_q{}, dec{};
   uint32_t* d_gauss_t = nullptr;    // thresholds of the Gaussian sampler (uploaded on first use)
   uint32_t* d_dec_tab = nullptr;    // [k][3] constants of the decrypt rounding
@@ -328,12 +330,10 @@ int upload(hcnn_ctx* c, const std::vector<T>& h, T** d) {
 template <class K> struct KernelClass { static constexpr int id = HCNN_PROF_OTHER; };
 template <int A, int B, int C, int D> struct KernelClass<NttFwd<A, B, C, D>> { static constexpr int id = HCNN_PROF_NTT_FWD; };
 template <int A, int B, int C> struct KernelClass<NttInv<A, B, C>> { static constexpr int id = HCNN_PROF_NTT_INV; };
-template <> struct KernelClass<ExtKernel> { static constexpr int id = HCNN_PROF_BASE_EXT; };
-template <int A, int B> struct KernelClass<ExtKernelT<A, B>> { static constexpr int id = HCNN_PROF_BASE_EXT; };
-template <int A, int B> struct KernelClass<ScaleKernelR<A, B>> { static constexpr int id = HCNN_PROF_SCALE; };
+template <int A> struct KernelClass<ExtKernel<A>> { static constexpr int id = HCNN_PROF_BASE_EXT; };
+template <int A> struct KernelClass<ScaleKernel<A>> { static constexpr int id = HCNN_PROF_SCALE; };
 template <int O> struct KernelClass<RelinSharedMac<O>> { static constexpr int id = HCNN_PROF_RELIN_MAC; };
 template <int A, int B> struct KernelClass<RelinBack<A, B>> { static constexpr int id = HCNN_PROF_NTT_INV; };
-template <> struct KernelClass<ScaleKernel> { static constexpr int id = HCNN_PROF_SCALE; };
 template <int A> struct KernelClass<RelinMacKernel<A>> { static constexpr int id = HCNN_PROF_RELIN_MAC; };
 template <int A, int B, int C> struct KernelClass<RelinFused<A, B, C>> { static constexpr int id = HCNN_PROF_RELIN_FUSED; };
 template <int A, int B> struct KernelClass<TensorFused<A, B>> { static constexpr int id = HCNN_PROF_TENSOR; };
@@ -388,13 +388,12 @@ int fold_profile(hcnn_ctx* c) {
 
 // Tables of an exact centred base conversion src -> dst.
 //   zfac[i]   extra factor folded into z_i (1 or t), also used as xmul
-//   fold_inv  when true the tables give -(x * M^-1): Bp = m'_j - m_i^-1, Vp = 1
-//             otherwise they give x:                 Bp = M/m_i mod m'_j, Vp = m'_j - M mod m'_j
-//   dst_is_rns_prime  the destinations are ciphertext / auxiliary primes (dst_pinv holds -m'_j^-1 mod 2^32)
-//   extra_terms       further products of the same size that the kernels add to each destination sum; when the
-//             whole sum fits (bconv_use_mont) Bp and Vp are stored with an extra factor 2^32 mod m'_j (Montgomery form)
-BConvHost make_bconv(const std::vector<uint32_t>& src, const std::vector<uint32_t>& dst, uint64_t zfac,
-                     bool fold_inv, bool dst_is_rns_prime, uint32_t extra_terms = 0) {
+//   fold_inv  when true the tables give -(x * M^-1): B = -m_i^-1, V = 1
+//             otherwise they give x:                 B = M/m_i,   V = -M   (all mod m'_j, centred, times 2^32)
+int32_t h_centred(uint32_t x, uint32_t p) { return x > p / 2 ? (int32_t)x - (int32_t)p : (int32_t)x; }
+int32_t h_mont(uint32_t x, uint32_t p) { return h_centred(h_mulmod(x, (uint32_t)((1ull << 32) % p), p), p); }
+
+BConvHost make_bconv(const std::vector<uint32_t>& src, const std::vector<uint32_t>& dst, uint64_t zfac, bool fold_inv) {
   BConvHost h;
   h.ks = (uint32_t)src.size();
   h.kd = (uint32_t)dst.size();
@@ -402,8 +401,10 @@ BConvHost make_bconv(const std::vector<uint32_t>& src, const std::vector<uint32_
     const uint32_t m = src[i];
     h.src_mod.push_back(h_mod(m));
     const uint32_t Mi_inv = h_inv(h_prod_mod(src, (int)i, m), m);        // (M/m_i)^-1 mod m_i
-    h.zmul.push_back(h_shoup(h_mulmod(Mi_inv, (uint32_t)(zfac % m), m), m));
+    const uint32_t zm = h_mulmod(Mi_inv, (uint32_t)(zfac % m), m);
+    h.zmul.push_back(h_shoup(zm, m));
     h.xmul.push_back(h_shoup((uint32_t)(zfac % m), m));
+    h.src.push_back(BConvSrc{m, h_neg_inv32(m), h_mont(1, m), h_mont(zm, m)});
   }
   h.ginv.assign((size_t)h.ks * h.ks, 0);
   for (uint32_t i = 0; i < h.ks; ++i)
@@ -419,45 +420,34 @@ BConvHost make_bconv(const std::vector<uint32_t>& src, const std::vector<uint32_
     }
     h.half[i] = tt;
   }
-  h.Bp.assign((size_t)h.ks * h.kd, 0);
-  h.Vp.assign(h.kd, 0);
+  h.B.assign((size_t)h.ks * h.kd, 0);
+  h.BT.assign((size_t)h.ks * h.kd, 0);
   for (uint32_t j = 0; j < h.kd; ++j) {
     const uint32_t mj = dst[j];
-    if (dst_is_rns_prime) h.dst_mod.push_back(h_mod(mj));
-    else { Mod dm{}; dm.p = mj; h.dst_mod.push_back(dm); }
-    for (uint32_t i = 0; i < h.ks; ++i)
-      h.Bp[(size_t)i * h.kd + j] = fold_inv ? mj - h_inv(src[i] % mj, mj) : h_prod_mod(src, (int)i, mj);
-    h.Vp[j] = fold_inv ? 1u : (mj - h_prod_mod(src, -1, mj)) % mj;
-    h.mont = (dst_is_rns_prime && bconv_use_mont(h.ks, extra_terms)) ? 1u : 0u;
-    if (h.mont) {
-      const uint32_t r32 = (uint32_t)((1ull << 32) % mj);
-      for (uint32_t i = 0; i < h.ks; ++i) h.Bp[(size_t)i * h.kd + j] = h_mulmod(h.Bp[(size_t)i * h.kd + j], r32, mj);
-      h.Vp[j] = h_mulmod(h.Vp[j], r32, mj);
+    for (uint32_t i = 0; i < h.ks; ++i) {
+      const uint32_t b = fold_inv ? mj - h_inv(src[i] % mj, mj) : h_prod_mod(src, (int)i, mj);
+      h.B[(size_t)i * h.kd + j] = h.BT[(size_t)j * h.ks + i] = h_mont(b, mj);
     }
-    h.dst_pinv.push_back(dst_is_rns_prime ? h_neg_inv32(mj) : 0u);
+    h.dst.push_back(BConvDst{mj, h_neg_inv32(mj), h_mont(1, mj), fold_inv ? h_mont(1, mj) : -h_mont(h_prod_mod(src, -1, mj), mj)});
   }
-  h.BpT.assign((size_t)h.ks * h.kd, 0);
-  for (uint32_t i = 0; i < h.ks; ++i)
-    for (uint32_t j = 0; j < h.kd; ++j) h.BpT[(size_t)j * h.ks + i] = h.Bp[(size_t)i * h.kd + j];
   return h;
 }
 
 int upload_bconv(hcnn_ctx* c, const BConvHost& h, BConvDev* d) {
   int e;
-  Mod* sm; Mod* dm; ShoupConst* zm; ShoupConst* xm; uint32_t* gi; uint32_t* hf; uint32_t* B; uint32_t* BT; uint32_t* Mm; uint32_t* pi;
+  Mod* sm; ShoupConst* zm; ShoupConst* xm; uint32_t* gi; uint32_t* hf; BConvDst* dd; BConvSrc* ss; int32_t* B; int32_t* BT;
   if ((e = upload(c, h.src_mod, &sm))) return e;
-  if ((e = upload(c, h.dst_mod, &dm))) return e;
   if ((e = upload(c, h.zmul, &zm))) return e;
   if ((e = upload(c, h.xmul, &xm))) return e;
   if ((e = upload(c, h.ginv, &gi))) return e;
   if ((e = upload(c, h.half, &hf))) return e;
-  if ((e = upload(c, h.Bp, &B))) return e;
-  if ((e = upload(c, h.BpT, &BT))) return e;
-  if ((e = upload(c, h.Vp, &Mm))) return e;
-  if ((e = upload(c, h.dst_pinv, &pi))) return e;
+  if ((e = upload(c, h.dst, &dd))) return e;
+  if ((e = upload(c, h.src, &ss))) return e;
+  if ((e = upload(c, h.B, &B))) return e;
+  if ((e = upload(c, h.BT, &BT))) return e;
   d->ks = h.ks; d->kd = h.kd;
-  d->src_mod = sm; d->dst_mod = dm; d->zmul = zm; d->xmul = xm;
-  d->ginv = gi; d->half = hf; d->Bp = B; d->BpT = BT; d->Vp = Mm; d->dst_pinv = pi; d->mont = h.mont;
+  d->src_mod = sm; d->zmul = zm; d->xmul = xm; d->ginv = gi; d->half = hf;
+  d->dst = dd; d->src = ss; d->B = B; d->BT = BT;
   return 0;
 }
 
@@ -555,7 +545,7 @@ int build_tables(hcnn_ctx* c) {
 
   // decryption: r = [t*x]_q converted to the modulus t; the table carries the factor -q^-1 (DecRoundKernel)
   {
-    BConvHost h = make_bconv(c->q, std::vector<uint32_t>{}, c->t, false, false);
+    BConvHost h = make_bconv(c->q, std::vector<uint32_t>{}, c->t, false);
     if ((e = upload_bconv(c, h, &c->dec))) return e;
     const uint64_t qinv_t = h_powmod64(q_mod_t, c->t - 2, c->t);
     std::vector<uint32_t> tab;
@@ -580,20 +570,14 @@ int build_tables(hcnn_ctx* c) {
     if ((e = upload(c, crt, &c->d_crt))) return e;
   }
   if (c->kp) {
-    BConvHost h_ext = make_bconv(c->q, c->p, 1, false, true);
-    BConvHost h_to_p = make_bconv(c->q, c->p, c->t, true, true, 1);      // + the term of d'_j
-    BConvHost h_to_q = make_bconv(c->p, c->q, 1, false, true);
+    BConvHost h_ext = make_bconv(c->q, c->p, 1, false);
+    BConvHost h_to_p = make_bconv(c->q, c->p, c->t, true);
+    BConvHost h_to_q = make_bconv(c->p, c->q, 1, false);
     if ((e = upload_bconv(c, h_ext, &c->ext))) return e;
     if ((e = upload_bconv(c, h_to_p, &c->to_p))) return e;
     if ((e = upload_bconv(c, h_to_q, &c->to_q))) return e;
-    std::vector<uint32_t> tq;
-    for (uint32_t j = 0; j < c->kp; ++j) {
-      const uint32_t pj = c->p[j];
-      // t * q^-1 mod p_j, in the form of the constants it is summed with
-      uint32_t v = h_mulmod((uint32_t)(c->t % pj), h_inv(h_prod_mod(c->q, -1, pj), pj), pj);
-      if (h_to_p.mont) v = h_mulmod(v, (uint32_t)((1ull << 32) % pj), pj);
-      tq.push_back(v);
-    }
+    std::vector<int32_t> tq;
+    for (uint32_t pj : c->p) tq.push_back(h_mont(h_mulmod((uint32_t)(c->t % pj), h_inv(h_prod_mod(c->q, -1, pj), pj), pj), pj));
     if ((e = upload(c, tq, &c->d_tq_inv))) return e;
   }
   std::vector<unsigned long long> zeros(2, 0);
@@ -722,28 +706,27 @@ int ntt_dense(hcnn_ctx* c, const uint32_t* in, uint32_t* out, size_t rows, uint3
   return ntt_rows(c, r, inverse, io);
 }
 
-// Base-conversion kernels: register-resident variants for the basis sizes of the standard
-// parameter sets, the generic LDS-column kernels otherwise (about four times slower in the scaling step).
-// k' = k + 1 covers t = 65537 up to n = 8192, k' = k + 2 the larger rings and the larger plaintext moduli.
-#define HCNN_REGISTER_BASES(X)                                                                          \
-  X(2, 3) X(3, 4) X(4, 5) X(5, 6) X(6, 7) X(7, 8) X(8, 9) X(9, 10) X(10, 11) X(11, 12) X(12, 13)        \
-  X(4, 6) X(6, 8) X(8, 10) X(10, 12) X(11, 13) X(12, 14) X(14, 16) X(16, 18) X(24, 26)
+// Base-conversion kernels: one instance per number of ciphertext primes.
+#define HCNN_EVERY_K(X)                                                                               \
+  X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18)  \
+  X(19) X(20) X(21) X(22) X(23) X(24) X(25) X(26) X(27) X(28) X(29) X(30) X(31) X(32)
+static_assert(HCNN_MAX_LIMBS == 32, "HCNN_EVERY_K lists every number of primes");
 int ext_dispatch(hcnn_ctx* c, size_t grid, const ExtArgs& a) {
-  const uint32_t k = c->k, kp = c->kp;
-#define HCNN_EXT_CASE(K, KP) \
-  if (k == K && kp == KP) return run<ExtKernelT<K, KP>>(c, grid, ExtKernelT<K, KP>::lds_bytes(), a);
-  HCNN_REGISTER_BASES(HCNN_EXT_CASE)
+  switch (c->k) {
+#define HCNN_EXT_CASE(K) case K: return run<ExtKernel<K>>(c, grid, ExtKernel<K>::lds_bytes(), a);
+    HCNN_EVERY_K(HCNN_EXT_CASE)
 #undef HCNN_EXT_CASE
-  return run<ExtKernel>(c, grid, ExtKernel::lds_bytes(k), a);
+  }
+  return HCNN_ERR_ARG;
 }
 
 int scale_dispatch(hcnn_ctx* c, size_t grid, const ScaleArgs& a) {
-  const uint32_t k = c->k, kp = c->kp;
-#define HCNN_SCALE_CASE(K, KP) \
-  if (k == K && kp == KP) return run<ScaleKernelR<K, KP>>(c, grid, ScaleKernelR<K, KP>::lds_bytes(), a);
-  HCNN_REGISTER_BASES(HCNN_SCALE_CASE)
+  switch (c->k) {
+#define HCNN_SCALE_CASE(K) case K: return run<ScaleKernel<K>>(c, grid, ScaleKernel<K>::lds_bytes(c->kp), a);
+    HCNN_EVERY_K(HCNN_SCALE_CASE)
 #undef HCNN_SCALE_CASE
-  return run<ScaleKernel>(c, grid, ScaleKernel::lds_bytes(k, kp), a);
+  }
+  return HCNN_ERR_ARG;
 }
 
 template <int FT>
@@ -1176,8 +1159,6 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   }
   if (C < 1) C = 1;
   if (C > n_ct) C = n_ct;
-  const size_t need_lds_scale = ScaleKernel::lds_bytes(k, kp);
-  if (need_lds_scale > c->max_lds) return HCNN_ERR_NODEVICE;
   // ciphertexts of one internal batch that can take the separate kernels
   const size_t C_split = shared_min ? std::min(C, shared_min - 1) : (fused && fused_round) ? std::min(C, fused_round) : C;
   int e;

@@ -193,6 +193,12 @@ def test_measure_ceiling_arguments(backend):
     s.ctx.close()
 
 
+@pytest.mark.parametrize("k", [1, 9, 10, 11, 12, 13, 19, 20, 21, 22, 30])
+def test_square_relin_folds_of_the_base_changes(backend, k):
+    """Numbers of primes on both sides of the sums' folds (12 products, then 9 more), smallest and largest instance."""
+    pc.check_square_relin(backend, 1024, k, n_random=1, n_genuine=0)
+
+
 def test_general_hmult(backend):
     pc.check_mul_relin(backend, 1024, 2)
     pc.check_mul_relin(backend, 2048, 3, force_exact=True)

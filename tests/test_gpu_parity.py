@@ -179,6 +179,13 @@ def test_square_relin_register_variants_of_standard_bases(backend, k, k_aux, big
     pc.check_square_relin(backend, 1024, k, n_random=1, n_genuine=0, t=t, force_exact=True)
 
 
+@pytest.mark.parametrize("k", [1, 9, 10, 11, 12, 13, 19, 20, 21, 22, 30])
+def test_square_relin_folds_of_the_base_changes(backend, k):
+    """Numbers of primes on both sides of the sums' folds (12 products, then 9 more), smallest and largest instance."""
+    say("square_relin k=%d: folds of the base changes" % k)
+    pc.check_square_relin(backend, 1024, k, n_random=1, n_genuine=0)
+
+
 def test_general_hmult(backend):
     say("mul_relin")
     pc.check_mul_relin(backend, 1024, 2)
