@@ -834,6 +834,10 @@ template <int LOGN, int LOGR>
 int crypt_fused(hcnn_ctx* c, const CryptArgs& a, bool enc) {
   const size_t grid = ntt_grouped_grid(a.n_rows, c->k), lds = NttGeom<LOGN, LOGR>::kLdsBytes;
   if (enc) return run<CryptFused<LOGN, LOGR, true>>(c, grid, lds, a);
+  if (a.u) {
+    // (the largest ring does not hold a second row in its registers)
+    if constexpr (LOGN <= 14) return run<CryptFused<LOGN, LOGR, false, true>>(c, grid, lds, a);
+  }
   return run<CryptFused<LOGN, LOGR, false>>(c, grid, lds, a);
 }
 int crypt_rows(hcnn_ctx* c, CryptArgs a, size_t n_ct, bool enc) {
@@ -854,10 +858,14 @@ int secret_hat(hcnn_ctx* c, const int32_t* s, uint32_t* s_hat) {
   r.small = s;
   return ntt_rows(c, r, false, kNttSmallKey);
 }
+// Does every (ciphertext, limb) row find a compute unit of its own?  Then a workgroup's own transform of s is shorter than
+// a launch for it in front.
+bool decrypts_with_own_key(const hcnn_ctx* c, size_t n_ct) { return c->logn <= 14 && n_ct * c->k <= c->compute_units; }
 // x = c0 + c1*s mod q of cc ciphertexts
-int decrypt_rows(hcnn_ctx* c, const uint32_t* cts, size_t cc, const uint32_t* s_hat, uint32_t* x) {
+int decrypt_rows(hcnn_ctx* c, const int32_t* s, const uint32_t* cts, size_t cc, const uint32_t* s_hat, uint32_t* x, bool own) {
   CryptArgs a{};
   a.key = s_hat; a.cts = cts; a.out = x;
+  a.u = own ? s : nullptr;
   return crypt_rows(c, a, cc, false);
 }
 
@@ -1421,10 +1429,11 @@ static int decrypt_impl(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size
   if (e) return e;
   uint32_t* s_hat = c->work;
   uint32_t* x = s_hat + poly;
-  if ((e = secret_hat(c, sk, s_hat))) return e;
+  const bool own = decrypts_with_own_key(c, n_ct);
+  if (!own && (e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);
-    if ((e = decrypt_rows(c, ct + c0 * 2 * poly, cc, s_hat, x))) return e;
+    if ((e = decrypt_rows(c, sk, ct + c0 * 2 * poly, cc, s_hat, x, own))) return e;
     DecRoundArgs da;
     da.x = x; da.m_out = m_out ? m_out + c0 * rn : nullptr; da.m_out64 = m_out64 ? m_out64 + c0 * rn : nullptr;
     da.bc = c->dec; da.tab = c->d_dec_tab; da.t = c->t; da.n = n;
@@ -1458,10 +1467,11 @@ int hcnn_noise_bits(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size_t n
   uint32_t* s_hat = c->work;
   uint32_t* x = s_hat + poly;
   if ((e = dev_memset(bits_out, 0, n_ct * sizeof(uint32_t), c->stream))) return e;
-  if ((e = secret_hat(c, sk, s_hat))) return e;
+  const bool own = decrypts_with_own_key(c, n_ct);
+  if (!own && (e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);
-    if ((e = decrypt_rows(c, ct + c0 * 2 * poly, cc, s_hat, x))) return e;
+    if ((e = decrypt_rows(c, sk, ct + c0 * 2 * poly, cc, s_hat, x, own))) return e;
     NoiseArgs na;
     na.x = x; na.bits = bits_out + c0; na.bc = c->dec; na.n = n;
     if ((e = run<NoiseKernel>(c, cc * bpp, NoiseKernel::lds_bytes(k), na))) return e;

@@ -118,7 +118,9 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              // forward, shared-basis relinearisation: digit rows and key rows, stored in tiles of 64 coefficients (the key
              // product reads all rows of a tile: whole kilobytes in one place instead of 256 bytes from every row):
              // digits [ct][r][tile][i][64], key [r][tile][i][o][64]; the sums lie in [ct][r][tile][o][64]
-             kNttDigitTile = 27, kNttKeyTile = 28 };   // inverse, inside TensorFused: component
+             kNttDigitTile = 27, kNttKeyTile = 28,
+             // decryption of few ciphertexts: the secret's row into registers too, and the product of the two rows
+             kNttSecretToRegs = 29, kNttDecOwn = 30 };   // inverse, inside TensorFused: component
                                                            // b of the tensor formed from those registers (as kNttLoadTensor)
 
 // Per-thread state of TensorFused: the two transformed polynomials of the ciphertext, one limb.
@@ -140,10 +142,10 @@ template <int R>
 struct BackRegs {
   int32_t z0[R], z1[R];
 };
-// Per-thread state of CryptFused: one transformed polynomial.
+// Per-thread state of CryptFused: one transformed polynomial (and, where it makes its own, the key row).
 template <int R>
 struct RowRegs {
-  int32_t c0[R];
+  int32_t c0[R], c1[R];
 };
 
 struct NttArgs {
@@ -278,9 +280,9 @@ HCNN_HD void r4_inv(int32_t& x0, int32_t& x1, int32_t& x2, int32_t& x3, int32_t 
 template <int LOGN, int LOGR, int IO = kNttPlain, int SPLIT = 0>
 struct NttFwd {
   static constexpr bool kFused = IO == kNttFusedMac || IO == kNttFusedMac16 || IO == kNttFusedMacAny;
-  static constexpr bool kRowToRegs = IO == kNttSmallToRegs || IO == kNttCtToRegs;
+  static constexpr bool kRowToRegs = IO == kNttSmallToRegs || IO == kNttCtToRegs || IO == kNttSecretToRegs;
   static constexpr bool kToRegs = IO == kNttToRegs0 || IO == kNttToRegs1 || kRowToRegs;
-  static constexpr bool kSmallIn = IO == kNttSmallToRegs || IO == kNttSmallKey;
+  static constexpr bool kSmallIn = IO == kNttSmallToRegs || IO == kNttSmallKey || IO == kNttSecretToRegs;
   static constexpr bool kKeyOut = IO == kNttStoreKey || IO == kNttSmallKey || IO == kNttKeyTile;
   static constexpr bool kTileOut = IO == kNttDigitTile || IO == kNttKeyTile;
   static constexpr bool kDigitRow = IO == kNttLoadDigit || IO == kNttDigitTile;
@@ -339,7 +341,7 @@ struct NttFwd {
       const uint32_t kk = a.digits.d, ct = quot(group, a.digits);     // group = (ct, digit)
       gin = a.in + ((size_t)ct * 3 * kk + 2 * kk + (group - ct * kk)) * N;
     } else if constexpr (kSmallIn) {
-      gin = reinterpret_cast<const uint32_t*>(a.small) + (size_t)group * N;
+      gin = reinterpret_cast<const uint32_t*>(a.small) + (IO == kNttSecretToRegs ? 0 : (size_t)group * N);
     } else if constexpr (IO == kNttCtToRegs) {
       gin = a.in + ((size_t)(group * 2 + 1) * a.cycle.d + within) * N;
     } else if constexpr (kToRegs) {
@@ -442,8 +444,8 @@ struct NttFwd {
       } else if constexpr (kLast && kToRegs) {
 #pragma unroll
         for (int e = 0; e < NET; ++e) {
-          if constexpr (IO == kNttToRegs1) regs.c1[c * NET + e] = half_range(v[e], p);
-          else                             regs.c0[c * NET + e] = half_range(v[e], p);      // (the only row of RowRegs)
+          if constexpr (IO == kNttToRegs1 || IO == kNttSecretToRegs) regs.c1[c * NET + e] = half_range(v[e], p);
+          else                             regs.c0[c * NET + e] = half_range(v[e], p);
         }
       } else if constexpr (kLast) {
         static_assert(!kLast || TLAST == 1, "the last pass holds consecutive residues");
@@ -477,7 +479,7 @@ template <int LOGN, int LOGR, int IO = kNttPlain>
 struct NttInv {
   static_assert(IO == kNttPlain || IO == kNttLoadTensor || IO == kNttStoreAdd || IO == kNttLoadTensorMul ||
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
-                IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut || IO == kNttBackRow || IO == kNttBack0 ||
+                IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut || IO == kNttDecOwn || IO == kNttBackRow || IO == kNttBack0 ||
                 IO == kNttBack1 || IO == kNttBack2, "inverse NTT io mode");
   using G = NttGeom<LOGN, LOGR, IO == kNttPlain>;
   static constexpr int kThreads = G::kThreads;
@@ -488,7 +490,7 @@ struct NttInv {
   static constexpr bool kFromRegs = IO == kNttFromRegs0 || IO == kNttFromRegs1;
   static constexpr bool kTensorRegs = IO == kNttTensorRegs0 || IO == kNttTensorRegs1 || IO == kNttTensorRegs2;
   static constexpr bool kBack = IO == kNttBack0 || IO == kNttBack1 || IO == kNttBack2;
-  static constexpr bool kEncOut = IO == kNttEncOut0 || IO == kNttEncOut1, kKeyRegs = kEncOut || IO == kNttDecOut;
+  static constexpr bool kEncOut = IO == kNttEncOut0 || IO == kNttEncOut1, kDecOut = IO == kNttDecOut || IO == kNttDecOwn, kKeyRegs = kEncOut || kDecOut;
   using Regs = std::conditional_t<kFromRegs, RelinRegs<G::R>, std::conditional_t<kTensorRegs, TensorRegs<G::R>,
                std::conditional_t<kKeyRegs, RowRegs<G::R>, std::conditional_t<kBack, BackRegs<G::R>, NoRegs>>>>;
 
@@ -547,12 +549,12 @@ struct NttInv {
       // b = 0: c0*c0' ; b = 2: c1*c1' ; b = 1: c0*c1' + c1*c0'
       gin = gmul0 + (comp == 2 ? (size_t)LL * N : 0);
       gin2 = gmul1 + (comp == 0 ? 0 : (size_t)LL * N);
-    } else if constexpr (kKeyRegs) {
+    } else if constexpr (kKeyRegs && IO != kNttDecOwn) {
       gin = a.in + ((IO == kNttEncOut1 ? (size_t)a.cycle.d : 0) + within) * N;      // key row of this limb
     } else if constexpr (IO == kNttBackRow || kBack) {
       const uint32_t ct = kBack ? unit_ct : quot(group, a.digits), o = group - ct * a.digits.d;
       gin = a.in + (size_t)(ct * 3 + within) * (N / 64) * a.tile_words + o * 64;
-    } else if constexpr (!kFromRegs && !kTensorRegs) {
+    } else if constexpr (!kFromRegs && !kTensorRegs && !kKeyRegs) {
       gin = a.in + ((size_t)group * a.in_group_rows + a.in_row0 + within) * N;
     }
     uint32_t* gout;
@@ -570,7 +572,7 @@ struct NttInv {
       // o = (b, j), 2k = a.digits of them
       gout = a.out + ((size_t)unit_ct * a.digits.d + unit_o) * N;
       gaux = a.aux + ((size_t)unit_ct * (a.digits.d / 2 * 3) + unit_o) * N;            // y row (ct, b, j)
-    } else if constexpr (IO == kNttDecOut) {
+    } else if constexpr (kDecOut) {
       gout = a.out + (size_t)bid * N;
       gaux = a.aux + ((size_t)group * 2 * a.cycle.d + within) * N;                   // c0
     } else {
@@ -606,6 +608,11 @@ struct NttInv {
           const int32_t y = IO == kNttTensorRegs1 ? untraced(regs.c1[c * NET + e]) : x;
           v[e] = sredc((int64_t)(IO == kNttTensorRegs1 ? untraced(x + x) : x) * y, p, L.pinv);
         }
+      } else if constexpr (kFirst && IO == kNttDecOwn) {
+        // two plain rows: the product carries 2^-32, which the output scaling takes out
+#pragma unroll
+        for (int e = 0; e < NET; ++e)
+          v[e] = sredc((int64_t)untraced(regs.c0[c * NET + e]) * untraced(regs.c1[c * NET + e]), p, L.pinv);
       } else if constexpr (kFirst && kKeyRegs) {
         // |row| <= p, |key| <= p/2: products stay within (-p, p)
         int32_t y[NET];
@@ -650,7 +657,7 @@ struct NttInv {
         for (int e = 0; e < NET; ++e) v[e] = (int32_t)lds[lds_elem<LOG_TLAST>(sbase, e)];
       }
       const uint32_t root = (1u << S0) + i;
-      constexpr bool kMont = IO == kNttLoadTensor || IO == kNttLoadTensorMul || kTensorRegs;
+      constexpr bool kMont = IO == kNttLoadTensor || IO == kNttLoadTensorMul || kTensorRegs || IO == kNttDecOwn;
       constexpr bool kZ = IO == kNttBackRow || kBack;
       const InvRoot& top = kMont ? L.inv_r : kZ ? L.inv_z : L.inv;       // node 1: the output scaling folded in
 #pragma unroll
@@ -722,7 +729,7 @@ struct NttInv {
           if constexpr (IO == kNttEncOut0) r = add_mod(r, dm[e], p);
           st_at(gout + e * TLAST, base * 4, r);
         }
-      } else if constexpr (kLast && (IO == kNttStoreAdd || kFromRegs || IO == kNttDecOut)) {
+      } else if constexpr (kLast && (IO == kNttStoreAdd || kFromRegs || kDecOut)) {
         // all loads of the addend before the first store (the compiler must assume the buffers alias)
         uint32_t addend[NET];
 #pragma unroll
@@ -868,11 +875,13 @@ struct RelinBack {
 // Workgroup (ct, l), one row in registers from the forward transform to the last store:
 //   encryption  u -> forward; times pk0^, back, + e1 + floor(q/t) m -> c0; times pk1^, back, + e2 -> c1
 //   decryption  c1 -> forward; times s^, back, + c0 -> x
+// OWN (decryption of few ciphertexts): the workgroup transforms s itself instead of waiting for a launch that does
+// (10 ciphertexts at n = 8192, k = 8: 23.4 -> 20.7 us; 4 at n = 1024, k = 2: 14.1 -> 11.6).
 // As separate launches the same work moves every row through memory five times in between (and was cut into batches of 64
 // for its buffers): 784 encryptions at n = 8192, k = 8 took 1312 us.
 struct CryptArgs {
   const uint32_t* key;      // [2][k][n] (encryption) or [k][n]: transformed, as kNttStoreKey leaves it
-  const int32_t* u;         // encryption: [n_ct][n]
+  const int32_t* u;         // encryption: [n_ct][n]; OWN: s [n]
   const int32_t* e1;
   const int32_t* e2;
   const uint32_t* msg;      // as in NttArgs
@@ -887,12 +896,12 @@ struct CryptArgs {
   FastDiv cycle;            // k
 };
 
-template <int LOGN, int LOGR, bool ENC>
+template <int LOGN, int LOGR, bool ENC, bool OWN = false>
 struct CryptFused {
   using G = NttGeom<LOGN, LOGR>;
   static constexpr int P = G::kPhases;
   static constexpr int kThreads = G::kThreads;
-  static constexpr int kPhases = (ENC ? 3 : 2) * P;
+  static constexpr int kPhases = (ENC || OWN ? 3 : 2) * P;
   static constexpr int kMinWavesPerSimd = 4;
   using Regs = RowRegs<G::R>;
 
@@ -900,7 +909,13 @@ struct CryptFused {
   HCNN_HD static void phase(const CryptArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
     NttArgs na{};
     na.limbs = a.limbs; na.cycle = a.cycle; na.n_rows = a.n_rows;
-    if constexpr (PH < P) {
+    if constexpr (OWN) {
+      na.small = a.u; na.in = a.cts; na.out = a.out; na.aux = a.cts;
+      na.tw = PH < 2 * P ? a.tw_fwd : a.tw_inv;
+      if constexpr (PH < P) NttFwd<LOGN, LOGR, kNttSecretToRegs>::template phase<PH>(na, bid, tid, lds, regs);
+      else if constexpr (PH < 2 * P) NttFwd<LOGN, LOGR, kNttCtToRegs>::template phase<PH - P>(na, bid, tid, lds, regs);
+      else NttInv<LOGN, LOGR, kNttDecOwn>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
+    } else if constexpr (PH < P) {
       na.tw = a.tw_fwd; na.small = a.u; na.in = a.cts;
       NttFwd<LOGN, LOGR, ENC ? kNttSmallToRegs : kNttCtToRegs>::template phase<PH>(na, bid, tid, lds, regs);
     } else {
