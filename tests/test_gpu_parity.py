@@ -67,6 +67,21 @@ def test_encrypt_decrypt_of_every_ring(backend, n, k):
     pc.check_keygen_encrypt_decrypt(backend, n, k, count=1)
 
 
+@pytest.mark.parametrize("n,k,count", [(1024, 2, 150), (8192, 8, 40), (16384, 9, 30)])
+def test_decrypt_of_a_batch_equals_its_pieces(backend, n, k, count):
+    """More rows than compute units (the secret is transformed once, in front) against pieces of three ciphertexts
+    (every workgroup transforms it itself; those are compared with the oracle above)."""
+    say("decrypt n=%d k=%d count=%d" % (n, k, count))
+    cand = _capi.gen_primes(backend.lib, n, k)
+    ctx = backend.make_ctx(n, cand, [], 65537)
+    s = ctx.sample_ternary(3, 1, 1)[0]
+    x = ctx.sample_uniform(3, 2, 2 * count).reshape((count, 2, k, n))
+    whole = ctx.decrypt(s, x)
+    for i in range(0, count, 3):
+        assert (ctx.decrypt(s, x[i:i + 3]) == whole[i:i + 3]).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,k", [(1024, 2), (2048, 5)])
 def test_scalar_mac(backend, n, k):
     say("scalar_mac n=%d k=%d" % (n, k))
