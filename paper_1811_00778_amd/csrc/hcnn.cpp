@@ -1021,11 +1021,11 @@ int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
   if (e) return e;
   if (shared_basis_min(c)) {
     if (!c->d_evk_shared) {
+      // (three times the key's memory: a device that cannot spare it keeps the other forms)
       void* ptr = nullptr;
-      if ((e = dev_malloc(&ptr, rows * 3 * c->n * 4))) return e;
-      c->d_evk_shared = (uint32_t*)ptr;
+      if (dev_malloc(&ptr, rows * 3 * c->n * 4) == 0) c->d_evk_shared = (uint32_t*)ptr;
     }
-    for (uint32_t r = 0; r < 3; ++r) {
+    for (uint32_t r = 0; r < 3 && c->d_evk_shared; ++r) {
       NttRows kr{evk_dev, c->d_evk_shared, rows, 1, c->k + r, 1, 0, 1, r};
       kr.tile_words = (uint32_t)(rows * 64);
       if ((e = ntt_rows(c, kr, false, kNttKeyTile))) return e;
@@ -1145,7 +1145,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   // Its workgroups are long (k + 2 transforms each), so it only takes whole rounds of resident workgroups; what is
   // left of a batch (all of a small batch) goes through the three separate kernels, which spread k^2 rows per
   // ciphertext over the chip.
-  const size_t shared_min = c->fusion == 0 && !static_ws ? shared_basis_min(c) : 0;
+  const size_t shared_min = c->fusion == 0 && !static_ws && c->d_evk_shared ? shared_basis_min(c) : 0;
   const bool fused = c->fusion != 1 && (c->logn <= 13 || (c->logn == 14 && k <= 16));
   // (the k workgroups of a ciphertext share a die, for its L2: a round is counted per die)
   const size_t fused_round = fused ? relin_fused_slots(c) / kXcds / k * kXcds : 0;   // ciphertexts per round (0: never)

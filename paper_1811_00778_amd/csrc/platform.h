@@ -235,7 +235,11 @@ int launch(hcnn_stream_t, size_t grid, size_t lds_bytes, const Args& a) {
 
 #else
 // ------------------------------------------------------------------ HIP
-inline int dev_malloc(void** p, size_t bytes) { return (int)hipMalloc(p, bytes ? bytes : 1); }
+inline int dev_malloc(void** p, size_t bytes) {
+  const hipError_t e = hipMalloc(p, bytes ? bytes : 1);
+  if (e != hipSuccess) (void)hipGetLastError();      // reported here, not by the next launch
+  return (int)e;
+}
 inline int dev_free(void* p) { return (int)hipFree(p); }
 inline int dev_memset(void* p, int v, size_t bytes, hcnn_stream_t s) { return (int)hipMemsetAsync(p, v, bytes, s); }
 inline int copy_h2d(void* d, const void* h, size_t bytes, hcnn_stream_t s) {
