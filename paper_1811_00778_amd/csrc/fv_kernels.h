@@ -749,8 +749,9 @@ struct MacMfma {
   static constexpr uint32_t kTile = 64, kStreams = kThreads / 64 / GB;      // coefficients per wave and step; waves on one group
   HCNN_HOSTDEV static uint32_t terms(uint32_t T) { return (T + 15) / 16 * 16; }
   HCNN_HOSTDEV static uint32_t chunks(uint32_t T) { return (T + 63) / 64; }
-  HCNN_HOSTDEV static uint32_t group_words(uint32_t T) { return chunks(T) * (64 + 256); }   // offsets and weights of one group
-  static size_t lds_bytes(size_t T) { return (size_t)GB * group_words((uint32_t)T) * 4; }
+  // offsets and weights of one group (32 bits hold it for every row that lds_bytes lets through)
+  HCNN_HOSTDEV static uint32_t group_words(uint32_t T) { return chunks(T) * (64 + 256); }
+  static size_t lds_bytes(size_t T) { return (size_t)GB * ((T + 63) / 64 * (64 + 256)) * 4; }
   static uint32_t tile_blocks(const MacArgs& a) {
     const uint32_t per = a.steps * kStreams, tiles = 2 * a.k * a.n / kTile;
     return (tiles + per - 1) / per;

@@ -757,21 +757,31 @@ int mac_mfma_launch(hcnn_ctx* c, const MacArgs& a) {
   return run<MacMfma<GB>>(c, MacMfma<GB>::grid(b), MacMfma<GB>::lds_bytes(a.T), b);
 }
 
-int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
+// Neighbouring groups that a workgroup of the matrix form takes (4, 2 or 1); 0: the call takes the vector form.
+// Where the multiply-adds weigh more than the byte transposition (measured, matrix against vector form, us: 16 filters x 25
+// terms 600 / 666, x 32 553 / 638, x 144 543 / 884, x 576 1950 / 3540; 8 x 144 490 / 497, 8 x 32 464 / 347); where the vector
+// form's workgroups (1024 coefficients of one group) do not fill the chip (one group, 845 terms x 10 filters at n = 8192, k =
+// 8: 87 / 141; 1536 workgroups at n = 32768, k = 24 do: 1235 / 1188); and where the vector form could not stage its row
+// (1600 x 16: 1.42 / 20.2 ms).
+int mac_matrix_groups(const hcnn_ctx* c, size_t grid, const MacArgs& a) {
   const bool offsets_fit = (uint64_t)a.n_in * 2 * a.k * a.n / 4 <= 0xffffffffull;   // 16-byte offsets kept in 32 bits
   const size_t lds_max = std::min<size_t>(64 * 1024, c->max_lds);
-  // The matrix form: where the multiply-adds weigh more than the byte transposition (measured, matrix against vector form,
-  // us: 16 filters x 25 terms 600 / 666, x 32 553 / 638, x 144 543 / 884, x 576 1950 / 3540; 8 x 144 490 / 497, 8 x 32
-  // 464 / 347); where the vector form's workgroups (1024 coefficients of one group) do not fill the chip (one group, 845
-  // terms x 10 filters at n = 8192, k = 8: 87 / 141; 1536 workgroups at n = 32768, k = 24 do: 1235 / 1188); and where the
-  // vector form could not stage its row (1600 x 16: 1.42 / 20.2 ms).
+  // (a row of weights bounded by zero counts its terms too: the tables are sized by them)
+  const uint64_t w_max = a.w_abs_max > 0 ? (uint64_t)a.w_abs_max : 1;
+  if (a.w_abs_max > 127 || a.T * w_max > kMfmaMaxSum || !offsets_fit) return 0;
   const bool many = (a.F >= 10 && a.T >= 96) || (a.F >= 14 && a.T >= 25), few_blocks = grid < 4 * (size_t)c->compute_units;
   const bool long_row = MacKernel<1>::lds_bytes(a.F, a.T) > lds_max;
-  if ((a.G > 1 ? many : a.F >= 8 && a.T >= 64 && few_blocks) || long_row)
-  if (a.w_abs_max <= 127 && (uint64_t)a.T * (uint32_t)a.w_abs_max <= kMfmaMaxSum && offsets_fit) {
-    if (a.G >= 4 && MacMfma<4>::lds_bytes(a.T) <= lds_max) return mac_mfma_launch<4>(c, a);
-    if (a.G >= 2 && MacMfma<2>::lds_bytes(a.T) <= lds_max) return mac_mfma_launch<2>(c, a);
-    if (MacMfma<1>::lds_bytes(a.T) <= lds_max) return mac_mfma_launch<1>(c, a);
+  if (!(a.G > 1 ? many : a.F >= 8 && a.T >= 64 && few_blocks) && !long_row) return 0;
+  if (a.G >= 4 && MacMfma<4>::lds_bytes(a.T) <= lds_max) return 4;
+  if (a.G >= 2 && MacMfma<2>::lds_bytes(a.T) <= lds_max) return 2;
+  return MacMfma<1>::lds_bytes(a.T) <= lds_max ? 1 : 0;
+}
+
+int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
+  switch (mac_matrix_groups(c, grid, a)) {
+    case 4: return mac_mfma_launch<4>(c, a);
+    case 2: return mac_mfma_launch<2>(c, a);
+    case 1: return mac_mfma_launch<1>(c, a);
   }
   switch (a.F) {
     case 1: return mac_launch<1>(c, grid, a);

@@ -28,9 +28,9 @@ _OUT = os.path.join(_OUT_DIR, "libhcnn_emu_san.so" if SANITIZE else "libhcnn_emu
 _lib = _lib_shared = None
 
 
-def build(defines=(), out=_OUT) -> str:
+def build(defines=(), out=_OUT, source=os.path.join(_SRC_DIR, "hcnn.cpp")) -> str:
     os.makedirs(_OUT_DIR, exist_ok=True)
-    srcs = [os.path.join(_SRC_DIR, f) for f in os.listdir(_SRC_DIR)] + [os.path.join(_ROOT, "include", "hcnn.h")]
+    srcs = [os.path.join(_SRC_DIR, f) for f in os.listdir(_SRC_DIR)] + [os.path.join(_ROOT, "include", "hcnn.h"), source]
     if os.path.exists(out) and all(os.path.getmtime(s) <= os.path.getmtime(out) for s in srcs):
         return out
     tmp = out + ".tmp.%d" % os.getpid()
@@ -38,7 +38,7 @@ def build(defines=(), out=_OUT) -> str:
         if SANITIZE else ["-O2"]
     subprocess.check_call(["g++", "-std=c++17"] + extra + ["-DHCNN_HOSTEMU", *defines, "-fPIC", "-shared", "-Wall", "-Wextra",
                            "-Wno-unused-parameter", "-Wno-unknown-pragmas", "-o", tmp,
-                           os.path.join(_SRC_DIR, "hcnn.cpp")])
+                           source])
     os.replace(tmp, out)
     return out
 

@@ -1,0 +1,19 @@
+// The host-side rules of the library that no entry point shows, for tests/test_host_rules.py: the library's source with
+// plain functions around them.
+#include "../paper_1811_00778_amd/csrc/hcnn.cpp"
+
+extern "C" {
+
+// Groups per workgroup of the scalar MAC's matrix form on a device of `units` compute units, 0: the vector form.
+int rule_mac_matrix_groups(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in, uint32_t G, uint32_t F, uint32_t T, int32_t w_abs_max) {
+  hcnn_ctx c;
+  c.n = n; c.k = k; c.compute_units = units; c.max_lds = max_lds_bytes();
+  MacArgs a{};
+  a.k = k; a.n = n; a.n_in = n_in; a.G = G; a.F = F; a.T = T; a.w_abs_max = w_abs_max;
+  return mac_matrix_groups(&c, (size_t)G * (2 * k * n / (kEwThreads * kEwVec)), a);
+}
+size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
+  return groups == 4 ? MacMfma<4>::lds_bytes(T) : groups == 2 ? MacMfma<2>::lds_bytes(T) : MacMfma<1>::lds_bytes(T);
+}
+
+}  // extern "C"
