@@ -585,8 +585,15 @@ int build_tables(hcnn_ctx* c) {
   return 0;
 }
 
+// The work buffer grows on demand and is kept; growing waits for the stream, frees and allocates (25 to 450 us).  Its first
+// allocation holds what the decryption of 64 ciphertexts takes (65 polynomials: 17 MiB at n = 8192, k = 8, 195 at n = 32768,
+// k = 24; and no less than 512 rows, for the small bases), so that a decryption finds its place in what the key generation or
+// the encryption of the same context left.  First decryption after both, us, growing / not: 25 ciphertexts at n = 8192, k =
+// 8 335 / 42, 60 at n = 32768, k = 24 831 / 419.
+constexpr size_t kWorkPolys = 65, kWorkRows = 512;
 int ensure_work(hcnn_ctx* c, size_t bytes) {
   if (bytes <= c->work_bytes) return 0;
+  bytes = std::max(bytes, std::max(kWorkPolys * c->k, kWorkRows) * c->n * 4);
   if (c->work) {
     int e = stream_sync(c->stream);
     if (e) return e;
@@ -871,6 +878,13 @@ int secret_hat(hcnn_ctx* c, const int32_t* s, uint32_t* s_hat) {
 // Does every (ciphertext, limb) row find a compute unit of its own?  Then a workgroup's own transform of s is shorter than
 // a launch for it in front.
 bool decrypts_with_own_key(const hcnn_ctx* c, size_t n_ct) { return c->logn <= 14 && n_ct * c->k <= c->compute_units; }
+// Work buffer of a decryption or a noise read-out: x [C][k][n] of up to 256 MiB (C ciphertexts a piece), then s_hat [k][n]
+// unless the workgroups transform the secret themselves.
+int decrypt_work(hcnn_ctx* c, size_t n_ct, bool own, size_t* C) {
+  const size_t poly = (size_t)c->k * c->n;
+  *C = std::min<size_t>(n_ct, std::max<size_t>(64, ((size_t)256 << 20) / (poly * 4)));
+  return ensure_work(c, (*C + (own ? 0 : 1)) * poly * 4);
+}
 // x = c0 + c1*s mod q of cc ciphertexts
 int decrypt_rows(hcnn_ctx* c, const int32_t* s, const uint32_t* cts, size_t cc, const uint32_t* s_hat, uint32_t* x, bool own) {
   CryptArgs a{};
@@ -1433,13 +1447,12 @@ static int decrypt_impl(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size
   const uint32_t k = c->k, n = c->n;
   const size_t rn = n, poly = (size_t)k * rn;
   const size_t bpp = n / kEwThreads;
-  const size_t C = std::min<size_t>(n_ct, std::max<size_t>(64, ((size_t)256 << 20) / (poly * 4)));
-  // scratch: s_hat [k][n] | x [C][k][n], up to 256 MiB
-  int e = ensure_work(c, (poly + C * poly) * 4);
-  if (e) return e;
-  uint32_t* s_hat = c->work;
-  uint32_t* x = s_hat + poly;
   const bool own = decrypts_with_own_key(c, n_ct);
+  size_t C;
+  int e = decrypt_work(c, n_ct, own, &C);
+  if (e) return e;
+  uint32_t* x = c->work;
+  uint32_t* s_hat = x + C * poly;                // (not there with its own key)
   if (!own && (e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);
@@ -1470,14 +1483,13 @@ int hcnn_noise_bits(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size_t n
   const uint32_t k = c->k, n = c->n;
   const size_t rn = n, poly = (size_t)k * rn;
   const size_t bpp = n / kEwThreads;
-  const size_t C = std::min<size_t>(n_ct, std::max<size_t>(64, ((size_t)256 << 20) / (poly * 4)));
-  // scratch: s_hat [k][n] | x [C][k][n], up to 256 MiB
-  int e = ensure_work(c, (poly + C * poly) * 4);
-  if (e) return e;
-  uint32_t* s_hat = c->work;
-  uint32_t* x = s_hat + poly;
-  if ((e = dev_memset(bits_out, 0, n_ct * sizeof(uint32_t), c->stream))) return e;
   const bool own = decrypts_with_own_key(c, n_ct);
+  size_t C;
+  int e = decrypt_work(c, n_ct, own, &C);
+  if (e) return e;
+  uint32_t* x = c->work;
+  uint32_t* s_hat = x + C * poly;                // (not there with its own key)
+  if ((e = dev_memset(bits_out, 0, n_ct * sizeof(uint32_t), c->stream))) return e;
   if (!own && (e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);

@@ -6,6 +6,7 @@ import pytest
 
 import emu
 import parity_cases as pc
+from paper_1811_00778_amd import _capi
 
 
 class EmuBackend:
@@ -63,6 +64,30 @@ def test_keygen_encrypt_decrypt(backend, n, k):
 @pytest.mark.parametrize("n,k", [(4096, 3), (8192, 2), (16384, 2), (32768, 2)])
 def test_encrypt_decrypt_of_every_ring(backend, n, k):
     pc.check_keygen_encrypt_decrypt(backend, n, k, count=1)
+
+
+@pytest.mark.parametrize("n,k", [(1024, 1), (1024, 2), (8192, 8), (32768, 24)])
+def test_first_decryption_of_a_context_finds_its_work_buffer(backend, n, k):
+    """A decryption or noise read-out of up to 64 ciphertexts after key generation or one encryption allocates nothing."""
+    cand = _capi.gen_primes(backend.lib, n, k)
+    s, e = np.zeros(n, np.int32), np.zeros((1, n), np.int32)
+    a, m = np.zeros((k, n), np.uint32), np.zeros((1, n), np.uint32)
+    s[1], pk = 1, np.zeros((2, k, n), np.uint32)
+    for after in ("keygen", "encrypt"):
+        ctx = backend.make_ctx(n, cand, [], 65537)
+        if after == "keygen":
+            ctx.keygen(s, a, e[0])
+        else:
+            ctx.encrypt(pk, m, e, e, e)
+        held = ctx.scratch_bytes()
+        for count in ((1, 10) if n > 8192 else (1, 10, 25, 64)):
+            x = np.zeros((count, 2, k, n), np.uint32)
+            x[-1, 1] = 1
+            ctx.decrypt(s, x)
+            if n == 1024:
+                ctx.noise_bits(s, x)
+            assert ctx.scratch_bytes() == held, (after, count)
+        ctx.close()
 
 
 @pytest.mark.parametrize("n,k", [(1024, 2), (2048, 5)])
