@@ -733,10 +733,13 @@ struct MacKernel {
 // The GB groups of a workgroup are neighbours (kernel placements that share most of their inputs): their waves run through
 // the terms together and find each other's inputs in the compute unit's cache.  The XCD order of the tiles is that of MacKernel.
 // A term row is padded to a multiple of 16 with zero-weight terms on its last input.
-// Bound: the gather.  576 terms x 16 filters over 64 groups at n = 8192, k = 10: 3.54 -> 1.95 ms, 24 GB gathered at 23
-// bytes per clock and compute unit, vector unit 44 % used, matrix unit 9 %.  Measured and left out: a second register
-// buffer of inputs (spills: 2.6 ms); the waves kept in step by a barrier per chunk (L2 requests halved, 2.0 ms: the
-// waits it adds cost what it saves); eight groups on eight waves (2.0 ms).
+// Two groups, not four: a last workgroup of 4 is up to three quarters empty, and a launch of few groups stages twice the tables per
+// tile (us, four / two groups per workgroup: 16 filters x 576 terms, 64 groups, n = 8192, k = 10 1676 / 1548; 10 x 576, 9 groups
+// 395 / 347; 10 x 96, 8 groups, n = 4096, k = 4 21 / 15).
+// Bound: the gather.  576 terms x 16 filters over 64 groups at n = 8192, k = 10: vector form 3.40 ms, this one 1.50, 24 GB gathered at
+// 32 bytes per clock and compute unit (18 GB of it from L2), vector unit 55 % used, matrix unit 12 %.  Measured and left out: a second register
+// buffer of inputs (spills: a third slower); the waves kept in step by a barrier per chunk (L2 requests halved, no faster: the
+// waits it adds cost what it saves); eight groups on eight waves.
 constexpr uint32_t kMfmaMaxSum = 1u << 20;     // T * |w| <= 2^20: sums of weight * byte stay below 2^28, and 4 * 2^28 * p/2
                                                // leaves the Montgomery step within (-p, p)
 template <int GB>
@@ -770,38 +773,59 @@ struct MacMfma {
     if (tile0 >= tiles) return;                                       // padding blocks (whole block)
     const uint32_t words = group_words(a.T), T16 = terms(a.T);
     if constexpr (PH == 0) {
-      for (uint32_t gi = 0; gi < GB && g0 + gi < a.G; ++gi) {
-        const uint32_t* idx = a.idx + (size_t)(g0 + gi) * a.T;
-        const int32_t* w = a.w + (size_t)(g0 + gi) * a.F * a.T;
-        uint32_t* l_off = lds + gi * words;
-        uint32_t* l_w = l_off + chunks(a.T) * 64;
-        for (uint32_t t = tid; t < T16; t += kThreads) {
-          const bool pad = t >= a.T;
-          uint32_t src = idx[pad ? a.T - 1 : t];
-          if (src >= a.n_in) {
-            src = 0;
-            if (tb == 0 && !pad) atomic_inc64(a.bad_counter);
-          }
-          l_off[t] = src * (2u * a.k * a.n / 4);       // in 16-byte units (the host checked that it fits)
-        }
-        for (uint32_t x = tid; x < chunks(a.T) * 256; x += kThreads) {
-          const uint32_t q = x % 4, lane = x / 4 % 64, f = lane % 16;
-          const uint32_t t0 = x / 256 * 64 + q * 16 + lane / 16 * 4;
-          uint32_t packed = 0;
-          for (uint32_t b = 0; b < 4; ++b) {
-            const uint32_t t = t0 + b;
-            if (t >= a.T || f >= a.F) continue;
-            int32_t wf = w[(size_t)f * a.T + t];
-            if (wf > a.w_abs_max || wf < -a.w_abs_max) {
-              wf = 0;
-              if (tb == 0) atomic_inc64(a.bad_counter);
-            }
-            if (idx[t] >= a.n_in) wf = 0;
-            packed |= (uint32_t)(wf & 0xff) << (8 * b);
-          }
-          l_w[x] = packed;
+      // Every load is unconditional (clamped to the row's last term, the last filter, the last group) and the groups' loads
+      // are issued together: with a branch per load the eight loads of a word waited for one another, and a launch that
+      // runs few tiles per workgroup spent most of its time here (us, branches / now, four groups per workgroup: 14 filters x 25
+      // terms, 4 groups, n = 8192, k = 8 22.1 / 17.2; 10 x 96 36.6 / 30.0)
+      const uint32_t* idx[GB];
+      const int32_t* w[GB];
+#pragma unroll
+      for (uint32_t gi = 0; gi < GB; ++gi) {
+        const size_t g = g0 + gi < a.G ? g0 + gi : a.G - 1;
+        idx[gi] = a.idx + g * a.T;
+        w[gi] = a.w + g * a.F * a.T;
+      }
+      uint32_t bad = 0;
+      for (uint32_t t = tid; t < T16; t += kThreads) {
+        uint32_t src[GB];
+#pragma unroll
+        for (uint32_t gi = 0; gi < GB; ++gi) src[gi] = idx[gi][t < a.T ? t : a.T - 1];
+#pragma unroll
+        for (uint32_t gi = 0; gi < GB; ++gi) {
+          const bool out = src[gi] >= a.n_in;
+          bad += out && t < a.T && g0 + gi < a.G;
+          lds[gi * words + t] = (out ? 0 : src[gi]) * (2u * a.k * a.n / 4);       // in 16-byte units (the host checked that it fits)
         }
       }
+      for (uint32_t x = tid; x < chunks(a.T) * 256; x += kThreads) {
+        // four terms of a filter per thread; the 64 bytes of a quad step lie with four neighbours, so that a wave's load
+        // touches 16 short runs and not 64 words (rows of a multiple of 32 terms suffered most: 128 bytes apart)
+        const uint32_t lg = x % 4, f = x / 4 % 16, q = x / 64 % 4, t0 = x / 256 * 64 + q * 16 + lg * 4;
+        const uint32_t word = x / 256 * 256 + (lg * 16 + f) * 4 + q;
+        int32_t wf[GB][4];
+        uint32_t src[GB][4];
+#pragma unroll
+        for (uint32_t gi = 0; gi < GB; ++gi)
+#pragma unroll
+          for (uint32_t b = 0; b < 4; ++b) {
+            const uint32_t t = t0 + b < a.T ? t0 + b : a.T - 1;
+            wf[gi][b] = w[gi][(size_t)(f < a.F ? f : a.F - 1) * a.T + t];
+            src[gi][b] = idx[gi][t];
+          }
+#pragma unroll
+        for (uint32_t gi = 0; gi < GB; ++gi) {
+          uint32_t packed = 0;
+#pragma unroll
+          for (uint32_t b = 0; b < 4; ++b) {
+            const bool term = (t0 + b < a.T) & (f < a.F), beyond = (wf[gi][b] > a.w_abs_max) | (wf[gi][b] < -a.w_abs_max);
+            bad += term & beyond & (g0 + gi < a.G);
+            packed |= term & !beyond & (src[gi][b] < a.n_in) ? (uint32_t)(wf[gi][b] & 0xff) << (8 * b) : 0u;
+          }
+          lds[gi * words + chunks(a.T) * 64 + word] = packed;
+        }
+      }
+      if (tb == 0)
+        for (; bad != 0; --bad) atomic_inc64(a.bad_counter);
     } else {
       const uint32_t wave = wave_uniform((uint32_t)tid / 64), lane = (uint32_t)tid % 64;
       const uint32_t gi = wave % GB, g = g0 + gi, lg = lane / 16, ln = lane % 16;

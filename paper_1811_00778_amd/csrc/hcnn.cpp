@@ -764,12 +764,17 @@ int mac_mfma_launch(hcnn_ctx* c, const MacArgs& a) {
   return run<MacMfma<GB>>(c, MacMfma<GB>::grid(b), MacMfma<GB>::lds_bytes(a.T), b);
 }
 
-// Neighbouring groups that a workgroup of the matrix form takes (4, 2 or 1); 0: the call takes the vector form.
-// Where the multiply-adds weigh more than the byte transposition (measured, matrix against vector form, us: 16 filters x 25
-// terms 600 / 666, x 32 553 / 638, x 144 543 / 884, x 576 1950 / 3540; 8 x 144 490 / 497, 8 x 32 464 / 347); where the vector
-// form's workgroups (1024 coefficients of one group) do not fill the chip (one group, 845 terms x 10 filters at n = 8192, k =
-// 8: 87 / 141; 1536 workgroups at n = 32768, k = 24 do: 1235 / 1188); and where the vector form could not stage its row
-// (1600 x 16: 1.42 / 20.2 ms).
+// Neighbouring groups that a workgroup of the matrix form takes (2 or 1); 0: the call takes the vector form.
+// Measured, vector / matrix form, us:
+// - The matrix form, where the multiply-adds weigh more than the byte transposition (64 groups, n = 8192, k = 8: 14 filters x 25
+//   terms 227 / 217, 16 x 25 260 / 226, 10 x 96 335 / 273, 16 x 144 724 / 362; 8 x 32, 139 / 183, is not taken).
+// - The vector form, where the inputs are gathered less than 1.5 times and its workgroups (1024 coefficients of one group)
+//   fill the chip: reading the inputs bounds the call (2 x 2 kernels without overlap, 32 channels, 16 groups x 16 filters, n =
+//   8192, k = 10 310 / 325; gathered 1.65 times, 16 x 144, 9 groups, n = 16384, k = 16 513 / 462).  So does one group that fills it (8 x 64 at n = 32768, k = 24 64 / 69).
+// - The matrix form, where one group's vector workgroups do not fill the chip (10 x 845, n = 8192, k = 8 127 / 58) and where the
+//   vector form could not stage its row (16 x 1000, 9 groups, n = 8192, k = 10 6661 / 521).
+// - Three to six groups go one at a time: half of a pair may be empty, and two pairs read their shared inputs twice (14 x 72,
+//   4 groups, n = 32768, k = 12, pairs / single groups 205 / 181; 14 x 25, 3 groups, k = 24 156 / 136).
 int mac_matrix_groups(const hcnn_ctx* c, size_t grid, const MacArgs& a) {
   const bool offsets_fit = (uint64_t)a.n_in * 2 * a.k * a.n / 4 <= 0xffffffffull;   // 16-byte offsets kept in 32 bits
   const size_t lds_max = std::min<size_t>(64 * 1024, c->max_lds);
@@ -777,16 +782,15 @@ int mac_matrix_groups(const hcnn_ctx* c, size_t grid, const MacArgs& a) {
   const uint64_t w_max = a.w_abs_max > 0 ? (uint64_t)a.w_abs_max : 1;
   if (a.w_abs_max > 127 || a.T * w_max > kMfmaMaxSum || !offsets_fit) return 0;
   const bool many = (a.F >= 10 && a.T >= 96) || (a.F >= 14 && a.T >= 25), few_blocks = grid < 4 * (size_t)c->compute_units;
+  const bool read_bound = !few_blocks && 2 * (uint64_t)a.G * a.T < 3 * (uint64_t)a.n_in;
   const bool long_row = MacKernel<1>::lds_bytes(a.F, a.T) > lds_max;
-  if (!(a.G > 1 ? many : a.F >= 8 && a.T >= 64 && few_blocks) && !long_row) return 0;
-  if (a.G >= 4 && MacMfma<4>::lds_bytes(a.T) <= lds_max) return 4;
-  if (a.G >= 2 && MacMfma<2>::lds_bytes(a.T) <= lds_max) return 2;
+  if (!(a.G > 1 ? many && !read_bound : a.F >= 8 && a.T >= 64 && few_blocks) && !long_row) return 0;
+  if (a.G >= 2 && !(a.G >= 3 && a.G <= 6) && MacMfma<2>::lds_bytes(a.T) <= lds_max) return 2;
   return MacMfma<1>::lds_bytes(a.T) <= lds_max ? 1 : 0;
 }
 
 int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
   switch (mac_matrix_groups(c, grid, a)) {
-    case 4: return mac_mfma_launch<4>(c, a);
     case 2: return mac_mfma_launch<2>(c, a);
     case 1: return mac_mfma_launch<1>(c, a);
   }

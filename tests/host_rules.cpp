@@ -13,7 +13,7 @@ int rule_mac_matrix_groups(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in
   return mac_matrix_groups(&c, (size_t)G * (2 * k * n / (kEwThreads * kEwVec)), a);
 }
 size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
-  return groups == 4 ? MacMfma<4>::lds_bytes(T) : groups == 2 ? MacMfma<2>::lds_bytes(T) : MacMfma<1>::lds_bytes(T);
+  return groups == 2 ? MacMfma<2>::lds_bytes(T) : MacMfma<1>::lds_bytes(T);
 }
 
 }  // extern "C"

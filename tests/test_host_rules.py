@@ -24,12 +24,31 @@ def rules():
 def test_matrix_form_tables_fit_the_lds_that_a_launch_asks_for(rules, T, bound):
     """A staged group takes 64 offsets and 256 weight words per 64 terms; a row whose tables do not fit stays with the
     vector forms, whatever the bound on its weights."""
-    for groups in (1, 2, 4):
+    for groups in (1, 2):
         assert rules.rule_mac_matrix_lds(groups, T) == groups * ((T + 63) // 64) * 320 * 4
     for G, F in ((1, 1), (1, 16), (2, 16), (7, 16), (4, 3)):
         form = rules.rule_mac_matrix_groups(256, 1024, 2, 100, G, F, T, bound)
-        assert form in (0, 1, 2, 4) and form <= max(G, 1)
+        assert form in (0, 1, 2) and form <= max(G, 1)
         if form:
             assert rules.rule_mac_matrix_lds(form, T) <= 64 * 1024 and T * bound <= 1 << 20
         if T > 3264:
             assert form == 0
+
+
+@pytest.mark.parametrize("n,k,n_in,G,F,T,form", [
+    (8192, 8, 784, 144, 5, 25, 0),            # few filters: vector
+    (8192, 8, 784, 144, 13, 25, 0), (8192, 8, 784, 144, 14, 24, 0), (8192, 8, 784, 144, 14, 25, 2),
+    (8192, 10, 4096, 64, 9, 576, 0), (8192, 10, 4096, 64, 10, 95, 0), (8192, 10, 4096, 256, 10, 96, 2),
+    (8192, 10, 4096, 64, 16, 576, 2),
+    (8192, 10, 2048, 16, 16, 192, 2), (8192, 10, 2048, 16, 16, 191, 0),        # every input gathered 1.5 times, or less
+    (8192, 10, 2048, 16, 16, 128, 0), (1024, 2, 2048, 16, 16, 128, 2),         # ... where the launch fills the chip
+    (8192, 8, 100, 2, 10, 96, 2), (8192, 8, 100, 3, 10, 96, 1), (8192, 8, 100, 6, 10, 96, 1), (8192, 8, 100, 7, 10, 96, 2),
+    (8192, 8, 845, 1, 8, 64, 1), (8192, 8, 845, 1, 8, 63, 0), (8192, 8, 845, 1, 7, 64, 0),
+    (32768, 24, 64, 1, 16, 64, 0),            # one group that fills the chip
+    (8192, 8, 2000, 9, 16, 1600, 2), (8192, 8, 2000, 9, 16, 1601, 1),          # two groups' tables in 64 KiB, or one's
+    (8192, 8, 4000, 9, 4, 3264, 0), (8192, 8, 4000, 9, 5, 3264, 1), (8192, 8, 4000, 9, 16, 3265, 0),
+])
+def test_form_of_the_scalar_mac(rules, n, k, n_in, G, F, T, form):
+    """Both sides of every line of the rule, on a device of 256 compute units."""
+    assert rules.rule_mac_matrix_groups(256, n, k, n_in, G, F, T, 15) == form
+    assert rules.rule_mac_matrix_groups(256, n, k, n_in, G, F, T, 128) == 0          # weights beyond a signed byte
