@@ -236,8 +236,8 @@ enum {
                                     the default policy of HCNN_OPT_FUSION sizes its rounds from it: a round is
                                     8 * floor(this / 8 / k) ciphertexts                         */
   HCNN_STAT_TENSOR_FUSED_WGS = 4 /* the same for the one-kernel squaring tensor, taken for internal batches whose
-                                    (ciphertext, limb) pairs fill their rounds of compute units *
-                                    this to at least 7/8                                        */
+                                    n_ct * (k + k_aux) (ciphertext, limb) pairs fill their rounds of
+                                    this many workgroups to at least 7/8                        */
 };
 /* Synchronises the context's stream, then reads the counter. */
 int hcnn_get_stat(hcnn_ctx* ctx, int which, uint64_t* out);
@@ -260,12 +260,13 @@ enum {
                                    n <= 16384) and the relinearisation (step 3: digit transforms, inner product
                                    with the key, inverse transforms; n <= 8192, and n = 16384 with at most 16
                                    primes).  0 (default) = chosen per internal batch: the tensor kernel for
-                                   batches of several rounds of its workgroups, the relinearisation kernel for
-                                   as many ciphertexts as fill whole rounds, the separate kernels for the rest
-                                   and for small batches; the largest rings with many primes relinearise through
-                                   three auxiliary primes shared by all digits instead; 1 = always the separate kernels; 2 = always the
-                                   one-kernel forms where the ring allows them.  Same results either way; for
-                                   tests and tuning. */
+                                   batches that fill their rounds of its workgroups to at least 7/8, the
+                                   relinearisation kernel for as many ciphertexts as fill whole rounds, the
+                                   separate kernels for the rest and for small batches; n = 32768 with 12 or
+                                   more primes (batches of 4 or more) and n = 16384 with 16 or more (64 or
+                                   more) relinearise through three auxiliary primes shared by all digits
+                                   instead; 1 = always the separate kernels; 2 = always the one-kernel forms
+                                   where the ring allows them.  Same results either way; for tests and tuning. */
 };
 int hcnn_set_option(hcnn_ctx* ctx, int which, uint64_t value);
 

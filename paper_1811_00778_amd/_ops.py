@@ -207,9 +207,17 @@ class OpsMixin:
         the runtime reports for the compiled kernel; 0 when even one ciphertext's workgroups do not fit)."""
         return self.raw.stat(_capi.STAT_RELIN_FUSED_WGS) // 8 // self.k * 8
 
+    def takes_tensor_fused(self, n_ct):
+        """Does the default policy take the one-kernel squaring tensor for an internal batch of n_ct ciphertexts: its
+        (ciphertext, limb) pairs fill their rounds of resident workgroups to at least 7/8 (rings up to n = 16384)."""
+        slots, pairs = self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS), n_ct * (self.raw.k + self.raw.k_aux)
+        return self.n <= 16384 and 8 * pairs >= 7 * slots * -(-pairs // slots)
+
     def tensor_fused_threshold(self):
-        """(ciphertext, limb) pairs from which the default policy takes the one-kernel squaring tensor."""
-        return 6 * self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS)
+        """(ciphertext, limb) pairs of an internal batch from which the default policy takes the one-kernel squaring tensor
+        however full its last round is (7/8 of seven rounds: from eight rounds on one more is always filled enough);
+        takes_tensor_fused tells for smaller ones."""
+        return -(-49 * self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS) // 8)
 
     def reset_stats(self):
         self._call("hcnn_reset_stats")

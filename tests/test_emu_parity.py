@@ -143,6 +143,27 @@ def test_square_relin_batch_split_into_rounds_and_remainder(backend):
     s.ctx.close()
 
 
+def test_one_kernel_tensor_is_taken_where_its_rounds_are_filled(backend):
+    """Batches on both sides of 7/8 fill in one to seven rounds: the policy that the binding reports is the one that
+    runs, and from the reported threshold on it always does."""
+    s = pc.Setup(backend, 1024, 2)
+    s.ctx.set_relin_key(backend.dev(s.evk))
+    s.ctx.set_profile(True)
+    cts = backend.dev(pc.gen.uniform_residues(s.rng, s.q, 1024, lead=(24, 2)))
+    L, took = 2 + len(s.p), []
+    for n_ct in range(1, 25):
+        s.ctx.reset_stats()
+        s.ctx.ct_square_relin(cts[:n_ct])
+        took.append(s.ctx.profile()["tensor"][0] == 1)
+        assert took[-1] == s.ctx.takes_tensor_fused(n_ct), n_ct
+        assert took[-1] or n_ct * L < s.ctx.tensor_fused_threshold()
+    assert took[2] and not took[3] and not took[4] and took[5] and not took[7] and took[8]      # 15, 20, 25, 30, 40, 45 pairs, rounds of 16
+    slots = 16
+    assert s.ctx.tensor_fused_threshold() == 98
+    assert all(8 * p >= 7 * slots * -(-p // slots) for p in range(98, 1000)) and 8 * 97 < 7 * slots * -(-97 // slots)
+    s.ctx.close()
+
+
 def test_square_relin_noalloc_equals_allocating_entry_point(backend):
     """The entry point that works in the library's static array: same residues as hcnn_ct_square_relin on two calls in
     a row (the second smaller), no work buffer allocated; a parameter set beyond the array is refused."""
