@@ -819,7 +819,7 @@ struct MacMfma {
           for (uint32_t b = 0; b < 4; ++b) {
             const bool term = (t0 + b < a.T) & (f < a.F), beyond = (wf[gi][b] > a.w_abs_max) | (wf[gi][b] < -a.w_abs_max);
             bad += term & beyond & (g0 + gi < a.G);
-            packed |= term & !beyond & (src[gi][b] < a.n_in) ? (uint32_t)(wf[gi][b] & 0xff) << (8 * b) : 0u;
+            packed |= (term & !beyond & (src[gi][b] < a.n_in)) ? (uint32_t)(wf[gi][b] & 0xff) << (8 * b) : 0u;
           }
           lds[gi * words + chunks(a.T) * 64 + word] = packed;
         }

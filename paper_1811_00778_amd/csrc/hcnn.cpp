@@ -609,6 +609,14 @@ int ensure_work(hcnn_ctx* c, size_t bytes) {
   return 0;
 }
 
+// Checker builds may send every ring and basis through the shared-basis relinearisation (the product takes it for n = 16384
+// with 16 primes and n = 32768 with 12, and holds no kernels of it for others).
+#ifdef HCNN_SHARED_ALL
+constexpr bool kSharedAll = true;
+#else
+constexpr bool kSharedAll = false;
+#endif
+
 // ---------------------------------------------------------------- NTT dispatch
 struct NttRows {
   const uint32_t* in;
@@ -679,16 +687,20 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
       using K = NttFwd<LOGN, LOGR, kNttPlain, 1>;
       return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
     }
+    return io == kNttPlain ? run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a) : HCNN_ERR_ARG;
+  } else {
+    if constexpr (LOGN == 14 || kSharedAll) {
+      if (io == kNttDigitTile)
+        return run<NttFwd<LOGN, LOGR, kNttDigitTile>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
+      if (io == kNttKeyTile) return run<NttFwd<LOGN, LOGR, kNttKeyTile>>(c, r.rows, lds, a);
+    }
+    if (io == kNttLoadDigit)
+      return run<NttFwd<LOGN, LOGR, kNttLoadDigit>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
+    if (io == kNttStoreLazy) return run<NttFwd<LOGN, LOGR, kNttStoreLazy>>(c, r.rows, lds, a);
+    if (io == kNttSmallKey) return run<NttFwd<LOGN, LOGR, kNttSmallKey>>(c, r.rows, lds, a);
+    if (io == kNttStoreKey) return run<NttFwd<LOGN, LOGR, kNttStoreKey>>(c, r.rows, lds, a);
+    return io == kNttPlain ? run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a) : HCNN_ERR_ARG;
   }
-  if (io == kNttLoadDigit)
-    return run<NttFwd<LOGN, LOGR, kNttLoadDigit>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
-  if (io == kNttDigitTile)
-    return run<NttFwd<LOGN, LOGR, kNttDigitTile>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
-  if (io == kNttKeyTile) return run<NttFwd<LOGN, LOGR, kNttKeyTile>>(c, r.rows, lds, a);
-  if (io == kNttStoreLazy) return run<NttFwd<LOGN, LOGR, kNttStoreLazy>>(c, r.rows, lds, a);
-  if (io == kNttSmallKey) return run<NttFwd<LOGN, LOGR, kNttSmallKey>>(c, r.rows, lds, a);
-  if (io == kNttStoreKey) return run<NttFwd<LOGN, LOGR, kNttStoreKey>>(c, r.rows, lds, a);
-  return run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a);
 }
 
 int ntt_rows(hcnn_ctx* c, const NttRows& r, bool inverse, int io = kNttPlain) {
@@ -1027,12 +1039,9 @@ int hcnn_set_stream(hcnn_ctx* c, void* hip_stream) {
 //            k = 12  32: 1049 / 1100, 6: 250 / 257, 1: 110 / 100
 // n = 16384  k = 16  225: 3907 / 4110, 16: 334 / 333;  k = 11  225: 2547 / 2329;  n = 8192  k = 12  700: 3949 / 3592.
 static size_t shared_basis_min(const hcnn_ctx* c) {
-#ifdef HCNN_SHARED_ALL
-  return c->kp >= 3 ? 2 : 0;            // (checker builds: every ring and basis)
-#else
   if (c->kp < 3) return 0;
+  if (kSharedAll) return 2;
   return c->logn == 15 && c->k >= 12 ? 4 : c->logn == 14 && c->k >= 16 ? 64 : 0;
-#endif
 }
 
 int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
@@ -1126,8 +1135,10 @@ static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* d
   const size_t grid = (size_t)3 * (n / 64) * sa.n_grp;
   switch ((2 * k + 7) / 8) {
 #define HCNN_SHARED_MAC(O) case O: e = run<RelinSharedMac<O>>(c, grid, RelinSharedMac<O>::lds_bytes(k), sa); break;
-    HCNN_SHARED_MAC(1) HCNN_SHARED_MAC(2) HCNN_SHARED_MAC(3) HCNN_SHARED_MAC(4)
-    HCNN_SHARED_MAC(5) HCNN_SHARED_MAC(6) HCNN_SHARED_MAC(7) HCNN_SHARED_MAC(8)
+#ifdef HCNN_SHARED_ALL
+    HCNN_SHARED_MAC(1) HCNN_SHARED_MAC(2)
+#endif
+    HCNN_SHARED_MAC(3) HCNN_SHARED_MAC(4) HCNN_SHARED_MAC(5) HCNN_SHARED_MAC(6) HCNN_SHARED_MAC(7) HCNN_SHARED_MAC(8)
 #undef HCNN_SHARED_MAC
     default: e = HCNN_ERR_ARG; break;
   }
@@ -1144,7 +1155,10 @@ static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* d
   RelinBackArgs ba{acc, y, out, c->d_tw_inv, c->d_limbs, c->d_crt, c->crt_inv, k, fast_div(2 * k)};
   switch (c->logn) {
 #define HCNN_BACK(LOGN) case LOGN: return run<RelinBack<LOGN, 4>>(c, rows, NttGeom<LOGN, 4>::kLdsBytes, ba, 3 * rows);
-    HCNN_BACK(10) HCNN_BACK(11) HCNN_BACK(12) HCNN_BACK(13) HCNN_BACK(14)
+#ifdef HCNN_SHARED_ALL
+    HCNN_BACK(10) HCNN_BACK(11) HCNN_BACK(12) HCNN_BACK(13)
+#endif
+    HCNN_BACK(14)
 #undef HCNN_BACK
   }
   return HCNN_ERR_N;

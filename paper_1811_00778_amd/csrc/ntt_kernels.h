@@ -105,7 +105,8 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              kNttFusedMac16 = 9, kNttFusedMacAny = 10,     // the fused inner product for k <= 8, k <= 16, any k
              kNttToRegs0 = 11, kNttToRegs1 = 12,           // forward, inside TensorFused: c0 / c1 of workgroup (ct, limb); the
                                                            // transformed row stays in registers, signed in [-p, p)
-             kNttTensorRegs0 = 13, kNttTensorRegs1 = 14, kNttTensorRegs2 = 15,
+             kNttTensorRegs0 = 13, kNttTensorRegs1 = 14, kNttTensorRegs2 = 15,      // inverse, inside TensorFused: component b
+                                                           // of the tensor formed from those registers (as kNttLoadTensor)
              kNttStoreKey = 16,
              // forward, inside CryptFused: the encryption's u (small signed values, [ct][n], limb by limb) or the
              // decryption's c1 into registers; kNttSmallKey: the secret's rows, stored like kNttStoreKey
@@ -120,8 +121,7 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              // digits [ct][r][tile][i][64], key [r][tile][i][o][64]; the sums lie in [ct][r][tile][o][64]
              kNttDigitTile = 27, kNttKeyTile = 28,
              // decryption of few ciphertexts: the secret's row into registers too, and the product of the two rows
-             kNttSecretToRegs = 29, kNttDecOwn = 30 };   // inverse, inside TensorFused: component
-                                                           // b of the tensor formed from those registers (as kNttLoadTensor)
+             kNttSecretToRegs = 29, kNttDecOwn = 30 };
 
 // Per-thread state of TensorFused: the two transformed polynomials of the ciphertext, one limb.
 template <int R>

@@ -147,7 +147,6 @@ HCNN_HD uint32_t quot(uint32_t x, FastDiv f) {
 #endif
   return x - q * f.d >= f.d ? q + 1 : q;
 }
-HCNN_HD uint32_t rem(uint32_t x, FastDiv f) { return x - quot(x, f) * f.d; }
 
 // The value as it is, but not one the compiler can trace back to where it came from.
 template <class T>
