@@ -25,7 +25,7 @@ _OUT_DIR = os.path.join(_ROOT, "tests", "_build")
 #         python -m pytest tests/test_emu_parity.py -q
 SANITIZE = os.environ.get("HCNN_EMU_SANITIZE", "") not in ("", "0")
 _OUT = os.path.join(_OUT_DIR, "libhcnn_emu_san.so" if SANITIZE else "libhcnn_emu.so")
-_lib = _lib_shared = None
+_lib = _lib_shared = _lib_rules = None
 
 
 def build(defines=(), out=_OUT, source=os.path.join(_SRC_DIR, "hcnn.cpp")) -> str:
@@ -57,6 +57,17 @@ def lib_shared_basis():
     if _lib_shared is None:
         _lib_shared = _capi.declare(ctypes.CDLL(build(["-DHCNN_SHARED_ALL"], _OUT.replace(".so", "_shared.so"))))
     return _lib_shared
+
+
+def rules():
+    """The host-side rules of tests/host_rules.cpp."""
+    global _lib_rules
+    if _lib_rules is None:
+        lib = ctypes.CDLL(build(["-O0"], _OUT.replace("libhcnn_emu", "libhcnn_rules"), os.path.join(_ROOT, "tests", "host_rules.cpp")))
+        lib.rule_mac_matrix_groups.argtypes = [ctypes.c_uint32] * 7 + [ctypes.c_int32]
+        lib.rule_mac_matrix_lds.argtypes, lib.rule_mac_matrix_lds.restype = [ctypes.c_uint32, ctypes.c_size_t], ctypes.c_size_t
+        _lib_rules = lib
+    return _lib_rules
 
 
 class EmuContext(OpsMixin):

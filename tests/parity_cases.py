@@ -163,11 +163,14 @@ def check_scalar_mac(backend, n, k, seed_id=1):
     s.ctx.close()
 
 
+MATRIX_INPUTS = 11
+
+
 def check_scalar_mac_matrix_form(backend, G, F, T, bound, n=1024, k=2):
     """Rows and filter counts that take the matrix form of the scalar MAC (edges of its chunks of 64 terms and of its
     groups of workgroup neighbours), extreme residues and weights, then out-of-range table entries."""
     s = Setup(backend, n, k, with_keys=False)
-    n_in = 11
+    n_in = MATRIX_INPUTS
     cts = gen.uniform_residues(s.rng, s.q, n, lead=(n_in, 2))
     for l, p in enumerate(s.q):
         cts[0, :, l] = p - 1
@@ -193,6 +196,24 @@ def check_scalar_mac_matrix_form(backend, G, F, T, bound, n=1024, k=2):
     assert np.array_equal(out[F - 1, G - 1], want(G - 1, F - 1, (0, T - 1)))
     assert np.array_equal(out[0, G - 1], want(G - 1, 0, (T - 1,)))
     assert s.ctx.bad_inputs() == 2
+    s.ctx.close()
+
+
+def check_scalar_mac_matrix_tiles(backend, k, G, F, T, bound, blocks=None, n=1024):
+    """The matrix form of the scalar MAC where its waves go through several tiles of coefficients; `blocks`: the
+    workgroups that the launch must have.  All coefficients of outputs at the edges and in the middle."""
+    s = Setup(backend, n, k, with_keys=False)
+    cts = gen.uniform_residues(s.rng, s.q, n, lead=(MATRIX_INPUTS, 2))
+    idx = s.rng.integers(0, MATRIX_INPUTS, size=(G, T)).astype(np.uint32)
+    w = gen.int_weights(s.rng, (G, F, T), bound)
+    w[0, 0], w[G - 1, F - 1] = bound, -bound
+    s.ctx.set_profile(True)
+    out = s.ctx.ct_scalar_mac(backend.dev(cts), backend.dev(idx), backend.dev(w), bound)
+    launches, got_blocks, _ = s.ctx.profile()["scalar_mac"]
+    assert launches == 1 and (blocks is None or got_blocks == blocks), got_blocks
+    for g, f in ((0, 0), (0, F - 1), (G // 2, 1), (G - 2, F // 2), (G - 1, 0), (G - 1, F - 1)):
+        assert np.array_equal(backend.host(out[f, g]), fv.scalar_mac(s.octx, cts, idx[g], w[g, f])), ("tiles", G, F, T, g, f)
+    assert s.ctx.bad_inputs() == 0
     s.ctx.close()
 
 

@@ -99,7 +99,14 @@ def test_scalar_mac(backend, n, k):
 @pytest.mark.parametrize("G,F,T,bound", [(5, 16, 25, 7), (4, 14, 31, 127), (6, 10, 96, 127), (3, 11, 97, 15), (2, 16, 130, 31),
                                          (1, 8, 64, 127), (1, 13, 81, 7), (1, 16, 1000, 127), (9, 16, 48, 1)])
 def test_scalar_mac_matrix_form(backend, G, F, T, bound):
-    pc.check_scalar_mac_matrix_form(backend, G, F, T, bound)
+    k = 1 if G == 1 else 2                       # one group: few enough coefficients for this build's single compute unit
+    assert emu.rules().rule_mac_matrix_groups(1, 1024, k, pc.MATRIX_INPUTS, G, F, T, bound) == (2 if G in (2, 9) else 1)
+    pc.check_scalar_mac_matrix_form(backend, G, F, T, bound, k=k)
+
+
+def test_scalar_mac_matrix_form_with_several_tiles_per_wave(backend):
+    pc.check_scalar_mac_matrix_tiles(backend, 3, 3, 11, 97, 31)
+    pc.check_scalar_mac_matrix_tiles(backend, 3, 7, 14, 25, 7)
 
 
 def test_square_relin_tiny_config(backend):

@@ -93,7 +93,15 @@ def test_scalar_mac(backend, n, k):
                                          (1, 8, 64, 127), (1, 13, 81, 7), (1, 16, 1000, 127), (9, 16, 48, 1)])
 def test_scalar_mac_matrix_form(backend, G, F, T, bound):
     say("scalar_mac matrix form G=%d F=%d T=%d" % (G, F, T))
-    pc.check_scalar_mac_matrix_form(backend, G, F, T, bound)
+    pc.check_scalar_mac_matrix_form(backend, G, F, T, bound, k=1 if G == 1 else 2)
+
+
+@pytest.mark.parametrize("G,F,T,bound,blocks", [(130, 10, 1601, 127, 8 * 130), (257, 16, 25, 7, 8 * 129)])
+def test_scalar_mac_matrix_form_with_several_tiles_per_wave(backend, G, F, T, bound, blocks):
+    """Enough groups for eight tiles per wave (`blocks`: workgroups of the launch then; the vector forms have 6 or 8 per
+    group): one group per workgroup with the last wave's tiles beyond the ciphertext, and pairs with the last half empty."""
+    say("scalar_mac matrix form, several tiles per wave G=%d F=%d T=%d" % (G, F, T))
+    pc.check_scalar_mac_matrix_tiles(backend, 3, G, F, T, bound, blocks)
 
 
 def test_square_relin_tiny_config(backend):

@@ -1,21 +1,13 @@
 """The library's dispatch rules, called as plain functions on the CPU (tests/host_rules.cpp): the sizes at which a rule can go
 wrong are too large, or of too large a device, to be run through the entry points."""
-import ctypes
-import os
-
 import pytest
 
 import emu
 
-_U = ctypes.c_uint32
-
 
 @pytest.fixture(scope="module")
 def rules():
-    lib = ctypes.CDLL(emu.build(["-O0"], emu._OUT.replace("libhcnn_emu", "libhcnn_rules"), os.path.join(emu._ROOT, "tests", "host_rules.cpp")))
-    lib.rule_mac_matrix_groups.argtypes = [_U] * 7 + [ctypes.c_int32]
-    lib.rule_mac_matrix_lds.argtypes, lib.rule_mac_matrix_lds.restype = [_U, ctypes.c_size_t], ctypes.c_size_t
-    return lib
+    return emu.rules()
 
 
 # (858993409 terms: 13421773 times 320 words is 2^32 + 64)
