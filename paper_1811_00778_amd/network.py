@@ -25,7 +25,9 @@ CIFAR10_INPUT = (3, 32, 32)
 
 _MAX_FILTERS = 16            # filters per hcnn_ct_scalar_mac call
 _STAGED_LDS_BYTES = 64 * 1024   # the library stages a gather row and its weights in LDS up to this size
-_MATRIX_TERMS = 3264         # ... and in its matrix form (weights in bytes, all filters of a call at once) rows up to this length
+# ... and in its matrix form (weights in bytes, all filters of a call at once) rows up to this length with weights up to
+# this bound (the rule of mac_matrix_groups in hcnn.cpp; a test holds the two together)
+_MATRIX_TERMS, _MATRIX_WEIGHT = 3264, 127
 
 
 def shapes(spec, in_shape):
@@ -107,7 +109,7 @@ class Plan:
                 G, F, T = w.shape
                 t_pad = (T + 3) // 4 * 4
                 per_call = max(1, min(_MAX_FILTERS, (_STAGED_LDS_BYTES // 4 - 8) // t_pad - 1))
-                if T <= _MATRIX_TERMS and bound <= 127 and T * bound <= 1 << 20:
+                if T <= _MATRIX_TERMS and bound <= _MATRIX_WEIGHT:
                     per_call = _MAX_FILTERS
                 calls = [(f0, min(F, f0 + per_call), to_device(np.ascontiguousarray(w[:, f0:min(F, f0 + per_call), :])))
                          for f0 in range(0, F, per_call)]

@@ -3,6 +3,7 @@ wrong are too large, or of too large a device, to be run through the entry point
 import pytest
 
 import emu
+from paper_1811_00778_amd import network
 
 
 @pytest.fixture(scope="module")
@@ -44,3 +45,12 @@ def test_form_of_the_scalar_mac(rules, n, k, n_in, G, F, T, form):
     """Both sides of every line of the rule, on a device of 256 compute units."""
     assert rules.rule_mac_matrix_groups(256, n, k, n_in, G, F, T, 15) == form
     assert rules.rule_mac_matrix_groups(256, n, k, n_in, G, F, T, 128) == 0          # weights beyond a signed byte
+
+
+def test_network_plan_puts_16_outputs_into_rows_that_the_matrix_form_takes(rules):
+    """The length and the weights up to which the plan relies on the matrix form for rows that the vector form cannot stage."""
+    T, weight = network._MATRIX_TERMS, network._MATRIX_WEIGHT
+    for units, n, k in ((256, 1024, 2), (256, 32768, 24), (1, 1024, 1)):
+        for G in (1, 2, 4, 9):
+            form = lambda terms, bound: rules.rule_mac_matrix_groups(units, n, k, 5000, G, 16, terms, bound)
+            assert form(T, weight) == 1 and form(T + 1, weight) == 0 and form(T, weight + 1) == 0 and form(1000, weight) > 0
