@@ -99,7 +99,10 @@ int hcnn_set_stream(hcnn_ctx* ctx, void* hip_stream);
 
 /* Evaluation key of Sec. 2.1 (KeyGen), one component per RNS prime:
  * evk_dev = uint32[k][2][k][n], evk[i][0] = g_i*s^2 - (a_i*s + e_i), evk[i][1] = a_i,
- * coefficient domain.  The library keeps its own NTT-domain copy; the caller's
+ * coefficient domain.  The library keeps its own NTT-domain copy, and for n = 32768
+ * with 12 or more primes and n = 16384 with 16 or more three further copies modulo
+ * auxiliary primes (n = 32768, k = 24: 144 + 432 MiB); a device that cannot spare
+ * those relinearises through the other forms, with the same results.  The caller's
  * buffer is free again once the stream has passed this call. */
 int hcnn_set_relin_key(hcnn_ctx* ctx, const uint32_t* evk_dev);
 
@@ -144,7 +147,8 @@ int hcnn_ct_square_relin(hcnn_ctx* ctx, const uint32_t* in_cts_dev, size_t n_ct,
                          uint32_t* out_cts_dev);
 
 /* hcnn_ct_square_relin for callers that cannot allocate device memory: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments, same result, same kernels; the intermediate
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments, same result, same kernels (without the
+ * relinearisation through shared auxiliary primes, see HCNN_OPT_FUSION); the intermediate
  * polynomials live in a static device array of HCNN_STATIC_SCRATCH_BYTES (128 MiB) inside the library instead of a
  * buffer from hipMalloc, and the call makes no hipMalloc / hipFree (no first-call warm-up is needed for that).
  * The batch is processed in internal batches of as many ciphertexts as fit the array:
@@ -274,7 +278,8 @@ int hcnn_set_option(hcnn_ctx* ctx, int which, uint64_t value);
  * path (the classes follow the steps of HMult in Sec. 2.1 and the layer sum of Sec. 4.3).
  * `blocks` is the number of workgroups launched: one (polynomial, limb) row of n residues per
  * workgroup for the two NTT classes, 256 coefficient positions (1024 for RELIN_MAC and
- * SCALAR_MAC) per workgroup for the others; for RELIN_FUSED it is the number of rows the launch
+ * SCALAR_MAC; their forms for shared auxiliary primes and for many filters launch fewer or
+ * more) per workgroup for the others; for RELIN_FUSED it is the number of rows the launch
  * transforms (k forward + 2 inverse per workgroup).
  * hcnn_profile_read synchronises the stream; hcnn_reset_stats clears the accumulators. */
 enum {

@@ -779,10 +779,10 @@ int mac_mfma_launch(hcnn_ctx* c, const MacArgs& a) {
 // Neighbouring groups that a workgroup of the matrix form takes (2 or 1); 0: the call takes the vector form.
 // Measured, vector / matrix form, us:
 // - The matrix form, where the multiply-adds weigh more than the byte transposition (64 groups, n = 8192, k = 8: 14 filters x 25
-//   terms 227 / 217, 16 x 25 260 / 226, 10 x 96 335 / 273, 16 x 144 724 / 362; 8 x 32, 139 / 183, is not taken).
+//   terms 227 / 216, 16 x 25 259 / 237, 10 x 96 333 / 268, 16 x 144 731 / 372; 8 x 32, 135 / 174, is not taken).
 // - The vector form, where the inputs are gathered less than 1.5 times and its workgroups (1024 coefficients of one group)
 //   fill the chip: reading the inputs bounds the call (2 x 2 kernels without overlap, 32 channels, 16 groups x 16 filters, n =
-//   8192, k = 10 310 / 325; gathered 1.65 times, 16 x 144, 9 groups, n = 16384, k = 16 513 / 462).  So does one group that fills it (8 x 64 at n = 32768, k = 24 64 / 69).
+//   8192, k = 10 310 / 325; gathered 1.65 times, 16 x 144, 9 groups, n = 16384, k = 16 513 / 462).  So does one group that fills it (8 x 64 at n = 32768, k = 24 64 / 68).
 // - The matrix form, where one group's vector workgroups do not fill the chip (10 x 845, n = 8192, k = 8 127 / 58) and where the
 //   vector form could not stage its row (16 x 1000, 9 groups, n = 8192, k = 10 6661 / 521).
 // - Three to six groups go one at a time: half of a pair may be empty, and two pairs read their shared inputs twice (14 x 72,
@@ -1038,12 +1038,16 @@ int hcnn_set_stream(hcnn_ctx* c, void* hip_stream) {
 // n = 32768  k = 24  32 ciphertexts 2277 / 3070, 6: 530 / 690, 1: 251 / 193;  k = 18  32: 3194 / 3552;
 //            k = 12  32: 1049 / 1100, 6: 250 / 257, 1: 110 / 100
 // n = 16384  k = 16  225: 3907 / 4110, 16: 334 / 333;  k = 11  225: 2547 / 2329;  n = 8192  k = 12  700: 3949 / 3592.
+// Not measured: n = 16384 with 12 to 15 primes (left to the other forms) and with more than 16, where those forms have no
+// one-kernel relinearisation and the minimum of 64 is likely too high.
 static size_t shared_basis_min(const hcnn_ctx* c) {
   if (c->kp < 3) return 0;
   if (kSharedAll) return 2;
   return c->logn == 15 && c->k >= 12 ? 4 : c->logn == 14 && c->k >= 16 ? 64 : 0;
 }
 
+// (Where the shared-basis relinearisation is in use the key is held a second time modulo its three primes, whatever forms the
+// later calls take: 75 us more at n = 16384, k = 16 and 280 at n = 32768, k = 24, once per key.)
 int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
   if (!c || !evk_dev) return HCNN_ERR_NULL;
   if (!aligned16(evk_dev)) return HCNN_ERR_ALIGN;
