@@ -234,7 +234,7 @@ enum {
   HCNN_STAT_EXACT_FALLBACKS = 0, /* coefficients whose base conversion needed the exact
                                     mixed-radix comparison instead of the fixed-point estimate */
   HCNN_STAT_BAD_INPUT = 1,       /* out-of-range indices / weights seen by hcnn_ct_scalar_mac   */
-  HCNN_STAT_SCRATCH_BYTES = 2,   /* device work buffer currently held by the context            */
+  HCNN_STAT_SCRATCH_BYTES = 2,   /* device work buffers currently held by the context           */
   HCNN_STAT_RELIN_FUSED_WGS = 3, /* workgroups of the one-kernel relinearisation that the device holds at a time
                                     (compute units x the occupancy the runtime reports for the compiled kernel);
                                     the default policy of HCNN_OPT_FUSION sizes its rounds from it: a round is

@@ -289,8 +289,10 @@ struct hcnn_ctx {
   RelinCrtInv crt_inv{};
   bool has_key = false;
 
-  uint32_t* work = nullptr;       // device work buffer of the entry points that may allocate (grown on demand)
+  uint32_t* work = nullptr;       // device work buffers of the entry points that may allocate (work_buffer)
   size_t work_bytes = 0;
+  uint32_t* small_work = nullptr;
+  size_t small_work_bytes = 0;
   uint32_t* static_scratch = nullptr;   // this device's copy of the file-scope array `scratch` (kStaticScratchBytes)
 
   uint32_t band = 128;
@@ -585,27 +587,37 @@ int build_tables(hcnn_ctx* c) {
   return 0;
 }
 
-// The work buffer grows on demand and is kept; growing waits for the stream, frees and allocates (25 to 450 us).  Its first
-// allocation holds what the decryption of 64 ciphertexts takes (65 polynomials: 17 MiB at n = 8192, k = 8, 195 at n = 32768,
-// k = 24; and no less than 512 rows, for the small bases), so that a decryption finds its place in what the key generation or
-// the encryption of the same context left.  First decryption after both, us, growing / not: 25 ciphertexts at n = 8192, k =
-// 8 335 / 42, 60 at n = 32768, k = 24 831 / 419.
-constexpr size_t kWorkPolys = 65, kWorkRows = 512;
-int ensure_work(hcnn_ctx* c, size_t bytes) {
-  if (bytes <= c->work_bytes) return 0;
-  bytes = std::max(bytes, std::max(kWorkPolys * c->k, kWorkRows) * c->n * 4);
-  if (c->work) {
-    int e = stream_sync(c->stream);
+// Work buffer of a call that needs `bytes`: the small one, allocated on first use and kept as it is, or, for more, the
+// large one, which grows on demand (it waits for the stream, frees and allocates) and is kept.  Which of the two a call
+// takes depends on its size alone.
+// The small one holds what the decryption of 64 ciphertexts takes (65 polynomials: 17 MiB at n = 8192, k = 8, 195 at n = 32768,
+// k = 24; and no less than 512 rows, for the small bases), and so every key generation and encryption, the decryption of a
+// network's results and the squaring of a few ciphertexts: none of them finds a buffer to grow that another one left (first
+// decryption of 25 ciphertexts after key generation and encryption, n = 8192, k = 8, us: 335 with one buffer for all, 41 now).
+// A single growing buffer with that first size made the first squaring slower instead (16 ciphertexts after key generation
+// 186 -> 420 us, now 168: freeing 17 MiB takes 250 us).
+constexpr size_t kSmallWorkPolys = 65, kSmallWorkRows = 512;
+int work_buffer(hcnn_ctx* c, size_t bytes, uint32_t** out) {
+  const size_t small = std::max(kSmallWorkPolys * c->k, kSmallWorkRows) * c->n * 4;
+  const bool large = bytes > small;
+  uint32_t*& buf = large ? c->work : c->small_work;
+  size_t& held = large ? c->work_bytes : c->small_work_bytes;
+  if (bytes > held) {
+    if (buf) {
+      int e = stream_sync(c->stream);
+      if (e) return e;
+      dev_free(buf);
+      buf = nullptr;
+      held = 0;
+    }
+    const size_t want = large ? bytes : small;
+    void* ptr = nullptr;
+    int e = dev_malloc(&ptr, want);
     if (e) return e;
-    dev_free(c->work);
-    c->work = nullptr;
-    c->work_bytes = 0;
+    buf = (uint32_t*)ptr;
+    held = want;
   }
-  void* ptr = nullptr;
-  int e = dev_malloc(&ptr, bytes);
-  if (e) return e;
-  c->work = (uint32_t*)ptr;
-  c->work_bytes = bytes;
+  *out = buf;
   return 0;
 }
 
@@ -896,10 +908,10 @@ int secret_hat(hcnn_ctx* c, const int32_t* s, uint32_t* s_hat) {
 bool decrypts_with_own_key(const hcnn_ctx* c, size_t n_ct) { return c->logn <= 14 && n_ct * c->k <= c->compute_units; }
 // Work buffer of a decryption or a noise read-out: x [C][k][n] of up to 256 MiB (C ciphertexts a piece), then s_hat [k][n]
 // unless the workgroups transform the secret themselves.
-int decrypt_work(hcnn_ctx* c, size_t n_ct, bool own, size_t* C) {
+int decrypt_work(hcnn_ctx* c, size_t n_ct, bool own, size_t* C, uint32_t** x) {
   const size_t poly = (size_t)c->k * c->n;
   *C = std::min<size_t>(n_ct, std::max<size_t>(64, ((size_t)256 << 20) / (poly * 4)));
-  return ensure_work(c, (*C + (own ? 0 : 1)) * poly * 4);
+  return work_buffer(c, (*C + (own ? 0 : 1)) * poly * 4, x);
 }
 // x = c0 + c1*s mod q of cc ciphertexts
 int decrypt_rows(hcnn_ctx* c, const int32_t* s, const uint32_t* cts, size_t cc, const uint32_t* s_hat, uint32_t* x, bool own) {
@@ -1021,6 +1033,7 @@ int hcnn_ctx_destroy(hcnn_ctx* c) {
   if (c->d_evk_hat) dev_free(c->d_evk_hat);
   if (c->d_evk_shared) dev_free(c->d_evk_shared);
   if (c->work) dev_free(c->work);
+  if (c->small_work) dev_free(c->small_work);
   delete c;
   return HCNN_OK;
 }
@@ -1216,9 +1229,9 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   // ciphertexts of one internal batch that can take the separate kernels
   const size_t C_split = shared_min ? std::min(C, shared_min - 1) : (fused && fused_round) ? std::min(C, fused_round) : C;
   int e;
-  e = static_ws ? 0 : ensure_work(c, (C * words_main + std::max(C_split * words_split, shared_min ? C * words_shared : 0)) * 4);
+  uint32_t* ext = c->static_scratch;
+  e = static_ws ? 0 : work_buffer(c, (C * words_main + std::max(C_split * words_split, shared_min ? C * words_shared : 0)) * 4, &ext);
   if (e) return e;
-  uint32_t* ext = static_ws ? c->static_scratch : c->work;
   uint32_t* ext_b = ext + C * 2 * L * rn;                 // used only by the two-operand product
   uint32_t* d = ext + C * ext_rows * rn;
   uint32_t* y = d + C * 3 * L * rn;
@@ -1387,9 +1400,9 @@ int hcnn_keygen(hcnn_ctx* c, const int32_t* s, const uint32_t* a, const int32_t*
   const size_t rn = n, poly = (size_t)k * rn;
   const size_t bpp = n / kEwThreads;
   // scratch: s_hat [k][n] | s2 [k][n] | tmp [k*k][n]
-  int e = ensure_work(c, (2 * poly + (size_t)k * poly) * 4);
+  uint32_t* s_hat;
+  int e = work_buffer(c, (2 * poly + (size_t)k * poly) * 4, &s_hat);
   if (e) return e;
-  uint32_t* s_hat = c->work;
   uint32_t* s2 = s_hat + poly;
   uint32_t* tmp = s2 + poly;
 
@@ -1434,13 +1447,14 @@ static int encrypt_impl(hcnn_ctx* c, const uint32_t* pk, const uint32_t* m, cons
   const uint32_t k = c->k, n = c->n;
   const size_t rn = n, poly = (size_t)k * rn;
   // scratch: pk_hat [2][k][n]
-  int e = ensure_work(c, 2 * poly * 4);
+  uint32_t* pk_hat;
+  int e = work_buffer(c, 2 * poly * 4, &pk_hat);
   if (e) return e;
-  if ((e = ntt_dense(c, pk, c->work, 2 * (size_t)k, k, false, kNttStoreKey))) return e;
+  if ((e = ntt_dense(c, pk, pk_hat, 2 * (size_t)k, k, false, kNttStoreKey))) return e;
   const size_t C = kCryptRows / k;               // rows of a launch fit its 32-bit indices
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     CryptArgs a{};
-    a.key = c->work; a.u = u + c0 * rn; a.e1 = e1 + c0 * rn; a.e2 = e2 + c0 * rn;
+    a.key = pk_hat; a.u = u + c0 * rn; a.e1 = e1 + c0 * rn; a.e2 = e2 + c0 * rn;
     a.msg = m ? m + c0 * rn : nullptr; a.msg64 = m64 ? m64 + c0 * rn : nullptr; a.scale = c->d_delta;
     a.out = ct_out + c0 * 2 * poly;
     if ((e = crypt_rows(c, a, std::min(C, n_ct - c0), true))) return e;
@@ -1471,9 +1485,9 @@ static int decrypt_impl(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size
   const size_t bpp = n / kEwThreads;
   const bool own = decrypts_with_own_key(c, n_ct);
   size_t C;
-  int e = decrypt_work(c, n_ct, own, &C);
+  uint32_t* x;
+  int e = decrypt_work(c, n_ct, own, &C, &x);
   if (e) return e;
-  uint32_t* x = c->work;
   uint32_t* s_hat = x + C * poly;                // (not there with its own key)
   if (!own && (e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
@@ -1507,9 +1521,9 @@ int hcnn_noise_bits(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size_t n
   const size_t bpp = n / kEwThreads;
   const bool own = decrypts_with_own_key(c, n_ct);
   size_t C;
-  int e = decrypt_work(c, n_ct, own, &C);
+  uint32_t* x;
+  int e = decrypt_work(c, n_ct, own, &C, &x);
   if (e) return e;
-  uint32_t* x = c->work;
   uint32_t* s_hat = x + C * poly;                // (not there with its own key)
   if ((e = dev_memset(bits_out, 0, n_ct * sizeof(uint32_t), c->stream))) return e;
   if (!own && (e = secret_hat(c, sk, s_hat))) return e;
@@ -1563,7 +1577,7 @@ int hcnn_sample_uniform(hcnn_ctx* c, uint64_t seed, uint64_t stream, uint32_t* o
 int hcnn_get_stat(hcnn_ctx* c, int which, uint64_t* out) {
   if (!c || !out) return HCNN_ERR_NULL;
   if (which == HCNN_STAT_SCRATCH_BYTES) {
-    *out = c->work_bytes;
+    *out = c->work_bytes + c->small_work_bytes;
     return HCNN_OK;
   }
   if (which == HCNN_STAT_RELIN_FUSED_WGS || which == HCNN_STAT_TENSOR_FUSED_WGS) {

@@ -90,6 +90,24 @@ def test_first_decryption_of_a_context_finds_its_work_buffer(backend, n, k):
         ctx.close()
 
 
+def test_work_of_a_large_squaring_leaves_the_small_work_buffer_alone(backend):
+    """The first squaring after key generation frees nothing, and a decryption after it finds what it had."""
+    s = pc.Setup(backend, 1024, 2)
+    kr = {x: backend.dev(v) for x, v in s.kr.items()}
+    x = backend.dev(pc.gen.uniform_residues(s.rng, s.q, 1024, lead=(40, 2)))
+    s.ctx.set_relin_key(backend.dev(s.evk))
+    assert s.ctx.scratch_bytes() == 0
+    s.ctx.ct_square_relin(x)
+    large = s.ctx.scratch_bytes()
+    s.ctx.keygen(kr["s"], kr["a"], kr["e"], kr["a_evk"], kr["e_evk"])
+    small = s.ctx.scratch_bytes() - large
+    assert 0 < small < large
+    for call in (lambda: s.ctx.ct_square_relin(x[:3]), lambda: s.ctx.decrypt(kr["s"], x), lambda: s.ctx.ct_square_relin(x)):
+        call()
+        assert s.ctx.scratch_bytes() == small + large
+    s.ctx.close()
+
+
 @pytest.mark.parametrize("n,k", [(1024, 2), (2048, 5)])
 def test_scalar_mac(backend, n, k):
     pc.check_scalar_mac(backend, n, k)
