@@ -344,9 +344,10 @@ struct RelinMacKernel {
     const uint32_t c = (tile * kThreads + tid) * kEwVec;
     const NttLimb L = ldc(a.limbs, j);
     const size_t rn = a.n;
-    // signed digits in [-p, p), centred key values: 16 products stay below 8 p^2 < 2^63, 13 after a fold (whose
-    // result takes the room of two); inside a run the loop is unrolled so that the loads of several digits are in
-    // flight together
+    // signed digits in [-p, p), centred key values: 16 products stay below 8 p^2 < 2^63, 13 after a fold (whose result takes
+    // the room of two).  The loads of two digits are issued before the first product: left to the scheduler, which saves
+    // registers, every load was waited for by itself (squaring of 4 ciphertexts at n = 8192, k = 8 57.6 / 49.8 us, of 16 at n = 2048,
+    // k = 4 36.2 / 33.1)
     int64_t s0[CT][4], s1[CT][4];
 #pragma unroll
     for (int t = 0; t < CT; ++t)
@@ -358,21 +359,35 @@ struct RelinMacKernel {
           for (int q = 0; q < 4; ++q) { s0[t][q] = sfold(s0[t][q], L.rc); s1[t][q] = sfold(s1[t][q], L.rc); }
       }
       const uint32_t i1 = i0 + run < a.k ? i0 + run : a.k;
-#pragma unroll 2
-      for (uint32_t i = i0; i < i1; ++i) {
-        const U4 e0 = *reinterpret_cast<const U4*>(a.evk + (((size_t)i * 2 + 0) * a.k + j) * rn + c);
-        const U4 e1 = *reinterpret_cast<const U4*>(a.evk + (((size_t)i * 2 + 1) * a.k + j) * rn + c);
-        U4 d[CT];
+      auto load = [&](uint32_t i, U4& e0, U4& e1, U4 (&d)[CT]) {
+        e0 = *reinterpret_cast<const U4*>(a.evk + (((size_t)i * 2 + 0) * a.k + j) * rn + c);
+        e1 = *reinterpret_cast<const U4*>(a.evk + (((size_t)i * 2 + 1) * a.k + j) * rn + c);
 #pragma unroll
         for (int t = 0; t < CT; ++t)
           d[t] = *reinterpret_cast<const U4*>(a.dig + (((ct0 + t) * a.k + i) * a.k + j) * rn + c);
+      };
+      auto multiply = [&](const U4& E0, const U4& E1, const U4 (&D)[CT]) {
 #pragma unroll
         for (int t = 0; t < CT; ++t) {
-          s0[t][0] += mul_s32(d[t].x, e0.x); s0[t][1] += mul_s32(d[t].y, e0.y);
-          s0[t][2] += mul_s32(d[t].z, e0.z); s0[t][3] += mul_s32(d[t].w, e0.w);
-          s1[t][0] += mul_s32(d[t].x, e1.x); s1[t][1] += mul_s32(d[t].y, e1.y);
-          s1[t][2] += mul_s32(d[t].z, e1.z); s1[t][3] += mul_s32(d[t].w, e1.w);
+          s0[t][0] += mul_s32(D[t].x, E0.x); s0[t][1] += mul_s32(D[t].y, E0.y);
+          s0[t][2] += mul_s32(D[t].z, E0.z); s0[t][3] += mul_s32(D[t].w, E0.w);
+          s1[t][0] += mul_s32(D[t].x, E1.x); s1[t][1] += mul_s32(D[t].y, E1.y);
+          s1[t][2] += mul_s32(D[t].z, E1.z); s1[t][3] += mul_s32(D[t].w, E1.w);
         }
+      };
+      U4 e[2][2], d[2][CT];
+      uint32_t i = i0;
+      for (; i + 2 <= i1; i += 2) {
+        load(i, e[0][0], e[0][1], d[0]);
+        load(i + 1, e[1][0], e[1][1], d[1]);
+        sched_fence();
+        multiply(e[0][0], e[0][1], d[0]);
+        multiply(e[1][0], e[1][1], d[1]);
+      }
+      if (i < i1) {
+        load(i, e[0][0], e[0][1], d[0]);
+        sched_fence();
+        multiply(e[0][0], e[0][1], d[0]);
       }
     }
     // (the sums are left signed in (-p, p): the inverse transform that reads them takes them as they are)

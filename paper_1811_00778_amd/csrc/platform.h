@@ -157,6 +157,13 @@ HCNN_HD T untraced(T x) {
   return x;
 }
 
+// No instruction is scheduled across this point (loads in front of it are issued before what follows)
+HCNN_HD void sched_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
 // x, known to be the same in all lanes of a wave, as a scalar
 HCNN_HD uint32_t wave_uniform(uint32_t x) {
 #if defined(__HIP_DEVICE_COMPILE__)
