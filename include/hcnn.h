@@ -266,9 +266,9 @@ enum {
                                    primes).  0 (default) = chosen per internal batch: the tensor kernel for
                                    batches that fill their rounds of its workgroups to at least 7/8, the
                                    relinearisation kernel for as many ciphertexts as fill whole rounds, the
-                                   separate kernels for the rest and for small batches; n = 32768 with 12 or
-                                   more primes (batches of 4 or more) and n = 16384 with 16 or more (64 or
-                                   more) relinearise through three auxiliary primes shared by all digits
+                                   separate kernels for the rest and for small batches; n = 32768 with 12
+                                   primes (batches of 16 or more), 13 (5) or 18 (4) and n = 16384 with 16 or
+                                   more (64) relinearise through three auxiliary primes shared by all digits
                                    instead; 1 = always the separate kernels; 2 = always the one-kernel forms
                                    where the ring allows them.  Same results either way; for tests and tuning. */
 };

@@ -1048,15 +1048,17 @@ int hcnn_set_stream(hcnn_ctx* c, void* hip_stream) {
 
 // Smallest internal batch that takes the shared-basis relinearisation, 0: none does.  It saves k^2 - 7k transforms per
 // ciphertext and pays with three times the key products and a base change.  Measured against the other forms, us:
-// n = 32768  k = 24  32 ciphertexts 2277 / 3070, 6: 530 / 690, 1: 251 / 193;  k = 18  32: 3194 / 3552;
-//            k = 12  32: 1049 / 1100, 6: 250 / 257, 1: 110 / 100
+// n = 32768  k = 24  32 ciphertexts 2255 / 3103, 6: 546 / 716, 4: 452 / 491, 1: 251 / 193;  k = 18  32: 1693 / 2017, 5: 354 / 386, 4: 303 / 305
+//            k = 16  32: 1411 / 1677, 5: 295 / 327, 4: 272 / 264;  k = 13  32: 1185 / 1230, 8: 334 / 324, 5: 247 / 251, 4: 231 / 206
+//            k = 12  32: 1033 / 1081, 16: 537 / 555, 8: 321 / 298, 4: 200 / 173
 // n = 16384  k = 16  225: 3907 / 4110, 16: 334 / 333;  k = 11  225: 2547 / 2329;  n = 8192  k = 12  700: 3949 / 3592.
 // Not measured: n = 16384 with 12 to 15 primes (left to the other forms) and with more than 16, where those forms have no
 // one-kernel relinearisation and the minimum of 64 is likely too high.
 static size_t shared_basis_min(const hcnn_ctx* c) {
   if (c->kp < 3) return 0;
   if (kSharedAll) return 2;
-  return c->logn == 15 && c->k >= 12 ? 4 : c->logn == 14 && c->k >= 16 ? 64 : 0;
+  if (c->logn == 15) return c->k >= 18 ? 4 : c->k >= 13 ? 5 : c->k == 12 ? 16 : 0;
+  return c->logn == 14 && c->k >= 16 ? 64 : 0;
 }
 
 // (Where the shared-basis relinearisation is in use the key is held a second time modulo its three primes, whatever forms the

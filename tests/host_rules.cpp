@@ -16,4 +16,12 @@ size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
   return groups == 2 ? MacMfma<2>::lds_bytes(T) : MacMfma<1>::lds_bytes(T);
 }
 
+// Smallest batch that takes the shared-basis relinearisation, 0: none.
+size_t rule_shared_basis_min(uint32_t n, uint32_t k, uint32_t k_aux) {
+  hcnn_ctx c;
+  c.n = n; c.k = k; c.kp = k_aux;
+  while ((1u << c.logn) < n) ++c.logn;
+  return shared_basis_min(&c);
+}
+
 }  // extern "C"

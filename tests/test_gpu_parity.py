@@ -117,7 +117,7 @@ def test_square_relin_chunked_ragged(backend):
     pc.check_square_relin(backend, 8192, 2, n_random=6, n_genuine=0, relin_order=2)            # key-major order
 
 
-@pytest.mark.parametrize("n,k,cts", [(32768, 12, 5), (32768, 13, 12), (16384, 16, 65)])
+@pytest.mark.parametrize("n,k,cts", [(32768, 12, 17), (32768, 13, 12), (32768, 18, 4), (16384, 16, 65)])
 def test_square_relin_shared_basis_equals_the_separate_kernels(backend, n, k, cts):
     """Batches that take the shared-basis relinearisation by default, against the separate kernels (the deep-modulus
     configuration below compares the same path with the oracle)."""
@@ -128,7 +128,12 @@ def test_square_relin_shared_basis_equals_the_separate_kernels(backend, n, k, ct
     ctx.set_relin_key(ctx.sample_uniform(5, 1, 2 * k).reshape((k, 2, k, n)))
     x = ctx.sample_uniform(5, 2, 2 * cts).reshape((cts, 2, k, n))
     x[0, 0, :, :] = x[0, 0, :, :1]
+    ctx.set_profile(True)
     out = ctx.ct_square_relin(x)
+    prof = ctx.profile()
+    # one launch of key products with three workgroups per tile of 64 coefficients and eight ciphertexts
+    assert prof["relin_mac"][:2] == (1, 3 * (n // 64) * -(-cts // 8)) and prof["relin_fused"][0] == 0
+    ctx.set_profile(False)
     prod = ctx.ct_mul_relin(x, x)
     ctx.set_fusion(1)
     want = ctx.ct_square_relin(x)

@@ -54,3 +54,10 @@ def test_network_plan_puts_16_outputs_into_rows_that_the_matrix_form_takes(rules
         for G in (1, 2, 4, 9):
             form = lambda terms, bound: rules.rule_mac_matrix_groups(units, n, k, 5000, G, 16, terms, bound)
             assert form(T, weight) == 1 and form(T + 1, weight) == 0 and form(T, weight + 1) == 0 and form(1000, weight) > 0
+
+
+@pytest.mark.parametrize("n,k,least", [(32768, 11, 0), (32768, 12, 16), (32768, 13, 5), (32768, 17, 5), (32768, 18, 4), (32768, 32, 4),
+                                       (16384, 15, 0), (16384, 16, 64), (16384, 32, 64), (8192, 32, 0)])
+def test_smallest_batch_of_the_shared_basis_relinearisation(rules, n, k, least):
+    assert rules.rule_shared_basis_min(n, k, k + 1) == least
+    assert rules.rule_shared_basis_min(n, k, 0) == 0           # no auxiliary primes: no squarings
