@@ -590,15 +590,16 @@ int build_tables(hcnn_ctx* c) {
 // Work buffer of a call that needs `bytes`: the small one, allocated on first use and kept as it is, or, for more, the
 // large one, which grows on demand (it waits for the stream, frees and allocates) and is kept.  Which of the two a call
 // takes depends on its size alone.
-// The small one holds what the decryption of 64 ciphertexts takes (65 polynomials: 17 MiB at n = 8192, k = 8, 195 at n = 32768,
-// k = 24; and no less than 512 rows, for the small bases), and so every key generation and encryption, the decryption of a
-// network's results and the squaring of a few ciphertexts: none of them finds a buffer to grow that another one left (first
-// decryption of 25 ciphertexts after key generation and encryption, n = 8192, k = 8, us: 335 with one buffer for all, 41 now).
-// A single growing buffer with that first size made the first squaring slower instead (16 ciphertexts after key generation
-// 186 -> 420 us, now 168: freeing 17 MiB takes 250 us).
-constexpr size_t kSmallWorkPolys = 65, kSmallWorkRows = 512;
+// The small one holds what key generation takes (2 + k polynomials), and 34 polynomials where that is at most 16 MiB (9 MiB at
+// n = 8192, k = 8): every encryption, the decryption of up to 33 ciphertexts (a network's results) and the squaring of one or
+// two.  None of them finds a buffer to grow that another one left (first decryption of 25 ciphertexts after key generation
+// and encryption, n = 8192, k = 8, us: 335 with one buffer for all, 42 now).  A single growing buffer with a first size of
+// 17 MiB made the first squaring slower instead (16 ciphertexts after key generation 186 -> 420 us, now 156: freeing takes
+// up to 250 us, allocating 25 to 75).
+constexpr size_t kSmallWorkPolys = 34, kSmallWorkBytes = (size_t)16 << 20;
 int work_buffer(hcnn_ctx* c, size_t bytes, uint32_t** out) {
-  const size_t small = std::max(kSmallWorkPolys * c->k, kSmallWorkRows) * c->n * 4;
+  const size_t poly = (size_t)c->k * c->n * 4;
+  const size_t small = std::max((2 + c->k) * poly, std::min(kSmallWorkPolys * poly, kSmallWorkBytes));
   const bool large = bytes > small;
   uint32_t*& buf = large ? c->work : c->small_work;
   size_t& held = large ? c->work_bytes : c->small_work_bytes;

@@ -68,7 +68,7 @@ def test_encrypt_decrypt_of_every_ring(backend, n, k):
 
 @pytest.mark.parametrize("n,k", [(1024, 1), (1024, 2), (8192, 8), (32768, 24)])
 def test_first_decryption_of_a_context_finds_its_work_buffer(backend, n, k):
-    """A decryption or noise read-out of up to 64 ciphertexts after key generation or one encryption allocates nothing."""
+    """A decryption or noise read-out of up to 33 ciphertexts after key generation or one encryption allocates nothing."""
     cand = _capi.gen_primes(backend.lib, n, k)
     s, e = np.zeros(n, np.int32), np.zeros((1, n), np.int32)
     a, m = np.zeros((k, n), np.uint32), np.zeros((1, n), np.uint32)
@@ -80,7 +80,7 @@ def test_first_decryption_of_a_context_finds_its_work_buffer(backend, n, k):
         else:
             ctx.encrypt(pk, m, e, e, e)
         held = ctx.scratch_bytes()
-        for count in ((1, 10) if n > 8192 else (1, 10, 25, 64)):
+        for count in ((1, 10) if n > 8192 else (1, 10, 25, 33)):
             x = np.zeros((count, 2, k, n), np.uint32)
             x[-1, 1] = 1
             ctx.decrypt(s, x)
