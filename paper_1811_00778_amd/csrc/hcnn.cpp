@@ -712,6 +712,9 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
     if (io == kNttStoreLazy) return run<NttFwd<LOGN, LOGR, kNttStoreLazy>>(c, r.rows, lds, a);
     if (io == kNttSmallKey) return run<NttFwd<LOGN, LOGR, kNttSmallKey>>(c, r.rows, lds, a);
     if (io == kNttStoreKey) return run<NttFwd<LOGN, LOGR, kNttStoreKey>>(c, r.rows, lds, a);
+    if constexpr (LOGN == 11 || LOGN == 12) {        // (a pass less: latency, while a row finds a compute unit of its own)
+      if (io == kNttPlain && r.rows <= c->compute_units) return run<NttFwd<LOGN, LOGR, kNttPlainFew>>(c, r.rows, lds, a);
+    }
     return io == kNttPlain ? run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a) : HCNN_ERR_ARG;
   }
 }

@@ -121,7 +121,8 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              // digits [ct][r][tile][i][64], key [r][tile][i][o][64]; the sums lie in [ct][r][tile][o][64]
              kNttDigitTile = 27, kNttKeyTile = 28,
              // decryption of few ciphertexts: the secret's row into registers too, and the product of the two rows
-             kNttSecretToRegs = 29, kNttDecOwn = 30 };
+             kNttSecretToRegs = 29, kNttDecOwn = 30,
+             kNttPlainFew = 31 };    // forward: as kNttPlain, with the stage split of the launches that leave compute units idle
 
 // Per-thread state of TensorFused: the two transformed polynomials of the ciphertext, one limb.
 template <int R>
@@ -212,9 +213,11 @@ HCNN_HD constexpr uint32_t lds_elem(uint32_t sbase, int e) {
 // pass is a whole number of radix-4 levels.  The last forward pass (the first inverse one) has every thread store (load)
 // 2^ns consecutive residues: two stages there make it one 16-byte word per lane, so that the lanes of a wave touch
 // consecutive words.
-// PLAIN: the transforms of the public entry points, which only move rows.  At n = 2048 and 4096 they keep that rule;
-// inside the squaring, the encryption and the decryption a pass less counts for more (n = 4096: 4000 x 4 rows forward and
-// back 403 us with four passes, 457 with three; 1000 squarings 621 and 593, one squaring 29.2 and 27.0).
+// PLAIN: the forward transforms of the public entry points, which only move rows.  At n = 2048 and 4096 they keep that rule
+// once every compute unit has a row (four passes / three, us: 4096 rows of n = 4096 28.0 / 33.2, 1024 9.6 / 12.2, of n = 2048 6.3 / 7.0;
+// 64 rows 4.5 / 4.2 and 4.0 / 3.5: kNttPlainFew).  Everything else takes a pass less there: the inverse gains nothing from the
+// fourth (4096 rows 27.5 / 27.5 and 14.5 / 14.4, 4 rows 3.8 / 3.7 and 3.5 / 3.1), and inside the squaring, the encryption and
+// the decryption the pass counts for more (n = 4096: 1000 squarings 621 / 593, one 29.2 / 27.0).
 template <int LOGN, int LOGR, bool PLAIN = false>
 struct NttGeom;
 template <int LOGN, int LOGR>
@@ -286,7 +289,7 @@ struct NttFwd {
   static constexpr bool kKeyOut = IO == kNttStoreKey || IO == kNttSmallKey || IO == kNttKeyTile;
   static constexpr bool kTileOut = IO == kNttDigitTile || IO == kNttKeyTile;
   static constexpr bool kDigitRow = IO == kNttLoadDigit || IO == kNttDigitTile;
-  static_assert(IO == kNttPlain || kDigitRow || IO == kNttStoreLazy || kKeyOut || kFused || kToRegs,
+  static_assert(IO == kNttPlain || IO == kNttPlainFew || kDigitRow || IO == kNttStoreLazy || kKeyOut || kFused || kToRegs,
                 "forward NTT: plain, digit load, lazy or key store, fused inner product or register output");
   static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kToRegs && LOGN % 2 == 1), "the split form stores its rows");
   using G = NttGeom<LOGN - SPLIT, LOGR, IO == kNttPlain>;      // the stages after the split one
@@ -481,7 +484,7 @@ struct NttInv {
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
                 IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut || IO == kNttDecOwn || IO == kNttBackRow || IO == kNttBack0 ||
                 IO == kNttBack1 || IO == kNttBack2, "inverse NTT io mode");
-  using G = NttGeom<LOGN, LOGR, IO == kNttPlain>;
+  using G = NttGeom<LOGN, LOGR>;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
   // a 1024-thread workgroup whose row leaves LDS for a second one: keep the registers within what two of them need

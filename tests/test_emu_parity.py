@@ -51,6 +51,11 @@ def test_ntt_all_sizes(backend, n, k, n_polys, rows):
     pc.check_ntt(backend, n, k, n_polys, rows)
 
 
+@pytest.mark.parametrize("n", [2048, 4096])
+def test_ntt_of_few_rows(backend, n):
+    pc.check_ntt(backend, n, 1, 1, None)          # one row for this build's one compute unit: a pass less
+
+
 @pytest.mark.parametrize("n", [1024, 2048])
 def test_transform_ranges_at_both_ends_of_the_prime_interval(backend, n):
     pc.check_transform_ranges(backend, n)

@@ -49,6 +49,13 @@ def test_ntt_all_sizes(backend, n, k, n_polys, rows):
     pc.check_ntt(backend, n, k, n_polys, rows)
 
 
+@pytest.mark.parametrize("n,k,n_polys", [(2048, 2, 128), (2048, 3, 86), (4096, 4, 64), (4096, 1, 257)])
+def test_ntt_rows_of_all_compute_units_or_fewer(backend, n, k, n_polys):
+    """256 rows and one more: both stage splits of the forward transform."""
+    say("ntt n=%d rows=%d" % (n, k * n_polys))
+    pc.check_ntt(backend, n, k, n_polys, 4)
+
+
 @pytest.mark.parametrize("n", [1024, 2048])
 def test_transform_ranges_at_both_ends_of_the_prime_interval(backend, n):
     say("transform ranges n=%d" % n)
