@@ -850,7 +850,7 @@ int query_fused_occupancy(hcnn_ctx* c) {
   int e = 0, r = 1, t = 1;
 #define HCNN_OCC(LOGN, LOGR)                                                                                          \
   {                                                                                                                   \
-    const size_t lds = NttGeom<LOGN, LOGR>::kLdsBytes;                                                                \
+    const size_t lds = RelinFused<LOGN, LOGR>::kLdsBytes;                                                             \
     e = k <= 8    ? resident_workgroups_per_cu<RelinFused<LOGN, LOGR, kNttFusedMac>, RelinFusedArgs>(lds, &r)         \
         : k <= 16 ? resident_workgroups_per_cu<RelinFused<LOGN, LOGR, kNttFusedMac16>, RelinFusedArgs>(lds, &r)       \
                   : resident_workgroups_per_cu<RelinFused<LOGN, LOGR, kNttFusedMacAny>, RelinFusedArgs>(lds, &r);     \
@@ -865,11 +865,11 @@ int query_fused_occupancy(hcnn_ctx* c) {
 #undef HCNN_OCC
   if (e) return e;
   switch (c->logn) {
-    case 10: e = resident_workgroups_per_cu<TensorFused<10, 4>, TensorFusedArgs>(NttGeom<10, 4>::kLdsBytes, &t); break;
-    case 11: e = resident_workgroups_per_cu<TensorFused<11, 4>, TensorFusedArgs>(NttGeom<11, 4>::kLdsBytes, &t); break;
-    case 12: e = resident_workgroups_per_cu<TensorFused<12, 4>, TensorFusedArgs>(NttGeom<12, 4>::kLdsBytes, &t); break;
-    case 13: e = resident_workgroups_per_cu<TensorFused<13, 4>, TensorFusedArgs>(NttGeom<13, 4>::kLdsBytes, &t); break;
-    case 14: e = resident_workgroups_per_cu<TensorFused<14, 4>, TensorFusedArgs>(NttGeom<14, 4>::kLdsBytes, &t); break;
+    case 10: e = resident_workgroups_per_cu<TensorFused<10, 4>, TensorFusedArgs>(TensorFused<10, 4>::kLdsBytes, &t); break;
+    case 11: e = resident_workgroups_per_cu<TensorFused<11, 4>, TensorFusedArgs>(TensorFused<11, 4>::kLdsBytes, &t); break;
+    case 12: e = resident_workgroups_per_cu<TensorFused<12, 4>, TensorFusedArgs>(TensorFused<12, 4>::kLdsBytes, &t); break;
+    case 13: e = resident_workgroups_per_cu<TensorFused<13, 4>, TensorFusedArgs>(TensorFused<13, 4>::kLdsBytes, &t); break;
+    case 14: e = resident_workgroups_per_cu<TensorFused<14, 4>, TensorFusedArgs>(TensorFused<14, 4>::kLdsBytes, &t); break;
   }
   if (e) return e;
   c->relin_fused_wgs = (uint32_t)r;
@@ -881,7 +881,7 @@ int query_fused_occupancy(hcnn_ctx* c) {
 constexpr size_t kCryptRows = (size_t)1 << 26;     // rows of one launch
 template <int LOGN, int LOGR>
 int crypt_fused(hcnn_ctx* c, const CryptArgs& a, bool enc) {
-  const size_t grid = ntt_grouped_grid(a.n_rows, c->k), lds = NttGeom<LOGN, LOGR>::kLdsBytes;
+  const size_t grid = ntt_grouped_grid(a.n_rows, c->k), lds = CryptFused<LOGN, LOGR, true>::kLdsBytes;
   if (enc) return run<CryptFused<LOGN, LOGR, true>>(c, grid, lds, a);
   if (a.u) {
     // (the largest ring does not hold a second row in its registers)
@@ -1177,7 +1177,7 @@ static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* d
   }
   RelinBackArgs ba{acc, y, out, c->d_tw_inv, c->d_limbs, c->d_crt, c->crt_inv, k, fast_div(2 * k)};
   switch (c->logn) {
-#define HCNN_BACK(LOGN) case LOGN: return run<RelinBack<LOGN, 4>>(c, rows, NttGeom<LOGN, 4>::kLdsBytes, ba, 3 * rows);
+#define HCNN_BACK(LOGN) case LOGN: return run<RelinBack<LOGN, 4>>(c, rows, RelinBack<LOGN, 4>::kLdsBytes, ba, 3 * rows);
 #ifdef HCNN_SHARED_ALL
     HCNN_BACK(10) HCNN_BACK(11) HCNN_BACK(12) HCNN_BACK(13)
 #endif
@@ -1293,11 +1293,11 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
       TensorFusedArgs ta{in + c0 * ct_words, b_ext, b_d, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, L, (uint32_t)(cc * L), fast_div(L)};
       const size_t rows = cc * L * 5;
       switch (c->logn) {
-        case 10: e = run<TensorFused<10, 4>>(c, cc * L, NttGeom<10, 4>::kLdsBytes, ta, rows); break;
-        case 11: e = run<TensorFused<11, 4>>(c, cc * L, NttGeom<11, 4>::kLdsBytes, ta, rows); break;
-        case 12: e = run<TensorFused<12, 4>>(c, cc * L, NttGeom<12, 4>::kLdsBytes, ta, rows); break;
-        case 13: e = run<TensorFused<13, 4>>(c, cc * L, NttGeom<13, 4>::kLdsBytes, ta, rows); break;
-        case 14: e = run<TensorFused<14, 4>>(c, cc * L, NttGeom<14, 4>::kLdsBytes, ta, rows); break;
+        case 10: e = run<TensorFused<10, 4>>(c, cc * L, TensorFused<10, 4>::kLdsBytes, ta, rows); break;
+        case 11: e = run<TensorFused<11, 4>>(c, cc * L, TensorFused<11, 4>::kLdsBytes, ta, rows); break;
+        case 12: e = run<TensorFused<12, 4>>(c, cc * L, TensorFused<12, 4>::kLdsBytes, ta, rows); break;
+        case 13: e = run<TensorFused<13, 4>>(c, cc * L, TensorFused<13, 4>::kLdsBytes, ta, rows); break;
+        case 14: e = run<TensorFused<14, 4>>(c, cc * L, TensorFused<14, 4>::kLdsBytes, ta, rows); break;
         default: e = HCNN_ERR_N; break;
       }
       if (e) return e;
@@ -1327,9 +1327,9 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
       RelinFusedArgs fa{b_y, c->d_evk_hat, out + c0 * ct_words, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, (uint32_t)(nf * k), fast_div(k)};
       const size_t grid = ntt_grouped_grid(nf * k, k), rows = nf * k * (k + 2);
 #define HCNN_FUSED(LOGN, LOGR)                                                                                      \
-  (k <= 8 ? run<RelinFused<LOGN, LOGR, kNttFusedMac>>(c, grid, NttGeom<LOGN, LOGR>::kLdsBytes, fa, rows)             \
-          : k <= 16 ? run<RelinFused<LOGN, LOGR, kNttFusedMac16>>(c, grid, NttGeom<LOGN, LOGR>::kLdsBytes, fa, rows) \
-                    : run<RelinFused<LOGN, LOGR, kNttFusedMacAny>>(c, grid, NttGeom<LOGN, LOGR>::kLdsBytes, fa, rows))
+  (k <= 8 ? run<RelinFused<LOGN, LOGR, kNttFusedMac>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMac>::kLdsBytes, fa, rows)             \
+          : k <= 16 ? run<RelinFused<LOGN, LOGR, kNttFusedMac16>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMac16>::kLdsBytes, fa, rows) \
+                    : run<RelinFused<LOGN, LOGR, kNttFusedMacAny>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMacAny>::kLdsBytes, fa, rows))
       switch (c->logn) {
         case 10: e = HCNN_FUSED(10, 4); break;
         case 11: e = HCNN_FUSED(11, 4); break;

@@ -7,7 +7,7 @@
 //
 // The log2(n) stages are cut into passes of at most LOGR stages.  In a pass every
 // thread keeps R = 2^LOGR residues in registers and runs complete radix-2^NS
-// networks on them; between passes the row lives in LDS (one barrier per pass).
+// networks on them; between passes the row lives in LDS (one barrier per transform, see net_index).
 // The first pass reads HBM with unit stride across lanes, the last pass writes HBM.
 //
 // Residues are SIGNED inside a transform and the stages are taken two at a time, as one
@@ -245,6 +245,22 @@ HCNN_GEOM_SPEC(14, 5, false, 4, 4, 4, 4, 2)      // the half rows of n = 32768's
 HCNN_GEOM_SPEC(15, 5, false, 4, 5, 4, 4, 2)
 #undef HCNN_GEOM_SPEC
 
+// Which networks a thread takes.  The first forward pass (the last inverse one) joins elements of the whole row; after it
+// no stage reaches beyond 1024 consecutive residues, and those belong to one wave in every other pass: network c of
+// thread `tid` lies in block d of the wave.  So only one exchange of a transform crosses waves and needs a barrier; the
+// others go through LDS words that no other wave touches, which are in order by themselves.
+template <class G, int PH>
+HCNN_HD uint32_t net_index(int tid, int c) {
+  constexpr int NET = 1 << G::ns(PH);
+  if constexpr (PH == 0 || NET >= 16) {
+    return (uint32_t)tid + (uint32_t)G::kThreads * c;
+  } else {
+    constexpr int kPerBlock = 16 / NET;
+    const uint32_t wave = wave_uniform((uint32_t)tid / 64);
+    return (wave + (uint32_t)(G::kThreads / 64) * (c / kPerBlock)) * (1024 / NET) + (uint32_t)(c % kPerBlock) * 64 + (uint32_t)tid % 64;
+  }
+}
+
 // Two Cooley-Tukey stages on (x0, x1, x2, x3): pairs (0,2), (1,3) with W, then (0,1) with V and (2,3) with U.
 // Twiddles c are centred and carry 2^32, so sredc(c * x) is the product: |sum of two products| <= p |x|max, which the
 // reduction brings to p |x|max / 2^32 + p/2 <= p for any 32-bit x; every output is a sum or difference of two: in (-2p, 2p).
@@ -297,6 +313,7 @@ struct NttFwd {
   static constexpr int kPhases = G::kPhases;
   static constexpr bool kDigitIn = kDigitRow || kFused;
   using Regs = std::conditional_t<kFused, RelinRegs<G::R>, std::conditional_t<kRowToRegs, RowRegs<G::R>, std::conditional_t<kToRegs, TensorRegs<G::R>, NoRegs>>>;
+  static constexpr bool wave_sync(int ph) { return ph != 0; }        // one exchange across waves (net_index)
   // workgroups of a launch over `slots` row positions (a multiple of the die count for the split form)
   static size_t grid(size_t slots) { return SPLIT ? 2 * ((slots + kNttXcds - 1) / kNttXcds * kNttXcds) : slots; }
 
@@ -387,7 +404,7 @@ struct NttFwd {
 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const uint32_t nu = (uint32_t)tid + (uint32_t)kThreads * c;   // network id
+      const uint32_t nu = net_index<G, PH>(tid, c);                 // network id
       const uint32_t o = nu & (TLAST - 1);
       uint32_t i = nu >> LOG_TLAST;
       if constexpr (TLAST >= 64) i = wave_uniform(i);               // (scalar twiddle loads)
@@ -490,6 +507,7 @@ struct NttInv {
   // a 1024-thread workgroup whose row leaves LDS for a second one: keep the registers within what two of them need
   // (the plain transform of n = 16384 took 68 and ran alone on its compute unit, a third slower per row)
   static constexpr int kMinWavesPerSimd = (G::kThreads == 1024 && 2 * G::kLdsBytes <= 160 * 1024) ? 8 : 1;
+  static constexpr bool wave_sync(int ph) { return ph != kPhases - 2; }        // one exchange across waves (net_index)
   static constexpr bool kFromRegs = IO == kNttFromRegs0 || IO == kNttFromRegs1;
   static constexpr bool kTensorRegs = IO == kNttTensorRegs0 || IO == kNttTensorRegs1 || IO == kNttTensorRegs2;
   static constexpr bool kBack = IO == kNttBack0 || IO == kNttBack1 || IO == kNttBack2;
@@ -588,7 +606,7 @@ struct NttInv {
 
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const uint32_t nu = (uint32_t)tid + (uint32_t)kThreads * c;
+      const uint32_t nu = net_index<G, PH>(tid, c);
       const uint32_t o = nu & (TLAST - 1);
       uint32_t i = nu >> LOG_TLAST;
       if constexpr (TLAST >= 64) i = wave_uniform(i);
@@ -751,6 +769,21 @@ struct NttInv {
   }
 };
 
+// Several transforms of one workgroup, one after the other, P phases each: is transform t (forward up to `fwd` of them) done
+// with phase ph without a barrier behind it?  Its own exchange takes one.  Between two transforms none is needed where they
+// alternate between two row buffers (whoever writes a buffer again has passed the barrier of the transform in between, and so has
+// every wave that read it), nor in front of an inverse transform that follows a forward one (it starts inside its waves' own words).
+// Two buffers where the registers leave no room for a further workgroup anyway; otherwise the workgroup that one buffer leaves
+// room for is worth more than the barriers (n = 8192, us, one / two buffers: tensor of 512 ciphertexts, three workgroups per
+// compute unit / two, 516 / 588; 784 encryptions 319 / 345).
+constexpr bool seq_wave_sync(int ph, int P, int fwd, int buffers) {
+  const int t = ph / P, r = ph % P;
+  if (r == P - 1) return buffers == 2 || t + 1 == fwd;
+  return t < fwd ? r != 0 : r != P - 2;
+}
+template <class G, int BUFFERS>
+HCNN_HD uint32_t* seq_buffer(uint32_t* lds, uint32_t t) { return BUFFERS == 2 ? lds + (t & 1u) * (uint32_t)(G::kLdsBytes / 4) : lds; }
+
 // ------------------------------------------------------------------------- relinearisation in one kernel
 // Workgroup (ct, j): for every digit i of y2[ct] -- forward transform modulo q_j, products with the two key rows
 // added to register-held sums -- then the two sums go back through the inverse transform and leave as
@@ -774,6 +807,8 @@ struct RelinFused {
   using Inv0 = NttInv<LOGN, LOGR, kNttFromRegs0>;
   using Inv1 = NttInv<LOGN, LOGR, kNttFromRegs1>;
   static constexpr int P = G::kPhases;
+  static constexpr int kBuffers = 2;
+  static constexpr size_t kLdsBytes = kBuffers * G::kLdsBytes;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kLoopPhases = P;
   // room for two workgroups per compute unit (one of 1024 threads)
@@ -781,6 +816,7 @@ struct RelinFused {
   static constexpr int kPhases = 3 * P;
   using Regs = RelinRegs<G::R>;
   HCNN_HD static uint32_t loop_count(const RelinFusedArgs& a) { return a.k; }
+  static constexpr bool wave_sync(int ph) { return seq_wave_sync(ph, P, 1, kBuffers); }
 
   template <int PH>
   HCNN_HD static void phase(const RelinFusedArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
@@ -788,9 +824,10 @@ struct RelinFused {
     na.limbs = a.limbs; na.cycle = a.cycle; na.limb_base = 0; na.n_rows = a.n_rows;
     if constexpr (PH < P) {
       na.in = a.y; na.aux = a.evk; na.tw = a.tw_fwd;
-      Fwd::template phase<PH>(na, bid, tid, lds, regs);
+      Fwd::template phase<PH>(na, bid, tid, seq_buffer<G, kBuffers>(lds, regs.iter), regs);
     } else {
       na.aux = a.y; na.out = a.out; na.tw = a.tw_inv;
+      lds = seq_buffer<G, kBuffers>(lds, a.k + (PH < 2 * P ? 0 : 1));
       if constexpr (PH < 2 * P) Inv0::template phase<PH - P>(na, bid, tid, lds, regs);
       else Inv1::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
     }
@@ -817,13 +854,17 @@ template <int LOGN, int LOGR>
 struct TensorFused {
   using G = NttGeom<LOGN, LOGR>;
   static constexpr int P = G::kPhases;
+  static constexpr int kBuffers = LOGN == 14 ? 2 : 1;
+  static constexpr size_t kLdsBytes = kBuffers * G::kLdsBytes;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = 5 * P;
   static constexpr int kMinWavesPerSimd = 4;     // 128 registers: two 512-thread or four 256-thread workgroups per compute unit
   using Regs = TensorRegs<G::R>;
+  static constexpr bool wave_sync(int ph) { return seq_wave_sync(ph, P, 2, kBuffers); }
 
   template <int PH>
   HCNN_HD static void phase(const TensorFusedArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
+    lds = seq_buffer<G, kBuffers>(lds, PH / P);
     NttArgs na{};
     na.limbs = a.limbs; na.cycle = a.cycle; na.limb_base = 0; na.n_rows = a.n_rows;
     if constexpr (PH < 2 * P) {
@@ -858,12 +899,16 @@ template <int LOGN, int LOGR>
 struct RelinBack {
   using G = NttGeom<LOGN, LOGR>;
   static constexpr int P = G::kPhases;
+  static constexpr int kBuffers = 2;
+  static constexpr size_t kLdsBytes = kBuffers * G::kLdsBytes;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = 3 * P;
   static constexpr int kMinWavesPerSimd = 4;
   using Regs = BackRegs<G::R>;
+  static constexpr bool wave_sync(int ph) { return seq_wave_sync(ph, P, 0, kBuffers); }
   template <int PH>
   HCNN_HD static void phase(const RelinBackArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
+    lds = seq_buffer<G, kBuffers>(lds, PH / P);
     NttArgs na{};
     na.in = a.acc; na.aux = a.y; na.out = a.out; na.tw = a.tw_inv; na.limbs = a.limbs; na.limb_base = a.limb_base;
     na.cycle = FastDiv{3, 0x55555555u}; na.tile_words = a.outputs.d * 64;
@@ -903,13 +948,17 @@ template <int LOGN, int LOGR, bool ENC, bool OWN = false>
 struct CryptFused {
   using G = NttGeom<LOGN, LOGR>;
   static constexpr int P = G::kPhases;
+  static constexpr int kBuffers = LOGN == 14 ? 2 : 1;
+  static constexpr size_t kLdsBytes = kBuffers * G::kLdsBytes;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = (ENC || OWN ? 3 : 2) * P;
   static constexpr int kMinWavesPerSimd = 4;
   using Regs = RowRegs<G::R>;
+  static constexpr bool wave_sync(int ph) { return seq_wave_sync(ph, P, OWN ? 2 : 1, kBuffers); }
 
   template <int PH>
   HCNN_HD static void phase(const CryptArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
+    lds = seq_buffer<G, kBuffers>(lds, PH / P);
     NttArgs na{};
     na.limbs = a.limbs; na.cycle = a.cycle; na.n_rows = a.n_rows;
     if constexpr (OWN) {

@@ -14,6 +14,10 @@
 // a GPU) runs the same phase bodies as plain loops over blocks and threads; it is
 // a checker for the kernel sources, not a product path, and the Python binding
 // never loads it.
+// Optional: wave_sync(ph)       true: up to the next barrier the phases after ph touch only LDS words that no other
+//                               wave touches in between, and no barrier stands after ph (of the last repeated phase: in front
+//                               of what follows it, the next iteration or the rest).  The checker runs the phases
+//                               between two barriers wave after wave, so that a wave which relies on another one is seen.
 #pragma once
 #include <cstddef>
 #include <cstdint>
@@ -21,6 +25,7 @@
 #include <atomic>
 #include <cstring>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #ifdef HCNN_HOSTEMU
@@ -176,6 +181,8 @@ HCNN_HD uint32_t wave_uniform(uint32_t x) {
 // kMinWavesPerSimd (optional): occupancy the register allocation of the kernel must allow
 template <class K, class = void> struct MinWavesPerSimd { static constexpr int value = 1; };
 template <class K> struct MinWavesPerSimd<K, std::void_t<decltype(K::kMinWavesPerSimd)>> { static constexpr int value = K::kMinWavesPerSimd; };
+template <class K, class = void> struct WaveSync { static constexpr bool after(int) { return false; } };
+template <class K> struct WaveSync<K, std::void_t<decltype(K::wave_sync(0))>> { static constexpr bool after(int ph) { return K::wave_sync(ph); } };
 template <class K, class = void> struct LoopPhases { static constexpr int value = 0; };
 template <class K> struct LoopPhases<K, std::void_t<decltype(K::kLoopPhases)>> { static constexpr int value = K::kLoopPhases; };
 
@@ -211,14 +218,15 @@ int resident_workgroups_per_cu(size_t, int* out) {
   return 0;
 }
 
-template <class K, int PH, int END>
-struct EmuPhases {
-  template <class Args>
-  static void run(const Args& a, unsigned bid, uint32_t* lds, std::vector<typename K::Regs>& regs) {
-    for (int tid = 0; tid < K::kThreads; ++tid) K::template phase<PH>(a, bid, tid, lds, regs[tid]);
-    if constexpr (PH + 1 < END) EmuPhases<K, PH + 1, END>::run(a, bid, lds, regs);
-  }
-};
+template <class K, class Args>
+using EmuPhase = void (*)(const Args&, unsigned, int, uint32_t*, typename K::Regs&);
+template <class K, class Args, int... PH>
+EmuPhase<K, Args> emu_phase(int ph, std::integer_sequence<int, PH...>) {
+  static constexpr EmuPhase<K, Args> all[] = {[](const Args& a, unsigned bid, int tid, uint32_t* lds, typename K::Regs& r) {
+    K::template phase<PH>(a, bid, tid, lds, r);
+  }...};
+  return all[ph];
+}
 
 template <class K, class Args>
 int launch(hcnn_stream_t, size_t grid, size_t lds_bytes, const Args& a) {
@@ -226,15 +234,34 @@ int launch(hcnn_stream_t, size_t grid, size_t lds_bytes, const Args& a) {
   std::vector<uint32_t> lds(lds_bytes / 4 + 4);
   std::vector<typename K::Regs> regs(K::kThreads);
   constexpr int LP = LoopPhases<K>::value;
+  // the phases of a workgroup in order; `next`: the first one behind the next barrier
+  struct Step { EmuPhase<K, Args> run; uint32_t iter; size_t next; };
+  std::vector<Step> steps;
+  std::vector<bool> barrier;
+  auto add = [&](int ph, uint32_t it) {
+    steps.push_back(Step{emu_phase<K, Args>(ph, std::make_integer_sequence<int, K::kPhases>{}), it, 0});
+    barrier.push_back(!WaveSync<K>::after(ph));
+  };
+  uint32_t count = 0;
+  if constexpr (LP > 0) {
+    count = K::loop_count(a);
+    for (uint32_t it = 0; it < count; ++it)
+      for (int ph = 0; ph < LP; ++ph) add(ph, it);
+  }
+  for (int ph = LP; ph < K::kPhases; ++ph) add(ph, count);
+  for (size_t i = steps.size(); i-- > 0;) steps[i].next = i + 1 == steps.size() || barrier[i] ? i + 1 : steps[i + 1].next;
+  const int waves = (K::kThreads + 63) / 64;
   for (size_t bid = 0; bid < grid; ++bid) {
-    if constexpr (LP > 0) {
-      const uint32_t count = K::loop_count(a);
-      for (uint32_t it = 0; it < count; ++it) {
-        for (auto& r : regs) r.iter = it;
-        EmuPhases<K, 0, LP>::run(a, (unsigned)bid, lds.data(), regs);
-      }
-    }
-    if constexpr (LP < K::kPhases) EmuPhases<K, LP, K::kPhases>::run(a, (unsigned)bid, lds.data(), regs);
+    bool up = true;                                    // waves in ascending, then in descending order
+    for (size_t s = 0; s < steps.size(); s = steps[s].next, up = !up)
+      for (int w = 0; w < waves; ++w)
+        for (size_t i = s; i < steps[s].next; ++i) {
+          const int t0 = (up ? w : waves - 1 - w) * 64, t1 = t0 + 64 < K::kThreads ? t0 + 64 : K::kThreads;
+          for (int tid = t0; tid < t1; ++tid) {
+            if constexpr (LP > 0) regs[tid].iter = steps[i].iter;
+            steps[i].run(a, (unsigned)bid, tid, lds.data(), regs[tid]);
+          }
+        }
   }
   return 0;
 }
@@ -282,12 +309,25 @@ inline uint32_t compute_unit_count() {
 HCNN_HD void atomic_inc64(unsigned long long* p) { atomicAdd(p, 1ull); }
 HCNN_HD void atomic_max32(uint32_t* p, uint32_t v) { atomicMax(p, v); }
 
+// What separates phase PH from the next one.  A wave's own LDS accesses take effect in order, so that between phases that
+// exchange data within a wave only the compiler has to be kept from reordering them.
+template <class K, int PH>
+__device__ __forceinline__ void phase_sync() {
+  if constexpr (WaveSync<K>::after(PH)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+
 template <class K, int PH, int END, class Args>
 __device__ __forceinline__ void run_phases(const Args& a, unsigned bid, int tid, uint32_t* lds,
                                            typename K::Regs& regs) {
   K::template phase<PH>(a, bid, tid, lds, regs);
   if constexpr (PH + 1 < END) {
-    __syncthreads();
+    phase_sync<K, PH>();
     run_phases<K, PH + 1, END, Args>(a, bid, tid, lds, regs);
   }
 }
@@ -302,8 +342,9 @@ __global__ void __launch_bounds__(K::kThreads, MinWavesPerSimd<K>::value) kernel
     for (uint32_t it = 0; it < count; ++it) {
       regs.iter = it;
       run_phases<K, 0, LP, Args>(a, blockIdx.x, (int)threadIdx.x, hcnn_lds, regs);
-      __syncthreads();
+      phase_sync<K, LP - 1>();
     }
+    regs.iter = count;
   }
   if constexpr (LP < K::kPhases) run_phases<K, LP, K::kPhases, Args>(a, blockIdx.x, (int)threadIdx.x, hcnn_lds, regs);
 }
