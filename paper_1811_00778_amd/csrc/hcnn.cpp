@@ -276,7 +276,7 @@ struct hcnn_ctx {
   Mod* d_mods = nullptr;            // [k + kp]
   NttLimb* d_limbs = nullptr;       // [k + kp]
   TwTable d_tw_fwd{}, d_tw_inv{};   // [k + kp][n/2]
-  ShoupConst* d_delta = nullptr;    // [k] floor(q/t) mod q_l
+  EncScale* d_delta = nullptr;      // [k]
   int32_t* d_tq_inv = nullptr;      // [kp] t * q^-1 mod p_j
   BConvDev ext{}, to_p{}, to_q{}, dec{};
   uint32_t* d_gauss_t = nullptr;    // thresholds of the Gaussian sampler (uploaded on first use)
@@ -537,11 +537,13 @@ int build_tables(hcnn_ctx* c) {
 
   // floor(q/t) mod q_l = -(q mod t) * t^-1 mod q_l   (q = 0 mod q_l)
   const uint64_t q_mod_t = h_prod_mod64(c->q, -1, c->t);
-  std::vector<ShoupConst> delta;
+  std::vector<EncScale> delta;
   for (uint32_t l = 0; l < c->k; ++l) {
     const uint32_t ql = c->q[l];
     const uint32_t v = h_mulmod((ql - (uint32_t)(q_mod_t % ql)) % ql, h_inv((uint32_t)(c->t % ql), ql), ql);
-    delta.push_back(h_shoup(v, ql));
+    const uint32_t r32 = (uint32_t)((1ull << 32) % ql), v2 = h_mulmod(v, r32, ql);
+    const int32_t c32 = h_mont(h_mulmod(v, 1u << 31, ql), ql), c64 = h_mont(h_mulmod((v + v2) % ql, 1u << 31, ql), ql);
+    delta.push_back(EncScale{h_mont(v, ql), h_mont(v2, ql), c32, c64});
   }
   if ((e = upload(c, delta, &c->d_delta))) return e;
 
