@@ -750,23 +750,182 @@ struct MacKernel {
 // A term row is padded to a multiple of 16 with zero-weight terms on its last input.
 // Two groups, not four: a last workgroup of 4 is up to three quarters empty, and a launch of few groups stages twice the tables per
 // tile (us, four / two groups per workgroup: 16 filters x 576 terms, 64 groups, n = 8192, k = 10 1676 / 1548; 10 x 576, 9 groups
-// 395 / 347; 10 x 96, 8 groups, n = 4096, k = 4 21 / 15).
+// 395 / 347; 10 x 96, 8 groups, n = 4096, k = 4 21 / 15).  Where a launch has enough tiles, MacPair takes the pairs.
 // Bound: the gather.  576 terms x 16 filters over 64 groups at n = 8192, k = 10: vector form 3.40 ms, this one 1.50, 24 GB gathered at
 // 32 bytes per clock and compute unit (18 GB of it from L2), vector unit 55 % used, matrix unit 12 %.  Measured and left out: a second register
 // buffer of inputs (spills: a third slower); the waves kept in step by a barrier per chunk (L2 requests halved, no faster: the
 // waits it adds cost what it saves); eight groups on eight waves.
 constexpr uint32_t kMfmaMaxSum = 1u << 20;     // T * |w| <= 2^20: sums of weight * byte stay below 2^28, and 4 * 2^28 * p/2
                                                // leaves the Montgomery step within (-p, p)
+// What the two kernels below share: the sums of one tile for NG groups over one list of terms.
+struct MacMatrix {
+  static constexpr uint32_t kTile = 64;
+  HCNN_HOSTDEV static uint32_t chunks(uint32_t T) { return (T + 63) / 64; }
+  // the next workgroup's share of the grid: die, tile block and first group
+  static size_t grid(uint32_t tile_blocks, size_t group_blocks) { return (size_t)kXcds * ((tile_blocks + kXcds - 1) / kXcds) * group_blocks; }
+
+#if defined(HCNN_HOSTEMU)
+  // The checker runs lane by lane: every lane forms its own 4 filters x 4 coefficients from the staged tables.
+  struct Sums { int32_t v[4] = {0, 0, 0, 0}; };
+  static int32_t weight(const uint32_t* l_w, uint32_t f, uint32_t t) {          // term t of a chunk
+    return (int8_t)(l_w[((t / 4 % 4 * 16 + f) * 4) + t / 16] >> (8 * (t % 4)));
+  }
+  static void weight_sums(const uint32_t* l_w, uint32_t n_chunks, uint32_t lane, Sums& out) {
+    for (int r = 0; r < 4; ++r)
+      for (uint32_t t = 0; t < n_chunks * 64; ++t) out.v[r] += 128 * weight(l_w + t / 64 * 256, lane / 16 * 4 + r, t % 64);
+  }
+  template <int Q> struct Inputs { const uint32_t *in, *l_off; uint32_t unit; };
+  template <bool WIDE, int Q>
+  static void load(const uint32_t* in, const uint32_t* l_off, uint32_t lane, Inputs<Q>& x, uint32_t) { x = Inputs<Q>{in + lane % 16 * 4, l_off, WIDE ? 16u : 1u}; }
+  template <int Q, int NG>
+  static void multiply(const Inputs<Q>& chunk, const uint32_t* l_w, uint32_t w_stride, uint32_t lane, Sums (&acc)[NG][4][4]) {
+    const uint32_t *in = chunk.in, *l_off = chunk.l_off;
+    for (uint32_t t = 0; t < 16 * Q; ++t)
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t x = in[(size_t)l_off[t] * chunk.unit / 4 + s];
+        for (int g = 0; g < NG; ++g)
+          for (int r = 0; r < 4; ++r)
+            for (int j = 0; j < 4; ++j)
+              acc[g][s][j].v[r] += weight(l_w + g * w_stride, lane / 16 * 4 + r, t) * ((int32_t)(x >> (8 * j) & 0xff) - (j < 3 ? 128 : 0));
+      }
+  }
+#elif !defined(__HIP_DEVICE_COMPILE__)
+  // (the host pass of the device build only parses the callers)
+  struct Sums { int32_t v[4] = {0, 0, 0, 0}; };
+  __device__ static void weight_sums(const uint32_t*, uint32_t, uint32_t, Sums&);
+  template <int Q> struct Inputs {};
+  template <bool WIDE, int Q> __device__ static void load(const uint32_t*, const uint32_t*, uint32_t, Inputs<Q>&, uint32_t);
+  template <int Q, int NG> __device__ static void multiply(const Inputs<Q>&, const uint32_t*, uint32_t, uint32_t, Sums (&)[NG][4][4]);
+#else
+  typedef int32_t Vec __attribute__((ext_vector_type(4)));
+  struct Sums { Vec v = {0, 0, 0, 0}; };
+  __device__ __forceinline__ static void weight_sums(const uint32_t* l_w, uint32_t n_chunks, uint32_t lane, Sums& out) {
+    const Vec ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    for (uint32_t c = 0; c < n_chunks; ++c)
+      out.v = __builtin_amdgcn_mfma_i32_16x16x64_i8(reinterpret_cast<const Vec*>(l_w + c * 256)[lane], ones, out.v, 0, 0, 0);
+    out.v *= 128;
+  }
+  // The inputs of Q quad steps of 16 terms, four coefficients per lane
+  template <int Q> struct Inputs { hcnn_word4 x[Q][4]; };
+  // in: the tile's first coefficient of input 0; offsets count 16 bytes (WIDE) or bytes.  terms (a multiple of 16): what is left
+  template <bool WIDE, int Q>
+  __device__ __forceinline__ static void load(const uint32_t* in, const uint32_t* l_off, uint32_t lane, Inputs<Q>& to, uint32_t terms) {
+    typedef const hcnn_word4 __attribute__((address_space(1))) * gptr;
+    const uint32_t ln = lane % 16;
+    const gptr src = (gptr)(const hcnn_word4*)in + ln;
+    auto one = [&](uint32_t off) -> hcnn_word4 {
+      if constexpr (WIDE) return src[off];
+      else {
+        const U4 t = ld4_at(in, off + ln * 16);
+        return hcnn_word4{t.x, t.y, t.z, t.w};
+      }
+    };
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (!WIDE && q * 16u >= terms) break;
+      const hcnn_word4 off = *reinterpret_cast<const hcnn_word4*>(l_off + q * 16 + lane / 16 * 4);
+      to.x[q][0] = one(off.x); to.x[q][1] = one(off.y); to.x[q][2] = one(off.z); to.x[q][3] = one(off.w);
+      if (!WIDE) sched_fence();
+    }
+  }
+  // ... and their products with the weights of NG groups, w_stride words apart; operand words beyond the Q steps are zero
+  template <int Q, int NG>
+  __device__ __forceinline__ static void multiply(const Inputs<Q>& in, const uint32_t* l_w, uint32_t w_stride, uint32_t lane, Sums (&acc)[NG][4][4]) {
+    const auto& x = in.x;
+    Vec w[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) w[g] = reinterpret_cast<const Vec*>(l_w + g * w_stride)[lane];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      Vec b[4] = {};
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const uint32_t lo01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x05010400u);    // a0 b0 a1 b1
+        const uint32_t hi01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x07030602u);    // a2 b2 a3 b3
+        const uint32_t lo23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x05010400u);
+        const uint32_t hi23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x07030602u);
+        b[0][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u);
+        b[1][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u);
+        b[2][q] = (int32_t)(__builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u);
+        b[3][q] = (int32_t)__builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+      }
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[g][s][j].v = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[g], b[j], acc[g][s][j].v, 0, 0, 0);
+      if (NG > 1) sched_fence();
+    }
+  }
+#endif
+
+  // Sums of the 64 coefficients of tile t for NG groups, as residues in [0, p): word s of out[group][r] belongs to filter
+  // 4 (lane / 16) + r and coefficient 4 (lane % 16) + s.  l_off: `terms` offsets (a multiple of 16; WIDE: in 16-byte units, else
+  // bytes), l_w the groups' weight words, w_stride apart, zero beyond the last term, wsum 128 times the sums of their weights.
+  template <int NG, bool WIDE>
+  HCNN_HD static void tile(const MacArgs& a, uint32_t t, const uint32_t* l_off, const uint32_t* l_w, uint32_t w_stride, uint32_t terms,
+                           uint32_t lane, const Sums (&wsum)[NG], U4 (&out)[NG][4]) {
+    const NttLimb L = ldc(a.limbs, t / (a.n / kTile) % a.k);
+    const uint32_t* in = a.in + t * kTile;
+    Sums acc[NG][4][4];                                               // [group][s][byte]
+#pragma unroll
+    for (int gi = 0; gi < NG; ++gi)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[gi][s][j] = j < 3 ? wsum[gi] : Sums{};
+    if constexpr (NG > 1) {
+      // one loop body (a second one does not hold the sums in registers): a quad step beyond the last is not loaded, what its
+      // operand words hold meets weights of zero
+      Inputs<4> x{};
+      for (uint32_t c = 0; c * 64 < terms; ++c) {
+        load<WIDE>(in, l_off + c * 64, lane, x, terms - c * 64);
+        multiply(x, l_w + c * 256, w_stride, lane, acc);
+      }
+    } else {
+      auto step = [&](auto q, uint32_t c) {
+        Inputs<decltype(q)::value> x;
+        load<WIDE>(in, l_off + c * 64, lane, x, 64);
+        multiply(x, l_w + c * 256, w_stride, lane, acc);
+      };
+      for (uint32_t c = 0; c * 64 < terms; ++c) {
+        if (c * 64 + 64 <= terms) step(std::integral_constant<int, 4>{}, c);
+        else if (c * 64 + 48 <= terms) step(std::integral_constant<int, 3>{}, c);
+        else if (c * 64 + 32 <= terms) step(std::integral_constant<int, 2>{}, c);
+        else step(std::integral_constant<int, 1>{}, c);
+      }
+    }
+#pragma unroll
+    for (int gi = 0; gi < NG; ++gi) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        uint32_t o[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          int64_t x = (int64_t)acc[gi][s][0].v[r] * L.rc;
+          x += (int64_t)acc[gi][s][1].v[r] * L.byte_c[0];
+          x += (int64_t)acc[gi][s][2].v[r] * L.byte_c[1];
+          x += (int64_t)acc[gi][s][3].v[r] * L.byte_c[2];
+          o[s] = canon_p(sredc(x, L.m.p, L.pinv), L.m.p);
+        }
+        out[gi][r].x = o[0]; out[gi][r].y = o[1]; out[gi][r].z = o[2]; out[gi][r].w = o[3];
+      }
+    }
+  }
+  HCNN_HD static void store(const MacArgs& a, uint32_t f, uint32_t g, uint32_t t, uint32_t lane, const U4& u) {
+    if (f < a.F && g < a.G) *reinterpret_cast<U4*>(a.out + ((size_t)f * a.G + g) * ((size_t)2 * a.k * a.n) + t * kTile + lane % 16 * 4) = u;
+  }
+};
+
 template <int GB>
-struct MacMfma {
+struct MacMfma : MacMatrix {
   // (one group: the workgroup's waves take tiles, and eight of them share the staged tables)
   static constexpr int kThreads = GB == 1 ? 512 : 256;
   static constexpr int kPhases = 2;
   static constexpr int kMinWavesPerSimd = 2;     // 64 registers of inputs in flight, 64 of sums
   struct Regs {};
-  static constexpr uint32_t kTile = 64, kStreams = kThreads / 64 / GB;      // coefficients per wave and step; waves on one group
+  static constexpr uint32_t kStreams = kThreads / 64 / GB;      // waves on one group
+  static uint32_t max_steps(const MacArgs&) { return 8; }
   HCNN_HOSTDEV static uint32_t terms(uint32_t T) { return (T + 15) / 16 * 16; }
-  HCNN_HOSTDEV static uint32_t chunks(uint32_t T) { return (T + 63) / 64; }
   // offsets and weights of one group (32 bits hold it for every row that lds_bytes lets through)
   HCNN_HOSTDEV static uint32_t group_words(uint32_t T) { return chunks(T) * (64 + 256); }
   static size_t lds_bytes(size_t T) { return (size_t)GB * ((T + 63) / 64 * (64 + 256)) * 4; }
@@ -774,9 +933,7 @@ struct MacMfma {
     const uint32_t per = a.steps * kStreams, tiles = 2 * a.k * a.n / kTile;
     return (tiles + per - 1) / per;
   }
-  static size_t grid(const MacArgs& a) {
-    return (size_t)kXcds * ((tile_blocks(a) + kXcds - 1) / kXcds) * ((a.G + GB - 1) / GB);
-  }
+  static size_t grid(const MacArgs& a) { return MacMatrix::grid(tile_blocks(a), (a.G + GB - 1) / GB); }
 
   template <int PH>
   HCNN_HD static void phase(const MacArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
@@ -843,118 +1000,149 @@ struct MacMfma {
         for (; bad != 0; --bad) atomic_inc64(a.bad_counter);
     } else {
       const uint32_t wave = wave_uniform((uint32_t)tid / 64), lane = (uint32_t)tid % 64;
-      const uint32_t gi = wave % GB, g = g0 + gi, lg = lane / 16, ln = lane % 16;
+      const uint32_t gi = wave % GB, g = g0 + gi;
       if (g >= a.G) return;
       const uint32_t* l_off = lds + gi * words;
       const uint32_t* l_w = l_off + chunks(a.T) * 64;
-      const size_t ct_words = (size_t)2 * a.k * a.n;
-      const uint32_t n_chunks = chunks(a.T);
-      Sums wsum;                                                      // 128 * sum of the weights, per filter
-      weight_sums(l_w, n_chunks, lane, wsum);
+      Sums wsum[1];                                                      // 128 * sum of the weights, per filter
+      weight_sums(l_w, chunks(a.T), lane, wsum[0]);
       for (uint32_t st = 0; st < a.steps; ++st) {
-        const uint32_t tile = tile0 + st * kStreams + wave / GB;
-        if (tile >= tiles) break;
-        const uint32_t limb = tile / (a.n / kTile) % a.k;
-        const NttLimb L = ldc(a.limbs, limb);
-        const uint32_t pos = tile * kTile + ln * 4;                   // word inside a ciphertext
-        Sums acc[4][4];                                               // [s][byte]
+        const uint32_t t = tile0 + st * kStreams + wave / GB;
+        if (t >= tiles) break;
+        U4 u[1][4];
+        tile<1, true>(a, t, l_off, l_w, 0, T16, lane, wsum, u);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[s][j] = j < 3 ? wsum : Sums{};
-        for (uint32_t c = 0; c < n_chunks; ++c) {
-          if (c * 64 + 64 <= T16) chunk<4>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
-          else if (c * 64 + 48 <= T16) chunk<3>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
-          else if (c * 64 + 32 <= T16) chunk<2>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
-          else chunk<1>(a.in + pos, l_off + c * 64, l_w + c * 256, lane, acc);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const uint32_t f = lg * 4 + r;
-          if (f >= a.F) break;
-          uint32_t o[4];
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            int64_t t = (int64_t)acc[s][0].v[r] * L.rc;
-            t += (int64_t)acc[s][1].v[r] * L.byte_c[0];
-            t += (int64_t)acc[s][2].v[r] * L.byte_c[1];
-            t += (int64_t)acc[s][3].v[r] * L.byte_c[2];
-            o[s] = canon_p(sredc(t, L.m.p, L.pinv), L.m.p);
-          }
-          U4 u;
-          u.x = o[0]; u.y = o[1]; u.z = o[2]; u.w = o[3];
-          *reinterpret_cast<U4*>(a.out + ((size_t)f * a.G + g) * ct_words + pos) = u;
-        }
+        for (uint32_t r = 0; r < 4; ++r) store(a, lane / 16 * 4 + r, g, t, lane, u[0][r]);
       }
     }
   }
+};
 
-#if defined(HCNN_HOSTEMU)
-  // The checker runs lane by lane: every lane forms its own 4 filters x 4 coefficients from the staged tables.
-  struct Sums { int32_t v[4] = {0, 0, 0, 0}; };
-  static int32_t weight(const uint32_t* l_w, uint32_t f, uint32_t t) {          // term t of a chunk
-    return (int8_t)(l_w[((t / 4 % 4 * 16 + f) * 4) + t / 16] >> (8 * (t % 4)));
+// Two neighbouring groups as one, over the union of their rows.  Neighbouring placements of a 3 x 3 kernel share two thirds of their
+// inputs, and the kernel above is bound by the gather, which takes 12 loads here for every 18 there; a term that only one of the
+// two has meets a zero weight of the other in the matrix unit, which has room.
+// The tables are built from the rows as they are, in any order: phases
+//   0  clear         1  a bit per group and input that a term of non-zero weight names      2-4  prefix sums of the union's bits: a slot
+//   per input        5  offsets and weight bytes to their slots; a term that names an input a second time in its row gets a slot of
+//   its own behind them (the slots hold at most the terms of both rows)
+//   6, 7  per tile of 64 coefficients: each of the four waves sums a quarter of the slots; the residues of the four are added through LDS.
+//   6  sums: every wave its own tiles of 64 coefficients, as above
+// Measured, the kernel above / this one, us: 16 filters x 576 terms (3 x 3 padded, 8 x 8 map), 64 groups, n = 8192, k = 10 1502 / 1249;
+// 12 x 144, 100 groups, k = 8 704 / 562; 16 x 25 (5 x 5, stride 2), 144 groups 523 / 439; 16 x 144, 36 groups, n = 16384, k = 16 1273 / 1000; no input
+// shared (2 x 2, stride 2), 16 x 192, 16 groups 356 / 352.
+// Bound: inputs from beyond L2.  The first of these gathers 13 GB (24 above) but misses L2 for 9.4 GB of them (5.2 above, inputs
+// 2.7): 256 waves of a die are at twice as many tiles, 8 MiB of inputs, and drift apart.  Measured and left out, same layer: a wave per quarter of the
+// slots, so that four share a tile (sums added through LDS: 1554, two barriers and four reductions per tile), tiles of 32
+// coefficients (8-byte loads: 1494), one wave per SIMD with two buffers of inputs (1425 - 1527).  A second loop body for the last terms
+// does not hold the sums in registers (100 spilled).
+struct MacPair : MacMatrix {
+  static constexpr int kThreads = 256;
+  static constexpr int kPhases = 7;
+  static constexpr int kMinWavesPerSimd = 2;     // 64 registers of inputs in flight, 128 of sums
+  static constexpr uint32_t kStreams = kThreads / 64;
+  // tiles per wave: long rows take fewer, or neighbouring workgroups drift too far apart to find each other's inputs in L2 (us, 8 / 4 /
+  // 2: 16 x 576, 64 groups 1342 / 1249 / 1294; 16 x 800, 16 groups 379 / 377 / 395; 12 x 144, 100 groups 563 / 600 / 710)
+  static uint32_t max_steps(const MacArgs& a) { return a.T >= 512 ? 4 : 8; }
+  struct Regs {};
+  // LDS: offsets, weights of both groups; a bit per input that either names, each group's claimed ones, prefix sums, partial sums
+  HCNN_HOSTDEV static uint32_t bit_words(uint32_t n_in) { return (n_in + 31) / 32; }
+  static size_t lds_bytes(size_t T, size_t n_in) { return ((2 * T + 63) / 64 * (64 + 512) + (n_in + 31) / 32 * 4 + kThreads + 16 + 4) * 4; }
+  static uint32_t tile_blocks(const MacArgs& a) {
+    const uint32_t per = a.steps * kStreams, tiles = 2 * a.k * a.n / kTile;
+    return (tiles + per - 1) / per;
   }
-  static void weight_sums(const uint32_t* l_w, uint32_t n_chunks, uint32_t lane, Sums& out) {
-    for (int r = 0; r < 4; ++r)
-      for (uint32_t t = 0; t < n_chunks * 64; ++t) out.v[r] += 128 * weight(l_w + t / 64 * 256, lane / 16 * 4 + r, t % 64);
-  }
-  template <int Q>
-  static void chunk(const uint32_t* in, const uint32_t* l_off, const uint32_t* l_w, uint32_t lane, Sums (&acc)[4][4]) {
-    for (uint32_t t = 0; t < 16 * Q; ++t)
-      for (int s = 0; s < 4; ++s) {
-        const uint32_t x = in[(size_t)l_off[t] * 4 + s];
-        for (int r = 0; r < 4; ++r)
-          for (int j = 0; j < 4; ++j)
-            acc[s][j].v[r] += weight(l_w, lane / 16 * 4 + r, t) * ((int32_t)(x >> (8 * j) & 0xff) - (j < 3 ? 128 : 0));
+  static size_t grid(const MacArgs& a) { return MacMatrix::grid(tile_blocks(a), (a.G + 1) / 2); }
+
+  template <int PH>
+  HCNN_HD static void phase(const MacArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
+    const uint32_t g_blocks = (a.G + 1) / 2;
+    const uint32_t xcd = bid % kXcds, local = bid / kXcds;
+    const uint32_t tb = (local / g_blocks) * kXcds + xcd, g0 = local % g_blocks * 2;
+    const uint32_t tiles = 2 * a.k * a.n / kTile, tile0 = tb * a.steps * kStreams;
+    if (tile0 >= tiles) return;                                       // padding blocks (whole block)
+    const uint32_t cap = chunks(2 * a.T), bw = bit_words(a.n_in);
+    uint32_t* l_off = lds;
+    uint32_t* l_w = lds + cap * 64;                                   // [2][cap][256]
+    uint32_t* bits = l_w + cap * 512;
+    uint32_t* claim = bits + bw;                                      // [2][bw]
+    uint32_t* first = claim + 2 * bw;                                 // slots in front of a word's
+    uint32_t* part = first + bw;                                      // [256 + 16]
+    uint32_t* count = part + kThreads + 16;                           // slots of repeated terms
+    const uint32_t per = (bw + kThreads - 1) / kThreads, w0 = (uint32_t)tid * per, w1 = w0 + per < bw ? w0 + per : bw;     // words of this thread
+    const uint32_t wave = wave_uniform((uint32_t)tid / 64), lane = (uint32_t)tid % 64;
+    if constexpr (PH == 0) {
+      for (uint32_t i = tid; i < cap * 576 + 3 * bw; i += kThreads) lds[i] = 0;
+      if (tid == 0) *count = 0;
+    } else if constexpr (PH == 1 || PH == 5) {
+      uint32_t bad = 0;
+      for (uint32_t gi = 0; gi < 2 && g0 + gi < a.G; ++gi) {
+        const uint32_t* idx = a.idx + (size_t)(g0 + gi) * a.T;
+        const int32_t* w = a.w + (size_t)(g0 + gi) * a.F * a.T;
+        for (uint32_t t = tid; t < a.T; t += kThreads) {
+          const uint32_t src = idx[t];
+          int32_t wf[16];
+#pragma unroll
+          for (uint32_t f = 0; f < 16; ++f) wf[f] = w[(size_t)(f < a.F ? f : a.F - 1) * a.T + t];        // (all loads together)
+          uint32_t any = 0;
+#pragma unroll
+          for (uint32_t f = 0; f < 16; ++f) {
+            const bool beyond = (wf[f] > a.w_abs_max) | (wf[f] < -a.w_abs_max);
+            bad += beyond & (f < a.F);
+            if (beyond | (f >= a.F)) wf[f] = 0;
+            any |= (uint32_t)wf[f];
+          }
+          bad += src >= a.n_in;
+          if (src >= a.n_in || any == 0) continue;
+          const uint32_t word = src / 32, bit = 1u << (src % 32);
+          if constexpr (PH == 1) {
+            lds_or(bits + word, bit);
+          } else {
+            uint32_t slot;
+            if (lds_or(claim + gi * bw + word, bit) & bit) slot = part[kThreads + 15] + lds_add(count, 1);
+            else slot = first[word] + (uint32_t)__builtin_popcount(bits[word] & (bit - 1));
+            l_off[slot] = src * (2u * a.k * a.n * 4);                  // in bytes (the host checked that it fits)
+            uint8_t* bytes = reinterpret_cast<uint8_t*>(l_w + (gi * cap + slot / 64) * 256 + slot / 4 % 4 * 64 + slot / 16 % 4) + slot % 4;
+#pragma unroll
+            for (uint32_t f = 0; f < 16; ++f) bytes[f * 16] = (uint8_t)wf[f];
+          }
+        }
       }
-  }
-#elif !defined(__HIP_DEVICE_COMPILE__)
-  // (the host pass of the device build only parses the callers)
-  struct Sums { int32_t v[4] = {0, 0, 0, 0}; };
-  __device__ static void weight_sums(const uint32_t*, uint32_t, uint32_t, Sums&);
-  template <int Q> __device__ static void chunk(const uint32_t*, const uint32_t*, const uint32_t*, uint32_t, Sums (&)[4][4]);
-#else
-  typedef int32_t Vec __attribute__((ext_vector_type(4)));
-  struct Sums { Vec v = {0, 0, 0, 0}; };
-  __device__ __forceinline__ static void weight_sums(const uint32_t* l_w, uint32_t n_chunks, uint32_t lane, Sums& out) {
-    const Vec ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
-    for (uint32_t c = 0; c < n_chunks; ++c)
-      out.v = __builtin_amdgcn_mfma_i32_16x16x64_i8(reinterpret_cast<const Vec*>(l_w + c * 256)[lane], ones, out.v, 0, 0, 0);
-    out.v *= 128;
-  }
-  // Q quad steps of 16 terms; operand words beyond them are zero
-  template <int Q>
-  __device__ __forceinline__ static void chunk(const uint32_t* in, const uint32_t* l_off, const uint32_t* l_w, uint32_t lane,
-                                               Sums (&acc)[4][4]) {
-    typedef const hcnn_word4 __attribute__((address_space(1))) * gptr;
-    const gptr g = (gptr)(const hcnn_word4*)in;
-    hcnn_word4 x[Q][4];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const hcnn_word4 off = *reinterpret_cast<const hcnn_word4*>(l_off + q * 16 + lane / 16 * 4);
-      x[q][0] = g[off.x]; x[q][1] = g[off.y]; x[q][2] = g[off.z]; x[q][3] = g[off.w];
-    }
-    const Vec w = reinterpret_cast<const Vec*>(l_w)[lane];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      Vec b[4] = {};
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const uint32_t lo01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x05010400u);    // a0 b0 a1 b1
-        const uint32_t hi01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x07030602u);    // a2 b2 a3 b3
-        const uint32_t lo23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x05010400u);
-        const uint32_t hi23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x07030602u);
-        b[0][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u);
-        b[1][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u);
-        b[2][q] = (int32_t)(__builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u);
-        b[3][q] = (int32_t)__builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+      if (PH == 1 && tb == 0)
+        for (; bad != 0; --bad) atomic_inc64(a.bad_counter);
+    } else if constexpr (PH == 2) {
+      uint32_t n = 0;
+      for (uint32_t i = w0; i < w1; ++i) n += (uint32_t)__builtin_popcount(bits[i]);
+      part[tid] = n;
+    } else if constexpr (PH == 3) {
+      if (tid < 16) {
+        uint32_t n = 0;
+        for (int i = 0; i < 16 * (tid + 1); ++i) n += part[i];
+        part[kThreads + tid] = n;                                     // up to the end of sixteen threads' words
       }
+    } else if constexpr (PH == 4) {
+      uint32_t n = tid >= 16 ? part[kThreads + tid / 16 - 1] : 0;
+      for (int i = tid / 16 * 16; i < tid; ++i) n += part[i];
+      for (uint32_t i = w0; i < w1; ++i) {
+        first[i] = n;
+        n += (uint32_t)__builtin_popcount(bits[i]);
+      }
+    } else {
+      const uint32_t used = wave_uniform(part[kThreads + 15] + *count);
+      Sums wsum[2];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[s][j].v = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, b[j], acc[s][j].v, 0, 0, 0);
+      for (int gi = 0; gi < 2; ++gi) weight_sums(l_w + gi * cap * 256, chunks(used), lane, wsum[gi]);
+      for (uint32_t st = 0; st < a.steps; ++st) {
+        const uint32_t t = tile0 + st * kStreams + wave;
+        if (t >= tiles) break;
+        U4 u[2][4];
+        tile<2, false>(a, t, l_off, l_w, cap * 256, (used + 15) / 16 * 16, lane, wsum, u);
+#pragma unroll
+        for (uint32_t gi = 0; gi < 2; ++gi)
+#pragma unroll
+          for (uint32_t r = 0; r < 4; ++r) store(a, lane / 16 * 4 + r, g0 + gi, t, lane, u[gi][r]);
+      }
     }
   }
-#endif
 };
 
 // ---------------------------------------------------------------- helpers for KeyGen / Encrypt / Decrypt

@@ -341,6 +341,7 @@ template <int A, int B, int C> struct KernelClass<RelinFused<A, B, C>> { static 
 template <int A, int B> struct KernelClass<TensorFused<A, B>> { static constexpr int id = HCNN_PROF_TENSOR; };
 template <int F, bool S> struct KernelClass<MacKernel<F, S>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <int B> struct KernelClass<MacMfma<B>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
+template <> struct KernelClass<MacPair> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <int F> struct KernelClass<MacKernelDirect<F>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 
 int take_event(hcnn_ctx* c, hcnn_event_t* ev) {
@@ -784,14 +785,15 @@ int mac_launch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
   return run<MacKernelDirect<FT>>(c, grid, 0, a);
 }
 
-template <int GB>
-int mac_mfma_launch(hcnn_ctx* c, const MacArgs& a) {
+template <class K>
+int mac_matrix_launch(hcnn_ctx* c, const MacArgs& a, size_t lds_bytes) {
   // tiles per wave: up to 8, so that staging the group's tables is spread over many coefficients, fewer while the
-  // launch would not hold several rounds of workgroups
+  // launch would not hold several rounds of workgroups or have no tiles for half of the dies (16 filters x 72 terms, 400 groups, n = 1024,
+  // k = 2 151 / 72 us)
   MacArgs b = a;
-  b.steps = 8;
-  while (b.steps > 1 && MacMfma<GB>::grid(b) < 4 * (size_t)c->compute_units) b.steps /= 2;
-  return run<MacMfma<GB>>(c, MacMfma<GB>::grid(b), MacMfma<GB>::lds_bytes(a.T), b);
+  b.steps = K::max_steps(a);
+  while (b.steps > 1 && (K::grid(b) < 4 * (size_t)c->compute_units || K::tile_blocks(b) <= kXcds / 2)) b.steps /= 2;
+  return run<K>(c, K::grid(b), lds_bytes, b);
 }
 
 // Neighbouring groups that a workgroup of the matrix form takes (2 or 1); 0: the call takes the vector form.
@@ -819,10 +821,21 @@ int mac_matrix_groups(const hcnn_ctx* c, size_t grid, const MacArgs& a) {
   return MacMfma<1>::lds_bytes(a.T) <= lds_max ? 1 : 0;
 }
 
+// Does a call that takes two groups per workgroup take MacPair?  Its inputs lie within 4 GiB (byte offsets in 32 bits), two workgroups'
+// tables fit a compute unit, and a launch that fills the chip leaves every wave two tiles (with one the building of the union
+// shows: 16 x 288, 16 groups, n = 4096, k = 4 97 / 99 us).
+bool mac_takes_pairs(const hcnn_ctx* c, const MacArgs& a) {
+  const size_t tiles = (size_t)2 * a.k * a.n / MacPair::kTile;
+  return (uint64_t)a.n_in * 2 * a.k * a.n * 4 <= 0xffffffffull && MacPair::lds_bytes(a.T, a.n_in) <= std::min<size_t>(80 * 1024, c->max_lds) &&
+         ((size_t)a.G + 1) / 2 * tiles >= 2 * MacPair::kStreams * 4 * (size_t)c->compute_units;
+}
+
 int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
   switch (mac_matrix_groups(c, grid, a)) {
-    case 2: return mac_mfma_launch<2>(c, a);
-    case 1: return mac_mfma_launch<1>(c, a);
+    case 2:
+      if (mac_takes_pairs(c, a)) return mac_matrix_launch<MacPair>(c, a, MacPair::lds_bytes(a.T, a.n_in));
+      return mac_matrix_launch<MacMfma<2>>(c, a, MacMfma<2>::lds_bytes(a.T));
+    case 1: return mac_matrix_launch<MacMfma<1>>(c, a, MacMfma<1>::lds_bytes(a.T));
   }
   switch (a.F) {
     case 1: return mac_launch<1>(c, grid, a);

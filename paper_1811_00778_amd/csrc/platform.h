@@ -207,6 +207,9 @@ inline size_t max_lds_bytes() { return 160 * 1024; }
 inline uint32_t compute_unit_count() { return 1; }   // small rounds: the checker's little batches reach every batch-splitting path
 HCNN_HD void atomic_inc64(unsigned long long* p) { *p += 1; }
 HCNN_HD void atomic_max32(uint32_t* p, uint32_t v) { if (v > *p) *p = v; }
+// on LDS words, returning the value before
+HCNN_HD uint32_t lds_or(uint32_t* p, uint32_t v) { const uint32_t o = *p; *p = o | v; return o; }
+HCNN_HD uint32_t lds_add(uint32_t* p, uint32_t v) { const uint32_t o = *p; *p = o + v; return o; }
 // Workgroups of kernel K that one compute unit holds at a time.  The checker has no device to ask: it counts 16
 // wavefronts per compute unit (8 for workgroups of 256 threads, the shape whose register use halves the occupancy
 // on the device), which with its single compute unit gives rounds of a few workgroups.
@@ -308,6 +311,8 @@ inline uint32_t compute_unit_count() {
 }
 HCNN_HD void atomic_inc64(unsigned long long* p) { atomicAdd(p, 1ull); }
 HCNN_HD void atomic_max32(uint32_t* p, uint32_t v) { atomicMax(p, v); }
+HCNN_HD uint32_t lds_or(uint32_t* p, uint32_t v) { return atomicOr(p, v); }
+HCNN_HD uint32_t lds_add(uint32_t* p, uint32_t v) { return atomicAdd(p, v); }
 
 // What separates phase PH from the next one.  A wave's own LDS accesses take effect in order, so that between phases that
 // exchange data within a wave only the compiler has to be kept from reordering them.

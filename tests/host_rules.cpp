@@ -12,6 +12,14 @@ int rule_mac_matrix_groups(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in
   a.k = k; a.n = n; a.n_in = n_in; a.G = G; a.F = F; a.T = T; a.w_abs_max = w_abs_max;
   return mac_matrix_groups(&c, (size_t)G * (2 * k * n / (kEwThreads * kEwVec)), a);
 }
+// Does a call whose workgroups take two groups form the union of their rows?
+int rule_mac_takes_pairs(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in, uint32_t G, uint32_t T) {
+  hcnn_ctx c;
+  c.compute_units = units; c.max_lds = max_lds_bytes();
+  MacArgs a{};
+  a.k = k; a.n = n; a.n_in = n_in; a.G = G; a.T = T;
+  return mac_takes_pairs(&c, a);
+}
 size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
   return groups == 2 ? MacMfma<2>::lds_bytes(T) : MacMfma<1>::lds_bytes(T);
 }

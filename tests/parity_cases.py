@@ -199,6 +199,41 @@ def check_scalar_mac_matrix_form(backend, G, F, T, bound, n=1024, k=2):
     s.ctx.close()
 
 
+def check_scalar_mac_pairs(backend, c_in, side, f, stride, pad, F, base, n=1024, k=2):
+    """The matrix form over the union of two neighbouring groups' rows: convolution rows (overlapping, padded or apart) whose inputs
+    start at `base` of the ciphertexts, one row in descending order, one that names an input three times, one without weights.
+    All weights whole numbers below 16: every residue has one right value."""
+    s = Setup(backend, n, k, with_keys=False)
+    idx, valid, _ = layers.conv_index_table(c_in, side, side, f, f, stride, pad)
+    G, T = idx.shape
+    idx = (idx + base).astype(np.uint32)
+    used = int(idx.max()) + 1
+    cts = np.zeros((used, 2, k, n), dtype=np.uint32)
+    cts[base:] = gen.uniform_residues(s.rng, s.q, n, lead=(used - base, 2))
+    for l, p in enumerate(s.q):
+        cts[base, :, l] = p - 1
+    w = gen.int_weights(s.rng, (G, F, T), 15) * valid[:, None, :].astype(np.int32)
+    w[0, 0], w[G // 2] = 15, 0
+    idx[G - 1], w[G - 1] = idx[G - 1, ::-1].copy(), w[G - 1, :, ::-1].copy()
+    idx[1, 1] = idx[1, T - 1] = idx[1, 0]
+    if used - base >= 2 * T:                    # a pair that shares nothing
+        idx[2], idx[3] = base + np.arange(T), base + T + np.arange(T)
+    out = backend.host(s.ctx.ct_scalar_mac(backend.dev(cts), backend.dev(idx), backend.dev(w), 15))
+    for g in {0, 1, 2, 3, G // 2 - 1, G // 2, G // 2 + 1, G - 2, G - 1}:
+        for o in (0, F // 2, F - 1):
+            assert np.array_equal(out[o, g], fv.scalar_mac(s.octx, cts, idx[g], w[g, o])), ("pairs", g, o)
+    assert s.ctx.bad_inputs() == 0
+    s.ctx.close()
+
+
+PAIR_CASES = [                  # c_in, side, f, stride, pad, F, base, (n, k)
+    (3, 6, 3, 1, 1, 14, 0, (1024, 2)),          # 27 terms; unions of 8 to 36
+    (11, 5, 3, 1, 0, 10, 7, (1024, 2)),         # 99 terms, a last pair with one group
+    (7, 8, 4, 2, 0, 16, 31, (2048, 1)),         # 112 terms; unions of 168: two chunks and a half
+    (16, 5, 2, 1, 0, 16, 0, (1024, 2)),         # 64 terms; unions of 96, and of two rows that share nothing: two whole chunks
+]
+
+
 def check_scalar_mac_matrix_tiles(backend, k, G, F, T, bound, blocks=None, n=1024):
     """The matrix form of the scalar MAC where its waves go through several tiles of coefficients; `blocks`: the
     workgroups that the launch must have.  All coefficients of outputs at the edges and in the middle."""

@@ -132,6 +132,14 @@ def test_scalar_mac_matrix_form_with_several_tiles_per_wave(backend):
     pc.check_scalar_mac_matrix_tiles(backend, 3, 7, 14, 25, 7)
 
 
+@pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,ring", pc.PAIR_CASES)
+def test_scalar_mac_over_the_union_of_two_rows(backend, c_in, side, f, stride, pad, F, base, ring):
+    G, T, n_in = ((side + 2 * pad - f) // stride + 1) ** 2, c_in * f * f, base + c_in * side * side
+    assert emu.rules().rule_mac_matrix_groups(1, *ring, n_in, G, F, T, 15) == 2
+    assert emu.rules().rule_mac_takes_pairs(1, *ring, n_in, G, T)
+    pc.check_scalar_mac_pairs(backend, c_in, side, f, stride, pad, F, base, *ring)
+
+
 def test_square_relin_tiny_config(backend):
     pc.check_square_relin(backend, 1024, 2)
 

@@ -111,6 +111,17 @@ def test_scalar_mac_matrix_form_with_several_tiles_per_wave(backend, G, F, T, bo
     pc.check_scalar_mac_matrix_tiles(backend, 3, G, F, T, bound, blocks)
 
 
+@pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,n,k", [(11, 11, 3, 1, 1, 10, 7, 8192, 1), (7, 24, 4, 2, 0, 16, 31, 2048, 3),
+                                                              (3, 26, 4, 1, 0, 16, 9000, 1024, 2)])
+def test_scalar_mac_over_the_union_of_two_rows(backend, c_in, side, f, stride, pad, F, base, n, k):
+    """Launches that give every wave two tiles of coefficients or more, which is when the union is formed; the last with two
+    words of input bits per thread."""
+    say("scalar_mac over unions c_in=%d side=%d f=%d n=%d" % (c_in, side, f, n))
+    G = ((side + 2 * pad - f) // stride + 1) ** 2
+    assert (G + 1) // 2 * (2 * k * n // 64) >= 32 * 256
+    pc.check_scalar_mac_pairs(backend, c_in, side, f, stride, pad, F, base, n, k)
+
+
 def test_square_relin_tiny_config(backend):
     say("square_relin n=1024 k=2")
     pc.check_square_relin(backend, 1024, 2)
