@@ -459,20 +459,33 @@ struct RelinSharedMac {
             for (int o = 0; o < O; ++o) s[t][o] = sfold(s[t][o], L.rc);
         }
         const uint32_t i1 = i0 + run < a.k ? i0 + run : a.k;
-#pragma unroll 4
-        for (uint32_t i = i0; i < i1; ++i) {
-          int32_t e[O];
+        // The key words of the next digit are on their way while one is multiplied; unrolled by four without the fence, the loop waited
+        // for its loads (n = 16384, k = 16, 225 ciphertexts, us: 700, now 608; two or four digits ahead 624, 636)
+        auto load = [&](uint32_t i, int32_t (&e)[O]) {
+          const uint32_t ii = i < i1 ? i : i1 - 1;
 #pragma unroll
           for (int o = 0; o < O; ++o) {
             const uint32_t oo = o0 + o < outs ? o0 + o : outs - 1;
-            e[o] = (int32_t)ld_at(key + ((size_t)i * outs + oo) * 64, lane * 4);
+            e[o] = (int32_t)ld_at(key + ((size_t)ii * outs + oo) * 64, lane * 4);
           }
+          sched_fence();
+        };
+        auto multiply = [&](uint32_t i, const int32_t (&e)[O]) {
 #pragma unroll
           for (int t = 0; t < CT; ++t) {
             const int32_t d = (int32_t)lds[(t * a.k + i) * 64 + lane];
 #pragma unroll
             for (int o = 0; o < O; ++o) s[t][o] += (int64_t)d * e[o];
           }
+        };
+        int32_t e[2][O];
+        load(i0, e[0]);
+        for (uint32_t i = i0; i < i1; i += 2) {
+          load(i + 1, e[1]);
+          multiply(i, e[0]);
+          if (i + 1 >= i1) break;
+          load(i + 2, e[0]);
+          multiply(i + 1, e[1]);
         }
       }
 #pragma unroll
