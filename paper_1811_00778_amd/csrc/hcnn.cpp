@@ -785,14 +785,33 @@ int mac_launch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
   return run<MacKernelDirect<FT>>(c, grid, 0, a);
 }
 
+// Tiles per wave of a matrix form: up to K::max_steps, so that staging the tables is spread over many coefficients; fewer while the
+// launch would not hold several rounds of workgroups, or while half as many leave the fullest die a sixth less to do.  The dies take whole
+// blocks of tiles: 1 to 4 blocks leave half of them idle, 9 to 12 are two rounds of which the second is half empty, 17 to 20 three (us, twice the
+// tiles / these: 10 filters x 1601 terms, 130 groups, n = 1024, k = 2 1304 / 238; 16 x 1700, 130 groups, n = 8192, k = 3 2585 / 2015, k = 5 3773 /
+// 3218; 16 x 1200, 256 groups, n = 2048, k = 3 861 / 752; 16 x 144, 361 groups 321 / 267; over unions 16 x 288, 196 groups, n = 4096, k = 3 491 /
+// 398, k = 5 (144 groups) 533 / 490; 16 x 576, 256 groups, n = 2048, k = 3 548 / 449).  Less does not pay for staging twice: 25 to 28 blocks, an
+// eighth, over unions 16 x 200, 400 groups, n = 1024, k = 13 538 / 575.
+template <class K>
+uint32_t mac_matrix_steps(const hcnn_ctx* c, const MacArgs& a) {
+  MacArgs b = a;
+  auto fullest_die = [&](uint32_t steps) {
+    b.steps = steps;
+    return (K::tile_blocks(b) + kXcds - 1) / kXcds * steps;
+  };
+  uint32_t steps = K::max_steps(a);
+  while (steps > 1) {
+    const uint32_t half = fullest_die(steps / 2), full = fullest_die(steps);       // (leaves b.steps = steps)
+    if (K::grid(b) >= 4 * (size_t)c->compute_units && 6 * half > 5 * full) break;
+    steps /= 2;
+  }
+  return steps;
+}
+
 template <class K>
 int mac_matrix_launch(hcnn_ctx* c, const MacArgs& a, size_t lds_bytes) {
-  // tiles per wave: up to 8, so that staging the group's tables is spread over many coefficients, fewer while the
-  // launch would not hold several rounds of workgroups or have no tiles for half of the dies (16 filters x 72 terms, 400 groups, n = 1024,
-  // k = 2 151 / 72 us)
   MacArgs b = a;
-  b.steps = K::max_steps(a);
-  while (b.steps > 1 && (K::grid(b) < 4 * (size_t)c->compute_units || K::tile_blocks(b) <= kXcds / 2)) b.steps /= 2;
+  b.steps = mac_matrix_steps<K>(c, a);
   return run<K>(c, K::grid(b), lds_bytes, b);
 }
 

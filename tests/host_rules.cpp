@@ -20,6 +20,14 @@ int rule_mac_takes_pairs(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in, 
   a.k = k; a.n = n; a.n_in = n_in; a.G = G; a.T = T;
   return mac_takes_pairs(&c, a);
 }
+// Tiles per wave of MacMfma<1> (groups = 1), MacMfma<2> (2) or MacPair (0).
+uint32_t rule_mac_matrix_steps(uint32_t groups, uint32_t units, uint32_t n, uint32_t k, uint32_t G, uint32_t T) {
+  hcnn_ctx c;
+  c.compute_units = units;
+  MacArgs a{};
+  a.k = k; a.n = n; a.G = G; a.T = T;
+  return groups == 0 ? mac_matrix_steps<MacPair>(&c, a) : groups == 1 ? mac_matrix_steps<MacMfma<1>>(&c, a) : mac_matrix_steps<MacMfma<2>>(&c, a);
+}
 size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
   return groups == 2 ? MacMfma<2>::lds_bytes(T) : MacMfma<1>::lds_bytes(T);
 }

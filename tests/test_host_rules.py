@@ -47,6 +47,21 @@ def test_form_of_the_scalar_mac(rules, n, k, n_in, G, F, T, form):
     assert rules.rule_mac_matrix_groups(256, n, k, n_in, G, F, T, 128) == 0          # weights beyond a signed byte
 
 
+@pytest.mark.parametrize("groups,n,k,G,T,steps", [
+    (1, 1024, 2, 130, 1601, 1), (1, 1024, 9, 130, 1601, 8),                       # 1 block at eight tiles per wave (2 at four, 4 at two), 5
+    (1, 8192, 3, 130, 1700, 4), (1, 8192, 4, 130, 1700, 8),                       # 12, 16
+    (1, 8192, 5, 130, 1700, 4), (1, 8192, 7, 130, 1700, 8),                       # 20, 28
+    (2, 1024, 2, 600, 25, 4), (2, 1024, 3, 300, 25, 8), (2, 2048, 3, 256, 1200, 4),      # 4, 6, 12
+    (0, 1024, 2, 600, 300, 2), (0, 1024, 3, 600, 144, 4), (0, 2048, 3, 256, 144, 8),     # 2, 3, 6
+    (0, 4096, 3, 256, 288, 4), (0, 4096, 5, 256, 288, 4), (0, 4096, 6, 256, 288, 8), (0, 4096, 7, 256, 288, 8),       # 12, 20, 24, 28
+    (0, 8192, 8, 64, 511, 8), (0, 8192, 8, 64, 512, 4), (0, 2048, 3, 256, 576, 2),       # long rows start from four tiles: 128 blocks, 12
+    (0, 8192, 8, 32, 25, 8), (0, 8192, 8, 30, 25, 4), (0, 8192, 8, 9, 25, 2), (0, 1024, 3, 7, 25, 1),      # too few workgroups
+])
+def test_tiles_per_wave_of_the_matrix_forms(rules, groups, n, k, G, T, steps):
+    """No die waits for a last round that few of them have; blocks of tiles at the number that a form starts from beside the cases."""
+    assert rules.rule_mac_matrix_steps(groups, 256, n, k, G, T) == steps
+
+
 def test_network_plan_puts_16_outputs_into_rows_that_the_matrix_form_takes(rules):
     """The length and the weights up to which the plan relies on the matrix form for rows that the vector form cannot stage."""
     T, weight = network._MATRIX_TERMS, network._MATRIX_WEIGHT
