@@ -841,12 +841,18 @@ int mac_matrix_groups(const hcnn_ctx* c, size_t grid, const MacArgs& a) {
 }
 
 // Does a call that takes two groups per workgroup take MacPair?  Its inputs lie within 4 GiB (byte offsets in 32 bits), two workgroups'
-// tables fit a compute unit, and a launch that fills the chip leaves every wave two tiles (with one the building of the union
-// shows: 16 x 288, 16 groups, n = 4096, k = 4 97 / 99 us).
+// tables fit a compute unit, and every workgroup has enough to do for the union that it builds (us, MacMfma<2> / MacPair, 16 filters):
+// - all the tiles per wave that the form starts from: any row (n = 8192, k = 8: 25 terms (5 x 5, one channel, stride 2), 36 groups 138 / 129;
+//   99 terms, 64 groups 393 / 342);
+// - fewer, but two at least: 576 terms of rows over a wave's tiles, of inputs that are gathered 2.5 times or more, which says that neighbours
+//   share them.  Two tiles: 25 terms, 9 groups, n = 8192, k = 8 30 / 45; n = 4096, k = 6, 25 groups: 99 terms 47 / 64, 198 98 / 102, 288 143 / 138,
+//   400 (5 x 5) 158 / 149.  Four tiles, 49 groups: 99 terms 121 / 127, 144 163 / 148; 180 of stride 2, gathered 2.2 times, 258 / 275.
+// Rows of fewer than 256 terms that share nothing lose up to a sixth here (100 random ones, 288 groups, n = 2048, k = 4 295 / 343), longer
+// ones gain.
 bool mac_takes_pairs(const hcnn_ctx* c, const MacArgs& a) {
-  const size_t tiles = (size_t)2 * a.k * a.n / MacPair::kTile;
-  return (uint64_t)a.n_in * 2 * a.k * a.n * 4 <= 0xffffffffull && MacPair::lds_bytes(a.T, a.n_in) <= std::min<size_t>(80 * 1024, c->max_lds) &&
-         ((size_t)a.G + 1) / 2 * tiles >= 2 * MacPair::kStreams * 4 * (size_t)c->compute_units;
+  if ((uint64_t)a.n_in * 2 * a.k * a.n * 4 > 0xffffffffull || MacPair::lds_bytes(a.T, a.n_in) > std::min<size_t>(80 * 1024, c->max_lds)) return false;
+  const uint32_t steps = mac_matrix_steps<MacPair>(c, a);
+  return steps == MacPair::max_steps(a) || (steps >= 2 && steps * (uint64_t)a.T >= 576 && 2 * (uint64_t)a.G * a.T >= 5 * (uint64_t)a.n_in);
 }
 
 int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {

@@ -223,14 +223,23 @@ def check_scalar_mac_pairs(backend, c_in, side, f, stride, pad, F, base, n=1024,
         for o in (0, F // 2, F - 1):
             assert np.array_equal(out[o, g], fv.scalar_mac(s.octx, cts, idx[g], w[g, o])), ("pairs", g, o)
     assert s.ctx.bad_inputs() == 0
+    # an index beyond the inputs in the first pair, a weight beyond the bound in the last: left out and counted once each
+    bad_idx, bad_w = idx.copy(), w.copy()
+    bad_idx[1, T - 1], bad_w[G - 1, F - 1, 2] = used, 16
+    out = backend.host(s.ctx.ct_scalar_mac(backend.dev(cts), backend.dev(bad_idx), backend.dev(bad_w), 15))
+    for g, o, skip in ((0, 0, ()), (1, 0, (T - 1,)), (1, F - 1, (T - 1,)), (G - 1, 0, ()), (G - 1, F - 1, (2,))):
+        keep = [t for t in range(T) if t not in skip]
+        assert np.array_equal(out[o, g], fv.scalar_mac(s.octx, cts, bad_idx[g, keep], bad_w[g, o, keep])), ("pairs, bad entries", g, o)
+    assert s.ctx.bad_inputs() == 2
     s.ctx.close()
 
 
 PAIR_CASES = [                  # c_in, side, f, stride, pad, F, base, (n, k)
-    (3, 6, 3, 1, 1, 14, 0, (1024, 2)),          # 27 terms; unions of 8 to 36
-    (11, 5, 3, 1, 0, 10, 7, (1024, 2)),         # 99 terms, a last pair with one group
-    (7, 8, 4, 2, 0, 16, 31, (2048, 1)),         # 112 terms; unions of 168: two chunks and a half
-    (16, 5, 2, 1, 0, 16, 0, (1024, 2)),         # 64 terms; unions of 96, and of two rows that share nothing: two whole chunks
+    (3, 6, 3, 1, 1, 14, 0, (1024, 5)),          # 27 terms; unions of 8 to 36
+    (11, 5, 3, 1, 0, 10, 7, (1024, 5)),         # 99 terms, a last pair with one group
+    (7, 8, 4, 2, 0, 16, 31, (2048, 3)),         # 112 terms; unions of 168: two chunks and a half
+    (16, 5, 2, 1, 0, 16, 0, (1024, 5)),         # 64 terms; unions of 96, and of two rows that share nothing: two whole chunks
+    (32, 5, 3, 1, 0, 16, 0, (1024, 2)),         # 288 terms at two tiles per wave
 ]
 
 

@@ -6,6 +6,7 @@ import time
 import numpy as np
 import pytest
 
+import emu
 import parity_cases as pc
 from oracle import fv
 from paper_1811_00778_amd import _capi
@@ -40,6 +41,12 @@ class GpuBackend:
 @pytest.fixture(scope="module")
 def backend():
     return GpuBackend()
+
+
+def device_units():
+    """Compute units of the device: what the library's dispatch rules (emu.rules()) are asked with."""
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
 
 
 @pytest.mark.parametrize("n,k,n_polys,rows", [(1024, 2, 16, None), (2048, 3, 5, 4), (4096, 2, 3, 2),
@@ -111,14 +118,16 @@ def test_scalar_mac_matrix_form_with_several_tiles_per_wave(backend, G, F, T, bo
     pc.check_scalar_mac_matrix_tiles(backend, 3, G, F, T, bound, blocks)
 
 
-@pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,n,k", [(11, 11, 3, 1, 1, 10, 7, 8192, 1), (7, 24, 4, 2, 0, 16, 31, 2048, 3),
-                                                              (3, 26, 4, 1, 0, 16, 9000, 1024, 2)])
-def test_scalar_mac_over_the_union_of_two_rows(backend, c_in, side, f, stride, pad, F, base, n, k):
-    """Launches that give every wave two tiles of coefficients or more, which is when the union is formed; the last with two
-    words of input bits per thread."""
+@pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,n,k,steps", [(11, 17, 3, 1, 1, 10, 7, 8192, 1, 8), (7, 36, 4, 2, 0, 16, 31, 2048, 3, 8),
+                                                                    (18, 26, 4, 1, 0, 16, 9000, 1024, 2, 2), (16, 23, 3, 1, 1, 14, 0, 1024, 3, 4)])
+def test_scalar_mac_over_the_union_of_two_rows(backend, c_in, side, f, stride, pad, F, base, n, k, steps):
+    """Launches with all eight tiles of coefficients per wave and any rows (the second with blocks for six of the dies), with two and four and
+    long rows; the third with three words of input bits per thread."""
     say("scalar_mac over unions c_in=%d side=%d f=%d n=%d" % (c_in, side, f, n))
-    G = ((side + 2 * pad - f) // stride + 1) ** 2
-    assert (G + 1) // 2 * (2 * k * n // 64) >= 32 * 256
+    G, T, n_in = ((side + 2 * pad - f) // stride + 1) ** 2, c_in * f * f, base + c_in * side * side
+    rules, units = emu.rules(), device_units()
+    assert rules.rule_mac_matrix_groups(units, n, k, n_in, G, F, T, 15) == 2 and rules.rule_mac_takes_pairs(units, n, k, n_in, G, T)
+    assert rules.rule_mac_matrix_steps(0, units, n, k, G, T) == steps
     pc.check_scalar_mac_pairs(backend, c_in, side, f, stride, pad, F, base, n, k)
 
 
