@@ -919,15 +919,16 @@ int query_fused_occupancy(hcnn_ctx* c) {
 
 // Encryption and decryption rows: launches of CryptFused
 constexpr size_t kCryptRows = (size_t)1 << 26;     // rows of one launch
+template <class K>
+int crypt_launch(hcnn_ctx* c, const CryptArgs& a) { return run<K>(c, ntt_grouped_grid(a.n_rows, c->k), K::kLdsBytes, a); }
 template <int LOGN, int LOGR>
 int crypt_fused(hcnn_ctx* c, const CryptArgs& a, bool enc) {
-  const size_t grid = ntt_grouped_grid(a.n_rows, c->k), lds = CryptFused<LOGN, LOGR, true>::kLdsBytes;
-  if (enc) return run<CryptFused<LOGN, LOGR, true>>(c, grid, lds, a);
+  if (enc) return crypt_launch<CryptFused<LOGN, LOGR, true>>(c, a);
   if (a.u) {
     // (the largest ring does not hold a second row in its registers)
-    if constexpr (LOGN <= 14) return run<CryptFused<LOGN, LOGR, false, true>>(c, grid, lds, a);
+    if constexpr (LOGN <= 14) return crypt_launch<CryptFused<LOGN, LOGR, false, true>>(c, a);
   }
-  return run<CryptFused<LOGN, LOGR, false>>(c, grid, lds, a);
+  return crypt_launch<CryptFused<LOGN, LOGR, false>>(c, a);
 }
 int crypt_rows(hcnn_ctx* c, CryptArgs a, size_t n_ct, bool enc) {
   a.tw_fwd = c->d_tw_fwd; a.tw_inv = c->d_tw_inv; a.limbs = c->d_limbs; a.cycle = fast_div(c->k);

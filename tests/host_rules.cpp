@@ -32,6 +32,9 @@ size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
   return groups == 2 ? MacMfma<2>::lds_bytes(T) : MacMfma<1>::lds_bytes(T);
 }
 
+// LDS of a workgroup of the decryption that reads the secret's transform (n = 16384).
+size_t rule_decrypt_lds() { return CryptFused<14, 4, false>::kLdsBytes; }
+
 // Smallest batch that takes the shared-basis relinearisation, 0: none.
 size_t rule_shared_basis_min(uint32_t n, uint32_t k, uint32_t k_aux) {
   hcnn_ctx c;

@@ -93,3 +93,7 @@ def test_network_plan_puts_16_outputs_into_rows_that_the_matrix_form_takes(rules
 def test_smallest_batch_of_the_shared_basis_relinearisation(rules, n, k, least):
     assert rules.rule_shared_basis_min(n, k, k + 1) == least
     assert rules.rule_shared_basis_min(n, k, 0) == 0           # no auxiliary primes: no squarings
+
+
+def test_two_decryption_workgroups_of_the_second_largest_ring_fit_a_compute_unit(rules):
+    assert 2 * rules.rule_decrypt_lds() <= 160 * 1024
