@@ -335,7 +335,13 @@ struct NttFwd {
   static constexpr int kPhases = G::kPhases;
   static constexpr bool kDigitIn = kDigitRow || kFused;
   using Regs = std::conditional_t<kFused, RelinRegs<G::R>, std::conditional_t<kRowToRegs, RowRegs<G::R>, std::conditional_t<kToRegs, TensorRegs<G::R>, NoRegs>>>;
-  static constexpr bool wave_sync(int ph) { return ph != 0; }        // one exchange across waves (first_net)
+  // A whole row of n = 32768 in one workgroup (the public transform, in place): the two blocks of a wave lie further apart than the 64 KiB
+  // that an LDS instruction's offset reaches, so that every network has addresses of its own, and the last pass hands its networks out
+  // across the workgroup again, which stores 16 KiB in one piece, behind a second barrier (us, as the other rings / this; the first part
+  // alone, the second: 400 polynomials of 12 limbs 376 / 341; 358, 355; 128 of 18 182 / 174; 176, 181; 10 of 24 19.8 / 18.2; 19.0, 19.0).
+  static constexpr bool kWholeRow = LOGN == 15 && SPLIT == 0 && !kFused && !kToRegs;
+  // one exchange across waves (first_net), the first
+  static constexpr bool wave_sync(int ph) { return ph != 0 && !(kWholeRow && ph == kPhases - 2); }
   // workgroups of a launch over `slots` row positions (a multiple of the die count for the split form)
   static size_t grid(size_t slots) { return SPLIT ? 2 * ((slots + kNttXcds - 1) / kNttXcds * kNttXcds) : slots; }
 
@@ -422,16 +428,19 @@ struct NttFwd {
       }
     };
 
-    const uint32_t nu = first_net<G, PH>(tid), o = nu & (TLAST - 1);
+    constexpr bool kAcross = kWholeRow && kLast;
+    const uint32_t nu = kAcross ? (uint32_t)tid : first_net<G, PH>(tid), o = nu & (TLAST - 1);
     uint32_t i0 = nu >> LOG_TLAST;
     if constexpr (TLAST >= 64) i0 = wave_uniform(i0);               // (scalar twiddle loads)
-    const uint32_t base = i0 * (uint32_t)(NET * TLAST) + o;         // element e of network c at base + net_offset(c) + e*TLAST
-    const uint32_t sbase = lds_swz(base);
+    const uint32_t base0 = i0 * (uint32_t)(NET * TLAST) + o;        // network 0: element e at base0 + e*TLAST
     // node of the twiddle tree over the whole row (network 0): the half's own sub-tree in the split form
-    const uint32_t root = SPLIT ? ((2u + half) << S0) + i0 : (1u << S0) + i0;
+    const uint32_t root0 = SPLIT ? ((2u + half) << S0) + i0 : (1u << S0) + i0;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const uint32_t off = net_offset<G, PH>(c), i_off = off / (NET * TLAST);
+      // network c lies `far` behind network 0: a compile-time distance of every access (off), or part of its own addresses
+      const uint32_t far = kAcross ? (uint32_t)(kThreads * NET * c) : net_offset<G, PH>(c);
+      const uint32_t off = kWholeRow ? 0 : far, i_off = off / (NET * TLAST);
+      const uint32_t base = base0 + (far - off), sbase = lds_swz(base), root = root0 + (far - off) / (NET * TLAST);
       int32_t v[NET];
 #pragma unroll
       for (int e = 0; e < NET; ++e)
