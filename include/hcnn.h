@@ -112,7 +112,8 @@ int hcnn_set_relin_key(hcnn_ctx* ctx, const uint32_t* evk_dev);
  * polys_dev = uint32[n_polys][k][n].  Forward: row l becomes the values at
  * psi_l^(2*brev(j)+1), j = 0..n-1 -- the CRT decomposition of Sec. 2.1.1 applied to a
  * ciphertext prime; products in R_q (Sec. 2.1) become slot-wise products.  Inverse:
- * the exact inverse map (includes the factor n^-1).  Residues in and out are canonical. */
+ * the exact inverse map (includes the factor n^-1).  Residues in and out are canonical (the forward transform
+ * takes any below 2^30; nothing is reduced on the way in, and larger ones may give wrong rows). */
 int hcnn_ntt_fwd(hcnn_ctx* ctx, uint32_t* polys_dev, size_t n_polys);
 int hcnn_ntt_inv(hcnn_ctx* ctx, uint32_t* polys_dev, size_t n_polys);
 

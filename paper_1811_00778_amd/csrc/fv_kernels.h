@@ -549,7 +549,7 @@ struct MacArgs {
   uint32_t n_in, G, F, T;
   int32_t w_abs_max;
   uint32_t chunk;         // terms between reductions of the signed 64-bit accumulators
-  uint32_t steps;         // MacMfma: tiles per wave
+  uint32_t steps;         // matrix forms: tiles per wave
   unsigned long long* bad_counter;
 };
 // Fallback for gather rows too long to stage in LDS: indices and weights are read from global
@@ -763,7 +763,7 @@ struct MacKernel {
 // A term row is padded to a multiple of 16 with zero-weight terms on its last input.
 // Two groups, not four: a last workgroup of 4 is up to three quarters empty, and a launch of few groups stages twice the tables per
 // tile (us, four / two groups per workgroup: 16 filters x 576 terms, 64 groups, n = 8192, k = 10 1676 / 1548; 10 x 576, 9 groups
-// 395 / 347; 10 x 96, 8 groups, n = 4096, k = 4 21 / 15).  Where a launch has enough tiles, MacPair takes the pairs.
+// 395 / 347; 10 x 96, 8 groups, n = 4096, k = 4 21 / 15).  Where its workgroups have enough to do, MacPair takes the pairs.
 // Bound: the gather.  576 terms x 16 filters over 64 groups at n = 8192, k = 10: vector form 3.40 ms, this one 1.50, 24 GB gathered at
 // 32 bytes per clock and compute unit (18 GB of it from L2), vector unit 55 % used, matrix unit 12 %.  Measured and left out: a second register
 // buffer of inputs (spills: a third slower); the waves kept in step by a barrier per chunk (L2 requests halved, no faster: the
@@ -774,7 +774,7 @@ constexpr uint32_t kMfmaMaxSum = 1u << 20;     // T * |w| <= 2^20: sums of weigh
 struct MacMatrix {
   static constexpr uint32_t kTile = 64;
   HCNN_HOSTDEV static uint32_t chunks(uint32_t T) { return (T + 63) / 64; }
-  // the next workgroup's share of the grid: die, tile block and first group
+  // workgroups of a launch: every die takes the same number of tile blocks (the last ones may be empty), each for all blocks of groups
   static size_t grid(uint32_t tile_blocks, size_t group_blocks) { return (size_t)kXcds * ((tile_blocks + kXcds - 1) / kXcds) * group_blocks; }
 
 #if defined(HCNN_HOSTEMU)
@@ -1038,7 +1038,6 @@ struct MacMfma : MacMatrix {
 //   0  clear         1  a bit per group and input that a term of non-zero weight names      2-4  prefix sums of the union's bits: a slot
 //   per input        5  offsets and weight bytes to their slots; a term that names an input a second time in its row gets a slot of
 //   its own behind them (the slots hold at most the terms of both rows)
-//   6, 7  per tile of 64 coefficients: each of the four waves sums a quarter of the slots; the residues of the four are added through LDS.
 //   6  sums: every wave its own tiles of 64 coefficients, as above
 // Measured, the kernel above / this one, us: 16 filters x 576 terms (3 x 3 padded, 8 x 8 map), 64 groups, n = 8192, k = 10 1502 / 1249;
 // 12 x 144, 100 groups, k = 8 704 / 562; 16 x 25 (5 x 5, stride 2), 144 groups 523 / 439; 16 x 144, 36 groups, n = 16384, k = 16 1273 / 1000; no input
@@ -1053,11 +1052,17 @@ struct MacPair : MacMatrix {
   static constexpr int kPhases = 7;
   static constexpr int kMinWavesPerSimd = 2;     // 64 registers of inputs in flight, 128 of sums
   static constexpr uint32_t kStreams = kThreads / 64;
-  // tiles per wave: long rows take fewer, or neighbouring workgroups drift too far apart to find each other's inputs in L2 (us, 8 / 4 /
-  // 2: 16 x 576, 64 groups 1342 / 1249 / 1294; 16 x 800, 16 groups 379 / 377 / 395; 12 x 144, 100 groups 563 / 600 / 710)
+  // Tiles per wave at most.  A union leaves out the terms without weight, so that the workgroups at a map's padded border are done sooner and
+  // neighbours drift apart in L2, the more the longer they run; shorter runs build the union more often.  Long rows take four tiles: us, 8 /
+  // 4 tiles, 16 filters, n = 8192, 3 x 3 padded: 576 terms, 64 groups, k = 10 1339 / 1256, 100 groups, k = 8 1967 / 1815 (with weights on the
+  // padding too 1593 / 1620), 504, 144 groups 2484 / 2305; 5 x 5 padded, 600, 144 groups 2043 / 1824.  Without padding they cost up to 8 %:
+  // 5 x 5, 600 terms, 64 groups 966 / 1046, 1000 of k = 6 +5 %, 2 x 2, 800 of k = 4 +2 %.  Below, the loss is larger than the gain: 3 x 3
+  // padded, 360 terms, 144 groups -7 %, 288, 64 groups 686 / 698; without padding 400 (5 x 5), 64 groups +9 %, 12 x 144, 100 groups 562 / 591;
+  // 25 (5 x 5, stride 2), 144 groups 436 / 500.
   static uint32_t max_steps(const MacArgs& a) { return a.T >= 512 ? 4 : 8; }
   struct Regs {};
-  // LDS: offsets, weights of both groups; a bit per input that either names, each group's claimed ones, prefix sums, partial sums
+  // LDS: offsets, weights of both groups; a bit per input that either names, each group's claimed ones, the first slot of every 32 inputs,
+  // counts of the threads' and of sixteen threads' slots, slots of repeated terms
   HCNN_HOSTDEV static uint32_t bit_words(uint32_t n_in) { return (n_in + 31) / 32; }
   static size_t lds_bytes(size_t T, size_t n_in) { return ((2 * T + 63) / 64 * (64 + 512) + (n_in + 31) / 32 * 4 + kThreads + 16 + 4) * 4; }
   static uint32_t tile_blocks(const MacArgs& a) {

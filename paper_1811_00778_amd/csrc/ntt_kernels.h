@@ -253,8 +253,8 @@ HCNN_GEOM_SPEC(15, 5, false, 4, 5, 4, 4, 2)
 #undef HCNN_GEOM_SPEC
 
 // Which networks a thread takes.  The first forward pass (the last inverse one) joins elements of the whole row; after it
-// no stage reaches beyond 1024 consecutive residues, and those belong to one wave in every other pass: network c of
-// thread `tid` lies in block d of the wave.  So only one exchange of a transform crosses waves and needs a barrier; the
+// no stage reaches beyond 1024 consecutive residues, and those belong to one wave in every other pass (wave w of W takes the
+// blocks of 1024 residues w, w + W, ...).  So only one exchange of a transform crosses waves and needs a barrier; the
 // others go through LDS words that no other wave touches, which are in order by themselves.
 // First network of a thread, and how far behind its elements those of network c lie (a compile-time distance whose bits are
 // clear in every position of the first one: addresses are one register plus a constant).

@@ -356,6 +356,10 @@ def check_transform_ranges(backend, n, t=65537):
     for r in (0, 2, 4):
         for l, m in enumerate(q):
             assert np.array_equal(hat[r, l], fv.ntt_forward(x.reshape(6, len(q), n)[r, l], m)), ("forward", n, r, l)
+    beyond = backend.dev(np.full((1, len(q), n), (1 << 30) - 1, dtype=np.uint32))
+    ctx.ntt_fwd(beyond)
+    for l, m in enumerate(q):
+        assert np.array_equal(backend.host(beyond)[0, l], fv.ntt_forward(np.full(n, ((1 << 30) - 1) % m, dtype=np.uint32), m)), ("2^30 - 1", n, l)
     ctx.ntt_inv(buf)
     assert np.array_equal(backend.host(buf).reshape(x.shape), x), ("round trip", n)
     kr = gen.key_randomness(rng, q, n)
