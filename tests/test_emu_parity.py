@@ -124,12 +124,19 @@ def test_scalar_mac(backend, n, k):
 def test_scalar_mac_matrix_form(backend, G, F, T, bound):
     k = 1 if G == 1 else 2                       # one group: few enough coefficients for this build's single compute unit
     assert emu.rules().rule_mac_matrix_groups(1, 1024, k, pc.MATRIX_INPUTS, G, F, T, bound) == (2 if G in (2, 9) else 1)
+    assert not emu.rules().rule_mac_takes_pairs(1, 1024, k, pc.MATRIX_INPUTS, G, T)          # (MacMfma<2> or <1>, not the union form)
     pc.check_scalar_mac_matrix_form(backend, G, F, T, bound, k=k)
 
 
 def test_scalar_mac_matrix_form_with_several_tiles_per_wave(backend):
-    pc.check_scalar_mac_matrix_tiles(backend, 3, 3, 11, 97, 31)
-    pc.check_scalar_mac_matrix_tiles(backend, 3, 7, 14, 25, 7)
+    for G, F, T, bound, form, steps in ((3, 11, 97, 31, 1, 2), (7, 14, 25, 7, 2, 8)):
+        assert emu.rules().rule_mac_matrix_groups(1, 1024, 3, pc.MATRIX_INPUTS, G, F, T, bound) == form
+        assert not emu.rules().rule_mac_takes_pairs(1, 1024, 3, pc.MATRIX_INPUTS, G, T)
+        assert emu.rules().rule_mac_matrix_steps(form, 1, 1024, 3, G, T) == steps
+        pc.check_scalar_mac_matrix_tiles(backend, 3, G, F, T, bound)
+    # eight tiles per wave, the last block of tiles beyond the ciphertext by half
+    assert emu.rules().rule_mac_matrix_steps(1, 1, 1024, 9, 3, 97) == 8
+    pc.check_scalar_mac_matrix_tiles(backend, 9, 3, 11, 97, 31)
 
 
 @pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,ring", pc.PAIR_CASES)

@@ -112,10 +112,23 @@ def test_scalar_mac_matrix_form(backend, G, F, T, bound):
 
 @pytest.mark.parametrize("G,F,T,bound,blocks", [(130, 10, 1601, 127, 8 * 130), (257, 16, 25, 7, 8 * 129)])
 def test_scalar_mac_matrix_form_with_several_tiles_per_wave(backend, G, F, T, bound, blocks):
-    """Enough groups for eight tiles per wave (`blocks`: workgroups of the launch then; the vector forms have 6 or 8 per
-    group): one group per workgroup with the last wave's tiles beyond the ciphertext, and pairs with the last half empty."""
+    """One group per workgroup at two tiles per wave, and pairs of groups at eight with the last half empty (`blocks`: workgroups of the
+    launch; the vector forms have 6 or 8 per group)."""
     say("scalar_mac matrix form, several tiles per wave G=%d F=%d T=%d" % (G, F, T))
     pc.check_scalar_mac_matrix_tiles(backend, 3, G, F, T, bound, blocks)
+
+
+@pytest.mark.parametrize("k,G,F,T,bound,form,steps", [(9, 130, 10, 1601, 127, 1, 8), (3, 130, 10, 1601, 127, 1, 2), (3, 257, 16, 25, 7, 2, 8),
+                                                      (3, 257, 16, 1200, 7, 2, 8), (6, 257, 16, 1200, 7, 2, 4)])
+def test_scalar_mac_matrix_form_and_tiles_per_wave(backend, k, G, F, T, bound, form, steps):
+    """One group per workgroup (form 1) and two (2), the form and the tiles per wave asked of the rules: the first with the last block of
+    tiles beyond the ciphertext by half, the second without, short rows, and rows too long for the tables of a union, the last at four tiles."""
+    say("scalar_mac matrix form %d k=%d G=%d F=%d T=%d" % (form, k, G, F, T))
+    rules, units = emu.rules(), device_units()
+    assert rules.rule_mac_matrix_groups(units, 1024, k, pc.MATRIX_INPUTS, G, F, T, bound) == form
+    assert form == 1 or not rules.rule_mac_takes_pairs(units, 1024, k, pc.MATRIX_INPUTS, G, T)
+    assert rules.rule_mac_matrix_steps(form, units, 1024, k, G, T) == steps
+    pc.check_scalar_mac_matrix_tiles(backend, k, G, F, T, bound)
 
 
 @pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,n,k,steps", [(11, 17, 3, 1, 1, 10, 7, 8192, 1, 8), (7, 36, 4, 2, 0, 16, 31, 2048, 3, 8),
