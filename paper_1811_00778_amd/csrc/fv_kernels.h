@@ -422,6 +422,11 @@ struct RelinSharedMac {
   static constexpr int kThreads = 512;
   static constexpr int kPhases = 2;
   static constexpr int kMinWavesPerSimd = O <= 4 ? 4 : 2;
+  // The key words of the next digit are on their way while one is multiplied: left to the compiler, the loop waits for its loads (us: n = 32768,
+  // k = 24, 32 ciphertexts 395 / 347; k = 30, 12 374 / 313; n = 16384, k = 16, 225 704 / 683; more digits ahead were slower).  Seven outputs per
+  // wave do without: the second set of words takes the registers beyond 128, and with them the second workgroup of a compute unit (k = 26,
+  // 16 ciphertexts 250 without it, 286 with it; n = 16384, k = 27, 100 780 / 863); eight leave room for one workgroup either way.
+  static constexpr bool kAhead = O != 7;
   static constexpr int CT = 8;
   struct Regs {};
   static size_t lds_bytes(uint32_t k) { return (size_t)CT * k * 64 * 4; }
@@ -459,8 +464,6 @@ struct RelinSharedMac {
             for (int o = 0; o < O; ++o) s[t][o] = sfold(s[t][o], L.rc);
         }
         const uint32_t i1 = i0 + run < a.k ? i0 + run : a.k;
-        // The key words of the next digit are on their way while one is multiplied; unrolled by four without the fence, the loop waited
-        // for its loads (n = 16384, k = 16, 225 ciphertexts, us: 700, now 608; two or four digits ahead 624, 636)
         auto load = [&](uint32_t i, int32_t (&e)[O]) {
           const uint32_t ii = i < i1 ? i : i1 - 1;
 #pragma unroll
@@ -468,7 +471,6 @@ struct RelinSharedMac {
             const uint32_t oo = o0 + o < outs ? o0 + o : outs - 1;
             e[o] = (int32_t)ld_at(key + ((size_t)ii * outs + oo) * 64, lane * 4);
           }
-          sched_fence();
         };
         auto multiply = [&](uint32_t i, const int32_t (&e)[O]) {
 #pragma unroll
@@ -478,14 +480,26 @@ struct RelinSharedMac {
             for (int o = 0; o < O; ++o) s[t][o] += (int64_t)d * e[o];
           }
         };
-        int32_t e[2][O];
-        load(i0, e[0]);
-        for (uint32_t i = i0; i < i1; i += 2) {
-          load(i + 1, e[1]);
-          multiply(i, e[0]);
-          if (i + 1 >= i1) break;
-          load(i + 2, e[0]);
-          multiply(i + 1, e[1]);
+        if constexpr (kAhead) {
+          int32_t e[2][O];
+          load(i0, e[0]);
+          sched_fence();
+          for (uint32_t i = i0; i < i1; i += 2) {
+            load(i + 1, e[1]);
+            sched_fence();
+            multiply(i, e[0]);
+            if (i + 1 >= i1) break;
+            load(i + 2, e[0]);
+            sched_fence();
+            multiply(i + 1, e[1]);
+          }
+        } else {
+#pragma unroll 4
+          for (uint32_t i = i0; i < i1; ++i) {
+            int32_t e[O];
+            load(i, e);
+            multiply(i, e);
+          }
         }
       }
 #pragma unroll

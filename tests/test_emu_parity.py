@@ -35,7 +35,7 @@ class SharedBasisBackend(EmuBackend):
         return emu.EmuContext(n, q, p, t, emu.lib_shared_basis())
 
 
-@pytest.mark.parametrize("n,k,count", [(1024, 2, 3), (1024, 17, 9), (2048, 5, 8), (4096, 3, 2), (16384, 2, 2), (32768, 2, 2)])
+@pytest.mark.parametrize("n,k,count", [(1024, 2, 3), (1024, 17, 9), (1024, 26, 1), (2048, 5, 8), (4096, 3, 2), (16384, 2, 2), (32768, 2, 2)])
 def test_square_relin_shared_basis(n, k, count):
     """The shared-basis relinearisation: both of its last parts, groups of eight ciphertexts and a remainder, bases on
     both sides of its folds; residues at the ends of the transforms' ranges."""

@@ -157,7 +157,7 @@ def test_square_relin_chunked_ragged(backend):
     pc.check_square_relin(backend, 8192, 2, n_random=6, n_genuine=0, relin_order=2)            # key-major order
 
 
-@pytest.mark.parametrize("n,k,cts", [(32768, 12, 17), (32768, 13, 12), (32768, 18, 4), (16384, 16, 65)])
+@pytest.mark.parametrize("n,k,cts", [(32768, 12, 17), (32768, 13, 12), (32768, 18, 4), (32768, 26, 9), (16384, 16, 65)])
 def test_square_relin_shared_basis_equals_the_separate_kernels(backend, n, k, cts):
     """Batches that take the shared-basis relinearisation by default, against the separate kernels (the deep-modulus
     configuration below compares the same path with the oracle)."""
