@@ -4,6 +4,7 @@
 #include "../../include/hcnn.h"
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -840,19 +841,31 @@ int mac_matrix_groups(const hcnn_ctx* c, size_t grid, const MacArgs& a) {
   return MacMfma<1>::lds_bytes(a.T) <= lds_max ? 1 : 0;
 }
 
+// Tiles that a slot of the fullest die sums one after another: rounds of workgroups, two per compute unit, each with all its tiles.
+template <class K>
+double mac_matrix_serial_tiles(const hcnn_ctx* c, const MacArgs& a, uint32_t steps) {
+  MacArgs b = a;
+  b.steps = steps;
+  const size_t slots = std::max<size_t>(2 * (size_t)c->compute_units / kXcds, 1);
+  return (double)((K::grid(b) / kXcds + slots - 1) / slots) * steps * K::kStreams;
+}
+
 // Does a call that takes two groups per workgroup take MacPair?  Its inputs lie within 4 GiB (byte offsets in 32 bits), two workgroups'
-// tables fit a compute unit, and every workgroup has enough to do for the union that it builds (us, MacMfma<2> / MacPair, 16 filters):
-// - all the tiles per wave that the form starts from: any row (n = 8192, k = 8: 25 terms (5 x 5, one channel, stride 2), 36 groups 138 / 129;
-//   99 terms, 64 groups 393 / 342);
-// - fewer, but two at least: 576 terms of rows over a wave's tiles, of inputs that are gathered 2.5 times or more, which says that neighbours
-//   share them.  Two tiles: 25 terms, 9 groups, n = 8192, k = 8 30 / 45; n = 4096, k = 6, 25 groups: 99 terms 47 / 64, 198 98 / 102, 288 143 / 138,
-//   400 (5 x 5) 158 / 149.  Four tiles, 49 groups: 99 terms 121 / 127, 144 163 / 148; 180 of stride 2, gathered 2.2 times, 258 / 275.
-// Rows of fewer than 256 terms that share nothing lose up to a sixth here (100 random ones, 288 groups, n = 2048, k = 4 295 / 343), longer
-// ones gain.
+// tables fit a compute unit, and it is done sooner: the serial tiles of the fullest die times what a tile of two groups costs, counted
+// in terms of one group, staging spread over a wave's tiles.  The union has T (1 + 1 / sqrt(r)) terms where a convolution
+// gathers every input r times (neighbours of an f x f kernel at stride s share f - s of f columns, r = (f / s)^2).  The other constants are fitted to
+// 3000 convolutions in the sizes of all rings, both forms timed: the calls take 3.3 % less than with MacMfma<2> alone, 3.7 % less with the better
+// form of every call.  The largest losses are 12 to 17 % of 80 to 130 us (108 terms, 289 groups, n = 1024, k = 3 78 / 91), stride 2 loses
+// up to 8 %; rows that share nothing lose more (100 random terms, 288 groups, n = 2048, k = 4 295 / 343).  Staging and the ends of tiles weigh
+// most on short rows and small launches, dies without tiles on small rings.  Us, MacMfma<2> / MacPair, 16 filters, refused: 48 terms, 576
+// groups, n = 2048, k = 3 (6 blocks of tiles for 8 dies) 219 / 284; 25, 9 groups, n = 8192, k = 8 30 / 45; taken: 72, 289
+// groups, n = 2048, k = 4 187 / 160; 850, 225 groups, n = 1024, k = 3 376 / 329; 576, 64 groups, n = 8192, k = 10 1502 / 1249.
 bool mac_takes_pairs(const hcnn_ctx* c, const MacArgs& a) {
   if ((uint64_t)a.n_in * 2 * a.k * a.n * 4 > 0xffffffffull || MacPair::lds_bytes(a.T, a.n_in) > std::min<size_t>(80 * 1024, c->max_lds)) return false;
-  const uint32_t steps = mac_matrix_steps<MacPair>(c, a);
-  return steps == MacPair::max_steps(a) || (steps >= 2 && steps * (uint64_t)a.T >= 576 && 2 * (uint64_t)a.G * a.T >= 5 * (uint64_t)a.n_in);
+  const uint32_t sp = mac_matrix_steps<MacPair>(c, a), sm = mac_matrix_steps<MacMfma<2>>(c, a);
+  const double T = a.T, gathered = std::max(1.0, (double)a.G * T / a.n_in);
+  return mac_matrix_serial_tiles<MacPair>(c, a, sp) * (T * (1 + 1 / std::sqrt(gathered)) + 84 + 480.0 / sp) <
+         mac_matrix_serial_tiles<MacMfma<2>>(c, a, sm) * (2 * T + 150 + T / sm);
 }
 
 int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {

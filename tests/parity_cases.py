@@ -235,10 +235,10 @@ def check_scalar_mac_pairs(backend, c_in, side, f, stride, pad, F, base, n=1024,
 
 
 PAIR_CASES = [                  # c_in, side, f, stride, pad, F, base, (n, k)
-    (3, 6, 3, 1, 1, 14, 0, (1024, 5)),          # 27 terms; unions of 8 to 36
-    (11, 5, 3, 1, 0, 10, 7, (1024, 5)),         # 99 terms, a last pair with one group
-    (7, 8, 4, 2, 0, 16, 31, (2048, 3)),         # 112 terms; unions of 168: two chunks and a half
-    (16, 5, 2, 1, 0, 16, 0, (1024, 5)),         # 64 terms; unions of 96, and of two rows that share nothing: two whole chunks
+    (3, 6, 3, 1, 1, 14, 0, (1024, 7)),          # 27 terms; unions of 8 to 36
+    (11, 5, 3, 1, 0, 10, 7, (1024, 3)),         # 99 terms, a last pair with one group
+    (7, 8, 4, 2, 0, 16, 31, (2048, 4)),         # 112 terms; unions of 168: two chunks and a half
+    (16, 5, 2, 1, 0, 16, 0, (1024, 7)),         # 64 terms; unions of 96, and of two rows that share nothing: two whole chunks
     (32, 5, 3, 1, 0, 16, 0, (1024, 2)),         # 288 terms at two tiles per wave
 ]
 

@@ -131,11 +131,11 @@ def test_scalar_mac_matrix_form_and_tiles_per_wave(backend, k, G, F, T, bound, f
     pc.check_scalar_mac_matrix_tiles(backend, k, G, F, T, bound)
 
 
-@pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,n,k,steps", [(11, 17, 3, 1, 1, 10, 7, 8192, 1, 8), (7, 36, 4, 2, 0, 16, 31, 2048, 3, 8),
+@pytest.mark.parametrize("c_in,side,f,stride,pad,F,base,n,k,steps", [(11, 17, 3, 1, 1, 10, 7, 8192, 1, 8), (7, 36, 4, 2, 0, 16, 31, 2048, 4, 8),
                                                                     (18, 26, 4, 1, 0, 16, 9000, 1024, 2, 2), (16, 23, 3, 1, 1, 14, 0, 1024, 3, 4)])
 def test_scalar_mac_over_the_union_of_two_rows(backend, c_in, side, f, stride, pad, F, base, n, k, steps):
-    """Launches with all eight tiles of coefficients per wave and any rows (the second with blocks for six of the dies), with two and four and
-    long rows; the third with three words of input bits per thread."""
+    """Launches with all eight tiles of coefficients per wave and short rows, with two and four and long rows; the third with three words
+    of input bits per thread."""
     say("scalar_mac over unions c_in=%d side=%d f=%d n=%d" % (c_in, side, f, n))
     G, T, n_in = ((side + 2 * pad - f) // stride + 1) ** 2, c_in * f * f, base + c_in * side * side
     rules, units = emu.rules(), device_units()

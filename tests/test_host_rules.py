@@ -66,13 +66,16 @@ def test_tiles_per_wave_of_the_matrix_forms(rules, groups, n, k, G, T, steps):
     (8192, 8, 8191, 64, 576, 1), (8192, 8, 8192, 64, 576, 0),                      # inputs of 4 GiB
     (8192, 8, 1000, 64, 1088, 1), (8192, 8, 1000, 64, 1089, 0),                    # tables of 80 KiB: terms
     (1024, 3, 115552, 1000, 300, 1), (1024, 3, 115553, 1000, 300, 0),              # ... inputs
-    (8192, 8, 81, 32, 25, 1), (8192, 8, 81, 30, 25, 0), (8192, 8, 81, 9, 25, 0),   # short rows: 8, 4, 2 tiles per wave
-    (8192, 8, 900, 30, 143, 0), (8192, 8, 900, 30, 144, 1),                        # longer ones: 4 tiles per wave
-    (8192, 8, 900, 14, 287, 0), (8192, 8, 900, 14, 288, 1), (8192, 8, 900, 6, 1000, 0),      # 2, 1
-    (8192, 8, 1728, 30, 144, 1), (8192, 8, 1729, 30, 144, 0),                      # inputs gathered 2.5 times or less
-    (8192, 8, 4000, 30, 512, 1),                                                   # rows that start from four tiles per wave
-    (4096, 3, 800, 300, 99, 0), (4096, 3, 800, 300, 144, 1), (4096, 6, 800, 100, 99, 1),     # 12 blocks of eight tiles, taken at four; 24
-    (1024, 2, 800, 1000, 287, 0), (1024, 2, 800, 1000, 288, 1),                    # a ring of 64 tiles: two per wave whatever the groups
+    (8192, 8, 81, 31, 25, 1), (8192, 8, 81, 30, 25, 0), (8192, 8, 81, 9, 25, 0),   # short rows: 8, 4, 2 tiles per wave
+    (8192, 8, 81, 32, 25, 1), (8192, 8, 81, 33, 25, 0),                            # 16 and 17 pairs: four and five rounds of workgroups
+    (8192, 8, 900, 30, 95, 0), (8192, 8, 900, 30, 96, 1),                          # longer ones: 4 tiles per wave
+    (8192, 8, 900, 9, 270, 0), (8192, 8, 900, 9, 271, 1), (8192, 8, 900, 14, 238, 0), (8192, 8, 900, 14, 239, 1),      # 2
+    (8192, 8, 2429, 30, 144, 1), (8192, 8, 2430, 30, 144, 0),                      # inputs that fewer rows share
+    (2048, 3, 7500, 576, 142, 0), (2048, 3, 7500, 576, 143, 1), (2048, 4, 9408, 729, 48, 1),     # blocks of tiles for six dies, for all
+    (4096, 3, 800, 300, 59, 0), (4096, 3, 800, 300, 60, 1),                        # 12 blocks of eight tiles, taken at four
+    (1024, 2, 800, 1000, 147, 0), (1024, 2, 800, 1000, 148, 1),                    # a ring of 64 tiles: two per wave whatever the groups
+    (1024, 3, 12274, 225, 370, 0), (1024, 3, 12274, 225, 371, 1),                  # one
+    (8192, 10, 4096, 64, 576, 1),
 ])
 def test_calls_that_form_the_union_of_two_rows(rules, n, k, n_in, G, T, pairs):
     """Both sides of every line, on a device of 256 compute units."""
