@@ -1056,7 +1056,7 @@ struct MacMfma : MacMatrix {
 // Measured, the kernel above / this one, us: 16 filters x 576 terms (3 x 3 padded, 8 x 8 map), 64 groups, n = 8192, k = 10 1502 / 1249;
 // 12 x 144, 100 groups, k = 8 704 / 562; 16 x 25 (5 x 5, stride 2), 144 groups 523 / 439; 16 x 144, 36 groups, n = 16384, k = 16 1273 / 1000; no input
 // shared (2 x 2, stride 2), 16 x 192, 16 groups 356 / 352.
-// Bound: inputs from beyond L2.  The first of these gathers 13 GB (24 above) but misses L2 for 9.4 GB of them (5.2 above, inputs
+// Bound: inputs from beyond L2.  The first of these gathers 13.7 GB (24 above) but misses L2 for 8.5 GB of them (5.2 above, inputs
 // 2.7): 256 waves of a die are at twice as many tiles, 8 MiB of inputs, and drift apart.  Measured and left out, same layer: a wave per quarter of the
 // slots, so that four share a tile (sums added through LDS: 1554, two barriers and four reductions per tile), tiles of 32
 // coefficients (8-byte loads: 1494), one wave per SIMD with two buffers of inputs (1425 - 1527).  A second loop body for the last terms
