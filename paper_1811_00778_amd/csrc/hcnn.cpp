@@ -1351,7 +1351,12 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
         case 11: e = run<TensorFused<11, 4>>(c, cc * L, TensorFused<11, 4>::kLdsBytes, ta, rows); break;
         case 12: e = run<TensorFused<12, 4>>(c, cc * L, TensorFused<12, 4>::kLdsBytes, ta, rows); break;
         case 13: e = run<TensorFused<13, 4>>(c, cc * L, TensorFused<13, 4>::kLdsBytes, ta, rows); break;
-        case 14: e = run<TensorFused<14, 4>>(c, cc * L, TensorFused<14, 4>::kLdsBytes, ta, rows); break;
+        // (1024 threads while every pair has a compute unit of its own, else two workgroups of 512 on each; both are counted in rounds of
+        // one per compute unit.  Us, 1024 / 512 threads: 252 pairs 40 / 46, 504 77 / 71, 756 116 / 108, 7650 1140 / 1030)
+        case 14:
+          e = cc * L <= c->compute_units ? run<TensorFused<14, 4>>(c, cc * L, TensorFused<14, 4>::kLdsBytes, ta, rows)
+                                         : run<TensorFused<14, 5>>(c, cc * L, TensorFused<14, 5>::kLdsBytes, ta, rows);
+          break;
         default: e = HCNN_ERR_N; break;
       }
       if (e) return e;

@@ -918,7 +918,7 @@ template <int LOGN, int LOGR>
 struct TensorFused {
   using G = NttGeom<LOGN, LOGR>;
   static constexpr int P = G::kPhases;
-  static constexpr int kBuffers = LOGN == 14 ? 2 : 1;
+  static constexpr int kBuffers = LOGN == 14 && LOGR == 4 ? 2 : 1;
   static constexpr size_t kLdsBytes = kBuffers * G::kLdsBytes;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = 5 * P;
