@@ -100,8 +100,8 @@ int hcnn_set_stream(hcnn_ctx* ctx, void* hip_stream);
 /* Evaluation key of Sec. 2.1 (KeyGen), one component per RNS prime:
  * evk_dev = uint32[k][2][k][n], evk[i][0] = g_i*s^2 - (a_i*s + e_i), evk[i][1] = a_i,
  * coefficient domain.  The library keeps its own NTT-domain copy, and for n = 32768
- * with 12 or more primes and n = 16384 with 16 or more three further copies modulo
- * auxiliary primes (n = 32768, k = 24: 144 + 432 MiB); a device that cannot spare
+ * with 12 or more primes and n = 16384 with 16 or more another of twice its size modulo
+ * auxiliary primes (n = 32768, k = 24: 144 + 288 MiB); a device that cannot spare
  * those relinearises through the other forms, with the same results.  The caller's
  * buffer is free again once the stream has passed this call. */
 int hcnn_set_relin_key(hcnn_ctx* ctx, const uint32_t* evk_dev);
@@ -269,7 +269,7 @@ enum {
                                    relinearisation kernel for as many ciphertexts as fill whole rounds, the
                                    separate kernels for the rest and for small batches; n = 32768 with 12
                                    primes (batches of 16 or more), 13 (5) or 18 (4) and n = 16384 with 16 or
-                                   more (64) relinearise through three auxiliary primes shared by all digits
+                                   more (64) relinearise through four auxiliary primes shared by all digits
                                    instead; 1 = always the separate kernels; 2 = always the one-kernel forms
                                    where the ring allows them.  Same results either way; for tests and tuning. */
 };
@@ -279,8 +279,8 @@ int hcnn_set_option(hcnn_ctx* ctx, int which, uint64_t value);
  * path (the classes follow the steps of HMult in Sec. 2.1 and the layer sum of Sec. 4.3).
  * `blocks` is the number of workgroups launched: one (polynomial, limb) row of n residues per
  * workgroup for the two NTT classes, 256 coefficient positions (1024 for RELIN_MAC and
- * SCALAR_MAC; their forms for shared auxiliary primes and for many filters launch fewer or
- * more) per workgroup for the others; for RELIN_FUSED it is the number of rows the launch
+ * SCALAR_MAC; RELIN_MAC through shared auxiliary primes counts three per tile of 64 coefficients
+ * and eight ciphertexts, SCALAR_MAC's forms for many filters launch fewer or more) per workgroup for the others; for RELIN_FUSED it is the number of rows the launch
  * transforms (k forward + 2 inverse per workgroup).
  * hcnn_profile_read synchronises the stream; hcnn_reset_stats clears the accumulators. */
 enum {

@@ -404,29 +404,31 @@ struct RelinMacKernel {
 };
 
 // ---------------------------------------------------------------- shared-basis relinearisation
-// The inner product over the integers instead of modulo every q_j: digits and key coefficients are below 2^30, so
-// sum_i D_i * evk[i][b][j] is below k n 2^60 <= 2^80 in magnitude and three auxiliary primes (product above 2^87) hold it.
-// 3k digit transforms and 6k inverse ones replace k^2 and 2k; the inner product has three times the terms:
-//   acc[ct][o][r] = sum_i dig[ct][i][r] * key[i][o][r],   o = (b, j) of 2k, r < 3      (NTT domain, modulo p_r)
+// The inner product over the integers instead of modulo every q_j, for two primes of the ciphertext at a time: digits are below 2^30
+// and key coefficients modulo q_j q_j' within 0.63 * 2^60 of zero (RelinPair), so sum_i D_i * key[i] is below k n 0.63 * 2^90 <= 2^109.4 in magnitude
+// and four auxiliary primes (product above 2^116) hold it.  4k digit transforms and 4k inverse ones replace k^2 and 2k; the
+// inner product has twice the terms:
+//   acc[ct][o][r] = sum_i dig[ct][i][r] * key[i][o][r],   o = (b, pair) of 2 ceil(k/2), r < 4      (NTT domain, modulo p_r)
+// (Every q_j by itself takes three primes, 3k and 6k transforms and three times the terms; three at a time five, 5k + 10k/3 and 5/3.  Us, one q_j / two
+// at a time: n = 16384, k = 16, 225 squarings 3430 / 3195, of it digits 280 / 385, key product 714 / 502, back 818 / 648; n = 32768, k = 24,
+// 32 2107 / 1912: 150 / 200, 361 / 215, back rows and combination 559 / 385.)
 // A workgroup takes 64 coefficients of one r for CT ciphertexts: their digits go to LDS once, its eight waves share out
-// the 2k outputs (O each) and load every key word once for the CT ciphertexts.
+// the outputs (O each) and load every key word once for the CT ciphertexts.
 struct RelinSharedArgs {
-  const uint32_t* dig;   // [n_ct][3][n/64][k][64], signed in [-p, p)
-  const uint32_t* key;   // [3][n/64][k][2k][64], as kNttStoreKey leaves it
-  uint32_t* acc;         // [n_ct][3][n/64][2k][64], signed in (-p, p)
-  const NttLimb* limbs;  // of the three primes
-  uint32_t k, n, n_ct, n_grp;
+  const uint32_t* dig;   // [n_ct][4][n/64][k][64], signed in [-p, p)
+  const uint32_t* key;   // [4][n/64][k][outs][64], as kNttStoreKey leaves it
+  uint32_t* acc;         // [n_ct][4][n/64][outs][64], signed in (-p, p)
+  const NttLimb* limbs;  // of the four primes
+  uint32_t k, outs, n, n_ct, n_grp;
 };
 template <int O>
 struct RelinSharedMac {
   static constexpr int kThreads = 512;
   static constexpr int kPhases = 2;
-  static constexpr int kMinWavesPerSimd = O <= 4 ? 4 : 2;
-  // The key words of the next digit are on their way while one is multiplied: left to the compiler, the loop waits for its loads (us: n = 32768,
-  // k = 24, 32 ciphertexts 395 / 347; k = 30, 12 374 / 313; n = 16384, k = 16, 225 704 / 683; more digits ahead were slower).  Seven outputs per
-  // wave do without: the second set of words takes the registers beyond 128, and with them the second workgroup of a compute unit (k = 26,
-  // 16 ciphertexts 250 without it, 286 with it; n = 16384, k = 27, 100 780 / 863); eight leave room for one workgroup either way.
-  static constexpr bool kAhead = O != 7;
+  static constexpr int kMinWavesPerSimd = 4;
+  // The key words of the next digit are on their way while one is multiplied: left to the compiler, the loop waits for its loads (measured with
+  // three primes, us: n = 32768, k = 24, 32 ciphertexts 395 / 347; n = 16384, k = 16, 225 704 / 683; more digits ahead were slower).
+  // Bound: digits read and sums written (n = 16384, k = 16, 225 ciphertexts 502 us, 397 by bytes; 16 ciphertexts a workgroup 600).
   static constexpr int CT = 8;
   struct Regs {};
   static size_t lds_bytes(uint32_t k) { return (size_t)CT * k * 64 * 4; }
@@ -443,10 +445,10 @@ struct RelinSharedMac {
       for (uint32_t x = tid; x < CT * words; x += kThreads) {
         const uint32_t t = x / words, ct = ct0 + t < a.n_ct ? ct0 + t : a.n_ct - 1;
         reinterpret_cast<U4*>(lds)[x] =
-            *reinterpret_cast<const U4*>(a.dig + (((size_t)ct * 3 + r) * tiles + tile) * a.k * 64 + (x - t * words) * 4);
+            *reinterpret_cast<const U4*>(a.dig + (((size_t)ct * kSharedPrimes + r) * tiles + tile) * a.k * 64 + (x - t * words) * 4);
       }
     } else {
-      const uint32_t o0 = wave * O, outs = 2 * a.k;
+      const uint32_t o0 = wave * O, outs = a.outs;
       if (o0 >= outs) return;
       const NttLimb L = ldc(a.limbs, r);
       const uint32_t* key = a.key + ((size_t)r * tiles + tile) * a.k * outs * 64;
@@ -480,26 +482,17 @@ struct RelinSharedMac {
             for (int o = 0; o < O; ++o) s[t][o] += (int64_t)d * e[o];
           }
         };
-        if constexpr (kAhead) {
-          int32_t e[2][O];
-          load(i0, e[0]);
+        int32_t e[2][O];
+        load(i0, e[0]);
+        sched_fence();
+        for (uint32_t i = i0; i < i1; i += 2) {
+          load(i + 1, e[1]);
           sched_fence();
-          for (uint32_t i = i0; i < i1; i += 2) {
-            load(i + 1, e[1]);
-            sched_fence();
-            multiply(i, e[0]);
-            if (i + 1 >= i1) break;
-            load(i + 2, e[0]);
-            sched_fence();
-            multiply(i + 1, e[1]);
-          }
-        } else {
-#pragma unroll 4
-          for (uint32_t i = i0; i < i1; ++i) {
-            int32_t e[O];
-            load(i, e);
-            multiply(i, e);
-          }
+          multiply(i, e[0]);
+          if (i + 1 >= i1) break;
+          load(i + 2, e[0]);
+          sched_fence();
+          multiply(i + 1, e[1]);
         }
       }
 #pragma unroll
@@ -508,23 +501,23 @@ struct RelinSharedMac {
 #pragma unroll
         for (int o = 0; o < O; ++o)
           if (o0 + o < outs)
-            st_at(a.acc + ((((size_t)(ct0 + t) * 3 + r) * tiles + tile) * outs + o0 + o) * 64, lane * 4,
+            st_at(a.acc + ((((size_t)(ct0 + t) * kSharedPrimes + r) * tiles + tile) * outs + o0 + o) * 64, lane * 4,
                   (uint32_t)sredc(sfold(s[t][o], L.rc), L.m.p, L.pinv));
       }
     }
   }
 };
 
-// Largest ring: the three rows of an output, back in coefficients (kNttBackRow), to modulo q_j, plus y_b.
+// Largest ring: the four rows of an output, back in coefficients (kNttBackRow), to modulo the pair's primes, plus y_b.
 struct RelinCombineArgs {
-  const uint32_t* z;     // [n_ct][2k][3][n], dense rows
+  const uint32_t* z;     // [n_ct][outs][4][n], dense rows
   const uint32_t* y;     // [n_ct][3][k][n]
   uint32_t* out;         // [n_ct][2][k][n]
   const NttLimb* limbs;
   const RelinCrt* crt;   // [k]
   RelinCrtInv crt_inv;
-  FastDiv outputs;       // 2k
-  uint32_t n;
+  FastDiv outputs;       // (b, pair)
+  uint32_t k, n;
 };
 struct RelinCombine {
   static constexpr int kThreads = kEwThreads;
@@ -534,19 +527,31 @@ struct RelinCombine {
   HCNN_HD static void phase(const RelinCombineArgs& a, unsigned bid, int tid, uint32_t*, Regs&) {
     const uint32_t per_row = a.n / (kThreads * kEwVec);
     const uint32_t row = bid / per_row, c = (bid % per_row * kThreads + tid) * kEwVec;
-    const uint32_t ct = quot(row, a.outputs), o = row - ct * a.outputs.d, k = a.outputs.d / 2, j = o >= k ? o - k : o;
-    const NttLimb L = ldc(a.limbs, j);
-    const RelinCrt kc = ldc(a.crt, j);
-    const uint32_t* z = a.z + (size_t)row * 3 * a.n;
-    const U4 z0 = ld4_at(z, c * 4), z1 = ld4_at(z + a.n, c * 4), z2 = ld4_at(z + 2 * (size_t)a.n, c * 4);
-    const U4 y = ld4_at(a.y + ((size_t)ct * 3 * k + o) * a.n, c * 4);
-    auto one = [&](uint32_t x0, uint32_t x1, uint32_t x2, uint32_t add) {
-      return add_mod(relin_crt((int32_t)x0, (int32_t)x1, (int32_t)x2, kc, a.crt_inv, L.m.p, L.pinv), add, L.m.p);
-    };
-    U4 r;
-    r.x = one(z0.x, z1.x, z2.x, y.x); r.y = one(z0.y, z1.y, z2.y, y.y);
-    r.z = one(z0.z, z1.z, z2.z, y.z); r.w = one(z0.w, z1.w, z2.w, y.w);
-    st4_at(a.out + (size_t)row * a.n, c * 4, r);
+    const uint32_t ct = quot(row, a.outputs), o = row - ct * a.outputs.d;
+    const uint32_t b = o >= a.outputs.d / 2 ? 1u : 0u, j0 = 2 * (o - b * (a.outputs.d / 2));
+    const uint32_t* zp = a.z + (size_t)row * kSharedPrimes * a.n;
+    U4 w[kSharedPrimes];
+#pragma unroll
+    for (uint32_t r = 0; r < kSharedPrimes; ++r) w[r] = ld4_at(zp + (size_t)r * a.n, c * 4);
+    int32_t z[4][kSharedPrimes], v[4];
+#pragma unroll
+    for (uint32_t r = 0; r < kSharedPrimes; ++r) {
+      z[0][r] = (int32_t)w[r].x; z[1][r] = (int32_t)w[r].y; z[2][r] = (int32_t)w[r].z; z[3][r] = (int32_t)w[r].w;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = relin_crt_round(z[e], a.crt_inv);
+#pragma unroll
+    for (uint32_t h = 0; h < 2; ++h) {
+      const uint32_t j = j0 + h;
+      if (j >= a.k) break;
+      const NttLimb L = ldc(a.limbs, j);
+      const RelinCrt kc = ldc(a.crt, j);
+      const U4 y = ld4_at(a.y + ((size_t)(ct * 3 + b) * a.k + j) * a.n, c * 4);
+      auto one = [&](int e, uint32_t add) { return add_mod(relin_crt(z[e], v[e], kc, L.m.p, L.pinv), add, L.m.p); };
+      U4 r;
+      r.x = one(0, y.x); r.y = one(1, y.y); r.z = one(2, y.z); r.w = one(3, y.w);
+      st4_at(a.out + ((size_t)(ct * 2 + b) * a.k + j) * a.n, c * 4, r);
+    }
   }
 };
 

@@ -285,7 +285,8 @@ struct hcnn_ctx {
   unsigned long long* d_counters = nullptr;   // [2]
 
   uint32_t* d_evk_hat = nullptr;
-  uint32_t* d_evk_shared = nullptr;  // [3][n/64][k][2k][64], where the shared-basis relinearisation is in use
+  uint32_t* d_evk_shared = nullptr;  // [4][n/64][k][outputs][64], where the shared-basis relinearisation is in use
+  RelinPair* d_pair = nullptr;       // [outputs / 2]
   RelinCrt* d_crt = nullptr;         // [k]
   RelinCrtInv crt_inv{};
   bool has_key = false;
@@ -519,9 +520,9 @@ int build_tables(hcnn_ctx* c) {
     const uint32_t ninv = h_inv(n % p, p);
     nl.inv = inv_root(ninv);
     nl.inv_r = inv_root(h_mulmod(ninv, r32, p));
-    if (l >= c->k && l < c->k + 3 && c->kp >= 3) {
-      const std::vector<uint32_t> three(c->p.begin(), c->p.begin() + 3);
-      nl.inv_z = inv_root(h_mulmod(ninv, h_inv(h_prod_mod(three, (int)(l - c->k), p), p), p));
+    if (l >= c->k && l < c->k + kSharedPrimes && c->kp >= kSharedPrimes) {
+      const std::vector<uint32_t> four(c->p.begin(), c->p.begin() + kSharedPrimes);
+      nl.inv_z = inv_root(h_mulmod(ninv, h_inv(h_prod_mod(four, (int)(l - c->k), p), p), p));
     }
     mods.push_back(nl.m);
     limbs.push_back(nl);
@@ -561,19 +562,27 @@ int build_tables(hcnn_ctx* c) {
     }
     if ((e = upload(c, tab, &c->d_dec_tab))) return e;
   }
-  if (c->kp >= 3) {
-    const std::vector<uint32_t> three(c->p.begin(), c->p.begin() + 3);
+  if (c->kp >= kSharedPrimes) {
+    const std::vector<uint32_t> four(c->p.begin(), c->p.begin() + kSharedPrimes);
     std::vector<RelinCrt> crt;
+    std::vector<RelinPair> pairs;
     for (uint32_t j = 0; j < c->k; ++j) {
-      const uint32_t qj = c->q[j], r32 = (uint32_t)((1ull << 32) % qj);
-      auto centred = [&](uint32_t x) { return x > qj / 2 ? (int32_t)x - (int32_t)qj : (int32_t)x; };
+      const uint32_t qj = c->q[j];
       RelinCrt kc;
-      for (int r = 0; r < 3; ++r) kc.c[r] = centred(h_mulmod(h_prod_mod(three, r, qj), r32, qj));
-      kc.cv = -centred(h_mulmod(h_prod_mod(three, -1, qj), r32, qj));
+      for (uint32_t r = 0; r < kSharedPrimes; ++r) kc.c[r] = h_mont(h_prod_mod(four, (int)r, qj), qj);
+      kc.cv = -h_mont(h_prod_mod(four, -1, qj), qj);
       crt.push_back(kc);
+      if (j % 2 == 0) {
+        const bool alone = j + 1 == c->k;
+        RelinPair pr;
+        pr.inv = alone ? 0 : h_mont(h_inv(qj, c->q[j + 1]), c->q[j + 1]);
+        for (uint32_t r = 0; r < kSharedPrimes; ++r) pr.q[r] = h_mont(qj % four[r], four[r]);
+        pairs.push_back(pr);
+      }
     }
-    for (int r = 0; r < 3; ++r) c->crt_inv.f[r] = 1.0f / (float)three[r];
+    for (uint32_t r = 0; r < kSharedPrimes; ++r) c->crt_inv.f[r] = 1.0f / (float)four[r];
     if ((e = upload(c, crt, &c->d_crt))) return e;
+    if ((e = upload(c, pairs, &c->d_pair))) return e;
   }
   if (c->kp) {
     BConvHost h_ext = make_bconv(c->q, c->p, 1, false);
@@ -645,6 +654,7 @@ struct NttRows {
   uint32_t own_limbs = 0;
   const int32_t* small = nullptr;
   uint32_t digits = 0, tile_words = 0;      // 0 digits: k
+  const RelinPair* pair = nullptr;
 };
 
 template <int LOGN, int LOGR>
@@ -660,6 +670,7 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   a.own_limbs = r.own_limbs;
   a.digits = fast_div(r.digits ? r.digits : c->k);
   a.tile_words = r.tile_words;
+  a.pair = r.pair; a.k = c->k;
   const size_t lds = NttGeom<LOGN, LOGR>::kLdsBytes;
   if (inverse) {
     const size_t g3 = ntt_grouped_grid(r.rows, 3);
@@ -1104,23 +1115,26 @@ int hcnn_set_stream(hcnn_ctx* c, void* hip_stream) {
   return HCNN_OK;
 }
 
-// Smallest internal batch that takes the shared-basis relinearisation, 0: none does.  It saves k^2 - 7k transforms per
-// ciphertext and pays with three times the key products and a base change.  Measured against the other forms, us:
+// Smallest internal batch that takes the shared-basis relinearisation, 0: none does.  It saves k^2 - 6k transforms per
+// ciphertext and pays with twice the key products and a base change.  Measured against the other forms with one q_j at a time (three
+// primes, k^2 - 7k transforms, three times the products), us; two at a time the shared side takes 3 to 12 % of a squaring less, so that the lines lie on
+// the safe side (n = 32768, k = 24, 4 ciphertexts 365 / 491, k = 16, 5 288 / 327, k = 12, 16 471 / 555; n = 16384, k = 16, 64 1037 / 1136):
 // n = 32768  k = 24  32 ciphertexts 2255 / 3103, 6: 546 / 716, 4: 452 / 491, 1: 251 / 193;  k = 18  32: 1693 / 2017, 5: 354 / 386, 4: 303 / 305
 //            k = 16  32: 1411 / 1677, 5: 295 / 327, 4: 272 / 264;  k = 13  32: 1185 / 1230, 8: 334 / 324, 5: 247 / 251, 4: 231 / 206
 //            k = 12  32: 1033 / 1081, 16: 537 / 555, 8: 321 / 298, 4: 200 / 173
 // n = 16384  k = 16  225: 3907 / 4110, 16: 334 / 333;  k = 11  225: 2547 / 2329;  n = 8192  k = 12  700: 3949 / 3592.
 // Not measured: n = 16384 with 12 to 15 primes (left to the other forms) and with more than 16, where those forms have no
 // one-kernel relinearisation and the minimum of 64 is likely too high.
+static uint32_t shared_outputs(uint32_t k) { return 2 * ((k + 1) / 2); }       // (b, pair)
 static size_t shared_basis_min(const hcnn_ctx* c) {
-  if (c->kp < 3) return 0;
+  if (c->kp < kSharedPrimes) return 0;
   if (kSharedAll) return 2;
   if (c->logn == 15) return c->k >= 18 ? 4 : c->k >= 13 ? 5 : c->k == 12 ? 16 : 0;
   return c->logn == 14 && c->k >= 16 ? 64 : 0;
 }
 
-// (Where the shared-basis relinearisation is in use the key is held a second time modulo its three primes, whatever forms the
-// later calls take: 75 us more at n = 16384, k = 16 and 280 at n = 32768, k = 24, once per key.)
+// (Where the shared-basis relinearisation is in use the key is held a second time modulo its four primes, whatever forms the
+// later calls take: 4 k^2 rows beside 2 k^2, once per key.)
 int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
   if (!c || !evk_dev) return HCNN_ERR_NULL;
   if (!aligned16(evk_dev)) return HCNN_ERR_ALIGN;
@@ -1134,14 +1148,17 @@ int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
   int e = ntt_dense(c, evk_dev, c->d_evk_hat, rows, c->k, false, kNttStoreKey);
   if (e) return e;
   if (shared_basis_min(c)) {
+    const size_t shared_rows = (size_t)c->k * shared_outputs(c->k);
     if (!c->d_evk_shared) {
-      // (three times the key's memory: a device that cannot spare it keeps the other forms)
+      // (twice the key's memory: a device that cannot spare it keeps the other forms)
       void* ptr = nullptr;
-      if (dev_malloc(&ptr, rows * 3 * c->n * 4) == 0) c->d_evk_shared = (uint32_t*)ptr;
+      if (dev_malloc(&ptr, shared_rows * kSharedPrimes * c->n * 4) == 0) c->d_evk_shared = (uint32_t*)ptr;
     }
-    for (uint32_t r = 0; r < 3 && c->d_evk_shared; ++r) {
-      NttRows kr{evk_dev, c->d_evk_shared, rows, 1, c->k + r, 1, 0, 1, r};
-      kr.tile_words = (uint32_t)(rows * 64);
+    for (uint32_t r = 0; r < kSharedPrimes && c->d_evk_shared; ++r) {
+      NttRows kr{evk_dev, c->d_evk_shared, shared_rows, 1, c->k + r, 1, 0, 1, r};
+      kr.digits = shared_outputs(c->k);
+      kr.tile_words = (uint32_t)(shared_rows * 64);
+      kr.pair = c->d_pair;
       if ((e = ntt_rows(c, kr, false, kNttKeyTile))) return e;
     }
   }
@@ -1200,38 +1217,40 @@ int hcnn_ct_scalar_mac(hcnn_ctx* c, const uint32_t* in, size_t n_in, const uint3
 static size_t relin_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_units * c->relin_fused_wgs; }
 static size_t tensor_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_units * c->tensor_fused_wgs; }
 
-// Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 3k, acc 6k and (largest ring only) z 6k rows
+// Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 4k, acc 4 and (largest ring only) z 4 rows an output
 // per ciphertext.
 static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* dig, uint32_t* acc, uint32_t* z, uint32_t* out) {
-  const uint32_t k = c->k, n = c->n;
+  const uint32_t k = c->k, n = c->n, outs = shared_outputs(k);
   int e;
-  NttRows r{y, dig, n_ct * k * 3, 3, k, 3, 0, 3, 0};
+  NttRows r{y, dig, n_ct * k * kSharedPrimes, kSharedPrimes, k, kSharedPrimes, 0, kSharedPrimes, 0};
   r.tile_words = k * 64;
   if ((e = ntt_rows(c, r, false, kNttDigitTile))) return e;
-  RelinSharedArgs sa{dig, c->d_evk_shared, acc, c->d_limbs + k, k, n, (uint32_t)n_ct, (uint32_t)((n_ct + 7) / 8)};
-  const size_t grid = (size_t)3 * (n / 64) * sa.n_grp;
-  switch ((2 * k + 7) / 8) {
-#define HCNN_SHARED_MAC(O) case O: e = run<RelinSharedMac<O>>(c, grid, RelinSharedMac<O>::lds_bytes(k), sa); break;
+  RelinSharedArgs sa{dig, c->d_evk_shared, acc, c->d_limbs + k, k, outs, n, (uint32_t)n_ct, (uint32_t)((n_ct + 7) / 8)};
+  const size_t grid = (size_t)kSharedPrimes * (n / 64) * sa.n_grp;
+  // (the profile counts three per tile of 64 coefficients and eight ciphertexts)
+  const size_t units = (size_t)3 * (n / 64) * ((n_ct + 7) / 8);
+  switch ((outs + 7) / 8) {
+#define HCNN_SHARED_MAC(O) case O: e = run<RelinSharedMac<O>>(c, grid, RelinSharedMac<O>::lds_bytes(k), sa, units); break;
 #ifdef HCNN_SHARED_ALL
-    HCNN_SHARED_MAC(1) HCNN_SHARED_MAC(2)
+    HCNN_SHARED_MAC(1)
 #endif
-    HCNN_SHARED_MAC(3) HCNN_SHARED_MAC(4) HCNN_SHARED_MAC(5) HCNN_SHARED_MAC(6) HCNN_SHARED_MAC(7) HCNN_SHARED_MAC(8)
+    HCNN_SHARED_MAC(2) HCNN_SHARED_MAC(3) HCNN_SHARED_MAC(4)
 #undef HCNN_SHARED_MAC
     default: e = HCNN_ERR_ARG; break;
   }
   if (e) return e;
-  const size_t rows = n_ct * 2 * k;
+  const size_t rows = n_ct * outs;
   if (c->logn == 15) {
-    NttRows b{acc, z, rows * 3, 3, k, 3, 0, 3, 0};
-    b.digits = 2 * k;
-    b.tile_words = 2 * k * 64;
+    NttRows b{acc, z, rows * kSharedPrimes, kSharedPrimes, k, kSharedPrimes, 0, kSharedPrimes, 0};
+    b.digits = outs;
+    b.tile_words = outs * 64;
     if ((e = ntt_rows(c, b, true, kNttBackRow))) return e;
-    RelinCombineArgs ca{z, y, out, c->d_limbs, c->d_crt, c->crt_inv, fast_div(2 * k), n};
+    RelinCombineArgs ca{z, y, out, c->d_limbs, c->d_crt, c->crt_inv, fast_div(outs), k, n};
     return run<RelinCombine>(c, rows * (n / (kEwThreads * kEwVec)), 0, ca);
   }
-  RelinBackArgs ba{acc, y, out, c->d_tw_inv, c->d_limbs, c->d_crt, c->crt_inv, k, fast_div(2 * k)};
+  RelinBackArgs ba{acc, y, out, c->d_tw_inv, c->d_limbs, c->d_crt, c->crt_inv, k, fast_div(outs), k};
   switch (c->logn) {
-#define HCNN_BACK(LOGN) case LOGN: return run<RelinBack<LOGN, 4>>(c, rows, RelinBack<LOGN, 4>::kLdsBytes, ba, 3 * rows);
+#define HCNN_BACK(LOGN) case LOGN: return run<RelinBack<LOGN, 4>>(c, rows, RelinBack<LOGN, 4>::kLdsBytes, ba, kSharedPrimes * rows);
 #ifdef HCNN_SHARED_ALL
     HCNN_BACK(10) HCNN_BACK(11) HCNN_BACK(12) HCNN_BACK(13)
 #endif
@@ -1269,7 +1288,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   // (the k workgroups of a ciphertext share a die, for its L2: a round is counted per die)
   const size_t fused_round = fused ? relin_fused_slots(c) / kXcds / k * kXcds : 0;   // ciphertexts per round (0: never)
   const size_t words_main = (ext_rows + 3 * L + 3 * k) * rn;
-  const size_t words_split = ((size_t)k * k + 2 * k) * rn, words_shared = 9 * (size_t)k * rn;
+  const size_t words_split = ((size_t)k * k + 2 * k) * rn, words_shared = (size_t)kSharedPrimes * (k + shared_outputs(k)) * rn;
   const size_t words_per_ct = words_main + (shared_min ? words_shared : words_split);
   size_t C = c->square_chunk;
   // 6 GiB of work buffer (of 288 GB): enough rows per launch at every n
@@ -1332,7 +1351,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     uint32_t* const b_y = y;
     const bool shared = shared_min && cc >= shared_min;
     uint32_t* const b_dig = dig;
-    uint32_t* const b_acc = dig + (shared ? cc * 3 : (cc - nf) * k) * k * rn;
+    uint32_t* const b_acc = dig + (shared ? cc * kSharedPrimes : (cc - nf) * k) * k * rn;
     // 1. centred lift of c0, c1 extended to the auxiliary primes (only the new rows are written);
     // 2. forward NTT over all k + k' limbs, the first k read from the ciphertext itself
     // (n = 32768: the new rows are staged in the array of the tensor, free until step 3, because the two-workgroup
@@ -1380,7 +1399,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     sa.d = b_d; sa.y = b_y; sa.to_p = c->to_p; sa.to_q = c->to_q; sa.tq_inv = c->d_tq_inv; sa.n = n;
     sa.band = c->band; sa.fallback_counter = c->d_counters;
     if ((e = scale_dispatch(c, cc * 3 * bpp, sa))) return e;
-    if (shared) return relin_shared(c, b_y, cc, b_dig, b_acc, b_d, out + c0 * ct_words);     // (the tensor's rows, 3L > 6k, are free by now)
+    if (shared) return relin_shared(c, b_y, cc, b_dig, b_acc, b_d, out + c0 * ct_words);     // (the tensor's rows, 3L > 4k + 4, are free by now)
     // 6-8 in one kernel
     if (nf) {
       RelinFusedArgs fa{b_y, c->d_evk_hat, out + c0 * ct_words, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, (uint32_t)(nf * k), fast_div(k)};

@@ -57,23 +57,33 @@ struct NttLimb {
   int32_t byte_c[3];    // 2^40, 2^48, 2^56 mod p, centred (byte planes of MacMfma)
   InvRoot inv;          // scale = n^-1
   InvRoot inv_r;        // scale = n^-1 * 2^32: the tensor-forming loads leave a factor 2^-32 on every product
-  InvRoot inv_z;        // scale = n^-1 * (R/p)^-1: the three primes of the shared-basis relinearisation (product R)
+  InvRoot inv_z;        // scale = n^-1 * (R/p)^-1: the primes of the shared-basis relinearisation (product R)
 };
-// Shared-basis relinearisation: from the residues of a key product modulo the three primes p_0, p_1, p_2 to modulo q_j.
+// Shared-basis relinearisation: a key product modulo q_j q_j', two neighbouring primes of the ciphertext at a time (pair g: j = 2g,
+// j' = 2g + 1; the last prime of an odd basis alone), is computed modulo the four primes p_0 .. p_3 and taken to modulo q_j and q_j'.
 // With z_r = [x_r (R/p_r)^-1] in (-p_r, p_r) and |X| < R/64, sum_r z_r R/p_r = X + v R with v = round(sum_r z_r/p_r), and
 // that sum lies within 1/64 of an integer: fp32 decides it.
+constexpr uint32_t kSharedPrimes = 4;
 struct RelinCrt {
-  int32_t c[3];         // R/p_r * 2^32 mod q_j, centred
-  int32_t cv;           // -R * 2^32 mod q_j, centred
+  int32_t c[kSharedPrimes];         // R/p_r * 2^32 mod q_j, centred
+  int32_t cv;                       // -R * 2^32 mod q_j, centred
 };
-struct RelinCrtInv { float f[3]; };      // 1 / p_r
-HCNN_HD uint32_t relin_crt(int32_t z0, int32_t z1, int32_t z2, const RelinCrt& k, const RelinCrtInv& f, uint32_t q, uint32_t qinv) {
-  const float v = (float)z0 * f.f[0] + (float)z1 * f.f[1] + (float)z2 * f.f[2];
-  const int32_t iv = (int32_t)(v < 0.0f ? v - 0.5f : v + 0.5f);
-  // |z| < 2^30, |c| <= q/2: the reduced value lies within 3 q/8 + q/2 + 1
-  const int64_t s = (int64_t)z0 * k.c[0] + (int64_t)z1 * k.c[1] + (int64_t)z2 * k.c[2] + (int64_t)iv * k.cv;
+struct RelinCrtInv { float f[kSharedPrimes]; };      // 1 / p_r
+HCNN_HD int32_t relin_crt_round(const int32_t (&z)[kSharedPrimes], const RelinCrtInv& f) {
+  const float v = (float)z[0] * f.f[0] + (float)z[1] * f.f[1] + (float)z[2] * f.f[2] + (float)z[3] * f.f[3];
+  return (int32_t)(v < 0.0f ? v - 0.5f : v + 0.5f);
+}
+HCNN_HD uint32_t relin_crt(const int32_t (&z)[kSharedPrimes], int32_t v, const RelinCrt& k, uint32_t q, uint32_t qinv) {
+  // |z| < p < 2^30 - 2n, |c| <= q/2, |v| <= 4: the sum is below 2^61, and |reduced| <= 4 (p/2^30) q/8 + q/2 + 1 < q
+  const int64_t s = (int64_t)z[0] * k.c[0] + (int64_t)z[1] * k.c[1] + (int64_t)z[2] * k.c[2] + (int64_t)z[3] * k.c[3] + (int64_t)v * k.cv;
   return canon_p(sredc(s, q, qinv), q);
 }
+// A key coefficient modulo q_j q_j' from its residues a, a' is a + q_j t with t = [(a' - a) q_j^-1] modulo q_j', taken in
+// (-5/8 q_j', 5/8 q_j'), and so within 5/8 q_j q_j' + q_j of zero.
+struct RelinPair {
+  int32_t inv;                      // q_j^-1 * 2^32 mod q_j', centred; 0 for the prime without a partner (t = 0)
+  int32_t q[kSharedPrimes];         // q_j * 2^32 mod p_r, centred
+};
 
 // Encryption: floor(q/t) * m as products in front of the last reduction of an inverse transform, m taken in 32-bit words less
 // 2^31 (signed operands); the constants carry the factor 2^32 of the reduction and are centred.
@@ -121,11 +131,12 @@ enum NttIo { kNttPlain = 0, kNttLoadDigit = 1, kNttLoadTensor = 2, kNttStoreAdd 
              // inverse, inside CryptFused: the registers times a key row, plus what Encrypt / Decrypt add
              kNttEncOut0 = 20, kNttEncOut1 = 21, kNttDecOut = 22,
              // inverse, shared-basis relinearisation: row (ct, o, r) with the scaling of inv_z, output signed in (-p, p):
-             // to memory, or (inside RelinBack) to registers and, from the third, through the base change to the output
-             kNttBackRow = 23, kNttBack0 = 24, kNttBack1 = 25, kNttBack2 = 26,
+             // to memory, or (inside RelinBack) to registers and, from the last, through the base change to the outputs
+             kNttBackRow = 23, kNttBack0 = 24, kNttBack1 = 25, kNttBack2 = 26, kNttBack3 = 32,
              // forward, shared-basis relinearisation: digit rows and key rows, stored in tiles of 64 coefficients (the key
              // product reads all rows of a tile: whole kilobytes in one place instead of 256 bytes from every row):
-             // digits [ct][r][tile][i][64], key [r][tile][i][o][64]; the sums lie in [ct][r][tile][o][64]
+             // digits [ct][r][tile][i][64], key [r][tile][i][o][64]; the sums lie in [ct][r][tile][o][64], o = (b, pair).
+             // A key row is made modulo p_r from the rows of the pair's two primes while loading
              kNttDigitTile = 27, kNttKeyTile = 28,
              // decryption of few ciphertexts: the secret's row into registers too, and the product of the two rows
              kNttSecretToRegs = 29, kNttDecOwn = 30,
@@ -145,10 +156,11 @@ struct RelinRegs {
   int64_t s0[R], s1[R];
 };
 struct NoRegs {};
-// Per-thread state of RelinBack: the first two residues of every coefficient.
+// Per-thread state of RelinBack: all but the last residue of every coefficient.
 template <int R>
 struct BackRegs {
-  int32_t z0[R], z1[R];
+  int32_t z[kSharedPrimes - 1][R];
+  int32_t next[R];          // what the thread takes of the next row
 };
 // Per-thread state of CryptFused: one transformed polynomial (and, where it makes its own, the key row).
 template <int R>
@@ -164,10 +176,12 @@ struct NttArgs {
   const NttLimb* limbs;     // [L]
   FastDiv cycle;            // limbs per group of rows
   uint32_t limb_base;
-  FastDiv digits;           // digit loads: digits per ciphertext; kNttBackRow: 2k
+  FastDiv digits;           // digit loads: digits per ciphertext; kNttKeyTile, kNttBackRow: outputs (b, pair)
   uint32_t tile_words;      // tiled rows: words from one tile of a row to its next
-  const RelinCrt* crt;      // kNttBack2: [k]
+  const RelinCrt* crt;      // kNttBack3: [k]
   RelinCrtInv crt_inv;
+  const RelinPair* pair;    // kNttKeyTile: one per pair, and
+  uint32_t k;               // the primes of the ciphertext (kNttBack3 too)
   uint32_t in_group_rows, in_row0;
   uint32_t out_group_rows, out_row0;
   uint32_t n_rows;          // rows of this launch (the grid may be padded, see ntt_logical_row)
@@ -376,6 +390,9 @@ struct NttFwd {
     const int32_t* tn = a.tw.nuw + (size_t)limb * (N / 2);
     const uint32_t* gin;
     uint32_t* gout = nullptr;
+    const uint32_t* gin_pair = nullptr;   // kNttKeyTile: the row of the pair's second prime, and its constants
+    int32_t pair_inv = 0, pair_q = 0;
+    uint32_t pair_p = 0, pair_pinv = 0;
     const uint32_t* key0 = nullptr;       // kNttFusedMac: evk^[iter][0][j]; component 1 lies k rows further
     if constexpr (kFused) {
       const uint32_t kk = a.cycle.d;                   // rows are (ct, j)
@@ -390,6 +407,15 @@ struct NttFwd {
       gin = a.in + ((size_t)ct * 3 * kk + 2 * kk + (group - ct * kk)) * N;
     } else if constexpr (kSmallIn) {
       gin = reinterpret_cast<const uint32_t*>(a.small) + (IO == kNttSecretToRegs ? 0 : (size_t)group * N);
+    } else if constexpr (IO == kNttKeyTile) {
+      const uint32_t outs = a.digits.d, i = quot(group, a.digits), o = group - i * outs;          // group = (digit, b, pair)
+      const uint32_t b = o >= outs / 2 ? 1u : 0u, j0 = 2 * (o - b * (outs / 2)), j1 = j0 + 1 < a.k ? j0 + 1 : j0;
+      gin = a.in + ((size_t)(i * 2 + b) * a.k + j0) * N;
+      gin_pair = gin + (size_t)(j1 - j0) * N;
+      if constexpr (kFirst) {
+        const NttLimb Q = ldc(a.limbs, j1);
+        pair_inv = ldc(&a.pair[j0 / 2].inv, 0); pair_q = ldc(a.pair[j0 / 2].q, a.out_row0); pair_p = Q.m.p; pair_pinv = Q.pinv;
+      }
     } else if constexpr (IO == kNttCtToRegs) {
       gin = a.in + ((size_t)(group * 2 + 1) * a.cycle.d + within) * N;
     } else if constexpr (kToRegs) {
@@ -407,7 +433,7 @@ struct NttFwd {
     }
     if constexpr (IO == kNttDigitTile) {
       const uint32_t kk = a.digits.d, ct = quot(group, a.digits);
-      gout = a.out + (size_t)(ct * 3 + within) * (N / 64) * a.tile_words + (group - ct * kk) * 64;
+      gout = a.out + (size_t)(ct * kSharedPrimes + within) * (N / 64) * a.tile_words + (group - ct * kk) * 64;
     } else if constexpr (IO == kNttKeyTile) {
       gout = a.out + (size_t)a.out_row0 * (N / 64) * a.tile_words + (size_t)group * 64;
     } else if constexpr (!kFused && !kToRegs)
@@ -418,10 +444,20 @@ struct NttFwd {
     // (any 32 bits) are reduced on the X side; the T side and the radix-4 levels take them as they are.
     // split form: this half's output of the pair (i, i + n/2), on the way in.
     auto root_x = [&](int32_t x) -> int32_t { return kSmallIn ? sredc((int64_t)x * L.rc, p, L.pinv) : x; };
-    auto load_first = [&](uint32_t at, uint32_t e_off) -> int32_t {      // element at + e_off, e_off uniform
+    auto load_word = [&](uint32_t at, uint32_t e_off) -> int32_t {       // element at + e_off, e_off uniform
       const int32_t x = (int32_t)ld_at(gin + e_off, at * 4);
+      if constexpr (kFirst && IO == kNttKeyTile) {
+        // |x rc| and |t q| are below 2^59: the value lies in (-p, p)
+        const int32_t t = sredc((int64_t)((int32_t)ld_at(gin_pair + e_off, at * 4) - x) * pair_inv, pair_p, pair_pinv);
+        return sredc((int64_t)x * L.rc + (int64_t)t * pair_q, p, L.pinv);
+      } else {
+        return x;
+      }
+    };
+    auto load_first = [&](uint32_t at, uint32_t e_off) -> int32_t {
+      const int32_t x = load_word(at, e_off);
       if constexpr (SPLIT) {
-        const int32_t X = root_x(x), T = sredc((int64_t)(int32_t)ld_at(gin + e_off + N / 2, at * 4) * L.w1, p, L.pinv);
+        const int32_t X = root_x(x), T = sredc((int64_t)load_word(at, e_off + N / 2) * L.w1, p, L.pinv);
         return half ? X - T : X + T;
       } else {
         return x;
@@ -530,7 +566,7 @@ struct NttInv {
   static_assert(IO == kNttPlain || IO == kNttLoadTensor || IO == kNttStoreAdd || IO == kNttLoadTensorMul ||
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
                 IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut || IO == kNttDecOwn || IO == kNttBackRow || IO == kNttBack0 ||
-                IO == kNttBack1 || IO == kNttBack2, "inverse NTT io mode");
+                IO == kNttBack1 || IO == kNttBack2 || IO == kNttBack3, "inverse NTT io mode");
   using G = NttGeom<LOGN, LOGR>;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
@@ -540,7 +576,8 @@ struct NttInv {
   static constexpr bool wave_sync(int ph) { return ph != kPhases - 2; }        // one exchange across waves (first_net)
   static constexpr bool kFromRegs = IO == kNttFromRegs0 || IO == kNttFromRegs1;
   static constexpr bool kTensorRegs = IO == kNttTensorRegs0 || IO == kNttTensorRegs1 || IO == kNttTensorRegs2;
-  static constexpr bool kBack = IO == kNttBack0 || IO == kNttBack1 || IO == kNttBack2;
+  static constexpr bool kBack = IO == kNttBack0 || IO == kNttBack1 || IO == kNttBack2 || IO == kNttBack3;
+  static constexpr int kBackRow = IO == kNttBack3 ? 3 : IO - kNttBack0;
   static constexpr bool kEncOut = IO == kNttEncOut0 || IO == kNttEncOut1, kDecOut = IO == kNttDecOut || IO == kNttDecOwn, kKeyRegs = kEncOut || kDecOut;
   using Regs = std::conditional_t<kFromRegs, RelinRegs<G::R>, std::conditional_t<kTensorRegs, TensorRegs<G::R>,
                std::conditional_t<kKeyRegs, RowRegs<G::R>, std::conditional_t<kBack, BackRegs<G::R>, NoRegs>>>>;
@@ -574,7 +611,7 @@ struct NttInv {
     const uint32_t unit_ct = kBack ? quot(bid, a.digits) : 0, unit_o = bid - unit_ct * a.digits.d;     // RelinBack: (ct, o)
     if constexpr (kBack) {
       tid = opaque(tid);
-      bid = bid * 3 + (IO - kNttBack0);                // row (ct, o, r)
+      bid = bid * kSharedPrimes + kBackRow;            // row (ct, o, r)
     }
     const uint32_t group = quot(bid, a.cycle), within = bid - group * a.cycle.d, limb = a.limb_base + within;
     const NttLimb L = ldc(a.limbs, limb);
@@ -604,7 +641,7 @@ struct NttInv {
       gin = a.in + ((IO == kNttEncOut1 ? (size_t)a.cycle.d : 0) + within) * N;      // key row of this limb
     } else if constexpr (IO == kNttBackRow || kBack) {
       const uint32_t ct = kBack ? unit_ct : quot(group, a.digits), o = group - ct * a.digits.d;
-      gin = a.in + (size_t)(ct * 3 + within) * (N / 64) * a.tile_words + o * 64;
+      gin = a.in + (size_t)(ct * kSharedPrimes + within) * (N / 64) * a.tile_words + o * 64;
     } else if constexpr (!kFromRegs && !kTensorRegs && !kKeyRegs) {
       gin = a.in + ((size_t)group * a.in_group_rows + a.in_row0 + within) * N;
     }
@@ -620,9 +657,10 @@ struct NttInv {
     } else if constexpr (kEncOut) {
       gout = a.out + ((size_t)(group * 2 + (IO == kNttEncOut1 ? 1 : 0)) * a.cycle.d + within) * N;
     } else if constexpr (kBack) {
-      // o = (b, j), 2k = a.digits of them
-      gout = a.out + ((size_t)unit_ct * a.digits.d + unit_o) * N;
-      gaux = a.aux + ((size_t)unit_ct * (a.digits.d / 2 * 3) + unit_o) * N;            // y row (ct, b, j)
+      // o = (b, pair), a.digits of them: result and y row (ct, b, j) of the pair's first prime
+      const uint32_t b = unit_o >= a.digits.d / 2 ? 1u : 0u, j = 2 * (unit_o - b * (a.digits.d / 2));
+      gout = a.out + ((size_t)(unit_ct * 2 + b) * a.k + j) * N;
+      gaux = a.aux + ((size_t)(unit_ct * 3 + b) * a.k + j) * N;
     } else if constexpr (kDecOut) {
       gout = a.out + (size_t)bid * N;
       gaux = a.aux + ((size_t)group * 2 * a.cycle.d + within) * N;                   // c0
@@ -640,6 +678,20 @@ struct NttInv {
     const uint32_t base = i0 * (uint32_t)(NET * TLAST) + o;
     const uint32_t sbase = lds_swz(base);
     const uint32_t root = (1u << S0) + i0;
+    if constexpr (kLast && kBack && IO != kNttBack3) {
+      // the next row's words are on their way during this row's last pass
+      constexpr int F = kPhases - 1, NET_F = 1 << G::ns(F);
+      const uint32_t first = first_net<G, F>(tid) * NET_F;
+      const uint32_t* next = gin + (size_t)(N / 64) * a.tile_words;
+#pragma unroll
+      for (int c = 0; c < R / NET_F; ++c) {
+        int32_t w[NET_F];
+        load_row<NET_F>(w, next + (size_t)(net_offset<G, F>(c) / 64) * a.tile_words, (first >> 6) * a.tile_words + (first & 63u));
+#pragma unroll
+        for (int e = 0; e < NET_F; ++e) regs.next[c * NET_F + e] = w[e];
+      }
+      sched_fence();
+    }
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       const uint32_t off = net_offset<G, PH>(c), i_off = off / (NET * TLAST);
@@ -671,6 +723,9 @@ struct NttInv {
         load_row<NET>(y, gin + off, base);
 #pragma unroll
         for (int e = 0; e < NET; ++e) v[e] = sredc((int64_t)untraced(regs.c0[c * NET + e]) * y[e], p, L.pinv);
+      } else if constexpr (kFirst && kBack && IO != kNttBack0) {
+#pragma unroll
+        for (int e = 0; e < NET; ++e) v[e] = regs.next[c * NET + e];
       } else if constexpr (kFirst && (IO == kNttBackRow || kBack)) {
         load_row<NET>(v, gin + (size_t)(off / 64) * a.tile_words, (base >> 6) * a.tile_words + (base & 63u));
       } else if constexpr (kFirst) {
@@ -735,23 +790,41 @@ struct NttInv {
           v[x + NET / 2] = sredc((int64_t)(X - Y) * top.w, p, L.pinv);
         }
       }
-      if constexpr (kLast && (IO == kNttBack0 || IO == kNttBack1)) {
+      if constexpr (kLast && kBack && IO != kNttBack3) {
 #pragma unroll
-        for (int e = 0; e < NET; ++e) {
-          if constexpr (IO == kNttBack0) regs.z0[c * NET + e] = v[e];
-          else                           regs.z1[c * NET + e] = v[e];
+        for (int e = 0; e < NET; ++e) regs.z[kBackRow][c * NET + e] = opaque(v[e]);      // (in a register of its own, not half of a 64-bit one)
+      } else if constexpr (kLast && IO == kNttBack3) {
+        const uint32_t j0 = 2 * (unit_o >= a.digits.d / 2 ? unit_o - a.digits.d / 2 : unit_o);
+        const bool pair = j0 + 1 < a.k;
+        const uint32_t j1 = pair ? j0 + 1 : j0;
+        const uint32_t p0 = ldc(a.limbs, j0).m.p, p1 = ldc(a.limbs, j1).m.p, pinv0 = ldc(a.limbs, j0).pinv, pinv1 = ldc(a.limbs, j1).pinv;
+        const RelinCrt k0 = ldc(a.crt, j0), k1 = ldc(a.crt, j1);
+        const uint32_t second = pair ? N : 0;
+        // four elements at a time: the rest of the registers holds residues
+        constexpr int CH = 4;
+#pragma unroll
+        for (int e0 = 0; e0 < NET; e0 += CH) {
+          uint32_t y0[CH], y1[CH];
+#pragma unroll
+          for (int e = 0; e < CH; ++e) {
+            y0[e] = ld_at(gaux + off + (e0 + e) * TLAST, base * 4);
+            y1[e] = ld_at(gaux + second + off + (e0 + e) * TLAST, base * 4);
+          }
+#pragma unroll
+          for (int e = 0; e < CH; ++e) {
+            const int32_t z[kSharedPrimes] = {regs.z[0][c * NET + e0 + e], regs.z[1][c * NET + e0 + e],
+                                              regs.z[2][c * NET + e0 + e], v[e0 + e]};
+            const int32_t round = relin_crt_round(z, a.crt_inv);
+            y0[e] = add_mod(relin_crt(z, round, k0, p0, pinv0), y0[e], p0);
+            y1[e] = add_mod(relin_crt(z, round, k1, p1, pinv1), y1[e], p1);
+          }
+#pragma unroll
+          for (int e = 0; e < CH; ++e) {
+            st_at(gout + off + (e0 + e) * TLAST, base * 4, y0[e]);
+            if (pair) st_at(gout + N + off + (e0 + e) * TLAST, base * 4, y1[e]);
+          }
+          sched_fence();
         }
-      } else if constexpr (kLast && IO == kNttBack2) {
-        const uint32_t j = unit_o >= a.digits.d / 2 ? unit_o - a.digits.d / 2 : unit_o;
-        const NttLimb Q = ldc(a.limbs, j);
-        const RelinCrt kc = ldc(a.crt, j);
-        uint32_t addend[NET];
-#pragma unroll
-        for (int e = 0; e < NET; ++e) addend[e] = ld_at(gaux + off + e * TLAST, base * 4);
-#pragma unroll
-        for (int e = 0; e < NET; ++e)
-          st_at(gout + off + e * TLAST, base * 4,
-                add_mod(relin_crt(regs.z0[c * NET + e], regs.z1[c * NET + e], v[e], kc, a.crt_inv, Q.m.p, Q.pinv), addend[e], Q.m.p));
       } else if constexpr (kLast && IO == kNttBackRow) {
 #pragma unroll
         for (int e = 0; e < NET; ++e) st_at(gout + off + e * TLAST, base * 4, (uint32_t)v[e]);
@@ -945,19 +1018,22 @@ struct TensorFused {
 };
 
 // ------------------------------------------------------------------------- shared-basis relinearisation, last part
-// Workgroup (ct, o = (b, j)): the three rows acc[ct][o][r] back to coefficients, from modulo p_0, p_1, p_2 to modulo q_j,
-// plus y_b: one read of the sums, one write of the result.  (The largest ring does not hold two rows beside the one in
+// Workgroup (ct, o = (b, pair)): the four rows acc[ct][o][r] back to coefficients, from modulo p_0 .. p_3 to modulo the pair's two
+// primes, plus y_b: one read of the sums, one write of the result.  (The largest ring does not hold three rows beside the one in
 // work in its registers: kNttBackRow and RelinCombine.)
+// Bound: one 1024-thread workgroup per compute unit, in step with itself.  A row's words are loaded during the last pass of the row before
+// (n = 16384, k = 16, 225 ciphertexts 690 -> 648 us; 397 by bytes).
 struct RelinBackArgs {
-  const uint32_t* acc;      // [n_ct][3][n/64][2k][64]
+  const uint32_t* acc;      // [n_ct][4][n/64][outputs][64]
   const uint32_t* y;        // [n_ct][3][k][n]
   uint32_t* out;            // [n_ct][2][k][n]
   TwTable tw_inv;
   const NttLimb* limbs;
   const RelinCrt* crt;
   RelinCrtInv crt_inv;
-  uint32_t limb_base;       // of the three primes
-  FastDiv outputs;          // 2k
+  uint32_t limb_base;       // of the four primes
+  FastDiv outputs;          // (b, pair)
+  uint32_t k;
 };
 template <int LOGN, int LOGR>
 struct RelinBack {
@@ -966,7 +1042,7 @@ struct RelinBack {
   static constexpr int kBuffers = 2;
   static constexpr size_t kLdsBytes = kBuffers * G::kLdsBytes;
   static constexpr int kThreads = G::kThreads;
-  static constexpr int kPhases = 3 * P;
+  static constexpr int kPhases = (int)kSharedPrimes * P;
   static constexpr int kMinWavesPerSimd = 4;
   using Regs = BackRegs<G::R>;
   static constexpr bool wave_sync(int ph) { return seq_wave_sync(ph, P, 0, kBuffers); }
@@ -975,11 +1051,12 @@ struct RelinBack {
     lds = seq_buffer<G, kBuffers>(lds, PH / P);
     NttArgs na{};
     na.in = a.acc; na.aux = a.y; na.out = a.out; na.tw = a.tw_inv; na.limbs = a.limbs; na.limb_base = a.limb_base;
-    na.cycle = FastDiv{3, 0x55555555u}; na.tile_words = a.outputs.d * 64;
-    na.digits = a.outputs; na.crt = a.crt; na.crt_inv = a.crt_inv;
+    na.cycle = FastDiv{kSharedPrimes, 0x40000000u}; na.tile_words = a.outputs.d * 64;
+    na.digits = a.outputs; na.crt = a.crt; na.crt_inv = a.crt_inv; na.k = a.k;
     if constexpr (PH < P) NttInv<LOGN, LOGR, kNttBack0>::template phase<PH>(na, bid, tid, lds, regs);
     else if constexpr (PH < 2 * P) NttInv<LOGN, LOGR, kNttBack1>::template phase<PH - P>(na, bid, tid, lds, regs);
-    else NttInv<LOGN, LOGR, kNttBack2>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
+    else if constexpr (PH < 3 * P) NttInv<LOGN, LOGR, kNttBack2>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
+    else NttInv<LOGN, LOGR, kNttBack3>::template phase<PH - 3 * P>(na, bid, tid, lds, regs);
   }
 };
 
