@@ -261,8 +261,8 @@ enum {
                                    n >= 8192).  Same results either way; for tests and tuning. */
   HCNN_OPT_FUSION = 4           /* one-kernel forms of two parts of HMult that keep their intermediate
                                    polynomials in registers: the squaring tensor (step 1 with equal operands:
-                                   both forward transforms, the three products and inverse transforms; rings
-                                   n <= 16384) and the relinearisation (step 3: digit transforms, inner product
+                                   both forward transforms, the three products and inverse transforms)
+                                   and the relinearisation (step 3: digit transforms, inner product
                                    with the key, inverse transforms; n <= 8192, and n = 16384 with at most 16
                                    primes).  0 (default) = chosen per internal batch: the tensor kernel for
                                    batches that fill their rounds of its workgroups to at least 7/8, the

@@ -209,9 +209,9 @@ class OpsMixin:
 
     def takes_tensor_fused(self, n_ct):
         """Does the default policy take the one-kernel squaring tensor for an internal batch of n_ct ciphertexts: its
-        (ciphertext, limb) pairs fill their rounds of resident workgroups to at least 7/8 (rings up to n = 16384)."""
-        slots, pairs = self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS), n_ct * (self.raw.k + self.raw.k_aux)
-        return self.n <= 16384 and 8 * pairs >= 7 * slots * -(-pairs // slots)
+        (ciphertext, limb) pairs fill their rounds of resident workgroups to at least 7/8 (two workgroups per pair at n = 32768)."""
+        slots, wgs = self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS), n_ct * (self.raw.k + self.raw.k_aux) * (2 if self.n == 32768 else 1)
+        return 8 * wgs >= 7 * slots * -(-wgs // slots)
 
     def tensor_fused_threshold(self):
         """(ciphertext, limb) pairs of an internal batch from which the default policy takes the one-kernel squaring tensor

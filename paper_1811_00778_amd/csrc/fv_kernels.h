@@ -207,6 +207,8 @@ struct ScaleArgs {
   BConvDev to_p;              // src q (zmul = t*(q/q_i)^-1, xmul = t), dst p
   BConvDev to_q;              // src p (zmul = (p/p_j)^-1, xmul = 1), dst q
   const int32_t* tq_inv;      // [kp]  t * q^-1 mod p_j, in the form of the tables
+  const NttLimb* limbs;       // [k + kp]
+  const SplitRoot* root;      // HALVES: [2][k + kp]
   uint32_t n;
   uint32_t band;
   unsigned long long* fallback_counter;
@@ -215,40 +217,69 @@ struct ScaleArgs {
 // y_j is produced, used at once for the p -> q conversion (k running 64-bit sums) and parked in the LDS column for the exact
 // path, so the register footprint is 3k + O(1) and the code size does not grow with k*k'.
 // Bound: memory up to k = 8 (3 L rows read, 3 k written: 4.7 TB/s), the multiply-adds and reductions beyond.
-template <int K>
+// HALVES (n = 32768): d holds rows without the last stage of their inverse transforms.  The stage is one more product of every residue: its
+// constants carry the factor that the residue is multiplied with here (z_i directly, or the sum's term of p_j), so that it needs no
+// reduction of its own.  A wave takes the same 32 positions of both halves: its two loads of a row are a cache line each.  (The same words read by
+// waves of the two halves instead, and the stage by itself with constants picked per lane: 32 ciphertexts, k = 24 530 and 426 us; without the stage 313.)
+template <int K, bool HALVES>
 struct ScaleKernel {
   static constexpr int kThreads = kEwThreads;
-  static constexpr int kPhases = 1;
+  static constexpr int kPhases = HALVES ? 2 : 1;
   struct Regs {};
-  static size_t lds_bytes(uint32_t kp) { return (size_t)((uint32_t)K > kp ? (uint32_t)K : kp) * kThreads * 4; }
+  // a column per thread for the exact path, then (HALVES) the constants of both halves
+  HCNN_HOSTDEV static uint32_t col_words(uint32_t kp) { return ((uint32_t)K > kp ? (uint32_t)K : kp) * kThreads; }
+  static size_t lds_bytes(uint32_t kp) { return (col_words(kp) + (HALVES ? 4 * (K + kp) : 0)) * 4; }
   template <int PH>
   HCNN_HD static void phase(const ScaleArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
     const uint32_t n = a.n, kp = a.to_p.kd;
     const uint32_t L = K + kp;
+    uint32_t* const l_root = lds + col_words(kp);
+    if constexpr (HALVES && PH == 0) {
+      for (uint32_t x = tid; x < 4 * L; x += kThreads) l_root[x] = ld_at(reinterpret_cast<const uint32_t*>(a.root), x * 4);
+      return;
+    }
     const uint32_t blocks_per_poly = n / kThreads;
     const size_t poly = bid / blocks_per_poly;             // (ct, component)
-    const uint32_t c = (bid % blocks_per_poly) * kThreads + tid;
+    const uint32_t half = HALVES ? ((uint32_t)tid >> 5) & 1u : 0;
+    const uint32_t c = HALVES ? (bid % blocks_per_poly) * (kThreads / 2) + ((uint32_t)tid >> 6) * 32 + ((uint32_t)tid & 31u)
+                              : (bid % blocks_per_poly) * kThreads + tid;
     const uint32_t* src = a.d + poly * (size_t)L * n + c;
-    uint32_t* dst = a.y + poly * (size_t)K * n + c;
+    uint32_t* dst = a.y + poly * (size_t)K * n + half * (n / 2) + c;
     uint32_t* col = lds + tid;
+    // what lies at this coefficient in row l, and its product with the last stage's constants
+    struct Words { uint32_t lo, hi; };
+    auto load = [&](uint32_t l) { return Words{src[(size_t)l * n], HALVES ? src[(size_t)l * n + n / 2] : 0u}; };
+    auto rooted = [&](const Words& w, uint32_t l) {
+      const uint32_t* f = l_root + (half * L + l) * 2;
+      return untraced((int64_t)(int32_t)w.lo * (int32_t)f[0]) + (int64_t)(int32_t)w.hi * (int32_t)f[1];
+    };
+    // the residue itself, canonical up to one prime (the exact path needs it)
+    auto residue = [&](uint32_t i) -> uint32_t {
+      const Words w = load(i);
+      if constexpr (!HALVES) return w.lo;
+      const NttLimb m = ldc(a.limbs, i);
+      return (uint32_t)split_root((int32_t)w.lo, (int32_t)w.hi, split_root_factors(m.inv_r.c0, m.inv_r.w, half), m.m.p, m.pinv) + m.m.p;
+    };
 
     int32_t z[K];
     uint32_t S = 0;
     {
-      uint32_t dq[K];
+      Words dq[K];
 #pragma unroll
-      for (int i = 0; i < K; ++i) dq[i] = src[(size_t)i * n];
+      for (int i = 0; i < K; ++i) dq[i] = load(i);
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         const Mod m = ldc(a.to_p.src_mod, i);
-        const uint32_t zi = shoup_mul(dq[i], ldc(a.to_p.zmul, i), m.p);
+        uint32_t zi;
+        if constexpr (HALVES) zi = canon_p(sredc(rooted(dq[i], i), m.p, ldc(&a.limbs[i].pinv, 0)), m.p);
+        else zi = shoup_mul(dq[i].lo, ldc(a.to_p.zmul, i), m.p);
         S += frac_est(zi, m);
         z[i] = untraced((int32_t)zi);
       }
     }
     auto exact_q = [&]() {
       for (uint32_t i = 0; i < (uint32_t)K; ++i)
-        col[i * kThreads] = shoup_mul(src[(size_t)i * n], ldc(a.to_p.xmul, i), ldc(a.to_p.src_mod, i).p);
+        col[i * kThreads] = shoup_mul(residue(i), ldc(a.to_p.xmul, i), ldc(a.to_p.src_mod, i).p);
       return garner_gt_half(a.to_p, col, kThreads);
     };
     const int32_t v = untraced((int32_t)bconv_round(S, a.band, exact_q, a.fallback_counter));
@@ -257,15 +288,17 @@ struct ScaleKernel {
 #pragma unroll
     for (int i = 0; i < K; ++i) out_acc[i] = 0;
     uint32_t S2 = 0, room = kSumRoom;
-    uint32_t dp_next = src[(size_t)K * n];
+    Words dp_next = load(K);
 #pragma unroll 1
     for (uint32_t j = 0; j < kp; ++j) {
-      uint32_t dpj = dp_next;
-      if (j + 1 < kp) dp_next = src[(size_t)(K + j + 1) * n];
+      const Words dpj = dp_next;
+      if (j + 1 < kp) dp_next = load(K + j + 1);
       const BConvDst d = ldc_at(a.to_p.dst + j, 0u);
-      dpj = csub(dpj, d.p);                                       // arrives in [0, 2p)
-      const int64_t first = (int64_t)untraced((int32_t)dpj) * ldc(a.tq_inv, j) + (int64_t)v * d.v;
-      const int32_t yj = sredc(bconv_sum<K>(first, z, a.to_p.BT + (size_t)j * K, 2, d.rc), d.p, d.pinv);
+      int64_t first;
+      if constexpr (HALVES) first = rooted(dpj, K + j);
+      else first = (int64_t)untraced((int32_t)csub(dpj.lo, d.p)) * ldc(a.tq_inv, j);                // arrives in [0, 2p)
+      first += (int64_t)v * d.v;
+      const int32_t yj = sredc(bconv_sum<K>(first, z, a.to_p.BT + (size_t)j * K, HALVES ? 3 : 2, d.rc), d.p, d.pinv);
       col[j * kThreads] = (uint32_t)yj;                           // made canonical by the exact path if it runs
       const BConvSrc q = ldc_at(a.to_q.src + j, 0u);
       const uint32_t z2 = canon_p(sredc((int64_t)yj * q.zm, q.p, q.pinv), q.p);
@@ -508,7 +541,8 @@ struct RelinSharedMac {
   }
 };
 
-// Largest ring: the four rows of an output, back in coefficients (kNttBackRow), to modulo the pair's primes, plus y_b.
+// Largest ring: the four rows of an output, left at the last stage of their inverse transforms (kNttBackRow), through that stage, to modulo
+// the pair's primes, plus y_b.  A thread takes four coefficients of each half.
 struct RelinCombineArgs {
   const uint32_t* z;     // [n_ct][outs][4][n], dense rows
   const uint32_t* y;     // [n_ct][3][k][n]
@@ -520,37 +554,53 @@ struct RelinCombineArgs {
   uint32_t k, n;
 };
 struct RelinCombine {
+  static constexpr int kPer = 4;                 // coefficients of each half
   static constexpr int kThreads = kEwThreads;
   static constexpr int kPhases = 1;
   struct Regs {};
   template <int PH>
   HCNN_HD static void phase(const RelinCombineArgs& a, unsigned bid, int tid, uint32_t*, Regs&) {
-    const uint32_t per_row = a.n / (kThreads * kEwVec);
-    const uint32_t row = bid / per_row, c = (bid % per_row * kThreads + tid) * kEwVec;
+    const uint32_t per_row = a.n / (kThreads * kPer * 2);
+    const uint32_t row = bid / per_row, c = (bid % per_row * kThreads + tid) * kPer, h2 = a.n / 2;
     const uint32_t ct = quot(row, a.outputs), o = row - ct * a.outputs.d;
     const uint32_t b = o >= a.outputs.d / 2 ? 1u : 0u, j0 = 2 * (o - b * (a.outputs.d / 2));
     const uint32_t* zp = a.z + (size_t)row * kSharedPrimes * a.n;
-    U4 w[kSharedPrimes];
-#pragma unroll
-    for (uint32_t r = 0; r < kSharedPrimes; ++r) w[r] = ld4_at(zp + (size_t)r * a.n, c * 4);
-    int32_t z[4][kSharedPrimes], v[4];
+    U4 lo[kSharedPrimes], hi[kSharedPrimes];
 #pragma unroll
     for (uint32_t r = 0; r < kSharedPrimes; ++r) {
-      z[0][r] = (int32_t)w[r].x; z[1][r] = (int32_t)w[r].y; z[2][r] = (int32_t)w[r].z; z[3][r] = (int32_t)w[r].w;
+      lo[r] = ld4_at(zp + (size_t)r * a.n, c * 4);
+      hi[r] = ld4_at(zp + (size_t)r * a.n + h2, c * 4);
+    }
+    int32_t z[2][kPer][kSharedPrimes];
+#pragma unroll
+    for (uint32_t r = 0; r < kSharedPrimes; ++r) {
+      const NttLimb* lb = a.limbs + a.k + r;
+      const InvRoot top = ldc(&lb->inv_z, 0);
+      const uint32_t p = ldc(&lb->m.p, 0), pinv = ldc(&lb->pinv, 0);
+      const int32_t x[kPer] = {(int32_t)lo[r].x, (int32_t)lo[r].y, (int32_t)lo[r].z, (int32_t)lo[r].w};
+      const int32_t y[kPer] = {(int32_t)hi[r].x, (int32_t)hi[r].y, (int32_t)hi[r].z, (int32_t)hi[r].w};
+#pragma unroll
+      for (uint32_t h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) z[h][e][r] = split_root(x[e], y[e], split_root_factors(top.c0, top.w, h), p, pinv);
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = relin_crt_round(z[e], a.crt_inv);
-#pragma unroll
     for (uint32_t h = 0; h < 2; ++h) {
-      const uint32_t j = j0 + h;
-      if (j >= a.k) break;
-      const NttLimb L = ldc(a.limbs, j);
-      const RelinCrt kc = ldc(a.crt, j);
-      const U4 y = ld4_at(a.y + ((size_t)(ct * 3 + b) * a.k + j) * a.n, c * 4);
-      auto one = [&](int e, uint32_t add) { return add_mod(relin_crt(z[e], v[e], kc, L.m.p, L.pinv), add, L.m.p); };
-      U4 r;
-      r.x = one(0, y.x); r.y = one(1, y.y); r.z = one(2, y.z); r.w = one(3, y.w);
-      st4_at(a.out + ((size_t)(ct * 2 + b) * a.k + j) * a.n, c * 4, r);
+      int32_t v[kPer];
+#pragma unroll
+      for (int e = 0; e < kPer; ++e) v[e] = relin_crt_round(z[h][e], a.crt_inv);
+#pragma unroll
+      for (uint32_t s = 0; s < 2; ++s) {
+        const uint32_t j = j0 + s;
+        if (j >= a.k) break;
+        const NttLimb L = ldc(a.limbs, j);
+        const RelinCrt kc = ldc(a.crt, j);
+        const U4 y = ld4_at(a.y + ((size_t)(ct * 3 + b) * a.k + j) * a.n + h * h2, c * 4);
+        auto one = [&](int e, uint32_t add) { return add_mod(relin_crt(z[h][e], v[e], kc, L.m.p, L.pinv), add, L.m.p); };
+        U4 r;
+        r.x = one(0, y.x); r.y = one(1, y.y); r.z = one(2, y.z); r.w = one(3, y.w);
+        st4_at(a.out + ((size_t)(ct * 2 + b) * a.k + j) * a.n + h * h2, c * 4, r);
+      }
     }
   }
 };

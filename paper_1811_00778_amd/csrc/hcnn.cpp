@@ -279,6 +279,7 @@ struct hcnn_ctx {
   TwTable d_tw_fwd{}, d_tw_inv{};   // [k + kp][n/2]
   EncScale* d_delta = nullptr;      // [k]
   int32_t* d_tq_inv = nullptr;      // [kp] t * q^-1 mod p_j
+  SplitRoot* d_scale_root = nullptr;   // [2][k + kp], n = 32768: last inverse stage and the scaling's first factor in one
   BConvDev ext{}, to_p{}, to_q{}, dec{};
   uint32_t* d_gauss_t = nullptr;    // thresholds of the Gaussian sampler (uploaded on first use)
   uint32_t* d_dec_tab = nullptr;    // [k][3] constants of the decrypt rounding
@@ -333,14 +334,14 @@ int upload(hcnn_ctx* c, const std::vector<T>& h, T** d) {
 
 template <class K> struct KernelClass { static constexpr int id = HCNN_PROF_OTHER; };
 template <int A, int B, int C, int D> struct KernelClass<NttFwd<A, B, C, D>> { static constexpr int id = HCNN_PROF_NTT_FWD; };
-template <int A, int B, int C> struct KernelClass<NttInv<A, B, C>> { static constexpr int id = HCNN_PROF_NTT_INV; };
+template <int A, int B, int C, int D> struct KernelClass<NttInv<A, B, C, D>> { static constexpr int id = HCNN_PROF_NTT_INV; };
 template <int A> struct KernelClass<ExtKernel<A>> { static constexpr int id = HCNN_PROF_BASE_EXT; };
-template <int A> struct KernelClass<ScaleKernel<A>> { static constexpr int id = HCNN_PROF_SCALE; };
+template <int A, bool H> struct KernelClass<ScaleKernel<A, H>> { static constexpr int id = HCNN_PROF_SCALE; };
 template <int O> struct KernelClass<RelinSharedMac<O>> { static constexpr int id = HCNN_PROF_RELIN_MAC; };
 template <int A, int B> struct KernelClass<RelinBack<A, B>> { static constexpr int id = HCNN_PROF_NTT_INV; };
 template <int A> struct KernelClass<RelinMacKernel<A>> { static constexpr int id = HCNN_PROF_RELIN_MAC; };
 template <int A, int B, int C> struct KernelClass<RelinFused<A, B, C>> { static constexpr int id = HCNN_PROF_RELIN_FUSED; };
-template <int A, int B> struct KernelClass<TensorFused<A, B>> { static constexpr int id = HCNN_PROF_TENSOR; };
+template <int A, int B, int C> struct KernelClass<TensorFused<A, B, C>> { static constexpr int id = HCNN_PROF_TENSOR; };
 template <int F, bool S> struct KernelClass<MacKernel<F, S>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <int B> struct KernelClass<MacMfma<B>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <> struct KernelClass<MacPair> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
@@ -594,6 +595,19 @@ int build_tables(hcnn_ctx* c) {
     std::vector<int32_t> tq;
     for (uint32_t pj : c->p) tq.push_back(h_mont(h_mulmod((uint32_t)(c->t % pj), h_inv(h_prod_mod(c->q, -1, pj), pj), pj), pj));
     if ((e = upload(c, tq, &c->d_tq_inv))) return e;
+    if (c->logn == 15) {
+      std::vector<SplitRoot> root;
+      for (uint32_t half = 0; half < 2; ++half)
+        for (uint32_t l = 0; l < L; ++l) {
+          const uint32_t m = all[l];
+          const uint32_t f = l < c->k ? h_to_p.zmul[l].w
+                                      : h_mulmod((uint32_t)(c->t % m), h_inv(h_prod_mod(c->q, -1, m), m), m);
+          const int32_t top = half ? limbs[l].inv_r.w : limbs[l].inv_r.c0;
+          const int32_t x = h_centred(h_mulmod(top < 0 ? (uint32_t)(top + (int32_t)m) : (uint32_t)top, f, m), m);
+          root.push_back(split_root_factors(x, x, half));
+        }
+      if ((e = upload(c, root, &c->d_scale_root))) return e;
+    }
   }
   std::vector<unsigned long long> zeros(2, 0);
   if ((e = upload(c, zeros, &c->d_counters))) return e;
@@ -673,12 +687,18 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   a.pair = r.pair; a.k = c->k;
   const size_t lds = NttGeom<LOGN, LOGR>::kLdsBytes;
   if (inverse) {
-    const size_t g3 = ntt_grouped_grid(r.rows, 3);
-    if (io == kNttLoadTensor) return run<NttInv<LOGN, LOGR, kNttLoadTensor>>(c, g3, lds, a, r.rows);
-    if (io == kNttLoadTensorMul) return run<NttInv<LOGN, LOGR, kNttLoadTensorMul>>(c, g3, lds, a, r.rows);
+    // n = 32768: two workgroups per row, where the reader takes the last stage (4800 tensor rows 427 us with one, 348 with two; 3072
+    // rows of the shared basis 250, 195)
+    constexpr int kSplit = LOGN == 15;
+    constexpr size_t lds_s = NttGeom<LOGN - kSplit, LOGR>::kLdsBytes;
+    using Square = NttInv<LOGN, LOGR, kNttLoadTensor, kSplit>;
+    using Product = NttInv<LOGN, LOGR, kNttLoadTensorMul, kSplit>;
+    if (io == kNttLoadTensor) return run<Square>(c, Square::grid(r.rows), lds_s, a, r.rows);
+    if (io == kNttLoadTensorMul) return run<Product>(c, Product::grid(r.rows), lds_s, a, r.rows);
     if (io == kNttStoreAdd) return run<NttInv<LOGN, LOGR, kNttStoreAdd>>(c, r.rows, lds, a);
     if constexpr (LOGN == 15) {
-      if (io == kNttBackRow) return run<NttInv<LOGN, LOGR, kNttBackRow>>(c, r.rows, lds, a);
+      using Back = NttInv<LOGN, LOGR, kNttBackRow, 1>;
+      if (io == kNttBackRow) return run<Back>(c, Back::grid(r.rows), lds_s, a, r.rows);
     }
     return run<NttInv<LOGN, LOGR>>(c, r.rows, lds, a);
   }
@@ -772,7 +792,8 @@ int ext_dispatch(hcnn_ctx* c, size_t grid, const ExtArgs& a) {
 
 int scale_dispatch(hcnn_ctx* c, size_t grid, const ScaleArgs& a) {
   switch (c->k) {
-#define HCNN_SCALE_CASE(K) case K: return run<ScaleKernel<K>>(c, grid, ScaleKernel<K>::lds_bytes(c->kp), a);
+#define HCNN_SCALE_CASE(K) case K: return c->logn == 15 ? run<ScaleKernel<K, true>>(c, grid, ScaleKernel<K, true>::lds_bytes(c->kp), a) \
+                                                        : run<ScaleKernel<K, false>>(c, grid, ScaleKernel<K, false>::lds_bytes(c->kp), a);
     HCNN_EVERY_K(HCNN_SCALE_CASE)
 #undef HCNN_SCALE_CASE
   }
@@ -909,7 +930,6 @@ int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
 
 // Occupancy of the two long-running one-kernel forms for this ring and basis, asked of the runtime once.
 int query_fused_occupancy(hcnn_ctx* c) {
-  if (c->logn > 14) return 0;                       // neither form exists for the largest ring
   const uint32_t k = c->k;
   int e = 0, r = 1, t = 1;
 #define HCNN_OCC(LOGN, LOGR)                                                                                          \
@@ -924,7 +944,7 @@ int query_fused_occupancy(hcnn_ctx* c) {
     case 11: HCNN_OCC(11, 4) break;
     case 12: HCNN_OCC(12, 4) break;
     case 13: HCNN_OCC(13, 4) break;
-    case 14: HCNN_OCC(14, 4) break;
+    case 14: HCNN_OCC(14, 4) break;                 // (the largest ring has no one-kernel relinearisation)
   }
 #undef HCNN_OCC
   if (e) return e;
@@ -934,6 +954,7 @@ int query_fused_occupancy(hcnn_ctx* c) {
     case 12: e = resident_workgroups_per_cu<TensorFused<12, 4>, TensorFusedArgs>(TensorFused<12, 4>::kLdsBytes, &t); break;
     case 13: e = resident_workgroups_per_cu<TensorFused<13, 4>, TensorFusedArgs>(TensorFused<13, 4>::kLdsBytes, &t); break;
     case 14: e = resident_workgroups_per_cu<TensorFused<14, 4>, TensorFusedArgs>(TensorFused<14, 4>::kLdsBytes, &t); break;
+    case 15: e = resident_workgroups_per_cu<TensorFused<15, 5, 1>, TensorFusedArgs>(TensorFused<15, 5, 1>::kLdsBytes, &t); break;
   }
   if (e) return e;
   c->relin_fused_wgs = (uint32_t)r;
@@ -1246,7 +1267,7 @@ static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* d
     b.tile_words = outs * 64;
     if ((e = ntt_rows(c, b, true, kNttBackRow))) return e;
     RelinCombineArgs ca{z, y, out, c->d_limbs, c->d_crt, c->crt_inv, fast_div(outs), k, n};
-    return run<RelinCombine>(c, rows * (n / (kEwThreads * kEwVec)), 0, ca);
+    return run<RelinCombine>(c, rows * (n / (kEwThreads * RelinCombine::kPer * 2)), 0, ca);
   }
   RelinBackArgs ba{acc, y, out, c->d_tw_inv, c->d_limbs, c->d_crt, c->crt_inv, k, fast_div(outs), k};
   switch (c->logn) {
@@ -1334,11 +1355,12 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   };
   // Steps 2+3 in one kernel for squarings: its workgroups are long (five transforms), so it pays when they fill their
   // rounds.  Measured at n = 8192, k = 8: 1.06 us per ciphertext in full rounds against 1.25 of the two separate kernels
-  // (64 to 512 ciphertexts), a ratio of 0.85.
+  // (64 to 512 ciphertexts), a ratio of 0.85; at n = 32768, k = 24 15.5 against 18.8 (32), 0.82.
   auto takes_tensor_fused = [&](size_t cc) {
-    if (in_b || c->logn > 14 || c->fusion == 1) return false;
-    const size_t slots = tensor_fused_slots(c), rounds = (cc * L + slots - 1) / slots;
-    return c->fusion == 2 || cc * L * 8 >= rounds * slots * 7;
+    if (in_b || c->fusion == 1) return false;
+    const size_t wgs = c->logn == 15 ? 2 * cc * L : cc * L;                  // (n = 32768: two workgroups per pair)
+    const size_t slots = tensor_fused_slots(c), rounds = (wgs + slots - 1) / slots;
+    return c->fusion == 2 || wgs * 8 >= rounds * slots * 7;
   };
 
   // One internal batch: ciphertexts [c0, c0 + cc) of the call, nf of
@@ -1354,14 +1376,14 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     uint32_t* const b_acc = dig + (shared ? cc * kSharedPrimes : (cc - nf) * k) * k * rn;
     // 1. centred lift of c0, c1 extended to the auxiliary primes (only the new rows are written);
     // 2. forward NTT over all k + k' limbs, the first k read from the ciphertext itself
-    // (n = 32768: the new rows are staged in the array of the tensor, free until step 3, because the two-workgroup
+    // (n = 32768, separate kernels: the new rows are staged in the array of the tensor, free until step 3, because the two-workgroup
     // transform of that ring cannot work in place)
-    uint32_t* const b_new = c->logn == 15 ? b_d : b_ext;
+    const bool tensor_fused = takes_tensor_fused(cc);
+    uint32_t* const b_new = c->logn == 15 && !tensor_fused ? b_d : b_ext;
     ExtArgs ea;
     ea.in = in + c0 * ct_words; ea.out = b_new; ea.bc = c->ext; ea.n = n; ea.band = c->band;
     ea.fallback_counter = c->d_counters;
     if ((e = ext_dispatch(c, cc * 2 * bpp, ea))) return e;
-    const bool tensor_fused = takes_tensor_fused(cc);
     if (tensor_fused) {
       TensorFusedArgs ta{in + c0 * ct_words, b_ext, b_d, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, L, (uint32_t)(cc * L), fast_div(L)};
       const size_t rows = cc * L * 5;
@@ -1376,6 +1398,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
           e = cc * L <= c->compute_units ? run<TensorFused<14, 4>>(c, cc * L, TensorFused<14, 4>::kLdsBytes, ta, rows)
                                          : run<TensorFused<14, 5>>(c, cc * L, TensorFused<14, 5>::kLdsBytes, ta, rows);
           break;
+        case 15: e = run<TensorFused<15, 5, 1>>(c, TensorFused<15, 5, 1>::grid(cc * L), TensorFused<15, 5, 1>::kLdsBytes, ta, rows); break;
         default: e = HCNN_ERR_N; break;
       }
       if (e) return e;
@@ -1396,7 +1419,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     }
     // 5. y = round(t/q * d) mod q
     ScaleArgs sa;
-    sa.d = b_d; sa.y = b_y; sa.to_p = c->to_p; sa.to_q = c->to_q; sa.tq_inv = c->d_tq_inv; sa.n = n;
+    sa.d = b_d; sa.y = b_y; sa.to_p = c->to_p; sa.to_q = c->to_q; sa.tq_inv = c->d_tq_inv; sa.limbs = c->d_limbs; sa.root = c->d_scale_root; sa.n = n;
     sa.band = c->band; sa.fallback_counter = c->d_counters;
     if ((e = scale_dispatch(c, cc * 3 * bpp, sa))) return e;
     if (shared) return relin_shared(c, b_y, cc, b_dig, b_acc, b_d, out + c0 * ct_words);     // (the tensor's rows, 3L > 4k + 4, are free by now)

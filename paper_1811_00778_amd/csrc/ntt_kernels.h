@@ -95,6 +95,17 @@ struct EncScale {
 // Row r (= workgroup index) belongs to group r / cycle and limb limb_base + r % cycle.
 // Its data sits at row (group * group_rows + row0 + r % cycle) of the in / out arrays, so a
 // launch can pick one polynomial out of every ciphertext of a batch.
+// The last stage of an inverse transform left at its halves (NttInv, SPLIT = 1): element `half * n/2 + i` of the row from elements i and
+// i + n/2 as they were left, signed in (-p, p); c0, w: the root constants with the output scaling.  Result in (-p, p): two
+// products of at most p * p/2.
+struct SplitRoot { int32_t x, y; };
+HCNN_HOSTDEV SplitRoot split_root_factors(int32_t c0, int32_t w, uint32_t half) {
+  return half ? SplitRoot{w, -w} : SplitRoot{c0, c0};
+}
+HCNN_HD int32_t split_root(int32_t lo, int32_t hi, const SplitRoot& f, uint32_t p, uint32_t pinv) {
+  return sredc(untraced((int64_t)lo * f.x) + (int64_t)hi * f.y, p, pinv);
+}
+
 // Fused input / output stages (template parameter IO of the kernels):
 //   kNttPlain       rows are read and written as they are
 //   kNttLoadDigit   forward only: row (ct, i, j) reads digit i of y2, i.e. row (ct*3+2)*k + i of `in`
@@ -326,6 +337,11 @@ HCNN_HD void r4_inv_add(int32_t& x0, int32_t& x1, int32_t& x2, int32_t& x3, int3
   x3 = sredc(untraced(add[3] + (int64_t)d1 * t.vw) + (int64_t)d2 * nuw, p, L.pinv);
 }
 
+// Workgroup index of the split forms -> half and row (both halves of a row on one die, next to each other in time).
+HCNN_HD uint32_t split_half(uint32_t bid) { return (bid / kNttXcds) & 1u; }
+HCNN_HD uint32_t split_row(uint32_t bid) { return bid / (2 * kNttXcds) * kNttXcds + bid % kNttXcds; }
+inline size_t split_grid(size_t rows) { return 2 * ((rows + kNttXcds - 1) / kNttXcds * kNttXcds); }
+
 // ------------------------------------------------------------------------- forward
 // SPLIT = 1: two workgroups per row.  The first stage of the forward transform pairs element i with element
 // i + n/2 and leaves two halves that never meet again; workgroup (row, half) computes its half of that stage while
@@ -343,7 +359,7 @@ struct NttFwd {
   static constexpr bool kDigitRow = IO == kNttLoadDigit || IO == kNttDigitTile;
   static_assert(IO == kNttPlain || IO == kNttPlainFew || kDigitRow || IO == kNttStoreLazy || kKeyOut || kFused || kToRegs,
                 "forward NTT: plain, digit load, lazy or key store, fused inner product or register output");
-  static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kToRegs && LOGN % 2 == 1), "the split form stores its rows");
+  static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kRowToRegs && LOGN % 2 == 1), "the split form stores its rows or keeps them for the tensor");
   using G = NttGeom<LOGN - SPLIT, LOGR, IO == kNttPlain>;      // the stages after the split one
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
@@ -357,7 +373,7 @@ struct NttFwd {
   // one exchange across waves (first_net), the first
   static constexpr bool wave_sync(int ph) { return ph != 0 && !(kWholeRow && ph == kPhases - 2); }
   // workgroups of a launch over `slots` row positions (a multiple of the die count for the split form)
-  static size_t grid(size_t slots) { return SPLIT ? 2 * ((slots + kNttXcds - 1) / kNttXcds * kNttXcds) : slots; }
+  static size_t grid(size_t slots) { return SPLIT ? split_grid(slots) : slots; }
 
   template <int PH>
   HCNN_HD static void phase(const NttArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
@@ -373,8 +389,8 @@ struct NttFwd {
     uint32_t half = 0;
     if constexpr (SPLIT) {
       // both halves of a row on one die, next to each other in time
-      half = (bid / kNttXcds) & 1u;
-      bid = (bid / (2 * kNttXcds)) * kNttXcds + bid % kNttXcds;
+      half = split_half(bid);
+      bid = split_row(bid);
       if constexpr (!kDigitIn) {
         if (bid >= a.n_rows) return;                       // padding workgroups of the last round
       }
@@ -561,18 +577,28 @@ struct NttFwd {
 };
 
 // ------------------------------------------------------------------------- inverse
-template <int LOGN, int LOGR, int IO = kNttPlain>
+// SPLIT = 1: two workgroups per row, all stages but the last, which joins the halves: the reader of the row takes it while loading
+// (split_root).  The halves are left signed in (-p, p), without the output scaling.  Half the LDS and half the threads per
+// workgroup, as in the forward transform, and no pass of five stages.
+template <int LOGN, int LOGR, int IO = kNttPlain, int SPLIT = 0>
 struct NttInv {
+  static_assert(SPLIT == 0 || (SPLIT == 1 && LOGN % 2 == 1 && (IO == kNttLoadTensor || IO == kNttLoadTensorMul || IO == kNttTensorRegs0 ||
+                IO == kNttTensorRegs1 || IO == kNttTensorRegs2 || IO == kNttBackRow)), "rows whose reader takes the last stage");
   static_assert(IO == kNttPlain || IO == kNttLoadTensor || IO == kNttStoreAdd || IO == kNttLoadTensorMul ||
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
                 IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut || IO == kNttDecOwn || IO == kNttBackRow || IO == kNttBack0 ||
                 IO == kNttBack1 || IO == kNttBack2 || IO == kNttBack3, "inverse NTT io mode");
-  using G = NttGeom<LOGN, LOGR>;
+  using G = NttGeom<LOGN - SPLIT, LOGR>;
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
+  // workgroups of a launch over `rows` rows, or of three components of rows / 3 pairs
+  static size_t grid(size_t rows) {
+    if (IO == kNttLoadTensor || IO == kNttLoadTensorMul) return ntt_grouped_grid(rows, 3) << SPLIT;
+    return SPLIT ? split_grid(rows) : rows;
+  }
   // a 1024-thread workgroup whose row leaves LDS for a second one: keep the registers within what two of them need
   // (the plain transform of n = 16384 took 68 and ran alone on its compute unit, a third slower per row)
-  static constexpr int kMinWavesPerSimd = (G::kThreads == 1024 && 2 * G::kLdsBytes <= 160 * 1024) ? 8 : 1;
+  static constexpr int kMinWavesPerSimd = SPLIT ? 4 : (G::kThreads == 1024 && 2 * G::kLdsBytes <= 160 * 1024) ? 8 : 1;
   static constexpr bool wave_sync(int ph) { return ph != kPhases - 2; }        // one exchange across waves (first_net)
   static constexpr bool kFromRegs = IO == kNttFromRegs0 || IO == kNttFromRegs1;
   static constexpr bool kTensorRegs = IO == kNttTensorRegs0 || IO == kNttTensorRegs1 || IO == kNttTensorRegs2;
@@ -585,16 +611,28 @@ struct NttInv {
   template <int PHI>
   HCNN_HD static void phase(const NttArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
     constexpr int PH = kPhases - 1 - PHI;   // mirrors forward pass PH
-    constexpr int N = G::N, R = G::R;
+    constexpr int N = 1 << LOGN, R = G::R;                // N: residues of a row in memory
     constexpr int S0 = G::s0(PH), NS = G::ns(PH), NET = 1 << NS, C = R / NET;
-    constexpr int LOG_TLAST = LOGN - S0 - NS, TLAST = 1 << LOG_TLAST;
+    constexpr int LOG_TLAST = LOGN - SPLIT - S0 - NS, TLAST = 1 << LOG_TLAST;
     constexpr bool kFirst = PHI == 0, kLast = PHI == kPhases - 1;   // kLast <=> S0 == 0
     constexpr bool kOdd = NS % 2 == 1;
 
+    uint32_t half = 0;
+    if constexpr (SPLIT && IO != kNttLoadTensor && IO != kNttLoadTensorMul) {
+      half = split_half(bid);
+      bid = split_row(bid);
+      if (bid >= a.n_rows) return;
+    }
     if constexpr (IO == kNttLoadTensor || IO == kNttLoadTensorMul) {
       // the three components of one (ciphertext, limb) pair read the same c0^ / c1^ rows: same die
       const uint32_t LL = a.cycle.d;
-      const uint32_t xcd = bid % kNttXcds, local = bid / kNttXcds;
+      const uint32_t xcd = bid % kNttXcds;
+      uint32_t local = bid / kNttXcds;
+      if constexpr (SPLIT) {
+        // (the halves of a pair one after the other: they share nothing)
+        half = local / 3 & 1u;
+        local = local / 6 * 3 + local % 3;
+      }
       const uint32_t unit = local / 3 * kNttXcds + xcd, b = local % 3, ct = quot(unit, a.cycle);   // unit = ct*L + l
       bid = (ct * 3 + b) * LL + (unit - ct * LL);               // row (ct, b, l)
       if (unit >= a.n_rows / 3) return;
@@ -667,6 +705,13 @@ struct NttInv {
     } else {
       gout = a.out + ((size_t)group * a.out_group_rows + a.out_row0 + within) * N;
     }
+    if constexpr (SPLIT) {
+      const size_t at = (size_t)half * (N / 2);
+      gout += at;
+      if constexpr (IO == kNttBackRow) gin += at / 64 * a.tile_words;
+      else if constexpr (!kTensorRegs) { gin += at; gin2 += at; }
+      if constexpr (IO == kNttLoadTensorMul) { gmul0 += at; gmul1 += at; }
+    }
     if constexpr (IO == kNttStoreAdd) {
       const uint32_t kk = a.cycle.d;
       gaux = a.aux + ((size_t)(group / 2) * 3 * kk + (size_t)(group % 2) * kk + within) * N;
@@ -677,7 +722,7 @@ struct NttInv {
     if constexpr (TLAST >= 64) i0 = wave_uniform(i0);
     const uint32_t base = i0 * (uint32_t)(NET * TLAST) + o;
     const uint32_t sbase = lds_swz(base);
-    const uint32_t root = (1u << S0) + i0;
+    const uint32_t root = SPLIT ? ((2u + half) << S0) + i0 : (1u << S0) + i0;
     if constexpr (kLast && kBack && IO != kNttBack3) {
       // the next row's words are on their way during this row's last pass
       constexpr int F = kPhases - 1, NET_F = 1 << G::ns(F);
@@ -771,7 +816,7 @@ struct NttInv {
         const int q = NET >> (l + 2);
 #pragma unroll
         for (int h = 0; h < (1 << l); ++h) {
-          const bool outer = kLast && l == 0;
+          const bool outer = kLast && l == 0 && !SPLIT;
           const R4Twiddle t = outer ? R4Twiddle{top.w, top.v, top.vw, top.u} : ldc_at(tq + h + (i_off << l), (root << l) * 16);
           const int32_t nuw = outer ? top.nuw : ldc_at(tn + h + (i_off << l), (root << l) * 4), c0 = outer ? top.c0 : L.rc;
 #pragma unroll
@@ -825,7 +870,7 @@ struct NttInv {
           }
           sched_fence();
         }
-      } else if constexpr (kLast && IO == kNttBackRow) {
+      } else if constexpr (kLast && (SPLIT || IO == kNttBackRow)) {
 #pragma unroll
         for (int e = 0; e < NET; ++e) st_at(gout + off + e * TLAST, base * 4, (uint32_t)v[e]);
       } else if constexpr (kLast && kEncOut) {
@@ -987,9 +1032,13 @@ struct TensorFusedArgs {
   FastDiv cycle;            // L
 };
 
-template <int LOGN, int LOGR>
+// SPLIT = 1 (n = 32768): workgroup (ct, l, half), both ends as in the split transforms: it reads whole rows of c0 and c1, keeps its halves and leaves
+// its halves of the three components without the last stage.  Us, 32 ciphertexts of 24 + 26 limbs: the two separate kernels with a whole row per
+// inverse workgroup 681, with half a row 600, this one 497 (1024 MiB through memory: 230).
+template <int LOGN, int LOGR, int SPLIT = 0>
 struct TensorFused {
-  using G = NttGeom<LOGN, LOGR>;
+  using G = NttGeom<LOGN - SPLIT, LOGR>;
+  static size_t grid(size_t pairs) { return SPLIT ? split_grid(pairs) : pairs; }
   static constexpr int P = G::kPhases;
   static constexpr int kBuffers = LOGN == 14 && LOGR == 4 ? 2 : 1;
   static constexpr size_t kLdsBytes = kBuffers * G::kLdsBytes;
@@ -1006,13 +1055,13 @@ struct TensorFused {
     na.limbs = a.limbs; na.cycle = a.cycle; na.limb_base = 0; na.n_rows = a.n_rows;
     if constexpr (PH < 2 * P) {
       na.in = a.ext; na.aux = a.cts; na.own_limbs = a.k; na.tw = a.tw_fwd;
-      if constexpr (PH < P) NttFwd<LOGN, LOGR, kNttToRegs0>::template phase<PH>(na, bid, tid, lds, regs);
-      else NttFwd<LOGN, LOGR, kNttToRegs1>::template phase<PH - P>(na, bid, tid, lds, regs);
+      if constexpr (PH < P) NttFwd<LOGN, LOGR, kNttToRegs0, SPLIT>::template phase<PH>(na, bid, tid, lds, regs);
+      else NttFwd<LOGN, LOGR, kNttToRegs1, SPLIT>::template phase<PH - P>(na, bid, tid, lds, regs);
     } else {
       na.out = a.d; na.tw = a.tw_inv;
-      if constexpr (PH < 3 * P) NttInv<LOGN, LOGR, kNttTensorRegs0>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
-      else if constexpr (PH < 4 * P) NttInv<LOGN, LOGR, kNttTensorRegs1>::template phase<PH - 3 * P>(na, bid, tid, lds, regs);
-      else NttInv<LOGN, LOGR, kNttTensorRegs2>::template phase<PH - 4 * P>(na, bid, tid, lds, regs);
+      if constexpr (PH < 3 * P) NttInv<LOGN, LOGR, kNttTensorRegs0, SPLIT>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
+      else if constexpr (PH < 4 * P) NttInv<LOGN, LOGR, kNttTensorRegs1, SPLIT>::template phase<PH - 3 * P>(na, bid, tid, lds, regs);
+      else NttInv<LOGN, LOGR, kNttTensorRegs2, SPLIT>::template phase<PH - 4 * P>(na, bid, tid, lds, regs);
     }
   }
 };

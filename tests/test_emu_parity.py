@@ -271,6 +271,13 @@ def test_square_relin_largest_ring_two_workgroups_per_forward_row(backend):
     pc.check_square_relin(backend, 32768, 2, n_random=2, n_genuine=0)
 
 
+@pytest.mark.parametrize("k,options", [(2, dict(force_exact=True)), (3, dict(relin_order=1))])
+def test_square_relin_largest_ring_by_halves(backend, k, options):
+    # n = 32768: inverse transforms left at the halves of their rows, the scaling takes their last stage; the one-kernel tensor
+    # (taken here by default) with the exact comparison in the scaling, and the separate kernels
+    pc.check_square_relin(backend, 32768, k, n_random=1, n_genuine=0, **options)
+
+
 def test_measure_ceiling_arguments(backend):
     # the diagnostic rejects an unknown probe; the host emulation does not time its launches and reports 0
     from paper_1811_00778_amd import _capi

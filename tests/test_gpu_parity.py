@@ -190,6 +190,22 @@ def test_square_relin_largest_rings_residue_exact(backend):
     pc.check_square_relin(backend, 32768, 6, n_random=1, n_genuine=0)
 
 
+@pytest.mark.parametrize("mode", [1, 2])
+def test_square_relin_largest_ring_exact_comparison(backend, mode):
+    """n = 32768: the scaling's exact comparison rebuilds the residues from the halves that the inverse transforms leave."""
+    n, k = 32768, 2
+    say("square_relin n=32768 k=2, every comparison exact, form %d" % mode)
+    s = pc.Setup(backend, n, k)
+    s.ctx.set_relin_key(backend.dev(s.evk))
+    cts = gen.uniform_residues(s.rng, s.q, n, lead=(2, 2))
+    s.ctx.set_fusion(mode)
+    want = backend.host(s.ctx.ct_square_relin(backend.dev(cts)))
+    assert np.array_equal(want[0], fv.square_relin(s.octx, cts[0], s.evk))
+    s.ctx.set_ambiguity_band(2 ** 26)
+    assert np.array_equal(backend.host(s.ctx.ct_square_relin(backend.dev(cts))), want)
+    assert s.ctx.exact_fallbacks() > n
+
+
 def test_square_relin_whole_rounds_plus_remainder(backend):
     """A batch that the default policy splits: whole rounds of the one-kernel relinearisation (sized from the
     occupancy that the runtime reports for the compiled kernel), the rest through the separate kernels.  Sampled
