@@ -619,6 +619,8 @@ struct MacArgs {
   int32_t w_abs_max;
   uint32_t chunk;         // terms between reductions of the signed 64-bit accumulators
   uint32_t steps;         // matrix forms: tiles per wave
+  uint32_t pack;          // MacPack: groups that share the sixteen rows
+  FastDiv terms, filters; // unions: T, F
   unsigned long long* bad_counter;
 };
 // Fallback for gather rows too long to stage in LDS: indices and weights are read from global
@@ -842,6 +844,7 @@ constexpr uint32_t kMfmaMaxSum = 1u << 20;     // T * |w| <= 2^20: sums of weigh
 // What the two kernels below share: the sums of one tile for NG groups over one list of terms.
 struct MacMatrix {
   static constexpr uint32_t kTile = 64;
+  static constexpr uint32_t kLeastPerUnit = 4;     // workgroups per compute unit below which waves take fewer tiles (mac_matrix_steps)
   HCNN_HOSTDEV static uint32_t chunks(uint32_t T) { return (T + 63) / 64; }
   // workgroups of a launch: every die takes the same number of tile blocks (the last ones may be empty), each for all blocks of groups
   static size_t grid(uint32_t tile_blocks, size_t group_blocks) { return (size_t)kXcds * ((tile_blocks + kXcds - 1) / kXcds) * group_blocks; }
@@ -859,6 +862,15 @@ struct MacMatrix {
   template <int Q> struct Inputs { const uint32_t *in, *l_off; uint32_t unit; };
   template <bool WIDE, int Q>
   static void load(const uint32_t* in, const uint32_t* l_off, uint32_t lane, Inputs<Q>& x, uint32_t) { x = Inputs<Q>{in + lane % 16 * 4, l_off, WIDE ? 16u : 1u}; }
+  static void multiply_half(const Inputs<2>& half, const uint32_t* l_w, uint32_t h, uint32_t lane, Sums (&acc)[4][4]) {
+    for (uint32_t t = 0; t < 32; ++t)
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t x = half.in[(size_t)half.l_off[t] * half.unit / 4 + s];
+        for (int r = 0; r < 4; ++r)
+          for (int j = 0; j < 4; ++j)
+            acc[s][j].v[r] += weight(l_w, lane / 16 * 4 + r, 32 * h + t) * ((int32_t)(x >> (8 * j) & 0xff) - (j < 3 ? 128 : 0));
+      }
+  }
   template <int Q, int NG>
   static void multiply(const Inputs<Q>& chunk, const uint32_t* l_w, uint32_t w_stride, uint32_t lane, Sums (&acc)[NG][4][4]) {
     const uint32_t *in = chunk.in, *l_off = chunk.l_off;
@@ -878,6 +890,7 @@ struct MacMatrix {
   template <int Q> struct Inputs {};
   template <bool WIDE, int Q> __device__ static void load(const uint32_t*, const uint32_t*, uint32_t, Inputs<Q>&, uint32_t);
   template <int Q, int NG> __device__ static void multiply(const Inputs<Q>&, const uint32_t*, uint32_t, uint32_t, Sums (&)[NG][4][4]);
+  __device__ static void multiply_half(const Inputs<2>&, const uint32_t*, uint32_t, uint32_t, Sums (&)[4][4]);
 #else
   typedef int32_t Vec __attribute__((ext_vector_type(4)));
   struct Sums { Vec v = {0, 0, 0, 0}; };
@@ -910,10 +923,35 @@ struct MacMatrix {
       if (!WIDE) sched_fence();
     }
   }
+  // the bytes of four terms' words s as operand words, one per byte plane
+  template <class Planes>
+  __device__ __forceinline__ static void planes(const hcnn_word4 (&x)[4], int s, int q, Planes& b) {
+    const uint32_t lo01 = __builtin_amdgcn_perm(x[1][s], x[0][s], 0x05010400u);    // a0 b0 a1 b1
+    const uint32_t hi01 = __builtin_amdgcn_perm(x[1][s], x[0][s], 0x07030602u);    // a2 b2 a3 b3
+    const uint32_t lo23 = __builtin_amdgcn_perm(x[3][s], x[2][s], 0x05010400u);
+    const uint32_t hi23 = __builtin_amdgcn_perm(x[3][s], x[2][s], 0x07030602u);
+    b[0][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u);
+    b[1][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u);
+    b[2][q] = (int32_t)(__builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u);
+    b[3][q] = (int32_t)__builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+  }
+  // Two quad steps (half h of a chunk) times the weights of one set: half as many inputs in registers, half as long products
+  __device__ __forceinline__ static void multiply_half(const Inputs<2>& in, const uint32_t* l_w, uint32_t h, uint32_t lane, Sums (&acc)[4][4]) {
+    typedef int32_t Vec2 __attribute__((ext_vector_type(2)));
+    const int64_t w = __builtin_bit_cast(int64_t, *reinterpret_cast<const Vec2*>(l_w + lane * 4 + h * 2));
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      Vec2 b[4];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) planes(in.x[q], s, q, b);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[s][j].v = __builtin_amdgcn_mfma_i32_16x16x32_i8(w, __builtin_bit_cast(int64_t, b[j]), acc[s][j].v, 0, 0, 0);
+    }
+  }
   // ... and their products with the weights of NG groups, w_stride words apart; operand words beyond the Q steps are zero
   template <int Q, int NG>
   __device__ __forceinline__ static void multiply(const Inputs<Q>& in, const uint32_t* l_w, uint32_t w_stride, uint32_t lane, Sums (&acc)[NG][4][4]) {
-    const auto& x = in.x;
     Vec w[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g) w[g] = reinterpret_cast<const Vec*>(l_w + g * w_stride)[lane];
@@ -921,16 +959,7 @@ struct MacMatrix {
     for (int s = 0; s < 4; ++s) {
       Vec b[4] = {};
 #pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const uint32_t lo01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x05010400u);    // a0 b0 a1 b1
-        const uint32_t hi01 = __builtin_amdgcn_perm(x[q][1][s], x[q][0][s], 0x07030602u);    // a2 b2 a3 b3
-        const uint32_t lo23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x05010400u);
-        const uint32_t hi23 = __builtin_amdgcn_perm(x[q][3][s], x[q][2][s], 0x07030602u);
-        b[0][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u);
-        b[1][q] = (int32_t)(__builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u);
-        b[2][q] = (int32_t)(__builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u);
-        b[3][q] = (int32_t)__builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
-      }
+      for (int q = 0; q < Q; ++q) planes(in.x[q], s, q, b);
 #pragma unroll
       for (int g = 0; g < NG; ++g)
 #pragma unroll
@@ -955,7 +984,14 @@ struct MacMatrix {
       for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[gi][s][j] = j < 3 ? wsum[gi] : Sums{};
-    if constexpr (NG > 1) {
+    if constexpr (NG == 1 && !WIDE) {
+      // half a chunk at a time: four waves per SIMD
+      Inputs<2> x{};
+      for (uint32_t c = 0; c * 32 < terms; ++c) {
+        load<WIDE>(in, l_off + c * 32, lane, x, terms - c * 32);
+        multiply_half(x, l_w + c / 2 * 256, c % 2, lane, acc[0]);
+      }
+    } else if constexpr (NG > 1) {
       // one loop body (a second one does not hold the sums in registers): a quad step beyond the last is not loaded, what its
       // operand words hold meets weights of zero
       Inputs<4> x{};
@@ -1100,98 +1136,93 @@ struct MacMfma : MacMatrix {
   }
 };
 
-// Two neighbouring groups as one, over the union of their rows.  Neighbouring placements of a 3 x 3 kernel share two thirds of their
-// inputs, and the kernel above is bound by the gather, which takes 12 loads here for every 18 there; a term that only one of the
-// two has meets a zero weight of the other in the matrix unit, which has room.
+// Neighbouring groups as one, over the union of their rows.  Neighbouring placements of a 3 x 3 kernel share two thirds of their
+// inputs, and the kernel above is bound by the gather; a term that only some of the groups have meets zero weights of the others in the
+// matrix unit, which has room.
+//   MacPair: two groups of up to 16 filters, a set of sums each (12 loads for every 18 of the kernel above)
+//   MacPack: 16 / F groups of F <= 8 filters side by side in the sixteen rows of one set.  Half a chunk of terms at a time, so that four waves
+//   fit a SIMD (121 registers; whole chunks take 180: 5 x 25, stride 2, 144 groups, n = 8192, k = 8 192 us, 174 with halves, vector form
+//   224; its inputs and outputs take 166 at the copy rate)
 // The tables are built from the rows as they are, in any order: phases
 //   0  clear         1  a bit per group and input that a term of non-zero weight names      2-4  prefix sums of the union's bits: a slot
 //   per input        5  offsets and weight bytes to their slots; a term that names an input a second time in its row gets a slot of
 //   its own behind them (the slots hold at most the terms of both rows)
 //   6  sums: every wave its own tiles of 64 coefficients, as above
-// Measured, the kernel above / this one, us: 16 filters x 576 terms (3 x 3 padded, 8 x 8 map), 64 groups, n = 8192, k = 10 1502 / 1249;
-// 12 x 144, 100 groups, k = 8 704 / 562; 16 x 25 (5 x 5, stride 2), 144 groups 523 / 439; 16 x 144, 36 groups, n = 16384, k = 16 1273 / 1000; no input
-// shared (2 x 2, stride 2), 16 x 192, 16 groups 356 / 352.
-// Bound: inputs from beyond L2.  The first of these gathers 13.7 GB (24 above) but misses L2 for 8.5 GB of them (5.2 above, inputs
-// 2.7): 256 waves of a die are at twice as many tiles, 8 MiB of inputs, and drift apart.  Measured and left out, same layer: a wave per quarter of the
-// slots, so that four share a tile (sums added through LDS: 1554, two barriers and four reductions per tile), tiles of 32
-// coefficients (8-byte loads: 1494), one wave per SIMD with two buffers of inputs (1425 - 1527).  A second loop body for the last terms
-// does not hold the sums in registers (100 spilled).
-struct MacPair : MacMatrix {
+template <int SETS>
+struct MacUnion : MacMatrix {
   static constexpr int kThreads = 256;
   static constexpr int kPhases = 7;
-  static constexpr int kMinWavesPerSimd = 2;     // 64 registers of inputs in flight, 128 of sums
+  static constexpr int kMinWavesPerSimd = SETS == 1 ? 4 : 2;     // 64 registers of sums per set, 32 or 64 of inputs in flight
   static constexpr uint32_t kStreams = kThreads / 64;
-  // Tiles per wave at most.  A union leaves out the terms without weight, so that the workgroups at a map's padded border are done sooner and
-  // neighbours drift apart in L2, the more the longer they run; shorter runs build the union more often.  Long rows take four tiles: us, 8 /
-  // 4 tiles, 16 filters, n = 8192, 3 x 3 padded: 576 terms, 64 groups, k = 10 1339 / 1256, 100 groups, k = 8 1967 / 1815 (with weights on the
-  // padding too 1593 / 1620), 504, 144 groups 2484 / 2305; 5 x 5 padded, 600, 144 groups 2043 / 1824.  Without padding they cost up to 8 %:
-  // 5 x 5, 600 terms, 64 groups 966 / 1046, 1000 of k = 6 +5 %, 2 x 2, 800 of k = 4 +2 %.  Below, the loss is larger than the gain: 3 x 3
-  // padded, 360 terms, 144 groups -7 %, 288, 64 groups 686 / 698; without padding 400 (5 x 5), 64 groups +9 %, 12 x 144, 100 groups 562 / 591;
-  // 25 (5 x 5, stride 2), 144 groups 436 / 500.
-  static uint32_t max_steps(const MacArgs& a) { return a.T >= 512 ? 4 : 8; }
+  static constexpr uint32_t kRows = SETS == 1 ? 8 : 16;              // filters at most
   struct Regs {};
-  // LDS: offsets, weights of both groups; a bit per input that either names, each group's claimed ones, the first slot of every 32 inputs,
-  // counts of the threads' and of sixteen threads' slots, slots of repeated terms
+  HCNN_HOSTDEV static uint32_t groups(const MacArgs& a) { return SETS == 1 ? a.pack : (uint32_t)SETS; }
+  // LDS: offsets, weights of every set; a bit per input that a group names, each group's claimed ones, the first slot of every 32 inputs,
+  // counts of the threads' and of sixteen threads' slots and their sum, slots of repeated terms
   HCNN_HOSTDEV static uint32_t bit_words(uint32_t n_in) { return (n_in + 31) / 32; }
-  static size_t lds_bytes(size_t T, size_t n_in) { return ((2 * T + 63) / 64 * (64 + 512) + (n_in + 31) / 32 * 4 + kThreads + 16 + 4) * 4; }
+  static size_t lds_bytes(size_t groups, size_t T, size_t n_in) {
+    return ((groups * T + 63) / 64 * (64 + SETS * 256) + (n_in + 31) / 32 * (2 + groups) + kThreads + 16 + 4) * 4;
+  }
   static uint32_t tile_blocks(const MacArgs& a) {
     const uint32_t per = a.steps * kStreams, tiles = 2 * a.k * a.n / kTile;
     return (tiles + per - 1) / per;
   }
-  static size_t grid(const MacArgs& a) { return MacMatrix::grid(tile_blocks(a), (a.G + 1) / 2); }
+  static size_t grid(const MacArgs& a) { return MacMatrix::grid(tile_blocks(a), (a.G + groups(a) - 1) / groups(a)); }
 
   template <int PH>
   HCNN_HD static void phase(const MacArgs& a, unsigned bid, int tid, uint32_t* lds, Regs&) {
-    const uint32_t g_blocks = (a.G + 1) / 2;
+    const uint32_t n_grp = groups(a), g_blocks = (a.G + n_grp - 1) / n_grp;
     const uint32_t xcd = bid % kXcds, local = bid / kXcds;
-    const uint32_t tb = (local / g_blocks) * kXcds + xcd, g0 = local % g_blocks * 2;
+    const uint32_t tb = (local / g_blocks) * kXcds + xcd, g0 = local % g_blocks * n_grp;
     const uint32_t tiles = 2 * a.k * a.n / kTile, tile0 = tb * a.steps * kStreams;
     if (tile0 >= tiles) return;                                       // padding blocks (whole block)
-    const uint32_t cap = chunks(2 * a.T), bw = bit_words(a.n_in);
+    const uint32_t cap = chunks(n_grp * a.T), bw = bit_words(a.n_in);
     uint32_t* l_off = lds;
-    uint32_t* l_w = lds + cap * 64;                                   // [2][cap][256]
-    uint32_t* bits = l_w + cap * 512;
-    uint32_t* claim = bits + bw;                                      // [2][bw]
-    uint32_t* first = claim + 2 * bw;                                 // slots in front of a word's
+    uint32_t* l_w = lds + cap * 64;                                   // [SETS][cap][256]
+    uint32_t* bits = l_w + cap * SETS * 256;
+    uint32_t* claim = bits + bw;                                      // [n_grp][bw]
+    uint32_t* first = claim + n_grp * bw;                             // slots in front of a word's
     uint32_t* part = first + bw;                                      // [256 + 16]
-    uint32_t* count = part + kThreads + 16;                           // slots of repeated terms
+    uint32_t* total = part + kThreads + 16;                           // slots without the repeated terms'
+    uint32_t* count = total + 1;                                      // slots of repeated terms
     const uint32_t per = (bw + kThreads - 1) / kThreads, w0 = (uint32_t)tid * per, w1 = w0 + per < bw ? w0 + per : bw;     // words of this thread
     const uint32_t wave = wave_uniform((uint32_t)tid / 64), lane = (uint32_t)tid % 64;
     if constexpr (PH == 0) {
-      for (uint32_t i = tid; i < cap * 576 + 3 * bw; i += kThreads) lds[i] = 0;
+      for (uint32_t i = tid; i < cap * (64 + SETS * 256) + (1 + n_grp) * bw; i += kThreads) lds[i] = 0;
       if (tid == 0) *count = 0;
     } else if constexpr (PH == 1 || PH == 5) {
       uint32_t bad = 0;
-      for (uint32_t gi = 0; gi < 2 && g0 + gi < a.G; ++gi) {
-        const uint32_t* idx = a.idx + (size_t)(g0 + gi) * a.T;
+      const uint32_t here = g0 + n_grp <= a.G ? n_grp : a.G - g0;
+      for (uint32_t x = tid; x < here * a.T; x += kThreads) {
+        const uint32_t gi = quot(x, a.terms), t = x - gi * a.T;
+        const uint32_t src = a.idx[(size_t)(g0 + gi) * a.T + t];
         const int32_t* w = a.w + (size_t)(g0 + gi) * a.F * a.T;
-        for (uint32_t t = tid; t < a.T; t += kThreads) {
-          const uint32_t src = idx[t];
-          int32_t wf[16];
+        int32_t wf[kRows];
 #pragma unroll
-          for (uint32_t f = 0; f < 16; ++f) wf[f] = w[(size_t)(f < a.F ? f : a.F - 1) * a.T + t];        // (all loads together)
-          uint32_t any = 0;
+        for (uint32_t f = 0; f < kRows; ++f) wf[f] = w[(size_t)(f < a.F ? f : a.F - 1) * a.T + t];        // (all loads together)
+        uint32_t any = 0;
 #pragma unroll
-          for (uint32_t f = 0; f < 16; ++f) {
-            const bool beyond = (wf[f] > a.w_abs_max) | (wf[f] < -a.w_abs_max);
-            bad += beyond & (f < a.F);
-            if (beyond | (f >= a.F)) wf[f] = 0;
-            any |= (uint32_t)wf[f];
-          }
-          bad += src >= a.n_in;
-          if (src >= a.n_in || any == 0) continue;
-          const uint32_t word = src / 32, bit = 1u << (src % 32);
-          if constexpr (PH == 1) {
-            lds_or(bits + word, bit);
-          } else {
-            uint32_t slot;
-            if (lds_or(claim + gi * bw + word, bit) & bit) slot = part[kThreads + 15] + lds_add(count, 1);
-            else slot = first[word] + (uint32_t)__builtin_popcount(bits[word] & (bit - 1));
-            l_off[slot] = src * (2u * a.k * a.n * 4);                  // in bytes (the host checked that it fits)
-            uint8_t* bytes = reinterpret_cast<uint8_t*>(l_w + (gi * cap + slot / 64) * 256 + slot / 4 % 4 * 64 + slot / 16 % 4) + slot % 4;
+        for (uint32_t f = 0; f < kRows; ++f) {
+          const bool beyond = (wf[f] > a.w_abs_max) | (wf[f] < -a.w_abs_max);
+          bad += beyond & (f < a.F);
+          if (beyond | (f >= a.F)) wf[f] = 0;
+          any |= (uint32_t)wf[f];
+        }
+        bad += src >= a.n_in;
+        if (src >= a.n_in || any == 0) continue;
+        const uint32_t word = src / 32, bit = 1u << (src % 32);
+        if constexpr (PH == 1) {
+          lds_or(bits + word, bit);
+        } else {
+          uint32_t slot;
+          if (lds_or(claim + gi * bw + word, bit) & bit) slot = *total + lds_add(count, 1);
+          else slot = first[word] + (uint32_t)__builtin_popcount(bits[word] & (bit - 1));
+          l_off[slot] = src * (2u * a.k * a.n * 4);                  // in bytes (the host checked that it fits)
+          const uint32_t set = SETS == 1 ? 0 : gi, row = SETS == 1 ? gi * a.F : 0;
+          uint8_t* bytes = reinterpret_cast<uint8_t*>(l_w + (set * cap + slot / 64) * 256 + slot / 4 % 4 * 64 + slot / 16 % 4) + slot % 4 + row * 16;
 #pragma unroll
-            for (uint32_t f = 0; f < 16; ++f) bytes[f * 16] = (uint8_t)wf[f];
-          }
+          for (uint32_t f = 0; f < kRows; ++f)
+            if (SETS > 1 || f < a.F) bytes[f * 16] = (uint8_t)wf[f];
         }
       }
       if (PH == 1 && tb == 0)
@@ -1203,33 +1234,61 @@ struct MacPair : MacMatrix {
     } else if constexpr (PH == 3) {
       if (tid < 16) {
         uint32_t n = 0;
-        for (int i = 0; i < 16 * (tid + 1); ++i) n += part[i];
-        part[kThreads + tid] = n;                                     // up to the end of sixteen threads' words
+        for (int i = 0; i < 16; ++i) n += part[16 * tid + i];
+        part[kThreads + tid] = n;
       }
     } else if constexpr (PH == 4) {
-      uint32_t n = tid >= 16 ? part[kThreads + tid / 16 - 1] : 0;
+      uint32_t n = 0;
+      for (int i = 0; i < tid / 16; ++i) n += part[kThreads + i];
       for (int i = tid / 16 * 16; i < tid; ++i) n += part[i];
+      if (tid == kThreads - 1) *total = n + part[tid];
       for (uint32_t i = w0; i < w1; ++i) {
         first[i] = n;
         n += (uint32_t)__builtin_popcount(bits[i]);
       }
     } else {
-      const uint32_t used = wave_uniform(part[kThreads + 15] + *count);
-      Sums wsum[2];
+      const uint32_t used = wave_uniform(*total + *count);
+      Sums wsum[SETS];
 #pragma unroll
-      for (int gi = 0; gi < 2; ++gi) weight_sums(l_w + gi * cap * 256, chunks(used), lane, wsum[gi]);
+      for (int gi = 0; gi < SETS; ++gi) weight_sums(l_w + gi * cap * 256, chunks(used), lane, wsum[gi]);
       for (uint32_t st = 0; st < a.steps; ++st) {
         const uint32_t t = tile0 + st * kStreams + wave;
         if (t >= tiles) break;
-        U4 u[2][4];
-        tile<2, false>(a, t, l_off, l_w, cap * 256, (used + 15) / 16 * 16, lane, wsum, u);
+        U4 u[SETS][4];
+        tile<SETS, false>(a, t, l_off, l_w, cap * 256, (used + 15) / 16 * 16, lane, wsum, u);
 #pragma unroll
-        for (uint32_t gi = 0; gi < 2; ++gi)
+        for (uint32_t gi = 0; gi < SETS; ++gi)
 #pragma unroll
-          for (uint32_t r = 0; r < 4; ++r) store(a, lane / 16 * 4 + r, g0 + gi, t, lane, u[gi][r]);
+          for (uint32_t r = 0; r < 4; ++r) {
+            const uint32_t row = lane / 16 * 4 + r, in_set = SETS == 1 ? quot(row, a.filters) : 0;
+            if (SETS > 1 || in_set < n_grp) store(a, row - in_set * a.F, g0 + gi + in_set, t, lane, u[gi][r]);
+          }
       }
     }
   }
+};
+// MacPair, measured, us, the kernel above / this one: 16 filters x 576 terms (3 x 3 padded, 8 x 8 map), 64 groups, n = 8192, k = 10 1502 / 1249;
+// 12 x 144, 100 groups, k = 8 704 / 562; 16 x 25 (5 x 5, stride 2), 144 groups 523 / 439; 16 x 144, 36 groups, n = 16384, k = 16 1273 / 1000; no input
+// shared (2 x 2, stride 2), 16 x 192, 16 groups 356 / 352.
+// Bound: inputs from beyond L2.  The first of these gathers 13.7 GB (24 above) but misses L2 for 8.5 GB of them (5.2 above, inputs
+// 2.7): 256 waves of a die are at twice as many tiles, 8 MiB of inputs, and drift apart.  Measured and left out, same layer: a wave per quarter of the
+// slots, so that four share a tile (sums added through LDS: 1554, two barriers and four reductions per tile), tiles of 32
+// coefficients (8-byte loads: 1494), one wave per SIMD with two buffers of inputs (1425 - 1527).  A second loop body for the last terms
+// does not hold the sums in registers (100 spilled).
+struct MacPair : MacUnion<2> {
+  // Tiles per wave at most.  A union leaves out the terms without weight, so that the workgroups at a map's padded border are done sooner and
+  // neighbours drift apart in L2, the more the longer they run; shorter runs build the union more often.  Long rows take four tiles: us, 8 /
+  // 4 tiles, 16 filters, n = 8192, 3 x 3 padded: 576 terms, 64 groups, k = 10 1339 / 1256, 100 groups, k = 8 1967 / 1815 (with weights on the
+  // padding too 1593 / 1620), 504, 144 groups 2484 / 2305; 5 x 5 padded, 600, 144 groups 2043 / 1824.  Without padding they cost up to 8 %:
+  // 5 x 5, 600 terms, 64 groups 966 / 1046, 1000 of k = 6 +5 %, 2 x 2, 800 of k = 4 +2 %.  Below, the loss is larger than the gain: 3 x 3
+  // padded, 360 terms, 144 groups -7 %, 288, 64 groups 686 / 698; without padding 400 (5 x 5), 64 groups +9 %, 12 x 144, 100 groups 562 / 591;
+  // 25 (5 x 5, stride 2), 144 groups 436 / 500.
+  static uint32_t max_steps(const MacArgs& a) { return a.T >= 512 ? 4 : 8; }
+  static size_t lds_bytes(size_t T, size_t n_in) { return MacUnion<2>::lds_bytes(2, T, n_in); }
+};
+struct MacPack : MacUnion<1> {
+  static constexpr uint32_t kLeastPerUnit = 2;
+  static uint32_t max_steps(const MacArgs&) { return 8; }
 };
 
 // ---------------------------------------------------------------- helpers for KeyGen / Encrypt / Decrypt

@@ -345,6 +345,7 @@ template <int A, int B, int C> struct KernelClass<TensorFused<A, B, C>> { static
 template <int F, bool S> struct KernelClass<MacKernel<F, S>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <int B> struct KernelClass<MacMfma<B>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <> struct KernelClass<MacPair> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
+template <> struct KernelClass<MacPack> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 template <int F> struct KernelClass<MacKernelDirect<F>> { static constexpr int id = HCNN_PROF_SCALAR_MAC; };
 
 int take_event(hcnn_ctx* c, hcnn_event_t* ev) {
@@ -819,7 +820,8 @@ int mac_launch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
 }
 
 // Tiles per wave of a matrix form: up to K::max_steps, so that staging the tables is spread over many coefficients; fewer while the
-// launch would not hold several rounds of workgroups, or while half as many leave the fullest die a sixth less to do.  The dies take whole
+// launch would not hold several rounds of workgroups (MacPack, whose unions take longest to stage: half as many; 4 filters x 18 terms, 16 groups, n =
+// 8192, k = 6 at one / two tiles 18.9 / 15.6), or while half as many leave the fullest die a sixth less to do.  The dies take whole
 // blocks of tiles: 1 to 4 blocks leave half of them idle, 9 to 12 are two rounds of which the second is half empty, 17 to 20 three (us, twice the
 // tiles / these: 10 filters x 1601 terms, 130 groups, n = 1024, k = 2 1304 / 238; 16 x 1700, 130 groups, n = 8192, k = 3 2585 / 2015, k = 5 3773 /
 // 3218; 16 x 1200, 256 groups, n = 2048, k = 3 861 / 752; 16 x 144, 361 groups 321 / 267; over unions 16 x 288, 196 groups, n = 4096, k = 3 491 /
@@ -835,7 +837,7 @@ uint32_t mac_matrix_steps(const hcnn_ctx* c, const MacArgs& a) {
   uint32_t steps = K::max_steps(a);
   while (steps > 1) {
     const uint32_t half = fullest_die(steps / 2), full = fullest_die(steps);       // (leaves b.steps = steps)
-    if (K::grid(b) >= 4 * (size_t)c->compute_units && 6 * half > 5 * full) break;
+    if (K::grid(b) >= K::kLeastPerUnit * (size_t)c->compute_units && 6 * half > 5 * full) break;
     steps /= 2;
   }
   return steps;
@@ -845,6 +847,7 @@ template <class K>
 int mac_matrix_launch(hcnn_ctx* c, const MacArgs& a, size_t lds_bytes) {
   MacArgs b = a;
   b.steps = mac_matrix_steps<K>(c, a);
+  b.terms = fast_div(a.T); b.filters = fast_div(a.F);
   return run<K>(c, K::grid(b), lds_bytes, b);
 }
 
@@ -900,12 +903,37 @@ bool mac_takes_pairs(const hcnn_ctx* c, const MacArgs& a) {
          mac_matrix_serial_tiles<MacMfma<2>>(c, a, sm) * (2 * T + 150 + T / sm);
 }
 
+// Groups of few filters that a call sums side by side in the sixteen rows of the matrix form (MacPack), over the union of their inputs; 0: it
+// takes the vector form.  Both forms were timed on 400 convolutions of up to 8 filters (all rings, 2 x 2 to 5 x 5, strides 1 and 2, up
+// to 64 channels, maps up to 32 x 32):
+// - Inputs gathered 3.5 times or more: geometric mean vector / pack 1.33, at 9 times and more 1.47; of 230 calls three lose more than 3 % (9 terms, 6
+//   filters, n = 8192, k = 4 25.4 / 28.0 us).  Us: 5 x 25, stride 2, 144 groups, n = 8192, k = 8 224 / 174; 8 x 72, padded, 100 groups, k = 6 271 / 195;
+//   8 x 288, 36 groups, n = 2048, k = 3 71 / 30; 1 x 72, padded 150 / 90.
+// - Less often: the union saves little, and reading the inputs bounds either form (2 x 2 without overlap, 1 to 8 filters, n = 4096, k = 4 46-63 / 55-65;
+//   3 x 3 at stride 2, gathered 1.7 times, n = 16384, k = 8, 4 filters 178 / 199, 8 filters 223 / 222; between 2.5 and 3.5 times as many gain as lose).
+//   A call whose neighbours share nothing, however often its inputs are gathered, loses too (rows are not known here).
+// - Fewer than 3/4 workgroups per compute unit with a tile per wave: the union's terms run one after another (1 x 125, 64 groups, n = 2048, k = 2 12 / 19).
+uint32_t mac_pack_groups(const hcnn_ctx* c, const MacArgs& a) {
+  const uint64_t w_max = a.w_abs_max > 0 ? (uint64_t)a.w_abs_max : 1;
+  if (a.F > 8 || a.w_abs_max > 127 || a.T * w_max > kMfmaMaxSum || (uint64_t)a.n_in * 2 * a.k * a.n * 4 > 0xffffffffull) return 0;
+  MacArgs b = a;
+  b.pack = 16 / a.F;
+  b.steps = 1;
+  if (2 * (uint64_t)a.G * a.T < 7 * (uint64_t)a.n_in || 4 * MacPack::grid(b) < 3 * (size_t)c->compute_units) return 0;
+  return MacPack::lds_bytes(b.pack, a.T, a.n_in) <= std::min<size_t>(64 * 1024, c->max_lds) ? b.pack : 0;
+}
+
 int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
   switch (mac_matrix_groups(c, grid, a)) {
     case 2:
       if (mac_takes_pairs(c, a)) return mac_matrix_launch<MacPair>(c, a, MacPair::lds_bytes(a.T, a.n_in));
       return mac_matrix_launch<MacMfma<2>>(c, a, MacMfma<2>::lds_bytes(a.T));
     case 1: return mac_matrix_launch<MacMfma<1>>(c, a, MacMfma<1>::lds_bytes(a.T));
+  }
+  if (const uint32_t pack = mac_pack_groups(c, a)) {
+    MacArgs b = a;
+    b.pack = pack;
+    return mac_matrix_launch<MacPack>(c, b, MacPack::lds_bytes(b.pack, a.T, a.n_in));
   }
   switch (a.F) {
     case 1: return mac_launch<1>(c, grid, a);

@@ -66,6 +66,7 @@ def rules():
         lib = ctypes.CDLL(build(["-O0"], _OUT.replace("libhcnn_emu", "libhcnn_rules"), os.path.join(_ROOT, "tests", "host_rules.cpp")))
         lib.rule_mac_matrix_groups.argtypes = [ctypes.c_uint32] * 7 + [ctypes.c_int32]
         lib.rule_mac_takes_pairs.argtypes = [ctypes.c_uint32] * 6
+        lib.rule_mac_pack_groups.argtypes, lib.rule_mac_pack_groups.restype = [ctypes.c_uint32] * 7 + [ctypes.c_int32], ctypes.c_uint32
         lib.rule_mac_matrix_steps.argtypes, lib.rule_mac_matrix_steps.restype = [ctypes.c_uint32] * 6, ctypes.c_uint32
         lib.rule_mac_matrix_lds.argtypes, lib.rule_mac_matrix_lds.restype = [ctypes.c_uint32, ctypes.c_size_t], ctypes.c_size_t
         lib.rule_decrypt_lds.restype = ctypes.c_size_t

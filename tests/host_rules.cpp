@@ -20,6 +20,14 @@ int rule_mac_takes_pairs(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in, 
   a.k = k; a.n = n; a.n_in = n_in; a.G = G; a.T = T;
   return mac_takes_pairs(&c, a);
 }
+// Groups that a call of few filters sums side by side, 0: the vector form.
+uint32_t rule_mac_pack_groups(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in, uint32_t G, uint32_t F, uint32_t T, int32_t w_abs_max) {
+  hcnn_ctx c;
+  c.compute_units = units; c.max_lds = max_lds_bytes();
+  MacArgs a{};
+  a.k = k; a.n = n; a.n_in = n_in; a.G = G; a.F = F; a.T = T; a.w_abs_max = w_abs_max;
+  return mac_pack_groups(&c, a);
+}
 // Tiles per wave of MacMfma<1> (groups = 1), MacMfma<2> (2) or MacPair (0).
 uint32_t rule_mac_matrix_steps(uint32_t groups, uint32_t units, uint32_t n, uint32_t k, uint32_t G, uint32_t T) {
   hcnn_ctx c;

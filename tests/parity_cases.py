@@ -243,6 +243,29 @@ PAIR_CASES = [                  # c_in, side, f, stride, pad, F, base, (n, k)
 ]
 
 
+PACK_CASES = [                  # as above, for groups of few filters side by side: rings whose launches are large enough on the device
+    (3, 6, 3, 1, 1, 5, 0, (1024, 3)),           # three groups a set, unions of 27 to 60
+    (5, 6, 3, 1, 0, 8, 0, (1024, 3)),           # two, filling the rows
+    (8, 6, 3, 1, 1, 2, 31, (1024, 5)),          # eight, a last set of four, unions of several chunks
+    (4, 7, 3, 1, 0, 3, 0, (1024, 6)),           # five
+    (2, 7, 3, 1, 0, 6, 0, (2048, 3)),           # two, four rows unused, a last set with one
+    (11, 5, 3, 1, 1, 7, 0, (1024, 3)),          # 99 terms: half a chunk over
+]
+
+
+def check_scalar_mac_one_filter(backend, n, k):
+    """Sixteen groups side by side, a last set of four: 100 placements of one 5 x 5 filter."""
+    s = Setup(backend, n, k, with_keys=False)
+    idx, _, _ = layers.conv_index_table(1, 14, 14, 5, 5, 1, 0)
+    cts = gen.uniform_residues(s.rng, s.q, n, lead=(196, 2))
+    w = gen.int_weights(s.rng, (100, 1, 25), 127)
+    w[0], w[1], w[99] = 127, -127, 0
+    out = backend.host(s.ctx.ct_scalar_mac(backend.dev(cts), backend.dev(idx.astype(np.uint32)), backend.dev(w), 127))
+    for g in range(100):
+        assert np.array_equal(out[0, g], fv.scalar_mac(s.octx, cts, idx[g], w[g, 0])), g
+    s.ctx.close()
+
+
 def check_scalar_mac_matrix_tiles(backend, k, G, F, T, bound, blocks=None, n=1024):
     """The matrix form of the scalar MAC where its waves go through several tiles of coefficients; `blocks`: the
     workgroups that the launch must have.  All coefficients of outputs at the edges and in the middle."""

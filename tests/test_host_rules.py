@@ -82,6 +82,18 @@ def test_calls_that_form_the_union_of_two_rows(rules, n, k, n_in, G, T, pairs):
     assert rules.rule_mac_takes_pairs(256, n, k, n_in, G, T) == pairs
 
 
+@pytest.mark.parametrize("n,k,n_in,G,F,T,bound,groups", [
+    (8192, 8, 784, 144, 5, 25, 15, 3), (8192, 8, 784, 144, 1, 25, 127, 16), (8192, 8, 784, 144, 8, 25, 15, 2), (8192, 8, 784, 144, 9, 25, 15, 0),
+    (8192, 8, 784, 144, 5, 25, 128, 0),                                            # weights beyond a signed byte
+    (8192, 8, 800, 112, 5, 25, 15, 3), (8192, 8, 801, 112, 5, 25, 15, 0),          # inputs gathered 3.5 times
+    (2048, 2, 720, 64, 1, 125, 15, 0), (2048, 3, 720, 64, 1, 125, 15, 16),         # 128, 192 workgroups
+    (8192, 8, 8191, 1200, 2, 27, 15, 8), (8192, 8, 8192, 1200, 2, 27, 15, 0),      # inputs of 4 GiB
+    (1024, 1, 1000, 10000, 8, 1568, 15, 2), (1024, 1, 1000, 10000, 8, 1569, 15, 0),    # tables of 64 KiB
+])
+def test_calls_of_few_filters_that_sum_groups_side_by_side(rules, n, k, n_in, G, F, T, bound, groups):
+    assert rules.rule_mac_pack_groups(256, n, k, n_in, G, F, T, bound) == groups
+
+
 def test_network_plan_puts_16_outputs_into_rows_that_the_matrix_form_takes(rules):
     """The length and the weights up to which the plan relies on the matrix form for rows that the vector form cannot stage."""
     T, weight = network._MATRIX_TERMS, network._MATRIX_WEIGHT
