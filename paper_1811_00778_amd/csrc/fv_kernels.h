@@ -185,8 +185,9 @@ struct ExtKernel {
     };
     const int32_t v = untraced((int32_t)bconv_round(S, a.band, exact, a.fallback_counter));
     // (rows 0..K-1 of `out` are not written: the forward transform reads those limbs from the ciphertext itself)
-    // rolled loop over the destination primes: row j of the transposed table is one contiguous scalar load
-#pragma unroll 1
+    // rolled loop over the destination primes (three at a time for short bases, whose small launches wait for the tables: one squaring of 8 primes
+    // at n = 8192 34.4 / 34.1 us with the same in the scaling): row j of the transposed table is one contiguous scalar load
+#pragma unroll (K <= 8 ? 3 : 1)
     for (uint32_t j = 0; j < kp; ++j) {
       const BConvDst d = ldc_at(a.bc.dst + j, 0u);
       dst[(size_t)(K + j) * n] = bconv_reduce(bconv_sum<K>((int64_t)v * d.v, z, a.bc.BT + (size_t)j * K, 1, d.rc), d);
@@ -217,7 +218,8 @@ struct ScaleArgs {
 // y_j is produced, used at once for the p -> q conversion (k running 64-bit sums) and parked in the LDS column for the exact
 // path, so the register footprint is 3k + O(1) and the code size does not grow with k*k'.
 // Bound: memory up to k = 8 (3 L rows read, 3 k written: 4.7 TB/s), the multiply-adds and reductions beyond.
-// HALVES (n = 32768): d holds rows without the last stage of their inverse transforms.  The stage is one more product of every residue: its
+// HALVES (log2(n) odd): d holds rows without the last stage of their inverse transforms (n = 32768, and calls of one or two ciphertexts; n = 8192 keeps
+// whole rows otherwise: 720 squarings 1977 us, 1993 by halves; 30 of 16 primes 271, 277).  The stage is one more product of every residue: its
 // constants carry the factor that the residue is multiplied with here (z_i directly, or the sum's term of p_j), so that it needs no
 // reduction of its own.  A wave takes the same 32 positions of both halves: its two loads of a row are a cache line each.  (The same words read by
 // waves of the two halves instead, and the stage by itself with constants picked per lane: 32 ciphertexts, k = 24 530 and 426 us; without the stage 313.)
@@ -289,7 +291,7 @@ struct ScaleKernel {
     for (int i = 0; i < K; ++i) out_acc[i] = 0;
     uint32_t S2 = 0, room = kSumRoom;
     Words dp_next = load(K);
-#pragma unroll 1
+#pragma unroll (K <= 8 ? 3 : 1)
     for (uint32_t j = 0; j < kp; ++j) {
       const Words dpj = dp_next;
       if (j + 1 < kp) dp_next = load(K + j + 1);

@@ -279,7 +279,7 @@ struct hcnn_ctx {
   TwTable d_tw_fwd{}, d_tw_inv{};   // [k + kp][n/2]
   EncScale* d_delta = nullptr;      // [k]
   int32_t* d_tq_inv = nullptr;      // [kp] t * q^-1 mod p_j
-  SplitRoot* d_scale_root = nullptr;   // [2][k + kp], n = 32768: last inverse stage and the scaling's first factor in one
+  SplitRoot* d_scale_root = nullptr;   // [2][k + kp], log2(n) odd: last inverse stage and the scaling's first factor in one
   BConvDev ext{}, to_p{}, to_q{}, dec{};
   uint32_t* d_gauss_t = nullptr;    // thresholds of the Gaussian sampler (uploaded on first use)
   uint32_t* d_dec_tab = nullptr;    // [k][3] constants of the decrypt rounding
@@ -596,7 +596,7 @@ int build_tables(hcnn_ctx* c) {
     std::vector<int32_t> tq;
     for (uint32_t pj : c->p) tq.push_back(h_mont(h_mulmod((uint32_t)(c->t % pj), h_inv(h_prod_mod(c->q, -1, pj), pj), pj), pj));
     if ((e = upload(c, tq, &c->d_tq_inv))) return e;
-    if (c->logn == 15) {
+    if (c->logn % 2 == 1) {
       std::vector<SplitRoot> root;
       for (uint32_t half = 0; half < 2; ++half)
         for (uint32_t l = 0; l < L; ++l) {
@@ -672,6 +672,13 @@ struct NttRows {
   const RelinPair* pair = nullptr;
 };
 
+// Do the squaring's transforms of `rows` rows (out of place, log2(n) odd) run as two workgroups per row?  n = 32768 always; otherwise while both
+// halves of every row find a compute unit of their own: half as many waves share one then (n = 8192, us: one squaring of 8 primes 38.0 / 34.5, of 4
+// 33.1 / 29.2, of 12 52.6 / 49.8, two of 8 42.4 / 38.6).
+bool splits_rows(const hcnn_ctx* c, size_t rows) {
+  return c->logn == 15 || (c->logn % 2 == 1 && (kSharedAll || 2 * rows <= c->compute_units));
+}
+
 template <int LOGN, int LOGR>
 int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   NttArgs a{};
@@ -688,14 +695,22 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   a.pair = r.pair; a.k = c->k;
   const size_t lds = NttGeom<LOGN, LOGR>::kLdsBytes;
   if (inverse) {
-    // n = 32768: two workgroups per row, where the reader takes the last stage (4800 tensor rows 427 us with one, 348 with two; 3072
-    // rows of the shared basis 250, 195)
-    constexpr int kSplit = LOGN == 15;
-    constexpr size_t lds_s = NttGeom<LOGN - kSplit, LOGR>::kLdsBytes;
-    using Square = NttInv<LOGN, LOGR, kNttLoadTensor, kSplit>;
-    using Product = NttInv<LOGN, LOGR, kNttLoadTensorMul, kSplit>;
-    if (io == kNttLoadTensor) return run<Square>(c, Square::grid(r.rows), lds_s, a, r.rows);
-    if (io == kNttLoadTensorMul) return run<Product>(c, Product::grid(r.rows), lds_s, a, r.rows);
+    // Two workgroups per row where the reader takes the last stage: n = 32768 (4800 tensor rows 427 us with one, 348 with two; 3072
+    // rows of the shared basis 250, 195), and launches that leave compute units idle otherwise
+    constexpr int kCanSplit = LOGN % 2;
+    constexpr size_t lds_s = NttGeom<LOGN - kCanSplit, LOGR>::kLdsBytes;
+    if (kCanSplit && (io == kNttLoadTensor || io == kNttLoadTensorMul) && splits_rows(c, r.rows)) {
+      using Square = NttInv<LOGN, LOGR, kNttLoadTensor, kCanSplit>;
+      using Product = NttInv<LOGN, LOGR, kNttLoadTensorMul, kCanSplit>;
+      if (io == kNttLoadTensor) return run<Square>(c, Square::grid(r.rows), lds_s, a, r.rows);
+      return run<Product>(c, Product::grid(r.rows), lds_s, a, r.rows);
+    }
+    if constexpr (LOGN < 15) {
+      using Square = NttInv<LOGN, LOGR, kNttLoadTensor>;
+      using Product = NttInv<LOGN, LOGR, kNttLoadTensorMul>;
+      if (io == kNttLoadTensor) return run<Square>(c, Square::grid(r.rows), lds, a, r.rows);
+      if (io == kNttLoadTensorMul) return run<Product>(c, Product::grid(r.rows), lds, a, r.rows);
+    }
     if (io == kNttStoreAdd) return run<NttInv<LOGN, LOGR, kNttStoreAdd>>(c, r.rows, lds, a);
     if constexpr (LOGN == 15) {
       using Back = NttInv<LOGN, LOGR, kNttBackRow, 1>;
@@ -738,6 +753,19 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
     }
     return io == kNttPlain ? run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a) : HCNN_ERR_ARG;
   } else {
+    if constexpr (LOGN % 2 == 1) {
+      if (r.in != r.out && splits_rows(c, r.rows)) {
+        const size_t lds_h = NttGeom<LOGN - 1, LOGR>::kLdsBytes;
+        if (io == kNttLoadDigit) {
+          using K = NttFwd<LOGN, LOGR, kNttLoadDigit, 1>;
+          return run<K>(c, K::grid(ntt_grouped_grid(r.rows, r.cycle)), lds_h, a, r.rows);
+        }
+        if (io == kNttStoreLazy) {
+          using K = NttFwd<LOGN, LOGR, kNttStoreLazy, 1>;
+          return run<K>(c, K::grid(r.rows), lds_h, a, r.rows);
+        }
+      }
+    }
     if constexpr (LOGN == 14 || kSharedAll) {
       if (io == kNttDigitTile)
         return run<NttFwd<LOGN, LOGR, kNttDigitTile>>(c, ntt_grouped_grid(r.rows, r.cycle), lds, a, r.rows);
@@ -793,7 +821,7 @@ int ext_dispatch(hcnn_ctx* c, size_t grid, const ExtArgs& a) {
 
 int scale_dispatch(hcnn_ctx* c, size_t grid, const ScaleArgs& a) {
   switch (c->k) {
-#define HCNN_SCALE_CASE(K) case K: return c->logn == 15 ? run<ScaleKernel<K, true>>(c, grid, ScaleKernel<K, true>::lds_bytes(c->kp), a) \
+#define HCNN_SCALE_CASE(K) case K: return a.root ? run<ScaleKernel<K, true>>(c, grid, ScaleKernel<K, true>::lds_bytes(c->kp), a) \
                                                         : run<ScaleKernel<K, false>>(c, grid, ScaleKernel<K, false>::lds_bytes(c->kp), a);
     HCNN_EVERY_K(HCNN_SCALE_CASE)
 #undef HCNN_SCALE_CASE
@@ -1404,10 +1432,11 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     uint32_t* const b_acc = dig + (shared ? cc * kSharedPrimes : (cc - nf) * k) * k * rn;
     // 1. centred lift of c0, c1 extended to the auxiliary primes (only the new rows are written);
     // 2. forward NTT over all k + k' limbs, the first k read from the ciphertext itself
-    // (n = 32768, separate kernels: the new rows are staged in the array of the tensor, free until step 3, because the two-workgroup
-    // transform of that ring cannot work in place)
+    // (forward rows by two workgroups: the new rows are staged in the array of the tensor, free until step 3, because that transform
+    // cannot work in place)
     const bool tensor_fused = takes_tensor_fused(cc);
-    uint32_t* const b_new = c->logn == 15 && !tensor_fused ? b_d : b_ext;
+    const bool staged = !tensor_fused && splits_rows(c, cc * 2 * L);
+    uint32_t* const b_new = staged ? b_d : b_ext;
     ExtArgs ea;
     ea.in = in + c0 * ct_words; ea.out = b_new; ea.bc = c->ext; ea.n = n; ea.band = c->band;
     ea.fallback_counter = c->d_counters;
@@ -1434,7 +1463,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
       return e;
     }
     if (in_b) {
-      uint32_t* const b_new_b = c->logn == 15 ? b_d : b_ext_b;
+      uint32_t* const b_new_b = staged ? b_d : b_ext_b;
       ea.in = in_b + c0 * ct_words; ea.out = b_new_b;
       if ((e = ext_dispatch(c, cc * 2 * bpp, ea))) return e;
       if ((e = ntt_dense(c, b_new_b, b_ext_b, cc * 2 * L, L, false, kNttStoreLazy, in_b + c0 * ct_words, k))) return e;
@@ -1446,8 +1475,9 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
       if ((e = ntt_dense(c, b_ext, b_d, cc * 3 * L, L, true, kNttLoadTensor))) return e;
     }
     // 5. y = round(t/q * d) mod q
+    const bool by_halves = c->logn == 15 || (!tensor_fused && splits_rows(c, cc * 3 * L));
     ScaleArgs sa;
-    sa.d = b_d; sa.y = b_y; sa.to_p = c->to_p; sa.to_q = c->to_q; sa.tq_inv = c->d_tq_inv; sa.limbs = c->d_limbs; sa.root = c->d_scale_root; sa.n = n;
+    sa.d = b_d; sa.y = b_y; sa.to_p = c->to_p; sa.to_q = c->to_q; sa.tq_inv = c->d_tq_inv; sa.limbs = c->d_limbs; sa.root = by_halves ? c->d_scale_root : nullptr; sa.n = n;
     sa.band = c->band; sa.fallback_counter = c->d_counters;
     if ((e = scale_dispatch(c, cc * 3 * bpp, sa))) return e;
     if (shared) return relin_shared(c, b_y, cc, b_dig, b_acc, b_d, out + c0 * ct_words);     // (the tensor's rows, 3L > 4k + 4, are free by now)

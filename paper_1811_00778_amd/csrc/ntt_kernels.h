@@ -577,9 +577,9 @@ struct NttFwd {
 };
 
 // ------------------------------------------------------------------------- inverse
-// SPLIT = 1: two workgroups per row, all stages but the last, which joins the halves: the reader of the row takes it while loading
-// (split_root).  The halves are left signed in (-p, p), without the output scaling.  Half the LDS and half the threads per
-// workgroup, as in the forward transform, and no pass of five stages.
+// SPLIT = 1 (odd log2(n)): two workgroups per row, all stages but the last, a single one that joins the halves: the reader of the row takes it while
+// loading (split_root).  The halves are left signed in (-p, p), without the output scaling.  Half the LDS and half the threads per
+// workgroup, as in the forward transform, and (n = 32768) no pass of five stages.
 template <int LOGN, int LOGR, int IO = kNttPlain, int SPLIT = 0>
 struct NttInv {
   static_assert(SPLIT == 0 || (SPLIT == 1 && LOGN % 2 == 1 && (IO == kNttLoadTensor || IO == kNttLoadTensorMul || IO == kNttTensorRegs0 ||

@@ -45,6 +45,13 @@ def test_square_relin_shared_basis(n, k, count):
         pc.check_transform_ranges(backend, n)
 
 
+@pytest.mark.parametrize("n,k", [(2048, 3), (8192, 2)])
+def test_square_relin_rows_by_two_workgroups(n, k):
+    # (this build runs every squaring of these rings as the device runs its smallest ones)
+    pc.check_square_relin(SharedBasisBackend(), n, k, n_random=1, n_genuine=0)
+    pc.check_square_relin(SharedBasisBackend(), n, k, n_random=1, n_genuine=0, force_exact=True)
+
+
 @pytest.mark.parametrize("n,k,n_polys,rows", [(1024, 2, 3, None), (2048, 3, 2, 3), (4096, 2, 1, 2),
                                              (8192, 2, 1, 1), (16384, 1, 1, 1), (32768, 1, 10, 1)])
 def test_ntt_all_sizes(backend, n, k, n_polys, rows):
