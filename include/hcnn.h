@@ -242,7 +242,7 @@ enum {
                                     8 * floor(this / 8 / k) ciphertexts                         */
   HCNN_STAT_TENSOR_FUSED_WGS = 4 /* the same for the one-kernel squaring tensor, taken for internal batches whose
                                     n_ct * (k + k_aux) (ciphertext, limb) pairs fill their rounds of
-                                    this many workgroups to at least 7/8                        */
+                                    this many workgroups to at least 7/8, or are enough in number */
 };
 /* Synchronises the context's stream, then reads the counter. */
 int hcnn_get_stat(hcnn_ctx* ctx, int which, uint64_t* out);
@@ -265,9 +265,10 @@ enum {
                                    and the relinearisation (step 3: digit transforms, inner product
                                    with the key, inverse transforms; n <= 8192, and n = 16384 with at most 16
                                    primes).  0 (default) = chosen per internal batch: the tensor kernel for
-                                   batches that fill their rounds of its workgroups to at least 7/8, the
-                                   relinearisation kernel for as many ciphertexts as fill whole rounds, the
-                                   separate kernels for the rest and for small batches; n = 32768 with 12
+                                   batches that fill their rounds of its workgroups to at least 7/8 or have
+                                   enough of them (320 to 640, none at n = 16384), the relinearisation kernel
+                                   for as many ciphertexts as fill whole rounds and for 16 to 288 workgroups
+                                   (by the ring) more, the separate kernels for less; n = 32768 with 12
                                    primes (batches of 16 or more), 13 (5) or 18 (4) and n = 16384 with 16 or
                                    more (64) relinearise through four auxiliary primes shared by all digits
                                    instead; 1 = always the separate kernels; 2 = always the one-kernel forms

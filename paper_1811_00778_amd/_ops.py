@@ -207,16 +207,21 @@ class OpsMixin:
         the runtime reports for the compiled kernel; 0 when even one ciphertext's workgroups do not fit)."""
         return self.raw.stat(_capi.STAT_RELIN_FUSED_WGS) // 8 // self.k * 8
 
+    # workgroups from which the one-kernel tensor is taken however its rounds are filled
+    _TENSOR_LEAST = {1024: 448, 2048: 640, 4096: 320, 8192: 384, 32768: 320}
+
     def takes_tensor_fused(self, n_ct):
         """Does the default policy take the one-kernel squaring tensor for an internal batch of n_ct ciphertexts: its
-        (ciphertext, limb) pairs fill their rounds of resident workgroups to at least 7/8 (two workgroups per pair at n = 32768)."""
+        (ciphertext, limb) pairs fill their rounds of resident workgroups to at least 7/8 (two workgroups per pair at n = 32768), or are
+        enough whatever their rounds."""
         slots, wgs = self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS), n_ct * (self.raw.k + self.raw.k_aux) * (2 if self.n == 32768 else 1)
-        return 8 * wgs >= 7 * slots * -(-wgs // slots)
+        return 8 * wgs >= 7 * slots * -(-wgs // slots) or wgs >= self._TENSOR_LEAST.get(self.n, wgs + 1)
 
     def tensor_fused_threshold(self):
         """(ciphertext, limb) pairs of an internal batch from which the default policy takes the one-kernel squaring tensor
         however full its last round is (7/8 of seven rounds: from eight rounds on one more is always filled enough);
         takes_tensor_fused tells for smaller ones."""
+        # (from _TENSOR_LEAST on it is taken too)
         return -(-49 * self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS) // 8)
 
     def reset_stats(self):

@@ -279,14 +279,14 @@ struct hcnn_ctx {
   TwTable d_tw_fwd{}, d_tw_inv{};   // [k + kp][n/2]
   EncScale* d_delta = nullptr;      // [k]
   int32_t* d_tq_inv = nullptr;      // [kp] t * q^-1 mod p_j
-  SplitRoot* d_scale_root = nullptr;   // [2][k + kp], log2(n) odd: last inverse stage and the scaling's first factor in one
+  SplitRoot* d_scale_root = nullptr;   // [2][k + kp], n = 8192 and 32768: last inverse stage and the scaling's first factor in one
   BConvDev ext{}, to_p{}, to_q{}, dec{};
   uint32_t* d_gauss_t = nullptr;    // thresholds of the Gaussian sampler (uploaded on first use)
   uint32_t* d_dec_tab = nullptr;    // [k][3] constants of the decrypt rounding
   unsigned long long* d_counters = nullptr;   // [2]
 
   uint32_t* d_evk_hat = nullptr;
-  uint32_t* d_evk_shared = nullptr;  // [4][n/64][k][outputs][64], where the shared-basis relinearisation is in use
+  uint32_t* d_evk_shared = nullptr;  // behind d_evk_hat in its allocation: [4][n/64][k][outputs][64], where the shared-basis relinearisation is in use
   RelinPair* d_pair = nullptr;       // [outputs / 2]
   RelinCrt* d_crt = nullptr;         // [k]
   RelinCrtInv crt_inv{};
@@ -596,7 +596,7 @@ int build_tables(hcnn_ctx* c) {
     std::vector<int32_t> tq;
     for (uint32_t pj : c->p) tq.push_back(h_mont(h_mulmod((uint32_t)(c->t % pj), h_inv(h_prod_mod(c->q, -1, pj), pj), pj), pj));
     if ((e = upload(c, tq, &c->d_tq_inv))) return e;
-    if (c->logn % 2 == 1) {
+    if (c->logn == 13 || c->logn == 15) {
       std::vector<SplitRoot> root;
       for (uint32_t half = 0; half < 2; ++half)
         for (uint32_t l = 0; l < L; ++l) {
@@ -672,11 +672,16 @@ struct NttRows {
   const RelinPair* pair = nullptr;
 };
 
-// Do the squaring's transforms of `rows` rows (out of place, log2(n) odd) run as two workgroups per row?  n = 32768 always; otherwise while both
-// halves of every row find a compute unit of their own: half as many waves share one then (n = 8192, us: one squaring of 8 primes 38.0 / 34.5, of 4
-// 33.1 / 29.2, of 12 52.6 / 49.8, two of 8 42.4 / 38.6).
+// Do the squaring's forward transforms of `rows` rows (out of place) run as two workgroups per row?  n = 32768 always; n = 8192 while both
+// halves of every row find a compute unit of their own: half as many waves share one then (us: one squaring of 8 primes 38.0 / 34.5, of 4
+// 33.1 / 29.2, of 12 52.6 / 49.8, two of 8 42.4 / 38.6; n = 2048 gains nothing, four of 4 primes 26.9 / 28.3).
 bool splits_rows(const hcnn_ctx* c, size_t rows) {
-  return c->logn == 15 || (c->logn % 2 == 1 && (kSharedAll || 2 * rows <= c->compute_units));
+  return c->logn == 15 || (c->logn == 13 && (kSharedAll || 2 * rows <= c->compute_units));
+}
+// And the inverse transforms of the tensor's rows?  n = 32768 not while whole rows, but not all halves, find a compute unit of their own (two squarings
+// of 16 primes 154 / 158 us).
+bool splits_tensor_rows(const hcnn_ctx* c, size_t rows) {
+  return splits_rows(c, rows) && (c->logn != 15 || 2 * rows <= c->compute_units || rows > c->compute_units);
 }
 
 template <int LOGN, int LOGR>
@@ -697,20 +702,18 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
   if (inverse) {
     // Two workgroups per row where the reader takes the last stage: n = 32768 (4800 tensor rows 427 us with one, 348 with two; 3072
     // rows of the shared basis 250, 195), and launches that leave compute units idle otherwise
-    constexpr int kCanSplit = LOGN % 2;
+    constexpr int kCanSplit = LOGN == 13 || LOGN == 15;
     constexpr size_t lds_s = NttGeom<LOGN - kCanSplit, LOGR>::kLdsBytes;
-    if (kCanSplit && (io == kNttLoadTensor || io == kNttLoadTensorMul) && splits_rows(c, r.rows)) {
+    if (kCanSplit && (io == kNttLoadTensor || io == kNttLoadTensorMul) && splits_tensor_rows(c, r.rows)) {
       using Square = NttInv<LOGN, LOGR, kNttLoadTensor, kCanSplit>;
       using Product = NttInv<LOGN, LOGR, kNttLoadTensorMul, kCanSplit>;
       if (io == kNttLoadTensor) return run<Square>(c, Square::grid(r.rows), lds_s, a, r.rows);
       return run<Product>(c, Product::grid(r.rows), lds_s, a, r.rows);
     }
-    if constexpr (LOGN < 15) {
-      using Square = NttInv<LOGN, LOGR, kNttLoadTensor>;
-      using Product = NttInv<LOGN, LOGR, kNttLoadTensorMul>;
-      if (io == kNttLoadTensor) return run<Square>(c, Square::grid(r.rows), lds, a, r.rows);
-      if (io == kNttLoadTensorMul) return run<Product>(c, Product::grid(r.rows), lds, a, r.rows);
-    }
+    using SquareRow = NttInv<LOGN, LOGR, kNttLoadTensor>;
+    using ProductRow = NttInv<LOGN, LOGR, kNttLoadTensorMul>;
+    if (io == kNttLoadTensor) return run<SquareRow>(c, SquareRow::grid(r.rows), lds, a, r.rows);
+    if (io == kNttLoadTensorMul) return run<ProductRow>(c, ProductRow::grid(r.rows), lds, a, r.rows);
     if (io == kNttStoreAdd) return run<NttInv<LOGN, LOGR, kNttStoreAdd>>(c, r.rows, lds, a);
     if constexpr (LOGN == 15) {
       using Back = NttInv<LOGN, LOGR, kNttBackRow, 1>;
@@ -753,7 +756,7 @@ int ntt_launch(hcnn_ctx* c, const NttRows& r, bool inverse, int io) {
     }
     return io == kNttPlain ? run<NttFwd<LOGN, LOGR>>(c, r.rows, lds, a) : HCNN_ERR_ARG;
   } else {
-    if constexpr (LOGN % 2 == 1) {
+    if constexpr (LOGN == 13) {
       if (r.in != r.out && splits_rows(c, r.rows)) {
         const size_t lds_h = NttGeom<LOGN - 1, LOGR>::kLdsBytes;
         if (io == kNttLoadDigit) {
@@ -1177,7 +1180,6 @@ int hcnn_ctx_destroy(hcnn_ctx* c) {
   for (auto ev : c->free_events) event_destroy(ev);
   for (void* p : c->owned) dev_free(p);
   if (c->d_evk_hat) dev_free(c->d_evk_hat);
-  if (c->d_evk_shared) dev_free(c->d_evk_shared);
   if (c->work) dev_free(c->work);
   if (c->small_work) dev_free(c->small_work);
   delete c;
@@ -1216,28 +1218,25 @@ int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
   if (!c || !evk_dev) return HCNN_ERR_NULL;
   if (!aligned16(evk_dev)) return HCNN_ERR_ALIGN;
   const size_t rows = (size_t)c->k * 2 * c->k;
+  const size_t shared_rows = shared_basis_min(c) ? (size_t)c->k * shared_outputs(c->k) : 0;
+  int e;
   if (!c->d_evk_hat) {
+    // one allocation for both (a second one of exactly 64 MiB takes a millisecond to free; a device that cannot spare the copy, twice the
+    // key's memory, keeps the other forms)
     void* ptr = nullptr;
-    int e = dev_malloc(&ptr, rows * c->n * 4);
-    if (e) return e;
+    const size_t own = rows * c->n, copy = shared_rows * kSharedPrimes * c->n;
+    if (copy && dev_malloc(&ptr, (own + copy) * 4) == 0) c->d_evk_shared = (uint32_t*)ptr + own;
+    else if ((e = dev_malloc(&ptr, own * 4))) return e;
     c->d_evk_hat = (uint32_t*)ptr;
   }
-  int e = ntt_dense(c, evk_dev, c->d_evk_hat, rows, c->k, false, kNttStoreKey);
+  e = ntt_dense(c, evk_dev, c->d_evk_hat, rows, c->k, false, kNttStoreKey);
   if (e) return e;
-  if (shared_basis_min(c)) {
-    const size_t shared_rows = (size_t)c->k * shared_outputs(c->k);
-    if (!c->d_evk_shared) {
-      // (twice the key's memory: a device that cannot spare it keeps the other forms)
-      void* ptr = nullptr;
-      if (dev_malloc(&ptr, shared_rows * kSharedPrimes * c->n * 4) == 0) c->d_evk_shared = (uint32_t*)ptr;
-    }
-    for (uint32_t r = 0; r < kSharedPrimes && c->d_evk_shared; ++r) {
-      NttRows kr{evk_dev, c->d_evk_shared, shared_rows, 1, c->k + r, 1, 0, 1, r};
-      kr.digits = shared_outputs(c->k);
-      kr.tile_words = (uint32_t)(shared_rows * 64);
-      kr.pair = c->d_pair;
-      if ((e = ntt_rows(c, kr, false, kNttKeyTile))) return e;
-    }
+  for (uint32_t r = 0; r < kSharedPrimes && c->d_evk_shared; ++r) {
+    NttRows kr{evk_dev, c->d_evk_shared, shared_rows, 1, c->k + r, 1, 0, 1, r};
+    kr.digits = shared_outputs(c->k);
+    kr.tile_words = (uint32_t)(shared_rows * 64);
+    kr.pair = c->d_pair;
+    if ((e = ntt_rows(c, kr, false, kNttKeyTile))) return e;
   }
   c->has_key = true;
   return HCNN_OK;
@@ -1293,6 +1292,27 @@ int hcnn_ct_scalar_mac(hcnn_ctx* c, const uint32_t* in, size_t n_in, const uint3
 // was created (query_fused_occupancy).  The rounds of these long-running kernels are sized from it.
 static size_t relin_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_units * c->relin_fused_wgs; }
 static size_t tensor_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_units * c->tensor_fused_wgs; }
+
+// Workgroups (ciphertext, prime) from which the one-kernel relinearisation takes `n_ct` ciphertexts that are not whole rounds of it, by
+// themselves or (with_rounds) behind whole rounds.  1800 squarings of 1 to 700 ciphertexts timed with either form, 256 compute units; time of a
+// squaring with this form / with the separate kernels: n = 1024, 16 workgroups 0.84-0.95, n = 2048, 36 to 40 0.88-0.99, n = 4096, 64 to 128 0.90-1.05,
+// more 0.8-0.95.  From n = 8192 on it matters whether the fullest die has a compute unit for each of its workgroups (the primes of a ciphertext share
+// a die): n = 8192 190 0.99, 208 to 240 0.91-0.96 where it has, 198 to 260 1.01-1.17 where not, 297 to 340 0.89-0.97; n = 16384 128
+// 1.0-1.04, 140 to 256 0.83-0.98 and 216 to 288 0.99-1.19, 320 0.97.
+constexpr uint32_t kRelinFusedMost = 288;
+static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds) {
+  static constexpr uint32_t least[5] = {16, 40, 96, 192, 136};              // n = 1024 .. 16384
+  const uint32_t l = least[c->logn - 10];
+  if (with_rounds) return l / 2;
+  return c->logn >= 13 && (n_ct + kXcds - 1) / kXcds * c->k > c->compute_units / kXcds ? kRelinFusedMost : l;
+}
+// Workgroups from which the one-kernel tensor is taken however its rounds are filled (the same measurements: with it / with two kernels, n =
+// 1024 from 448 0.95-1.0, n = 2048 from 640 0.9-1.03, n = 4096 from 320 0.88-1.01, n = 8192 from 384 0.94-1.01, n = 32768 from 320 0.93-1.02; n = 16384, 0.95-1.05
+// from 320 on, goes by its rounds alone).
+static size_t tensor_fused_least(uint32_t logn) {
+  static constexpr size_t least[6] = {448, 640, 320, 384, ~(size_t)0, 320};
+  return least[logn - 10];
+}
 
 // Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 4k, acc 4 and (largest ring only) z 4 rows an output
 // per ciphertext.
@@ -1357,9 +1377,8 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   // (At n = 16384 its 1024-thread workgroup fills a compute unit alone: measured +5..8 % up to 16 primes, no gain
   // with the in-loop folds of longer bases, which stay with the separate kernels; at n = 32768 a row and its sums
   // do not fit the registers of 1024 threads.)
-  // Its workgroups are long (k + 2 transforms each), so it only takes whole rounds of resident workgroups; what is
-  // left of a batch (all of a small batch) goes through the three separate kernels, which spread k^2 rows per
-  // ciphertext over the chip.
+  // Its workgroups are long (k + 2 transforms each): small batches go through the three separate kernels, which spread k^2
+  // rows per ciphertext over the chip (relin_fused_least).
   const size_t shared_min = c->fusion == 0 && !static_ws && c->d_evk_shared ? shared_basis_min(c) : 0;
   const bool fused = c->fusion != 1 && (c->logn <= 13 || (c->logn == 14 && k <= 16));
   // (the k workgroups of a ciphertext share a die, for its L2: a round is counted per die)
@@ -1383,7 +1402,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   if (C < 1) C = 1;
   if (C > n_ct) C = n_ct;
   // ciphertexts of one internal batch that can take the separate kernels
-  const size_t C_split = shared_min ? std::min(C, shared_min - 1) : (fused && fused_round) ? std::min(C, fused_round) : C;
+  const size_t C_split = shared_min ? std::min(C, shared_min - 1) : (fused && fused_round) ? std::min(C, std::min(fused_round, (size_t)kRelinFusedMost / k + 1)) : C;
   int e;
   uint32_t* ext = c->static_scratch;
   e = static_ws ? 0 : work_buffer(c, (C * words_main + std::max(C_split * words_split, shared_min ? C * words_shared : 0)) * 4, &ext);
@@ -1396,27 +1415,24 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   const size_t bpp = n / kEwThreads;                 // blocks per polynomial, 1 coefficient / thread
   const size_t bpr = n / (kEwThreads * kEwVec);      // blocks per row, 4 coefficients / thread
 
-  // How many ciphertexts of an internal batch of cc take the one-kernel relinearisation (steps 6-8 in one kernel
-  // for whole rounds of its workgroups: a row and its two 64-bit sums stay in registers).
+  // How many ciphertexts of an internal batch of cc take the one-kernel relinearisation (steps 6-8 in one kernel: a row and its two
+  // 64-bit sums stay in registers): all whole rounds of its workgroups, and what is left if that is enough by itself.
   auto fused_count = [&](size_t cc) -> size_t {
-    size_t nf = 0;
-    if (fused && fused_round) {
-      nf = cc / fused_round * fused_round;
-      // a last round joins when it is at least 3/8 full (3/4 if it is the only one): measured break-even points
-      const size_t rest = cc - nf;
-      if (nf ? rest * 8 >= fused_round * 3 : rest * 4 >= fused_round * 3) nf = cc;
-      if (c->fusion == 2) nf = cc;
-    }
-    return nf;
+    if (!fused || !fused_round) return 0;
+    if (c->fusion == 2) return cc;
+    const size_t whole = cc / fused_round * fused_round, rest = cc - whole;
+    return rest * k >= relin_fused_least(c, rest, whole != 0) ? cc : whole;
   };
   // Steps 2+3 in one kernel for squarings: its workgroups are long (five transforms), so it pays when they fill their
   // rounds.  Measured at n = 8192, k = 8: 1.06 us per ciphertext in full rounds against 1.25 of the two separate kernels
-  // (64 to 512 ciphertexts), a ratio of 0.85; at n = 32768, k = 24 15.5 against 18.8 (32), 0.82.
+  // (64 to 512 ciphertexts), a ratio of 0.85; at n = 32768, k = 24 15.5 against 18.8 (32), 0.82.  A last round that is only
+  // partly filled is shorter too (workgroups with a compute unit to themselves run faster), so that from tensor_fused_least
+  // workgroups on it pays whatever their number.
   auto takes_tensor_fused = [&](size_t cc) {
     if (in_b || c->fusion == 1) return false;
     const size_t wgs = c->logn == 15 ? 2 * cc * L : cc * L;                  // (n = 32768: two workgroups per pair)
     const size_t slots = tensor_fused_slots(c), rounds = (wgs + slots - 1) / slots;
-    return c->fusion == 2 || wgs * 8 >= rounds * slots * 7;
+    return c->fusion == 2 || wgs >= tensor_fused_least(c->logn) || wgs * 8 >= rounds * slots * 7;
   };
 
   // One internal batch: ciphertexts [c0, c0 + cc) of the call, nf of
@@ -1475,7 +1491,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
       if ((e = ntt_dense(c, b_ext, b_d, cc * 3 * L, L, true, kNttLoadTensor))) return e;
     }
     // 5. y = round(t/q * d) mod q
-    const bool by_halves = c->logn == 15 || (!tensor_fused && splits_rows(c, cc * 3 * L));
+    const bool by_halves = tensor_fused ? c->logn == 15 : splits_tensor_rows(c, cc * 3 * L);
     ScaleArgs sa;
     sa.d = b_d; sa.y = b_y; sa.to_p = c->to_p; sa.to_q = c->to_q; sa.tq_inv = c->d_tq_inv; sa.limbs = c->d_limbs; sa.root = by_halves ? c->d_scale_root : nullptr; sa.n = n;
     sa.band = c->band; sa.fallback_counter = c->d_counters;
