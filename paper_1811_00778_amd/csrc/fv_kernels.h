@@ -103,17 +103,30 @@ HCNN_HD uint32_t bconv_round(uint32_t S, uint32_t band, Exact exact, unsigned lo
 }
 
 // ---- generic (run-time ks, kd) helpers: per-thread columns in LDS -----------------------------
+// step(0 .. count - 1); FOURS: four at a time, so that their loads are in flight together (decryptions, us: 10 of 8 primes by halves, n = 8192
+// 16.0 / 14.1, 300 of 12 136 / 131, 60 of 16, n = 32768 210 / 200; up to three primes pay for the longer code: 900 of 3, n = 2048 37.4 / 39.4).
+template <bool FOURS, class Step>
+HCNN_HD void each_prime(uint32_t count, Step step) {
+  uint32_t i = 0;
+  if constexpr (FOURS) {
+    for (; i + 4 <= count; i += 4) {
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) step(i + j);
+    }
+  }
+  for (; i < count; ++i) step(i);
+}
 // Computes z_i (stored to zcol) and returns v.  gcol is a second private column for the exact path.
-template <class In>
+template <bool FOURS = false, class In>
 HCNN_HD uint32_t bconv_prepare(const BConvDev& bc, In in, uint32_t* zcol, uint32_t* gcol, int stride,
                                uint32_t band, unsigned long long* fallback_counter) {
   uint32_t S = 0;
-  for (uint32_t i = 0; i < bc.ks; ++i) {
+  each_prime<FOURS>(bc.ks, [&](uint32_t i) {
     const Mod m = ldc(bc.src_mod, i);
     const uint32_t z = shoup_mul(in(i), ldc(bc.zmul, i), m.p);
     zcol[i * stride] = z;
     S += frac_est(z, m);
-  }
+  });
   auto exact = [&]() {
     for (uint32_t i = 0; i < bc.ks; ++i) gcol[i * stride] = shoup_mul(in(i), ldc(bc.xmul, i), ldc(bc.src_mod, i).p);
     return garner_gt_half(bc, gcol, stride);
@@ -1403,11 +1416,17 @@ struct DecRoundArgs {
   uint64_t* m_out64;       // 64-bit ones
   BConvDev bc;             // source side only (zmul = t*(q/q_i)^-1, xmul = t)
   const uint32_t* tab;     // [k][3]: 16-bit pieces of b_i, least significant first
+  const uint32_t* cts;     // HALVES: [count][2][k][n]
+  const NttLimb* limbs;    // [k]
+  uint32_t plain_key;      // HALVES: 1 where the rows carry the factor 2^-32 of a product of two plain rows
   uint64_t t;
   uint32_t n;
   uint32_t band;
   unsigned long long* fallback_counter;
 };
+// HALVES: x holds c1*s without the last stage of its inverse transforms and without c0, both taken while loading (positions as in ScaleKernel).
+// FOURS: four primes or more (each_prime).
+template <bool HALVES, bool FOURS>
 struct DecRoundKernel {
   static constexpr int kThreads = kEwThreads;
   static constexpr int kPhases = 1;
@@ -1418,19 +1437,32 @@ struct DecRoundKernel {
     const uint32_t ks = a.bc.ks, n = a.n;
     const uint32_t per_poly = n / kThreads;
     const size_t poly = bid / per_poly;
-    const uint32_t c = (bid % per_poly) * kThreads + tid;
-    const uint32_t* src = a.x + poly * ks * n + c;
+    const uint32_t half = HALVES ? ((uint32_t)tid >> 5) & 1u : 0;
+    const uint32_t first = HALVES ? (bid % per_poly) * (kThreads / 2) + ((uint32_t)tid >> 6) * 32 + ((uint32_t)tid & 31u)
+                                  : (bid % per_poly) * kThreads + tid;
+    const uint32_t c = first + half * (n / 2);
+    const uint32_t* src = a.x + poly * ks * n + first;
     uint32_t* zcol = lds + tid;
     uint32_t* gcol = lds + (size_t)ks * kThreads + tid;
-    auto in = [&](uint32_t i) { return src[(size_t)i * n]; };
-    const uint32_t v = bconv_prepare(a.bc, in, zcol, gcol, kThreads, a.band, a.fallback_counter);
+    const uint32_t* c0 = HALVES ? a.cts + poly * 2 * ks * n + c : nullptr;
+    auto in = [&](uint32_t i) -> uint32_t {
+      const uint32_t* row = src + (size_t)i * n;
+      if constexpr (!HALVES) return row[0];
+      const NttLimb* m = a.limbs + i;
+      const InvRoot* top = a.plain_key ? &m->inv_r : &m->inv;
+      const uint32_t p = ldc(&m->m.p, 0);
+      // (below 3 p: the conversion takes any 32-bit value)
+      return (uint32_t)split_root((int32_t)row[0], (int32_t)row[n / 2], split_root_factors(ldc(&top->c0, 0), ldc(&top->w, 0), half), p, ldc(&m->pinv, 0)) +
+             p + c0[(size_t)i * n];
+    };
+    const uint32_t v = bconv_prepare<FOURS>(a.bc, in, zcol, gcol, kThreads, a.band, a.fallback_counter);
     uint64_t s0 = v, s1 = 0, s2 = 0;
-    for (uint32_t i = 0; i < ks; ++i) {
+    each_prime<FOURS>(ks, [&](uint32_t i) {
       const uint64_t z = zcol[i * kThreads];
       s0 += z * ldc(a.tab, 3 * i);
       s1 += z * ldc(a.tab, 3 * i + 1);
       s2 += z * ldc(a.tab, 3 * i + 2);
-    }
+    });
     uint64_t r = s2 % a.t;                       // below 2^47: the shifted sums stay below 2^63 + 2^52
     r = ((r << 16) + s1) % a.t;
     r = ((r << 16) + s0) % a.t;

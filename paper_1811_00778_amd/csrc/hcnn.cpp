@@ -1024,9 +1024,14 @@ int query_fused_occupancy(hcnn_ctx* c) {
 // Encryption and decryption rows: launches of CryptFused
 constexpr size_t kCryptRows = (size_t)1 << 26;     // rows of one launch
 template <class K>
-int crypt_launch(hcnn_ctx* c, const CryptArgs& a) { return run<K>(c, ntt_grouped_grid(a.n_rows, c->k), K::kLdsBytes, a); }
+int crypt_launch(hcnn_ctx* c, const CryptArgs& a) { return run<K>(c, K::grid(ntt_grouped_grid(a.n_rows, c->k)), K::kLdsBytes, a); }
 template <int LOGN, int LOGR>
-int crypt_fused(hcnn_ctx* c, const CryptArgs& a, bool enc) {
+int crypt_fused(hcnn_ctx* c, const CryptArgs& a, bool enc, bool split) {
+  if constexpr (LOGN == 13 || LOGN == 15) {
+    if (split) {
+      return crypt_launch<CryptFused<LOGN, LOGR, false, true, 1>>(c, a);
+    }
+  }
   if (enc) return crypt_launch<CryptFused<LOGN, LOGR, true>>(c, a);
   if (a.u) {
     // (the largest ring does not hold a second row in its registers)
@@ -1034,16 +1039,16 @@ int crypt_fused(hcnn_ctx* c, const CryptArgs& a, bool enc) {
   }
   return crypt_launch<CryptFused<LOGN, LOGR, false>>(c, a);
 }
-int crypt_rows(hcnn_ctx* c, CryptArgs a, size_t n_ct, bool enc) {
+int crypt_rows(hcnn_ctx* c, CryptArgs a, size_t n_ct, bool enc, bool split = false) {
   a.tw_fwd = c->d_tw_fwd; a.tw_inv = c->d_tw_inv; a.limbs = c->d_limbs; a.cycle = fast_div(c->k);
   a.n_rows = (uint32_t)(n_ct * c->k);
   switch (c->logn) {
-    case 10: return crypt_fused<10, 4>(c, a, enc);
-    case 11: return crypt_fused<11, 4>(c, a, enc);
-    case 12: return crypt_fused<12, 4>(c, a, enc);
-    case 13: return crypt_fused<13, 4>(c, a, enc);
-    case 14: return crypt_fused<14, 4>(c, a, enc);
-    case 15: return crypt_fused<15, 5>(c, a, enc);
+    case 10: return crypt_fused<10, 4>(c, a, enc, split);
+    case 11: return crypt_fused<11, 4>(c, a, enc, split);
+    case 12: return crypt_fused<12, 4>(c, a, enc, split);
+    case 13: return crypt_fused<13, 4>(c, a, enc, split);
+    case 14: return crypt_fused<14, 4>(c, a, enc, split);
+    case 15: return crypt_fused<15, 5>(c, a, enc, split);
   }
   return HCNN_ERR_N;
 }
@@ -1055,6 +1060,14 @@ int secret_hat(hcnn_ctx* c, const int32_t* s, uint32_t* s_hat) {
 // Does every (ciphertext, limb) row find a compute unit of its own?  Then a workgroup's own transform of s is shorter than
 // a launch for it in front.
 bool decrypts_with_own_key(const hcnn_ctx* c, size_t n_ct) { return c->logn <= 14 && n_ct * c->k <= c->compute_units; }
+// Does a decryption take two workgroups per row, the rounding the last stage of their inverse transforms?  n = 8192 while both halves of every row
+// find a compute unit of their own (us, 8 primes, 10 ciphertexts 17.5 / 14.1); n = 32768 up to 4/9 of as many rows as compute units (12 primes, 1 ciphertext 48.2 /
+// 38.9, 4 49.9 / 40.8, 10 51.6 / 54.8; 16 primes, 7 54.1 / 46.4) and 16 primes (24, 1 52.7 / 56.2: the rounding waits for its loads).
+bool decrypts_by_halves(const hcnn_ctx* c, size_t n_ct) {
+  const size_t rows = n_ct * c->k;
+  if (c->logn == 13) return kSharedAll || 2 * rows <= c->compute_units;
+  return c->logn == 15 && c->k <= 16 && (kSharedAll || 9 * rows <= 4 * (size_t)c->compute_units);
+}
 // Work buffer of a decryption or a noise read-out: x [C][k][n] of up to 256 MiB (C ciphertexts a piece), then s_hat [k][n]
 // unless the workgroups transform the secret themselves.
 int decrypt_work(hcnn_ctx* c, size_t n_ct, bool own, size_t* C, uint32_t** x) {
@@ -1063,11 +1076,11 @@ int decrypt_work(hcnn_ctx* c, size_t n_ct, bool own, size_t* C, uint32_t** x) {
   return work_buffer(c, (*C + (own ? 0 : 1)) * poly * 4, x);
 }
 // x = c0 + c1*s mod q of cc ciphertexts
-int decrypt_rows(hcnn_ctx* c, const int32_t* s, const uint32_t* cts, size_t cc, const uint32_t* s_hat, uint32_t* x, bool own) {
+int decrypt_rows(hcnn_ctx* c, const int32_t* s, const uint32_t* cts, size_t cc, const uint32_t* s_hat, uint32_t* x, bool own, bool split = false) {
   CryptArgs a{};
   a.key = s_hat; a.cts = cts; a.out = x;
   a.u = own ? s : nullptr;
-  return crypt_rows(c, a, cc, false);
+  return crypt_rows(c, a, cc, false, split);
 }
 
 // Median duration in milliseconds of `reps` launches of one kernel on the context's stream, one event pair each.
@@ -1664,7 +1677,7 @@ static int decrypt_impl(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size
   const uint32_t k = c->k, n = c->n;
   const size_t rn = n, poly = (size_t)k * rn;
   const size_t bpp = n / kEwThreads;
-  const bool own = decrypts_with_own_key(c, n_ct);
+  const bool split = decrypts_by_halves(c, n_ct), own = split || decrypts_with_own_key(c, n_ct);
   size_t C;
   uint32_t* x;
   int e = decrypt_work(c, n_ct, own, &C, &x);
@@ -1673,12 +1686,16 @@ static int decrypt_impl(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size
   if (!own && (e = secret_hat(c, sk, s_hat))) return e;
   for (size_t c0 = 0; c0 < n_ct; c0 += C) {
     const size_t cc = std::min(C, n_ct - c0);
-    if ((e = decrypt_rows(c, sk, ct + c0 * 2 * poly, cc, s_hat, x, own))) return e;
+    if ((e = decrypt_rows(c, sk, ct + c0 * 2 * poly, cc, s_hat, x, own, split))) return e;
     DecRoundArgs da;
+    da.cts = ct + c0 * 2 * poly; da.limbs = c->d_limbs; da.plain_key = own;
     da.x = x; da.m_out = m_out ? m_out + c0 * rn : nullptr; da.m_out64 = m_out64 ? m_out64 + c0 * rn : nullptr;
     da.bc = c->dec; da.tab = c->d_dec_tab; da.t = c->t; da.n = n;
     da.band = c->band; da.fallback_counter = c->d_counters;
-    if ((e = run<DecRoundKernel>(c, cc * bpp, DecRoundKernel::lds_bytes(k), da))) return e;
+    const size_t lds = DecRoundKernel<true, true>::lds_bytes(k);
+    if ((e = split    ? run<DecRoundKernel<true, true>>(c, cc * bpp, lds, da)
+             : k >= 4 ? run<DecRoundKernel<false, true>>(c, cc * bpp, lds, da)
+                      : run<DecRoundKernel<false, false>>(c, cc * bpp, lds, da))) return e;
   }
   return HCNN_OK;
 }

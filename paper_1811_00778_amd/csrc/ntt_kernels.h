@@ -359,7 +359,8 @@ struct NttFwd {
   static constexpr bool kDigitRow = IO == kNttLoadDigit || IO == kNttDigitTile;
   static_assert(IO == kNttPlain || IO == kNttPlainFew || kDigitRow || IO == kNttStoreLazy || kKeyOut || kFused || kToRegs,
                 "forward NTT: plain, digit load, lazy or key store, fused inner product or register output");
-  static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && !kRowToRegs && LOGN % 2 == 1), "the split form stores its rows or keeps them for the tensor");
+  static_assert(SPLIT == 0 || (SPLIT == 1 && !kFused && IO != kNttSmallToRegs && LOGN % 2 == 1),
+                "the split form stores its rows or keeps them for the tensor or the decryption");
   using G = NttGeom<LOGN - SPLIT, LOGR, IO == kNttPlain>;      // the stages after the split one
   static constexpr int kThreads = G::kThreads;
   static constexpr int kPhases = G::kPhases;
@@ -391,7 +392,7 @@ struct NttFwd {
       // both halves of a row on one die, next to each other in time
       half = split_half(bid);
       bid = split_row(bid);
-      if constexpr (!kDigitIn) {
+      if constexpr (!kDigitIn && !kRowToRegs) {
         if (bid >= a.n_rows) return;                       // padding workgroups of the last round
       }
     }
@@ -583,7 +584,8 @@ struct NttFwd {
 template <int LOGN, int LOGR, int IO = kNttPlain, int SPLIT = 0>
 struct NttInv {
   static_assert(SPLIT == 0 || (SPLIT == 1 && LOGN % 2 == 1 && (IO == kNttLoadTensor || IO == kNttLoadTensorMul || IO == kNttTensorRegs0 ||
-                IO == kNttTensorRegs1 || IO == kNttTensorRegs2 || IO == kNttBackRow)), "rows whose reader takes the last stage");
+                IO == kNttTensorRegs1 || IO == kNttTensorRegs2 || IO == kNttBackRow || IO == kNttDecOut || IO == kNttDecOwn)),
+                "rows whose reader takes the last stage");
   static_assert(IO == kNttPlain || IO == kNttLoadTensor || IO == kNttStoreAdd || IO == kNttLoadTensorMul ||
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
                 IO == kNttTensorRegs2 || IO == kNttEncOut0 || IO == kNttEncOut1 || IO == kNttDecOut || IO == kNttDecOwn || IO == kNttBackRow || IO == kNttBack0 ||
@@ -621,7 +623,9 @@ struct NttInv {
     if constexpr (SPLIT && IO != kNttLoadTensor && IO != kNttLoadTensorMul) {
       half = split_half(bid);
       bid = split_row(bid);
-      if (bid >= a.n_rows) return;
+      if constexpr (!kKeyRegs) {
+        if (bid >= a.n_rows) return;
+      }
     }
     if constexpr (IO == kNttLoadTensor || IO == kNttLoadTensorMul) {
       // the three components of one (ciphertext, limb) pair read the same c0^ / c1^ rows: same die
@@ -709,7 +713,8 @@ struct NttInv {
       const size_t at = (size_t)half * (N / 2);
       gout += at;
       if constexpr (IO == kNttBackRow) gin += at / 64 * a.tile_words;
-      else if constexpr (!kTensorRegs) { gin += at; gin2 += at; }
+      else if constexpr (!kTensorRegs && IO != kNttDecOwn) gin += at;
+      if constexpr (IO == kNttLoadTensor || IO == kNttLoadTensorMul) gin2 += at;
       if constexpr (IO == kNttLoadTensorMul) { gmul0 += at; gmul1 += at; }
     }
     if constexpr (IO == kNttStoreAdd) {
@@ -932,7 +937,7 @@ struct NttInv {
         };
         if (IO != kNttEncOut0 || a.msg != nullptr) root_level(std::false_type{});
         else root_level(std::true_type{});
-      } else if constexpr (kLast && (IO == kNttStoreAdd || kFromRegs || kDecOut)) {
+      } else if constexpr (kLast && (IO == kNttStoreAdd || kFromRegs || (kDecOut && !SPLIT))) {
         // all loads of the addend before the first store (the compiler must assume the buffers alias)
         uint32_t addend[NET];
 #pragma unroll
@@ -1134,9 +1139,12 @@ struct CryptArgs {
   FastDiv cycle;            // k
 };
 
-template <int LOGN, int LOGR, bool ENC, bool OWN = false>
+// SPLIT (decryption, n = 8192 and 32768): workgroup (ct, l, half), both ends as in the split transforms; c0 and the last stage are left to the rounding.
+template <int LOGN, int LOGR, bool ENC, bool OWN = false, int SPLIT = 0>
 struct CryptFused {
-  using G = NttGeom<LOGN, LOGR>;
+  static_assert(!ENC || !SPLIT, "an encryption's rows are results");
+  using G = NttGeom<LOGN - SPLIT, LOGR>;
+  static size_t grid(size_t slots) { return SPLIT ? split_grid(slots) : slots; }
   static constexpr int P = G::kPhases;
   // (a decryption that finds the key's transform has no exchange between its two transforms that a second buffer would spare a barrier, and
   // with one two workgroups of n = 16384 fit a compute unit: 500 ciphertexts, k = 8 358 us with two buffers, 322 with one)
@@ -1156,17 +1164,17 @@ struct CryptFused {
     if constexpr (OWN) {
       na.small = a.u; na.in = a.cts; na.out = a.out; na.aux = a.cts;
       na.tw = PH < 2 * P ? a.tw_fwd : a.tw_inv;
-      if constexpr (PH < P) NttFwd<LOGN, LOGR, kNttSecretToRegs>::template phase<PH>(na, bid, tid, lds, regs);
-      else if constexpr (PH < 2 * P) NttFwd<LOGN, LOGR, kNttCtToRegs>::template phase<PH - P>(na, bid, tid, lds, regs);
-      else NttInv<LOGN, LOGR, kNttDecOwn>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
+      if constexpr (PH < P) NttFwd<LOGN, LOGR, kNttSecretToRegs, SPLIT>::template phase<PH>(na, bid, tid, lds, regs);
+      else if constexpr (PH < 2 * P) NttFwd<LOGN, LOGR, kNttCtToRegs, SPLIT>::template phase<PH - P>(na, bid, tid, lds, regs);
+      else NttInv<LOGN, LOGR, kNttDecOwn, SPLIT>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
     } else if constexpr (PH < P) {
       na.tw = a.tw_fwd; na.small = a.u; na.in = a.cts;
-      NttFwd<LOGN, LOGR, ENC ? kNttSmallToRegs : kNttCtToRegs>::template phase<PH>(na, bid, tid, lds, regs);
+      NttFwd<LOGN, LOGR, ENC ? kNttSmallToRegs : kNttCtToRegs, SPLIT>::template phase<PH>(na, bid, tid, lds, regs);
     } else {
       na.tw = a.tw_inv; na.in = a.key; na.out = a.out; na.aux = a.cts;
       na.msg = a.msg; na.msg64 = a.msg64; na.scale = a.scale;
       na.small = PH < 2 * P ? a.e1 : a.e2;
-      if constexpr (!ENC) NttInv<LOGN, LOGR, kNttDecOut>::template phase<PH - P>(na, bid, tid, lds, regs);
+      if constexpr (!ENC) NttInv<LOGN, LOGR, kNttDecOut, SPLIT>::template phase<PH - P>(na, bid, tid, lds, regs);
       else if constexpr (PH < 2 * P) NttInv<LOGN, LOGR, kNttEncOut0>::template phase<PH - P>(na, bid, tid, lds, regs);
       else NttInv<LOGN, LOGR, kNttEncOut1>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
     }

@@ -73,6 +73,11 @@ def test_keygen_encrypt_decrypt(backend, n, k):
     pc.check_keygen_encrypt_decrypt(backend, n, k)
 
 
+def test_decrypt_rows_by_two_workgroups():
+    # (this build decrypts at n = 8192 as the device does the smallest calls; n = 32768 always goes by halves)
+    pc.check_keygen_encrypt_decrypt(SharedBasisBackend(), 8192, 2, count=2)
+
+
 @pytest.mark.parametrize("n,k", [(4096, 3), (8192, 2), (16384, 2), (32768, 2)])
 def test_encrypt_decrypt_of_every_ring(backend, n, k):
     pc.check_keygen_encrypt_decrypt(backend, n, k, count=1)
