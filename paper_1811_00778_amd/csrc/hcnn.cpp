@@ -1411,6 +1411,12 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     const size_t cap = std::max<size_t>(c->logn <= 13 ? 512 : 256, fused_round);
     if (C > cap) C = cap;
     if (!shared_min && fused_round && C > fused_round) C = C / fused_round * fused_round;   // whole rounds of the one-kernel relinearisation
+    if (c->logn >= 14 && n_ct > C && !static_ws) {
+      // batches of about the same size rather than a short last one, which would miss the shared basis (us: n = 16384, k = 16, 300 ciphertexts 4475 /
+      // 4370, k = 8, 400 2503 / 2485; smaller rings lose up to 1 %)
+      const size_t even = (n_ct + (n_ct + C - 1) / C - 1) / ((n_ct + C - 1) / C);
+      C = !shared_min && fused_round ? std::min(C, (even + fused_round - 1) / fused_round * fused_round) : even;
+    }
   }
   if (C < 1) C = 1;
   if (C > n_ct) C = n_ct;
