@@ -1447,9 +1447,10 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   // (64 to 512 ciphertexts), a ratio of 0.85; at n = 32768, k = 24 15.5 against 18.8 (32), 0.82.  A last round that is only
   // partly filled is shorter too (workgroups with a compute unit to themselves run faster), so that from tensor_fused_least
   // workgroups on it pays whatever their number.
+  auto tensor_fused_wgs = [&](size_t cc) { return c->logn == 15 ? 2 * cc * L : cc * L; };      // (n = 32768: two workgroups per pair)
   auto takes_tensor_fused = [&](size_t cc) {
     if (in_b || c->fusion == 1) return false;
-    const size_t wgs = c->logn == 15 ? 2 * cc * L : cc * L;                  // (n = 32768: two workgroups per pair)
+    const size_t wgs = tensor_fused_wgs(cc);
     const size_t slots = tensor_fused_slots(c), rounds = (wgs + slots - 1) / slots;
     return c->fusion == 2 || wgs >= tensor_fused_least(c->logn) || wgs * 8 >= rounds * slots * 7;
   };
@@ -1477,7 +1478,9 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     ea.fallback_counter = c->d_counters;
     if ((e = ext_dispatch(c, cc * 2 * bpp, ea))) return e;
     if (tensor_fused) {
-      TensorFusedArgs ta{in + c0 * ct_words, b_ext, b_d, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, L, (uint32_t)(cc * L), fast_div(L)};
+      TensorFusedArgs ta{in + c0 * ct_words, b_ext, b_d, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, L, (uint32_t)(cc * L), fast_div(L), {0, 0}};
+      // (up to one and a half rounds the order of the limbs gains nothing: n = 32768, k = 12, 8 ciphertexts 273 / 276 us)
+      if (2 * tensor_fused_wgs(cc) > 3 * tensor_fused_slots(c)) ta.cts_div = fast_div((uint32_t)cc);
       const size_t rows = cc * L * 5;
       switch (c->logn) {
         case 10: e = run<TensorFused<10, 4>>(c, cc * L, TensorFused<10, 4>::kLdsBytes, ta, rows); break;

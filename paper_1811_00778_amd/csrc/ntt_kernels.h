@@ -1035,6 +1035,7 @@ struct TensorFusedArgs {
   uint32_t k, L;
   uint32_t n_rows;          // n_ct * L
   FastDiv cycle;            // L
+  FastDiv cts_div;          // n_ct: pairs in the order of the limbs (n >= 16384); 0: of the ciphertexts
 };
 
 // SPLIT = 1 (n = 32768): workgroup (ct, l, half), both ends as in the split transforms: it reads whole rows of c0 and c1, keeps its halves and leaves
@@ -1053,9 +1054,27 @@ struct TensorFused {
   using Regs = TensorRegs<G::R>;
   static constexpr bool wave_sync(int ph) { return seq_wave_sync(ph, P, 2, kBuffers); }
 
+  // Large launches from n = 16384 on: every die takes its share of the pairs in the order of the limbs, so that its L2 holds the twiddles of the one or two limbs at
+  // work (5/3 n words a limb and direction: 7.1 MiB at n = 16384, L = 34).  Us, squarings with the pairs in the order of the ciphertexts / of the
+  // limbs: n = 32768, k = 24, 32 ciphertexts 1729 / 1688, k = 12 807 / 790; n = 16384, k = 16, 225 3198 / 3159, k = 12, 300 3199 / 3158.  At n = 8192,
+  // where the twiddles of all limbs stay in L2, 720 of 8 primes 1978 / 1972, but 1520 of 11 (a network) 7580 / 7605.
+  HCNN_HD static unsigned pair_of(const TensorFusedArgs& a, unsigned i) {
+    const uint32_t die = i % kNttXcds, share = a.n_rows / kNttXcds, rest = a.n_rows % kNttXcds;
+    const uint32_t at = die * share + (die < rest ? die : rest) + i / kNttXcds, l = quot(at, a.cts_div);
+    return (at - l * a.cts_div.d) * a.L + l;
+  }
+  HCNN_HD static unsigned place(const TensorFusedArgs& a, unsigned bid) {
+    if (LOGN < 14 || a.cts_div.d == 0) return bid;
+    if constexpr (!SPLIT) return pair_of(a, bid);
+    if (split_row(bid) >= a.n_rows) return bid;
+    const uint32_t row = pair_of(a, split_row(bid));
+    return row / kNttXcds * 2 * kNttXcds + split_half(bid) * kNttXcds + row % kNttXcds;
+  }
+
   template <int PH>
   HCNN_HD static void phase(const TensorFusedArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
     lds = seq_buffer<G, kBuffers>(lds, PH / P);
+    bid = place(a, bid);
     NttArgs na{};
     na.limbs = a.limbs; na.cycle = a.cycle; na.limb_base = 0; na.n_rows = a.n_rows;
     if constexpr (PH < 2 * P) {

@@ -43,6 +43,13 @@ size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
 // LDS of a workgroup of the decryption that reads the secret's transform (n = 16384).
 size_t rule_decrypt_lds() { return CryptFused<14, 4, false>::kLdsBytes; }
 
+// Pair (one workgroup of n <= 16384) or, n = 32768, place (half of a pair) that workgroup `bid` of the one-kernel tensor takes in the order of the limbs.
+uint32_t rule_tensor_place(uint32_t split, uint32_t n_ct, uint32_t L, uint32_t bid) {
+  TensorFusedArgs a{};
+  a.L = L; a.n_rows = n_ct * L; a.cts_div = fast_div(n_ct);
+  return split ? TensorFused<15, 5, 1>::place(a, bid) : TensorFused<14, 5>::place(a, bid);
+}
+
 // Smallest batch that takes the shared-basis relinearisation, 0: none.
 size_t rule_shared_basis_min(uint32_t n, uint32_t k, uint32_t k_aux) {
   hcnn_ctx c;

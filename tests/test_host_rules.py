@@ -112,3 +112,18 @@ def test_smallest_batch_of_the_shared_basis_relinearisation(rules, n, k, least):
 
 def test_two_decryption_workgroups_of_the_second_largest_ring_fit_a_compute_unit(rules):
     assert 2 * rules.rule_decrypt_lds() <= 160 * 1024
+
+
+@pytest.mark.parametrize("n_ct,L", [(1, 5), (1, 8), (3, 17), (7, 9), (64, 17), (225, 34), (32, 50)])
+def test_one_kernel_tensor_takes_every_pair_once_in_the_order_of_the_limbs(rules, n_ct, L):
+    rows = n_ct * L
+    pairs = [rules.rule_tensor_place(0, n_ct, L, i) for i in range(rows)]
+    assert sorted(pairs) == list(range(rows))
+    for die in range(8):                                       # each die's limbs ascend, and its share of the pairs is even
+        limbs = [p % L for p in pairs[die::8]]
+        assert limbs == sorted(limbs) and len(limbs) in (rows // 8, rows // 8 + 1)
+    # two workgroups per pair: (pair, half) of a place as the split transforms read it; those past the last pair stay past it
+    places = [rules.rule_tensor_place(1, n_ct, L, i) for i in range(2 * -(-rows // 8) * 8)]
+    taken = [(b // 16 * 8 + b % 8, b // 8 % 2) for b in places]
+    assert sorted(t for t in taken if t[0] < rows) == [(p, h) for p in range(rows) for h in (0, 1)]
+    assert [p for p, h in taken if p < rows and h == 0] == pairs
