@@ -1327,6 +1327,16 @@ static size_t tensor_fused_least(uint32_t logn) {
   return least[logn - 10];
 }
 
+// Limbs of a ciphertext whose workgroups run side by side on one die in the one-kernel relinearisation.  All k read every digit row once, but bring the
+// whole key (2 k^2 n words) into the die's L2 for the few ciphertexts that are there at a time; half of them read the digits on two dies
+// and half of the key, for twice the ciphertexts.  Us, all / half / a quarter: n = 8192, k = 8, 64 squarings 185 / 182.5 / 182.7, 720 1987 / 1979 / 1990,
+// k = 10, 64 266 / 263 / 266, k = 12, 512 2512 / 2475 / 2461; n = 16384, k = 12, 200 2123 / 2103 / 2108, k = 16, 40 726 / 717 / 717, k = 8, 64 411 / 407 / 406.
+// A key that one L2 (4 MiB) holds gains nothing: n = 8192, k = 6, 400 795 / 799 / 799, n = 4096, k = 6, 1000 970 / 970 / 973.  (An odd k has no even halves.)
+static uint32_t relin_share(const hcnn_ctx* c) {
+  const bool outgrows_l2 = (size_t)2 * c->k * c->k * c->n * 4 >= ((size_t)4 << 20);
+  return outgrows_l2 && c->k % 2 == 0 ? c->k / 2 : c->k;
+}
+
 // Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 4k, acc 4 and (largest ring only) z 4 rows an output
 // per ciphertext.
 static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* dig, uint32_t* acc, uint32_t* z, uint32_t* out) {
@@ -1521,8 +1531,8 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     if (shared) return relin_shared(c, b_y, cc, b_dig, b_acc, b_d, out + c0 * ct_words);     // (the tensor's rows, 3L > 4k + 4, are free by now)
     // 6-8 in one kernel
     if (nf) {
-      RelinFusedArgs fa{b_y, c->d_evk_hat, out + c0 * ct_words, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, (uint32_t)(nf * k), fast_div(k)};
-      const size_t grid = ntt_grouped_grid(nf * k, k), rows = nf * k * (k + 2);
+      RelinFusedArgs fa{b_y, c->d_evk_hat, out + c0 * ct_words, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, (uint32_t)(nf * k), fast_div(k), fast_div(relin_share(c))};
+      const size_t grid = ntt_grouped_grid(nf * k, relin_share(c)), rows = nf * k * (k + 2);
 #define HCNN_FUSED(LOGN, LOGR)                                                                                      \
   (k <= 8 ? run<RelinFused<LOGN, LOGR, kNttFusedMac>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMac>::kLdsBytes, fa, rows)             \
           : k <= 16 ? run<RelinFused<LOGN, LOGR, kNttFusedMac16>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMac16>::kLdsBytes, fa, rows) \

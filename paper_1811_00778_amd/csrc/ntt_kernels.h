@@ -186,6 +186,7 @@ struct NttArgs {
   TwTable tw;
   const NttLimb* limbs;     // [L]
   FastDiv cycle;            // limbs per group of rows
+  FastDiv share;            // one-kernel relinearisation: rows of a group that share a die
   uint32_t limb_base;
   FastDiv digits;           // digit loads: digits per ciphertext; kNttKeyTile, kNttBackRow: outputs (b, pair)
   uint32_t tile_words;      // tiled rows: words from one tile of a row to its next
@@ -397,7 +398,7 @@ struct NttFwd {
       }
     }
     if constexpr (kDigitIn || kRowToRegs) {
-      bid = ntt_grouped_index(bid, a.cycle);      // the k transforms of one digit row (or small row) share a die
+      bid = ntt_grouped_index(bid, kFused ? a.share : a.cycle);      // the k transforms of one digit row (or small row) share a die
       if (bid >= a.n_rows) return;
     }
     const uint32_t group = quot(bid, a.cycle), within = bid - group * a.cycle.d, limb = a.limb_base + within;
@@ -643,7 +644,7 @@ struct NttInv {
     }
     if constexpr (kFromRegs || kKeyRegs) {
       if constexpr (kKeyRegs) tid = opaque(tid);
-      bid = ntt_grouped_index(bid, a.cycle);      // the same workgroup -> (ct, j) map as the forward transforms
+      bid = ntt_grouped_index(bid, kFromRegs ? a.share : a.cycle);   // the same workgroup -> (ct, j) map as the forward transforms
       if (bid >= a.n_rows) return;
     }
     if constexpr (kTensorRegs) {
@@ -985,6 +986,7 @@ struct RelinFusedArgs {
   uint32_t k;
   uint32_t n_rows;          // n_ct * k
   FastDiv cycle;            // k
+  FastDiv share;            // k or k / 2: limbs of a ciphertext that run on one die (relin_share)
 };
 
 template <int LOGN, int LOGR, int MAC = kNttFusedMacAny>
@@ -1008,7 +1010,7 @@ struct RelinFused {
   template <int PH>
   HCNN_HD static void phase(const RelinFusedArgs& a, unsigned bid, int tid, uint32_t* lds, Regs& regs) {
     NttArgs na{};
-    na.limbs = a.limbs; na.cycle = a.cycle; na.limb_base = 0; na.n_rows = a.n_rows;
+    na.limbs = a.limbs; na.cycle = a.cycle; na.share = a.share; na.limb_base = 0; na.n_rows = a.n_rows;
     if constexpr (PH < P) {
       na.in = a.y; na.aux = a.evk; na.tw = a.tw_fwd;
       Fwd::template phase<PH>(na, bid, tid, seq_buffer<G, kBuffers>(lds, regs.iter), regs);

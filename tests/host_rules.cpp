@@ -50,6 +50,15 @@ uint32_t rule_tensor_place(uint32_t split, uint32_t n_ct, uint32_t L, uint32_t b
   return split ? TensorFused<15, 5, 1>::place(a, bid) : TensorFused<14, 5>::place(a, bid);
 }
 
+// Limbs of a ciphertext that share a die in the one-kernel relinearisation, and the (ciphertext, limb) row of one of its workgroups.
+uint32_t rule_relin_share(uint32_t n, uint32_t k) {
+  hcnn_ctx c;
+  c.n = n; c.k = k;
+  return relin_share(&c);
+}
+uint32_t rule_relin_grid(uint32_t rows, uint32_t share) { return (uint32_t)ntt_grouped_grid(rows, share); }
+uint32_t rule_relin_row(uint32_t bid, uint32_t share) { return ntt_grouped_index(bid, fast_div(share)); }
+
 // Smallest batch that takes the shared-basis relinearisation, 0: none.
 size_t rule_shared_basis_min(uint32_t n, uint32_t k, uint32_t k_aux) {
   hcnn_ctx c;

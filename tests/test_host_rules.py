@@ -127,3 +127,13 @@ def test_one_kernel_tensor_takes_every_pair_once_in_the_order_of_the_limbs(rules
     taken = [(b // 16 * 8 + b % 8, b // 8 % 2) for b in places]
     assert sorted(t for t in taken if t[0] < rows) == [(p, h) for p in range(rows) for h in (0, 1)]
     assert [p for p, h in taken if p < rows and h == 0] == pairs
+
+
+@pytest.mark.parametrize("n,k,share", [(8192, 7, 7), (8192, 8, 4), (8192, 9, 9), (8192, 12, 6), (16384, 6, 3), (16384, 16, 8), (4096, 6, 6), (4096, 12, 6)])
+def test_one_kernel_relinearisation_halves_the_limbs_of_a_die(rules, n, k, share):
+    assert rules.rule_relin_share(n, k) == share
+    for n_ct in (1, 3, 8, 37):
+        rows = [rules.rule_relin_row(i, share) for i in range(rules.rule_relin_grid(n_ct * k, share))]
+        assert sorted(r for r in rows if r < n_ct * k) == list(range(n_ct * k))
+        for die in range(8):                                   # a die meets one part of the limbs only
+            assert len({r % k // share for r in rows[die::8] if r < n_ct * k}) <= 1
