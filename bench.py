@@ -402,15 +402,16 @@ def main():
     # writes the result, the key comes from L2; the scalar MAC reads every input and writes every output once)
     plain_rows = ntt_buf.numel() // n
     step_bytes = {
-        "ntt_fwd": plain_rows * 2 * row4 + n_ct * 2 * L_ * 2 * row4,
-        "ntt_inv": plain_rows * 2 * row4 + n_ct * 5 * L_ * row4,
+        "ntt_fwd": plain_rows * 2 * row4 + (0 if "tensor" in kernels else n_ct * 2 * L_ * 2 * row4),
+        "ntt_inv": plain_rows * 2 * row4 + (0 if "tensor" in kernels else n_ct * 5 * L_ * row4),
+        "tensor": n_ct * 5 * L_ * row4,
         "relin_fused": n_ct * 5 * k * row4,
         "scalar_mac": (n_ct + F * G) * ct_bytes,
         "base_ext": n_ct * 2 * L_ * row4,
         "scale": n_ct * 3 * (L_ + k) * row4,
     }
-    profile_rows = {"ntt_fwd": "NttFwd<13, 4, 5, 0>", "ntt_inv": "NttInv<13, 4, 2>", "relin_fused": "RelinFused",
-                    "scalar_mac": "Mac", "base_ext": "ExtKernel", "scale": "ScaleKernel"}
+    profile_rows = {"ntt_fwd": "NttFwd<13, 4, 0, 0>", "ntt_inv": "NttInv<13, 4, 0, 0>", "tensor": "TensorFused",
+                    "relin_fused": "RelinFused", "scalar_mac": "Mac", "base_ext": "ExtKernel", "scale": "ScaleKernel"}
 
     def class_roofline(name):
         kd = kernels[name]
@@ -452,7 +453,7 @@ def main():
     if kernels:
         dom = max(kernels, key=lambda kname: kernels[kname]["total_ms"])
         roofline = class_roofline(dom)
-        roofline["classes"] = {name: class_roofline(name) for name in ("ntt_fwd", "ntt_inv", "scalar_mac", "relin_fused",
+        roofline["classes"] = {name: class_roofline(name) for name in ("ntt_fwd", "ntt_inv", "tensor", "scalar_mac", "relin_fused",
                                                                        "scale", "base_ext") if name in kernels and name != dom}
         # NTT launches of the step, time per row (the small launches of this batch fill one round of workgroups)
         roofline["ntt_ns_per_row"] = {name: round(kernels[name]["total_ms"] * 1e6 / kernels[name]["blocks"], 2)
