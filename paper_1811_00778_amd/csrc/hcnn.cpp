@@ -943,10 +943,14 @@ bool mac_takes_pairs(const hcnn_ctx* c, const MacArgs& a) {
 // - Less often: the union saves little, and reading the inputs bounds either form (2 x 2 without overlap, 1 to 8 filters, n = 4096, k = 4 46-63 / 55-65;
 //   3 x 3 at stride 2, gathered 1.7 times, n = 16384, k = 8, 4 filters 178 / 199, 8 filters 223 / 222; between 2.5 and 3.5 times as many gain as lose).
 //   A call whose neighbours share nothing, however often its inputs are gathered, loses too (rows are not known here).
+// - 5 or 6 filters and 200 terms or more over fewer than 64 groups at n >= 8192, gathered less than 6 times: two or three groups side by side, which often lie in different rows of
+//   the map, in one to two rounds of long workgroups (6 x 324, 49 groups, k = 8 581 / 628; 5 x 333, 16 groups, k = 10 261 / 288; but 6 x 75, 49 groups, k = 10 218 / 205,
+//   5 x 63, 49 groups, k = 11 186 / 174).
 // - Fewer than 3/4 workgroups per compute unit with a tile per wave: the union's terms run one after another (1 x 125, 64 groups, n = 2048, k = 2 12 / 19).
 uint32_t mac_pack_groups(const hcnn_ctx* c, const MacArgs& a) {
   const uint64_t w_max = a.w_abs_max > 0 ? (uint64_t)a.w_abs_max : 1;
   if (a.F > 8 || a.w_abs_max > 127 || a.T * w_max > kMfmaMaxSum || (uint64_t)a.n_in * 2 * a.k * a.n * 4 > 0xffffffffull) return 0;
+  if ((a.F == 5 || a.F == 6) && a.T >= 200 && a.G < 64 && a.n >= 8192 && (uint64_t)a.G * a.T < 6 * (uint64_t)a.n_in) return 0;
   MacArgs b = a;
   b.pack = 16 / a.F;
   b.steps = 1;

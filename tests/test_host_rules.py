@@ -86,6 +86,8 @@ def test_calls_that_form_the_union_of_two_rows(rules, n, k, n_in, G, T, pairs):
     (8192, 8, 784, 144, 5, 25, 15, 3), (8192, 8, 784, 144, 1, 25, 127, 16), (8192, 8, 784, 144, 8, 25, 15, 2), (8192, 8, 784, 144, 9, 25, 15, 0),
     (8192, 8, 784, 144, 5, 25, 128, 0),                                            # weights beyond a signed byte
     (8192, 8, 800, 112, 5, 25, 15, 3), (8192, 8, 801, 112, 5, 25, 15, 0),          # inputs gathered 3.5 times
+    (8192, 8, 2916, 63, 6, 277, 15, 0), (8192, 8, 2916, 63, 6, 278, 15, 2), (8192, 8, 2916, 64, 6, 273, 15, 2), (4096, 8, 2916, 63, 6, 277, 15, 2),
+    (8192, 8, 2101, 63, 6, 199, 15, 2), (8192, 8, 2100, 63, 6, 200, 15, 2), (8192, 8, 2101, 63, 6, 200, 15, 0),    # few groups of many terms
     (2048, 2, 720, 64, 1, 125, 15, 0), (2048, 3, 720, 64, 1, 125, 15, 16),         # 128, 192 workgroups
     (8192, 8, 8191, 1200, 2, 27, 15, 8), (8192, 8, 8192, 1200, 2, 27, 15, 0),      # inputs of 4 GiB
     (1024, 1, 1000, 10000, 8, 1568, 15, 2), (1024, 1, 1000, 10000, 8, 1569, 15, 0),    # tables of 64 KiB
