@@ -1303,7 +1303,15 @@ struct MacPair : MacUnion<2> {
 };
 struct MacPack : MacUnion<1> {
   static constexpr uint32_t kLeastPerUnit = 2;
-  static uint32_t max_steps(const MacArgs&) { return 8; }
+  // Tiles per wave at most.  Long unions take few: what building one costs is spread over its own terms, and many long workgroups come in one to
+  // three uneven rounds (us, 8 / 4 / 2 / 1 tiles: 7 x 575, 9 groups, n = 16384, k = 13 852 / 743 / 672 / 582, vector form 703; 4 x 416, 36 groups, n = 8192, k =
+  // 11 725 / 624 / 549 / 486, 644; 8 x 72, 169 groups, n = 2048, k = 3 55 / 47 / 38 / 48, 81; 1051 calls with 250 terms or more in the rows of a set take 5 % less
+  // with two tiles at most; one takes 3 % less again, but up to 39 % more where the launch has enough workgroups with two).  Short ones would be
+  // built too often (unions of up to 80 terms in launches of many rounds lose 7 to 17 % with two tiles).
+  static uint32_t max_steps(const MacArgs& a) {
+    const uint64_t terms = (uint64_t)a.pack * a.T;
+    return terms >= 250 ? 2 : terms >= 150 ? 4 : 8;
+  }
 };
 
 // ---------------------------------------------------------------- helpers for KeyGen / Encrypt / Decrypt

@@ -96,6 +96,14 @@ def test_calls_of_few_filters_that_sum_groups_side_by_side(rules, n, k, n_in, G,
     assert rules.rule_mac_pack_groups(256, n, k, n_in, G, F, T, bound) == groups
 
 
+@pytest.mark.parametrize("n,k,G,F,T,steps", [
+    (8192, 8, 144, 5, 25, 8), (8192, 8, 400, 4, 37, 8), (8192, 8, 400, 4, 38, 4), (8192, 8, 400, 4, 62, 4), (8192, 8, 400, 4, 63, 2),
+    (16384, 13, 9, 7, 575, 2), (8192, 11, 36, 4, 416, 2), (2048, 4, 49, 6, 288, 2), (2048, 4, 16, 6, 288, 1),
+])
+def test_long_unions_of_groups_side_by_side_take_few_tiles_per_wave(rules, n, k, G, F, T, steps):
+    assert rules.rule_mac_pack_steps(256, n, k, G, F, T) == steps
+
+
 def test_network_plan_puts_16_outputs_into_rows_that_the_matrix_form_takes(rules):
     """The length and the weights up to which the plan relies on the matrix form for rows that the vector form cannot stage."""
     T, weight = network._MATRIX_TERMS, network._MATRIX_WEIGHT
