@@ -935,26 +935,35 @@ bool mac_takes_pairs(const hcnn_ctx* c, const MacArgs& a) {
 }
 
 // Groups of few filters that a call sums side by side in the sixteen rows of the matrix form (MacPack), over the union of their inputs; 0: it
-// takes the vector form.  Both forms were timed on 400 convolutions of up to 8 filters (all rings, 2 x 2 to 5 x 5, strides 1 and 2, up
-// to 64 channels, maps up to 32 x 32):
-// - Inputs gathered 3.5 times or more: geometric mean vector / pack 1.33, at 9 times and more 1.47; of 230 calls three lose more than 3 % (9 terms, 6
-//   filters, n = 8192, k = 4 25.4 / 28.0 us).  Us: 5 x 25, stride 2, 144 groups, n = 8192, k = 8 224 / 174; 8 x 72, padded, 100 groups, k = 6 271 / 195;
-//   8 x 288, 36 groups, n = 2048, k = 3 71 / 30; 1 x 72, padded 150 / 90.
+// takes the vector form.  Both forms were timed on 3600 scalar MACs of up to 8 filters (all rings, 2 x 2 to 7 x 7, strides 1 and 2, up
+// to 64 channels, maps up to 32 x 32; rows of random inputs), us, vector / pack:
+// - Inputs gathered 3.5 times or more: geometric mean vector / pack 1.4 for convolutions.  5 x 25, stride 2, 144 groups, n = 8192, k = 8 224 / 174; 8 x 72, padded,
+//   100 groups, k = 6 271 / 195; 8 x 288, 36 groups, n = 2048, k = 3 71 / 30; 1 x 72, padded 150 / 90.
 // - Less often: the union saves little, and reading the inputs bounds either form (2 x 2 without overlap, 1 to 8 filters, n = 4096, k = 4 46-63 / 55-65;
 //   3 x 3 at stride 2, gathered 1.7 times, n = 16384, k = 8, 4 filters 178 / 199, 8 filters 223 / 222; between 2.5 and 3.5 times as many gain as lose).
-//   A call whose neighbours share nothing, however often its inputs are gathered, loses too (rows are not known here).
-// - 5 or 6 filters and 200 terms or more over fewer than 64 groups at n >= 8192, gathered less than 6 times: two or three groups side by side, which often lie in different rows of
-//   the map, in one to two rounds of long workgroups (6 x 324, 49 groups, k = 8 581 / 628; 5 x 333, 16 groups, k = 10 261 / 288; but 6 x 75, 49 groups, k = 10 218 / 205,
-//   5 x 63, 49 groups, k = 11 186 / 174).
+// - Little work: fewer than 150 multiply-adds a coefficient (F x T) times workgroups of the vector form for a compute unit of the fullest die.  Building the
+//   union takes longer than the sums do: such calls take 10 % longer packed, 20 % where the rows are random (3 x 9, 25 groups, n = 2048, k = 4 4.9 / 7.3; 1 x 16, 36 groups, n =
+//   4096, k = 3 5.3 / 8.2; 2 x 36, 31 groups of random rows, n = 2048, k = 2 5.1 / 9.9).
+// - One filter and fewer than four of those workgroups, two filters and fewer than two: the sixteen or eight rows of a set share one long union, whose terms
+//   run one after another in a launch that does not fill the chip (1 x 160, 16 groups, n = 2048, k = 3 10.1 / 22.4; 2 x 216, 25 groups, k = 4 21 / 27).
+// - 5 or 6 filters and 200 terms or more over fewer than 64 groups at n >= 8192, gathered less than 6 times: half of these gain nothing or lose up to 10 %.
 // - Fewer than 3/4 workgroups per compute unit with a tile per wave: the union's terms run one after another (1 x 125, 64 groups, n = 2048, k = 2 12 / 19).
+// Of 1576 convolutions gathered 3.5 to 13 times, with up to 60 of those workgroups, 77 take over 3 % longer than in the vector form, 35 of them over 10 % (1 to 3
+// filters in 10 to 50 us mostly); without the lines on little work and few filters, and with eight tiles for every union, 171 and 101 did.
 uint32_t mac_pack_groups(const hcnn_ctx* c, const MacArgs& a) {
   const uint64_t w_max = a.w_abs_max > 0 ? (uint64_t)a.w_abs_max : 1;
   if (a.F > 8 || a.w_abs_max > 127 || a.T * w_max > kMfmaMaxSum || (uint64_t)a.n_in * 2 * a.k * a.n * 4 > 0xffffffffull) return 0;
-  if ((a.F == 5 || a.F == 6) && a.T >= 200 && a.G < 64 && a.n >= 8192 && (uint64_t)a.G * a.T < 6 * (uint64_t)a.n_in) return 0;
+  const uint64_t products = (uint64_t)a.G * a.T, units = c->compute_units;
+  if (2 * products < 7 * (uint64_t)a.n_in) return 0;
+  const uint64_t tiles = 2 * (uint64_t)a.k * a.n / (kEwThreads * kEwVec);
+  const uint64_t vector_wgs = (tiles + kXcds - 1) / kXcds * a.G * kXcds;      // with every die as full as the fullest
+  if (vector_wgs < 150 * units && (uint64_t)a.F * a.T * vector_wgs < 150 * units) return 0;
+  if (a.F <= 2 && vector_wgs < (a.F == 1 ? 4 : 2) * units) return 0;
+  if ((a.F == 5 || a.F == 6) && a.T >= 200 && a.G < 64 && a.n >= 8192 && products < 6 * (uint64_t)a.n_in) return 0;
   MacArgs b = a;
   b.pack = 16 / a.F;
   b.steps = 1;
-  if (2 * (uint64_t)a.G * a.T < 7 * (uint64_t)a.n_in || 4 * MacPack::grid(b) < 3 * (size_t)c->compute_units) return 0;
+  if (4 * MacPack::grid(b) < 3 * (size_t)c->compute_units) return 0;
   return MacPack::lds_bytes(b.pack, a.T, a.n_in) <= std::min<size_t>(64 * 1024, c->max_lds) ? b.pack : 0;
 }
 

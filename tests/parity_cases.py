@@ -253,6 +253,25 @@ PACK_CASES = [                  # as above, for groups of few filters side by si
 ]
 
 
+PACK_ONE_FILTER = (1024, 6, 500, 64, 1, 45)          # n, k, inputs, groups, filters, terms: five channels 10 x 10, 3 x 3
+
+
+def check_scalar_mac_one_filter_per_set(backend):
+    """64 placements of one 3 x 3 filter over five channels: four sets of sixteen groups, a repeated input, a group without weights."""
+    n, k, n_in, G, F, T = PACK_ONE_FILTER
+    s = Setup(backend, n, k, with_keys=False)
+    idx = layers.conv_index_table(5, 10, 10, 3, 3, 1, 0)[0].astype(np.uint32)
+    assert idx.shape == (G, T) and idx.max() == n_in - 1
+    idx[17, 5] = idx[17, 40]
+    cts = gen.uniform_residues(s.rng, s.q, n, lead=(n_in, 2))
+    w = gen.int_weights(s.rng, (G, F, T), 15)
+    w[0], w[33] = 15, 0
+    out = backend.host(s.ctx.ct_scalar_mac(backend.dev(cts), backend.dev(idx), backend.dev(w), 15))
+    for g in range(G):
+        assert np.array_equal(out[0, g], fv.scalar_mac(s.octx, cts, idx[g], w[g, 0])), g
+    s.ctx.close()
+
+
 def check_scalar_mac_one_filter(backend, n, k):
     """Sixteen groups side by side, a last set of four: 100 placements of one 5 x 5 filter."""
     s = Setup(backend, n, k, with_keys=False)
