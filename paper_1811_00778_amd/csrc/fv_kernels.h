@@ -1303,14 +1303,17 @@ struct MacPair : MacUnion<2> {
 };
 struct MacPack : MacUnion<1> {
   static constexpr uint32_t kLeastPerUnit = 2;
-  // Tiles per wave at most.  Long unions take few: what building one costs is spread over its own terms, and many long workgroups come in one to
-  // three uneven rounds (us, 8 / 4 / 2 / 1 tiles: 7 x 575, 9 groups, n = 16384, k = 13 852 / 743 / 672 / 582, vector form 703; 4 x 416, 36 groups, n = 8192, k =
-  // 11 725 / 624 / 549 / 486, 644; 8 x 72, 169 groups, n = 2048, k = 3 55 / 47 / 38 / 48, 81; 1051 calls with 250 terms or more in the rows of a set take 5 % less
-  // with two tiles at most; one takes 3 % less again, but up to 39 % more where the launch has enough workgroups with two).  Short ones would be
-  // built too often (unions of up to 80 terms in launches of many rounds lose 7 to 17 % with two tiles).
+  // Tiles per wave at most.  What building a union costs (the terms of all its groups) is spread over its own terms times the tiles; many long workgroups
+  // come in one to three uneven rounds.  So unions that are long for what they are built of take few tiles (us, 8 / 4 / 2 / 1: 7 x 575, 9 groups, n = 16384,
+  // k = 13 852 / 743 / 672 / 582, vector form 703; 4 x 416, 36 groups, n = 8192, k = 11 725 / 624 / 549 / 486, 644; 8 x 72, 169 groups, n = 2048, k = 3 55 / 47 / 38
+  // / 48, 81), others eight (1 x 46, 69 groups over 46 inputs, n = 32768, k = 17 148 with eight, 185 with two).  The union is estimated as in
+  // mac_takes_pairs.  Of 3900 calls 982 take 3 % or more less than with eight tiles, 49 more, four of them over 10 %; one tile is better still for some and up to 39 %
+  // worse where two make enough workgroups.
   static uint32_t max_steps(const MacArgs& a) {
-    const uint64_t terms = (uint64_t)a.pack * a.T;
-    return terms >= 250 ? 2 : terms >= 150 ? 4 : 8;
+    const double T = a.T, groups = a.pack < a.G ? a.pack : a.G, gathered = (double)a.G * T / a.n_in;
+    const double of_rows = T * (1 + (groups - 1) / std::sqrt(gathered > 1 ? gathered : 1.0)), terms = of_rows < a.n_in ? of_rows : a.n_in;
+    const double kept = terms * terms / (groups * T);
+    return kept >= 120 ? 2 : kept >= 60 ? 4 : 8;
   }
 };
 

@@ -948,8 +948,9 @@ bool mac_takes_pairs(const hcnn_ctx* c, const MacArgs& a) {
 //   run one after another in a launch that does not fill the chip (1 x 160, 16 groups, n = 2048, k = 3 10.1 / 22.4; 2 x 216, 25 groups, k = 4 21 / 27).
 // - 5 or 6 filters and 200 terms or more over fewer than 64 groups at n >= 8192, gathered less than 6 times: half of these gain nothing or lose up to 10 %.
 // - Fewer than 3/4 workgroups per compute unit with a tile per wave: the union's terms run one after another (1 x 125, 64 groups, n = 2048, k = 2 12 / 19).
-// Of 1576 convolutions gathered 3.5 to 13 times, with up to 60 of those workgroups, 77 take over 3 % longer than in the vector form, 35 of them over 10 % (1 to 3
-// filters in 10 to 50 us mostly); without the lines on little work and few filters, and with eight tiles for every union, 171 and 101 did.
+// Of 2000 drawn convolutions whose inputs are gathered 3.5 times or more 56 take over 3 % longer than in the vector form, 27 over 10 %, nearly all of them less than
+// 60 us (3 x 16, 9 groups, n = 8192, k = 7 7.7 / 10.4; 6 x 4, 961 groups, n = 1024, k = 3 43 / 58); 108 and 65 did without the lines on little work and on
+// one and two filters and with eight tiles for every union.
 uint32_t mac_pack_groups(const hcnn_ctx* c, const MacArgs& a) {
   const uint64_t w_max = a.w_abs_max > 0 ? (uint64_t)a.w_abs_max : 1;
   if (a.F > 8 || a.w_abs_max > 127 || a.T * w_max > kMfmaMaxSum || (uint64_t)a.n_in * 2 * a.k * a.n * 4 > 0xffffffffull) return 0;

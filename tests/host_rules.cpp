@@ -37,11 +37,11 @@ uint32_t rule_mac_matrix_steps(uint32_t groups, uint32_t units, uint32_t n, uint
   return groups == 0 ? mac_matrix_steps<MacPair>(&c, a) : groups == 1 ? mac_matrix_steps<MacMfma<1>>(&c, a) : mac_matrix_steps<MacMfma<2>>(&c, a);
 }
 // Tiles per wave of MacPack.
-uint32_t rule_mac_pack_steps(uint32_t units, uint32_t n, uint32_t k, uint32_t G, uint32_t F, uint32_t T) {
+uint32_t rule_mac_pack_steps(uint32_t units, uint32_t n, uint32_t k, uint32_t n_in, uint32_t G, uint32_t F, uint32_t T) {
   hcnn_ctx c;
   c.compute_units = units;
   MacArgs a{};
-  a.k = k; a.n = n; a.G = G; a.F = F; a.T = T; a.pack = 16 / F;
+  a.k = k; a.n = n; a.n_in = n_in; a.G = G; a.F = F; a.T = T; a.pack = 16 / F;
   return mac_matrix_steps<MacPack>(&c, a);
 }
 size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {

@@ -108,12 +108,15 @@ def test_small_calls_of_few_filters_stay_in_the_vector_form(rules, n, k, n_in, G
     assert rules.rule_mac_pack_groups(256, n, k, n_in, G, F, T, 15) == groups
 
 
-@pytest.mark.parametrize("n,k,G,F,T,steps", [
-    (8192, 8, 144, 5, 25, 8), (8192, 8, 400, 4, 37, 8), (8192, 8, 400, 4, 38, 4), (8192, 8, 400, 4, 62, 4), (8192, 8, 400, 4, 63, 2),
-    (16384, 13, 9, 7, 575, 2), (8192, 11, 36, 4, 416, 2), (2048, 4, 49, 6, 288, 2), (2048, 4, 16, 6, 288, 1),
+@pytest.mark.parametrize("n,k,n_in,G,F,T,steps", [
+    (8192, 8, 784, 144, 5, 25, 8),
+    # four groups of 5 x 5 rows, r = 6.25: unions of 2.2 rows, 1.21 T terms of them for what they are built of
+    (8192, 8, 1568, 400, 4, 24, 8), (8192, 8, 3200, 400, 4, 50, 4), (8192, 8, 6336, 400, 4, 99, 4), (8192, 8, 6400, 400, 4, 100, 2),
+    (32768, 17, 46, 69, 1, 46, 8), (32768, 17, 1024, 69, 1, 1024, 4),      # all groups over the same inputs: a sixteenth
+    (16384, 13, 1127, 9, 7, 575, 2), (8192, 11, 2106, 36, 4, 416, 2), (2048, 4, 3200, 49, 6, 288, 2), (2048, 4, 1152, 16, 6, 288, 1),
 ])
-def test_long_unions_of_groups_side_by_side_take_few_tiles_per_wave(rules, n, k, G, F, T, steps):
-    assert rules.rule_mac_pack_steps(256, n, k, G, F, T) == steps
+def test_long_unions_of_groups_side_by_side_take_few_tiles_per_wave(rules, n, k, n_in, G, F, T, steps):
+    assert rules.rule_mac_pack_steps(256, n, k, n_in, G, F, T) == steps
 
 
 def test_network_plan_puts_16_outputs_into_rows_that_the_matrix_form_takes(rules):
