@@ -286,7 +286,7 @@ struct hcnn_ctx {
   unsigned long long* d_counters = nullptr;   // [2]
 
   uint32_t* d_evk_hat = nullptr;
-  uint32_t* d_evk_shared = nullptr;  // behind d_evk_hat in its allocation: [4][n/64][k][outputs][64], where the shared-basis relinearisation is in use
+  uint32_t* d_evk_shared = nullptr;  // behind d_evk_hat in its allocation, or in one of its own: [4][n/64][k][outputs][64], where the shared-basis relinearisation is in use
   RelinPair* d_pair = nullptr;       // [outputs / 2]
   RelinCrt* d_crt = nullptr;         // [k]
   RelinCrtInv crt_inv{};
@@ -1247,14 +1247,18 @@ int hcnn_set_relin_key(hcnn_ctx* c, const uint32_t* evk_dev) {
   const size_t rows = (size_t)c->k * 2 * c->k;
   const size_t shared_rows = shared_basis_min(c) ? (size_t)c->k * shared_outputs(c->k) : 0;
   int e;
+  const size_t own = rows * c->n, copy = shared_rows * kSharedPrimes * c->n;
+  void* ptr = nullptr;
   if (!c->d_evk_hat) {
     // one allocation for both (a second one of exactly 64 MiB takes a millisecond to free; a device that cannot spare the copy, twice the
     // key's memory, keeps the other forms)
-    void* ptr = nullptr;
-    const size_t own = rows * c->n, copy = shared_rows * kSharedPrimes * c->n;
     if (copy && dev_malloc(&ptr, (own + copy) * 4) == 0) c->d_evk_shared = (uint32_t*)ptr + own;
     else if ((e = dev_malloc(&ptr, own * 4))) return e;
     c->d_evk_hat = (uint32_t*)ptr;
+  } else if (copy && !c->d_evk_shared && dev_malloc(&ptr, copy * 4) == 0) {
+    // (the key stays where it is: graphs that the caller recorded read it there)
+    c->owned.push_back(ptr);
+    c->d_evk_shared = (uint32_t*)ptr;
   }
   e = ntt_dense(c, evk_dev, c->d_evk_hat, rows, c->k, false, kNttStoreKey);
   if (e) return e;
@@ -1933,5 +1937,9 @@ const char* hcnn_strerror(int code) {
 #endif
   return "unknown error";
 }
+
+#ifdef HCNN_HOSTEMU
+void hcnn_emu_device(uint32_t units, size_t largest_allocation) { emu_units = units; emu_largest = largest_allocation; }
+#endif
 
 }  // extern "C"

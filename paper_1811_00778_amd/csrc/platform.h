@@ -188,8 +188,11 @@ template <class K> struct LoopPhases<K, std::void_t<decltype(K::kLoopPhases)>> {
 
 #ifdef HCNN_HOSTEMU
 // ------------------------------------------------------------------ host emulation
+// What a test may set (hcnn_emu_device): compute units of the contexts created from then on, the largest allocation that is granted
+static uint32_t emu_units = 1;           // small rounds: the checker's little batches reach every batch-splitting path
+static size_t emu_largest = ~(size_t)0;
 inline int dev_malloc(void** p, size_t bytes) {
-  *p = std::malloc(bytes ? bytes : 1);
+  *p = bytes <= emu_largest ? std::malloc(bytes ? bytes : 1) : nullptr;
   return *p ? 0 : 2;
 }
 inline int dev_free(void* p) { std::free(p); return 0; }
@@ -204,7 +207,7 @@ inline int event_destroy(hcnn_event_t) { return 0; }
 inline int event_record(hcnn_event_t, hcnn_stream_t) { return 0; }
 inline int event_elapsed_ms(float* ms, hcnn_event_t, hcnn_event_t) { *ms = 0.f; return 0; }
 inline size_t max_lds_bytes() { return 160 * 1024; }
-inline uint32_t compute_unit_count() { return 1; }   // small rounds: the checker's little batches reach every batch-splitting path
+inline uint32_t compute_unit_count() { return emu_units; }
 HCNN_HD void atomic_inc64(unsigned long long* p) { *p += 1; }
 HCNN_HD void atomic_max32(uint32_t* p, uint32_t v) { if (v > *p) *p = v; }
 // on LDS words, returning the value before

@@ -79,6 +79,20 @@ def rules():
     return _lib_rules
 
 
+class device:
+    """The checker's device while the block runs: compute units that contexts made in it see, largest allocation granted."""
+
+    def __init__(self, library, units=1, largest=2 ** 64 - 1):
+        self.set, self.args = library.hcnn_emu_device, (units, largest)
+        self.set.argtypes, self.set.restype = [ctypes.c_uint32, ctypes.c_size_t], None
+
+    def __enter__(self):
+        self.set(*self.args)
+
+    def __exit__(self, *_):
+        self.set(1, 2 ** 64 - 1)
+
+
 class EmuContext(OpsMixin):
     def __init__(self, n, q, p, t, library=None):
         self.raw = _capi.RawContext(library or lib(), n, q, p, t, 0)

@@ -45,6 +45,32 @@ def test_square_relin_shared_basis(n, k, count):
         pc.check_transform_ranges(backend, n)
 
 
+def test_second_key_finds_the_room_for_its_copy_that_the_first_did_not():
+    """A device without memory for the copy of the key modulo the shared primes: the other forms until a key is set that finds it."""
+    n, k, backend = 1024, 3, SharedBasisBackend()
+    s = pc.Setup(backend, n, k)
+    cts = pc.gen.uniform_residues(s.rng, s.q, n, lead=(3, 2))
+    want = np.stack([pc.fv.square_relin(s.octx, c, s.evk) for c in cts])
+    s.ctx.set_profile(True)
+
+    def through_shared_primes():
+        s.ctx.reset_stats()
+        assert np.array_equal(s.ctx.ct_square_relin(backend.dev(cts)), want)
+        return s.ctx.profile()["relin_mac"][1] == 3 * (n // 64)          # one workgroup of eight ciphertexts per tile, counted three times
+
+    with emu.device(emu.lib_shared_basis(), largest=2 * k * k * n * 4):
+        s.ctx.set_relin_key(backend.dev(s.evk))
+    assert not through_shared_primes()
+    with emu.device(emu.lib_shared_basis(), largest=2 * k * k * n * 4):
+        s.ctx.set_relin_key(backend.dev(s.evk))
+    assert not through_shared_primes()
+    s.ctx.set_relin_key(backend.dev(s.evk))
+    assert through_shared_primes()
+    s.ctx.set_relin_key(backend.dev(s.evk))
+    assert through_shared_primes()
+    s.ctx.close()
+
+
 @pytest.mark.parametrize("n,k", [(8192, 2)])
 def test_square_relin_rows_by_two_workgroups(n, k):
     # (this build runs every squaring of these rings as the device runs its smallest ones)
