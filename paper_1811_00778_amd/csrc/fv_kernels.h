@@ -1429,7 +1429,6 @@ struct DecRoundArgs {
   const uint32_t* tab;     // [k][3]: 16-bit pieces of b_i, least significant first
   const uint32_t* cts;     // HALVES: [count][2][k][n]
   const NttLimb* limbs;    // [k]
-  uint32_t plain_key;      // HALVES: 1 where the rows carry the factor 2^-32 of a product of two plain rows
   uint64_t t;
   uint32_t n;
   uint32_t band;
@@ -1460,7 +1459,7 @@ struct DecRoundKernel {
       const uint32_t* row = src + (size_t)i * n;
       if constexpr (!HALVES) return row[0];
       const NttLimb* m = a.limbs + i;
-      const InvRoot* top = a.plain_key ? &m->inv_r : &m->inv;
+      const InvRoot* top = &m->inv_r;        // (the workgroups transform the secret themselves: a product of two plain rows carries 2^-32)
       const uint32_t p = ldc(&m->m.p, 0);
       // (below 3 p: the conversion takes any 32-bit value)
       return (uint32_t)split_root((int32_t)row[0], (int32_t)row[n / 2], split_root_factors(ldc(&top->c0, 0), ldc(&top->w, 0), half), p, ldc(&m->pinv, 0)) +

@@ -1725,7 +1725,7 @@ static int decrypt_impl(hcnn_ctx* c, const int32_t* sk, const uint32_t* ct, size
     const size_t cc = std::min(C, n_ct - c0);
     if ((e = decrypt_rows(c, sk, ct + c0 * 2 * poly, cc, s_hat, x, own, split))) return e;
     DecRoundArgs da;
-    da.cts = ct + c0 * 2 * poly; da.limbs = c->d_limbs; da.plain_key = own;
+    da.cts = ct + c0 * 2 * poly; da.limbs = c->d_limbs;
     da.x = x; da.m_out = m_out ? m_out + c0 * rn : nullptr; da.m_out64 = m_out64 ? m_out64 + c0 * rn : nullptr;
     da.bc = c->dec; da.tab = c->d_dec_tab; da.t = c->t; da.n = n;
     da.band = c->band; da.fallback_counter = c->d_counters;

@@ -585,7 +585,7 @@ struct NttFwd {
 template <int LOGN, int LOGR, int IO = kNttPlain, int SPLIT = 0>
 struct NttInv {
   static_assert(SPLIT == 0 || (SPLIT == 1 && LOGN % 2 == 1 && (IO == kNttLoadTensor || IO == kNttLoadTensorMul || IO == kNttTensorRegs0 ||
-                IO == kNttTensorRegs1 || IO == kNttTensorRegs2 || IO == kNttBackRow || IO == kNttDecOut || IO == kNttDecOwn)),
+                IO == kNttTensorRegs1 || IO == kNttTensorRegs2 || IO == kNttBackRow || IO == kNttDecOwn)),
                 "rows whose reader takes the last stage");
   static_assert(IO == kNttPlain || IO == kNttLoadTensor || IO == kNttStoreAdd || IO == kNttLoadTensorMul ||
                 IO == kNttFromRegs0 || IO == kNttFromRegs1 || IO == kNttTensorRegs0 || IO == kNttTensorRegs1 ||
@@ -1163,7 +1163,7 @@ struct CryptArgs {
 // SPLIT (decryption, n = 8192 and 32768): workgroup (ct, l, half), both ends as in the split transforms; c0 and the last stage are left to the rounding.
 template <int LOGN, int LOGR, bool ENC, bool OWN = false, int SPLIT = 0>
 struct CryptFused {
-  static_assert(!ENC || !SPLIT, "an encryption's rows are results");
+  static_assert(!SPLIT || (OWN && !ENC), "an encryption's rows are results, and a call small enough for halves transforms its own secret");
   using G = NttGeom<LOGN - SPLIT, LOGR>;
   static size_t grid(size_t slots) { return SPLIT ? split_grid(slots) : slots; }
   static constexpr int P = G::kPhases;
@@ -1190,12 +1190,12 @@ struct CryptFused {
       else NttInv<LOGN, LOGR, kNttDecOwn, SPLIT>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
     } else if constexpr (PH < P) {
       na.tw = a.tw_fwd; na.small = a.u; na.in = a.cts;
-      NttFwd<LOGN, LOGR, ENC ? kNttSmallToRegs : kNttCtToRegs, SPLIT>::template phase<PH>(na, bid, tid, lds, regs);
+      NttFwd<LOGN, LOGR, ENC ? kNttSmallToRegs : kNttCtToRegs>::template phase<PH>(na, bid, tid, lds, regs);
     } else {
       na.tw = a.tw_inv; na.in = a.key; na.out = a.out; na.aux = a.cts;
       na.msg = a.msg; na.msg64 = a.msg64; na.scale = a.scale;
       na.small = PH < 2 * P ? a.e1 : a.e2;
-      if constexpr (!ENC) NttInv<LOGN, LOGR, kNttDecOut, SPLIT>::template phase<PH - P>(na, bid, tid, lds, regs);
+      if constexpr (!ENC) NttInv<LOGN, LOGR, kNttDecOut>::template phase<PH - P>(na, bid, tid, lds, regs);
       else if constexpr (PH < 2 * P) NttInv<LOGN, LOGR, kNttEncOut0>::template phase<PH - P>(na, bid, tid, lds, regs);
       else NttInv<LOGN, LOGR, kNttEncOut1>::template phase<PH - 2 * P>(na, bid, tid, lds, regs);
     }

@@ -51,6 +51,13 @@ size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
 // LDS of a workgroup of the decryption that reads the secret's transform (n = 16384).
 size_t rule_decrypt_lds() { return CryptFused<14, 4, false>::kLdsBytes; }
 
+// Does a decryption take two workgroups per row?
+int rule_decrypts_by_halves(uint32_t units, uint32_t n, uint32_t k, size_t n_ct) {
+  hcnn_ctx c;
+  c.logn = (uint32_t)__builtin_ctz(n); c.k = k; c.compute_units = units;
+  return decrypts_by_halves(&c, n_ct);
+}
+
 // Pair (one workgroup of n <= 16384) or, n = 32768, place (half of a pair) that workgroup `bid` of the one-kernel tensor takes in the order of the limbs.
 uint32_t rule_tensor_place(uint32_t split, uint32_t n_ct, uint32_t L, uint32_t bid) {
   TensorFusedArgs a{};

@@ -99,6 +99,26 @@ def check_keygen_encrypt_decrypt(backend, n, k, count=3, seed_id=1):
     s.ctx.close()
 
 
+def check_decrypt_exact(backend, n, k, t, count=3):
+    """Decryption of uniform and of genuine ciphertexts with every comparison of the rounding exact, and with the default band: the
+    oracle's plaintext words either way."""
+    s = Setup(backend, n, k, t=t, stream=61)
+    cts = gen.uniform_residues(s.rng, s.q, n, lead=(count, 2))
+    for l, p in enumerate(s.q):
+        cts[0, :, l, :4] = [[0, 1, p - 1, p // 2], [p - 1, 0, 1, p - 1]]
+    m = s.rng.integers(0, t, size=n, dtype=np.int64).astype(np.uint64 if t >> 32 else np.uint32)
+    er = gen.encryption_randomness(s.rng, n, 1)
+    cts[count - 1] = fv.encrypt(s.octx, s.pk, [int(v) for v in m], er["u"][0], er["e1"][0], er["e2"][0])
+    want = np.stack([fv.decrypt(s.octx, s.kr["s"], c) for c in cts])
+    assert np.array_equal(want[count - 1], m)
+    for band in (128, 1 << 26):
+        s.ctx.set_ambiguity_band(band)
+        s.ctx.reset_stats()
+        assert np.array_equal(backend.host(s.ctx.decrypt(backend.dev(s.kr["s"]), backend.dev(cts))), want), ("decrypt", n, k, t, band)
+    assert s.ctx.exact_fallbacks() > n                            # the exact comparison really ran
+    s.ctx.close()
+
+
 def check_scalar_mac(backend, n, k, seed_id=1):
     s = Setup(backend, n, k, seed_id=seed_id, with_keys=False)
     n_in = 9

@@ -104,6 +104,11 @@ def test_decrypt_rows_by_two_workgroups():
     pc.check_keygen_encrypt_decrypt(SharedBasisBackend(), 8192, 2, count=2)
 
 
+@pytest.mark.parametrize("n,k,t", [(8192, 5, 65537), (8192, 6, pc.WIDE_T), (32768, 5, 65537)])
+def test_decrypt_by_halves_with_every_comparison_exact(n, k, t):
+    pc.check_decrypt_exact(SharedBasisBackend(), n, k, t)          # (this build takes halves at both rings)
+
+
 @pytest.mark.parametrize("n,k", [(4096, 3), (8192, 2), (16384, 2), (32768, 2)])
 def test_encrypt_decrypt_of_every_ring(backend, n, k):
     pc.check_keygen_encrypt_decrypt(backend, n, k, count=1)

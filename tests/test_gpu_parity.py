@@ -163,6 +163,13 @@ def test_scalar_mac_over_the_union_of_two_rows(backend, c_in, side, f, stride, p
     pc.check_scalar_mac_pairs(backend, c_in, side, f, stride, pad, F, base, n, k)
 
 
+@pytest.mark.parametrize("n,k,t", [(8192, 5, 65537), (8192, 6, pc.WIDE_T), (32768, 5, 65537), (32768, 6, pc.WIDE_T)])
+def test_decrypt_by_halves_with_every_comparison_exact(backend, n, k, t):
+    say("decrypt, two workgroups per row, every comparison exact, n=%d k=%d" % (n, k))
+    assert emu.rules().rule_decrypts_by_halves(device_units(), n, k, 3)
+    pc.check_decrypt_exact(backend, n, k, t)
+
+
 def test_square_relin_tiny_config(backend):
     say("square_relin n=1024 k=2")
     pc.check_square_relin(backend, 1024, 2)
