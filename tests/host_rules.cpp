@@ -51,6 +51,13 @@ size_t rule_mac_matrix_lds(uint32_t groups, size_t T) {
 // LDS of a workgroup of the decryption that reads the secret's transform (n = 16384).
 size_t rule_decrypt_lds() { return CryptFused<14, 4, false>::kLdsBytes; }
 
+// Do the inverse transforms of `rows` rows of a squaring's tensor take two workgroups per row?
+int rule_splits_tensor_rows(uint32_t units, uint32_t n, size_t rows) {
+  hcnn_ctx c;
+  c.logn = (uint32_t)__builtin_ctz(n); c.compute_units = units;
+  return splits_tensor_rows(&c, rows);
+}
+
 // Does a decryption take two workgroups per row?
 int rule_decrypts_by_halves(uint32_t units, uint32_t n, uint32_t k, size_t n_ct) {
   hcnn_ctx c;

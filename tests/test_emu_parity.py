@@ -330,6 +330,26 @@ def test_square_relin_largest_ring_two_workgroups_per_forward_row(backend):
     pc.check_square_relin(backend, 32768, 2, n_random=2, n_genuine=0)
 
 
+def test_largest_ring_with_whole_rows_and_with_halves():
+    """n = 32768, 18 rows of the tensor: whole-row inverse transforms in front of the scaling while the rows, but not their halves, find a
+    compute unit each; both ends of that range, squaring and product."""
+    n, k, backend = 32768, 2, EmuBackend()
+    s = pc.Setup(backend, n, k)
+    cts = pc.gen.uniform_residues(s.rng, s.q, n, lead=(2, 2))
+    square, product = pc.fv.square_relin(s.octx, cts[0], s.evk), pc.fv.hmult(s.octx, cts[0], cts[1], s.evk)
+    rows = 3 * (k + len(s.p))
+    for units, split in ((2 * rows, True), (2 * rows - 1, False), (rows, False), (rows - 1, True)):
+        assert emu.rules().rule_splits_tensor_rows(units, n, rows) == split
+        with emu.device(emu.lib(), units=units):
+            ctx = backend.make_ctx(n, s.q, s.p, s.t)
+        ctx.set_relin_key(backend.dev(s.evk))
+        ctx.set_profile(True)
+        assert np.array_equal(ctx.ct_square_relin(backend.dev(cts[:1]))[0], square), units
+        assert ctx.profile()["tensor"][0] == 0
+        assert np.array_equal(ctx.ct_mul_relin(backend.dev(cts[:1]), backend.dev(cts[1:]))[0], product), units
+        ctx.close()
+
+
 @pytest.mark.parametrize("k,options", [(2, dict(force_exact=True)), (3, dict(relin_order=1))])
 def test_square_relin_largest_ring_by_halves(backend, k, options):
     # n = 32768: inverse transforms left at the halves of their rows, the scaling takes their last stage; the one-kernel tensor

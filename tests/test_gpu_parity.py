@@ -216,6 +216,32 @@ def test_square_relin_largest_rings_residue_exact(backend):
     pc.check_square_relin(backend, 32768, 6, n_random=1, n_genuine=0)
 
 
+@pytest.mark.parametrize("cts", [7, 8, 14, 15])
+def test_largest_ring_with_whole_rows_and_with_halves(backend, cts):
+    """n = 32768, 18 rows of the tensor a ciphertext: both ends of the range in which whole rows, but not their halves, find a compute unit each."""
+    n, k = 32768, 2
+    say("square_relin and product n=32768 k=2, %d ciphertexts" % cts)
+    s = pc.Setup(backend, n, k)
+    rows = 3 * cts * (k + len(s.p))
+    assert emu.rules().rule_splits_tensor_rows(device_units(), n, rows) == (cts in (7, 15))
+    s.ctx.set_relin_key(backend.dev(s.evk))
+    x = gen.uniform_residues(s.rng, s.q, n, lead=(cts, 2))
+    a, b = backend.dev(x), backend.dev(x[::-1].copy())
+    s.ctx.set_profile(True)
+    square = backend.host(s.ctx.ct_square_relin(a))
+    assert s.ctx.profile()["tensor"][0] == 0                              # the separate transforms
+    s.ctx.set_profile(False)
+    product = backend.host(s.ctx.ct_mul_relin(a, b))
+    if cts in (7, 8):
+        assert np.array_equal(square[cts - 1], fv.square_relin(s.octx, x[cts - 1], s.evk))
+        assert np.array_equal(product[0], fv.hmult(s.octx, x[0], x[cts - 1], s.evk))
+    s.ctx.set_square_chunk(1)                                             # 18 rows at a time: halves
+    assert np.array_equal(backend.host(s.ctx.ct_mul_relin(a, b)), product)
+    s.ctx.set_fusion(2)
+    assert np.array_equal(backend.host(s.ctx.ct_square_relin(a)), square)
+    s.ctx.close()
+
+
 @pytest.mark.parametrize("mode", [1, 2])
 def test_square_relin_largest_ring_exact_comparison(backend, mode):
     """n = 32768: the scaling's exact comparison rebuilds the residues from the halves that the inverse transforms leave."""
