@@ -240,9 +240,12 @@ enum {
                                     (compute units x the occupancy the runtime reports for the compiled kernel);
                                     the default policy of HCNN_OPT_FUSION sizes its rounds from it: a round is
                                     8 * floor(this / 8 / k) ciphertexts                         */
-  HCNN_STAT_TENSOR_FUSED_WGS = 4 /* the same for the one-kernel squaring tensor, taken for internal batches whose
-                                    n_ct * (k + k_aux) (ciphertext, limb) pairs fill their rounds of
-                                    this many workgroups to at least 7/8, or are enough in number */
+  HCNN_STAT_TENSOR_FUSED_WGS = 4, /* the same for the one-kernel squaring tensor, which has a workgroup for each of the
+                                    n_ct * (k + k_aux) (ciphertext, limb) pairs of an internal batch, two at
+                                    n = 32768; taken for batches that fill their rounds of this many
+                                    workgroups to at least 7/8, or have as many as the next one says   */
+  HCNN_STAT_TENSOR_FUSED_LEAST = 5 /* workgroups from which it is taken however its rounds are filled, by the ring
+                                    (0: by its rounds alone)                                    */
 };
 /* Synchronises the context's stream, then reads the counter. */
 int hcnn_get_stat(hcnn_ctx* ctx, int which, uint64_t* out);

@@ -6,7 +6,7 @@ u64p = C.POINTER(C.c_uint64)
 ptr = C.c_void_p
 
 ERR = dict(OK=0, NULL=-1, N=-2, PRIME=-3, T=-4, AUX=-5, ARG=-6, NOKEY=-7, ALIGN=-8, NODEVICE=-9, SCRATCH=-10)
-STAT_EXACT_FALLBACKS, STAT_BAD_INPUT, STAT_SCRATCH_BYTES, STAT_RELIN_FUSED_WGS, STAT_TENSOR_FUSED_WGS = 0, 1, 2, 3, 4
+STAT_EXACT_FALLBACKS, STAT_BAD_INPUT, STAT_SCRATCH_BYTES, STAT_RELIN_FUSED_WGS, STAT_TENSOR_FUSED_WGS, STAT_TENSOR_FUSED_LEAST = 0, 1, 2, 3, 4, 5
 OPT_AMBIGUITY_BAND, OPT_SQUARE_CHUNK, OPT_PROFILE, OPT_RELIN_ORDER, OPT_FUSION = 0, 1, 2, 3, 4
 PROF_CLASSES = ["ntt_fwd", "ntt_inv", "base_ext", "tensor", "scale", "digit", "relin_mac", "relin_add",
                 "scalar_mac", "other", "relin_fused"]

@@ -207,22 +207,23 @@ class OpsMixin:
         the runtime reports for the compiled kernel; 0 when even one ciphertext's workgroups do not fit)."""
         return self.raw.stat(_capi.STAT_RELIN_FUSED_WGS) // 8 // self.k * 8
 
-    # workgroups from which the one-kernel tensor is taken however its rounds are filled
-    _TENSOR_LEAST = {1024: 448, 2048: 640, 4096: 320, 8192: 384, 32768: 320}
+    def _tensor_wgs_per_pair(self):
+        return 2 if self.n == 32768 else 1
 
     def takes_tensor_fused(self, n_ct):
-        """Does the default policy take the one-kernel squaring tensor for an internal batch of n_ct ciphertexts: its
-        (ciphertext, limb) pairs fill their rounds of resident workgroups to at least 7/8 (two workgroups per pair at n = 32768), or are
-        enough whatever their rounds."""
-        slots, wgs = self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS), n_ct * (self.raw.k + self.raw.k_aux) * (2 if self.n == 32768 else 1)
-        return 8 * wgs >= 7 * slots * -(-wgs // slots) or wgs >= self._TENSOR_LEAST.get(self.n, wgs + 1)
+        """Does the default policy take the one-kernel squaring tensor for an internal batch of n_ct ciphertexts: its workgroups (one for
+        each (ciphertext, limb) pair, two at n = 32768) fill their rounds to at least 7/8 or are enough whatever their rounds."""
+        slots, least = self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS), self.raw.stat(_capi.STAT_TENSOR_FUSED_LEAST)
+        wgs = n_ct * (self.raw.k + self.raw.k_aux) * self._tensor_wgs_per_pair()
+        return 8 * wgs >= 7 * slots * -(-wgs // slots) or 0 < least <= wgs
 
     def tensor_fused_threshold(self):
         """(ciphertext, limb) pairs of an internal batch from which the default policy takes the one-kernel squaring tensor
-        however full its last round is (7/8 of seven rounds: from eight rounds on one more is always filled enough);
-        takes_tensor_fused tells for smaller ones."""
-        # (from _TENSOR_LEAST on it is taken too)
-        return -(-49 * self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS) // 8)
+        however full its last round is: 7/8 of seven rounds (from eight rounds on one more is always filled enough) or the ring's
+        own line, whichever is less; takes_tensor_fused tells for smaller ones."""
+        slots, least = self.raw.stat(_capi.STAT_TENSOR_FUSED_WGS), self.raw.stat(_capi.STAT_TENSOR_FUSED_LEAST)
+        wgs = min(-(-49 * slots // 8), least or 49 * slots)
+        return -(-wgs // self._tensor_wgs_per_pair())
 
     def reset_stats(self):
         self._call("hcnn_reset_stats")

@@ -1339,10 +1339,21 @@ static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds
 }
 // Workgroups from which the one-kernel tensor is taken however its rounds are filled (the same measurements: with it / with two kernels, n =
 // 1024 from 448 0.95-1.0, n = 2048 from 640 0.9-1.03, n = 4096 from 320 0.88-1.01, n = 8192 from 384 0.94-1.01, n = 32768 from 320 0.93-1.02; n = 16384, 0.95-1.05
-// from 320 on, goes by its rounds alone).
-static size_t tensor_fused_least(uint32_t logn) {
-  static constexpr size_t least[6] = {448, 640, 320, 384, ~(size_t)0, 320};
-  return least[logn - 10];
+// from 320 on, goes by its rounds alone: 0).
+static size_t tensor_fused_least(const hcnn_ctx* c) {
+  static constexpr size_t least[6] = {448, 640, 320, 384, 0, 320};
+  return least[c->logn - 10];
+}
+// Workgroups of the one-kernel tensor of n_ct ciphertexts: one per (ciphertext, limb) pair, at n = 32768 two.
+static size_t tensor_fused_wgs(const hcnn_ctx* c, size_t n_ct) { return n_ct * (c->k + c->kp) * (c->logn == 15 ? 2 : 1); }
+// Does the default policy take it?  Its workgroups are long (five transforms), so it pays when they fill their rounds.  Measured at n = 8192, k = 8: 1.06 us
+// per ciphertext in full rounds against 1.25 of the two separate kernels (64 to 512 ciphertexts), a ratio of 0.85; at n = 32768, k = 24 15.5 against
+// 18.8 (32), 0.82.  A last round that is only partly filled is shorter too (workgroups with a compute unit to themselves run faster), so that from
+// tensor_fused_least workgroups on it pays whatever their number.
+static bool takes_tensor_fused(const hcnn_ctx* c, size_t n_ct) {
+  const size_t wgs = tensor_fused_wgs(c, n_ct), least = tensor_fused_least(c);
+  const size_t slots = tensor_fused_slots(c), rounds = (wgs + slots - 1) / slots;
+  return (least && wgs >= least) || wgs * 8 >= rounds * slots * 7;
 }
 
 // Limbs of a ciphertext whose workgroups run side by side on one die in the one-kernel relinearisation.  All k read every digit row once, but bring the
@@ -1470,19 +1481,6 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     const size_t whole = cc / fused_round * fused_round, rest = cc - whole;
     return rest * k >= relin_fused_least(c, rest, whole != 0) ? cc : whole;
   };
-  // Steps 2+3 in one kernel for squarings: its workgroups are long (five transforms), so it pays when they fill their
-  // rounds.  Measured at n = 8192, k = 8: 1.06 us per ciphertext in full rounds against 1.25 of the two separate kernels
-  // (64 to 512 ciphertexts), a ratio of 0.85; at n = 32768, k = 24 15.5 against 18.8 (32), 0.82.  A last round that is only
-  // partly filled is shorter too (workgroups with a compute unit to themselves run faster), so that from tensor_fused_least
-  // workgroups on it pays whatever their number.
-  auto tensor_fused_wgs = [&](size_t cc) { return c->logn == 15 ? 2 * cc * L : cc * L; };      // (n = 32768: two workgroups per pair)
-  auto takes_tensor_fused = [&](size_t cc) {
-    if (in_b || c->fusion == 1) return false;
-    const size_t wgs = tensor_fused_wgs(cc);
-    const size_t slots = tensor_fused_slots(c), rounds = (wgs + slots - 1) / slots;
-    return c->fusion == 2 || wgs >= tensor_fused_least(c->logn) || wgs * 8 >= rounds * slots * 7;
-  };
-
   // One internal batch: ciphertexts [c0, c0 + cc) of the call, nf of
   // them through the one-kernel relinearisation.
   auto one_batch = [&](size_t c0, size_t cc, size_t nf) -> int {
@@ -1498,7 +1496,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     // 2. forward NTT over all k + k' limbs, the first k read from the ciphertext itself
     // (forward rows by two workgroups: the new rows are staged in the array of the tensor, free until step 3, because that transform
     // cannot work in place)
-    const bool tensor_fused = takes_tensor_fused(cc);
+    const bool tensor_fused = !in_b && c->fusion != 1 && (c->fusion == 2 || takes_tensor_fused(c, cc));      // steps 2 and 3 in one kernel
     const bool staged = !tensor_fused && splits_rows(c, cc * 2 * L);
     uint32_t* const b_new = staged ? b_d : b_ext;
     ExtArgs ea;
@@ -1508,7 +1506,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
     if (tensor_fused) {
       TensorFusedArgs ta{in + c0 * ct_words, b_ext, b_d, c->d_tw_fwd, c->d_tw_inv, c->d_limbs, k, L, (uint32_t)(cc * L), fast_div(L), {0, 0}};
       // (up to one and a half rounds the order of the limbs gains nothing: n = 32768, k = 12, 8 ciphertexts 273 / 276 us)
-      if (2 * tensor_fused_wgs(cc) > 3 * tensor_fused_slots(c)) ta.cts_div = fast_div((uint32_t)cc);
+      if (2 * tensor_fused_wgs(c, cc) > 3 * tensor_fused_slots(c)) ta.cts_div = fast_div((uint32_t)cc);
       const size_t rows = cc * L * 5;
       switch (c->logn) {
         case 10: e = run<TensorFused<10, 4>>(c, cc * L, TensorFused<10, 4>::kLdsBytes, ta, rows); break;
@@ -1817,6 +1815,10 @@ int hcnn_get_stat(hcnn_ctx* c, int which, uint64_t* out) {
   }
   if (which == HCNN_STAT_RELIN_FUSED_WGS || which == HCNN_STAT_TENSOR_FUSED_WGS) {
     *out = which == HCNN_STAT_RELIN_FUSED_WGS ? relin_fused_slots(c) : tensor_fused_slots(c);
+    return HCNN_OK;
+  }
+  if (which == HCNN_STAT_TENSOR_FUSED_LEAST) {
+    *out = tensor_fused_least(c);
     return HCNN_OK;
   }
   if (which != HCNN_STAT_EXACT_FALLBACKS && which != HCNN_STAT_BAD_INPUT) return HCNN_ERR_ARG;

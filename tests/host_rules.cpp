@@ -65,6 +65,28 @@ int rule_decrypts_by_halves(uint32_t units, uint32_t n, uint32_t k, size_t n_ct)
   return decrypts_by_halves(&c, n_ct);
 }
 
+// Does a squaring's internal batch take the one-kernel tensor, and from how many workgroups on whatever their rounds (0: never)?
+static hcnn_ctx tensor_ctx(uint32_t units, uint32_t per_unit, uint32_t n, uint32_t k, uint32_t k_aux) {
+  hcnn_ctx c;
+  c.logn = (uint32_t)__builtin_ctz(n); c.k = k; c.kp = k_aux; c.compute_units = units; c.tensor_fused_wgs = per_unit;
+  return c;
+}
+int rule_takes_tensor_fused(uint32_t units, uint32_t per_unit, uint32_t n, uint32_t k, uint32_t k_aux, size_t n_ct) {
+  const hcnn_ctx c = tensor_ctx(units, per_unit, n, k, k_aux);
+  return takes_tensor_fused(&c, n_ct);
+}
+size_t rule_tensor_fused_least(uint32_t n) {
+  const hcnn_ctx c = tensor_ctx(256, 1, n, 1, 1);
+  return tensor_fused_least(&c);
+}
+
+// Workgroups from which the one-kernel relinearisation takes n_ct ciphertexts that are not whole rounds.
+size_t rule_relin_fused_least(uint32_t units, uint32_t n, uint32_t k, size_t n_ct, int with_rounds) {
+  hcnn_ctx c;
+  c.logn = (uint32_t)__builtin_ctz(n); c.k = k; c.compute_units = units;
+  return relin_fused_least(&c, n_ct, with_rounds);
+}
+
 // Pair (one workgroup of n <= 16384) or, n = 32768, place (half of a pair) that workgroup `bid` of the one-kernel tensor takes in the order of the limbs.
 uint32_t rule_tensor_place(uint32_t split, uint32_t n_ct, uint32_t L, uint32_t bid) {
   TensorFusedArgs a{};

@@ -3,7 +3,8 @@ wrong are too large, or of too large a device, to be run through the entry point
 import pytest
 
 import emu
-from paper_1811_00778_amd import network
+from paper_1811_00778_amd import _capi, network
+from paper_1811_00778_amd._ops import OpsMixin
 
 
 @pytest.fixture(scope="module")
@@ -152,6 +153,37 @@ def test_one_kernel_tensor_takes_every_pair_once_in_the_order_of_the_limbs(rules
     taken = [(b // 16 * 8 + b % 8, b // 8 % 2) for b in places]
     assert sorted(t for t in taken if t[0] < rows) == [(p, h) for p in range(rows) for h in (0, 1)]
     assert [p for p, h in taken if p < rows and h == 0] == pairs
+
+
+@pytest.mark.parametrize("n,least", [(1024, 448), (2048, 640), (4096, 320), (8192, 384), (16384, 0), (32768, 320)])
+def test_binding_reports_the_rule_of_the_one_kernel_tensor(rules, n, least):
+    """What the binding works out from the library's figures against the rule itself, on a device of 256 compute units."""
+    assert rules.rule_tensor_fused_least(n) == least
+    k, k_aux, per_unit = 3, 5, 2
+
+    class Raw:
+        stats = {_capi.STAT_TENSOR_FUSED_WGS: 256 * per_unit, _capi.STAT_TENSOR_FUSED_LEAST: least}
+
+        def stat(self, which):
+            return self.stats[which]
+
+    ops = OpsMixin()
+    ops.raw = Raw()
+    ops.raw.n, ops.raw.k, ops.raw.k_aux = n, k, k_aux
+    took = [ops.takes_tensor_fused(n_ct) for n_ct in range(1, 700)]
+    assert took == [bool(rules.rule_takes_tensor_fused(256, per_unit, n, k, k_aux, n_ct)) for n_ct in range(1, 700)]
+    threshold = ops.tensor_fused_threshold()
+    assert all(took[-(-threshold // (k + k_aux)) - 1:])
+    assert threshold == (least // (2 if n == 32768 else 1) if least else 49 * 512 // 8)
+
+
+@pytest.mark.parametrize("n,k,n_ct,rest,least", [
+    (1024, 2, 8, False, 16), (2048, 3, 8, False, 40), (4096, 4, 8, False, 96), (1024, 2, 8, True, 8), (8192, 8, 8, True, 96), (16384, 8, 8, True, 68),
+    # from n = 8192 on: does the fullest die have a compute unit for each of its workgroups?
+    (8192, 8, 32, False, 192), (8192, 8, 33, False, 288), (8192, 10, 24, False, 192), (8192, 10, 25, False, 288), (16384, 16, 16, False, 136), (16384, 16, 17, False, 288),
+])
+def test_workgroups_from_which_the_one_kernel_relinearisation_is_taken(rules, n, k, n_ct, rest, least):
+    assert rules.rule_relin_fused_least(256, n, k, n_ct, rest) == least
 
 
 @pytest.mark.parametrize("n,k,share", [(8192, 7, 7), (8192, 8, 4), (8192, 9, 9), (8192, 12, 6), (16384, 6, 3), (16384, 16, 8), (4096, 6, 6), (4096, 12, 6)])
