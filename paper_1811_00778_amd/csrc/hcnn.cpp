@@ -1001,6 +1001,10 @@ int mac_dispatch(hcnn_ctx* c, size_t grid, const MacArgs& a) {
   return HCNN_ERR_ARG;
 }
 
+// One-kernel relinearisation of more than 16 primes (n = 16384 takes it for up to 16)
+template <int LOGN, int LOGR>
+using RelinFusedLong = RelinFused<LOGN, LOGR, LOGN == 14 ? kNttFusedMac16 : kNttFusedMacAny>;
+
 // Occupancy of the two long-running one-kernel forms for this ring and basis, asked of the runtime once.
 int query_fused_occupancy(hcnn_ctx* c) {
   const uint32_t k = c->k;
@@ -1010,7 +1014,7 @@ int query_fused_occupancy(hcnn_ctx* c) {
     const size_t lds = RelinFused<LOGN, LOGR>::kLdsBytes;                                                             \
     e = k <= 8    ? resident_workgroups_per_cu<RelinFused<LOGN, LOGR, kNttFusedMac>, RelinFusedArgs>(lds, &r)         \
         : k <= 16 ? resident_workgroups_per_cu<RelinFused<LOGN, LOGR, kNttFusedMac16>, RelinFusedArgs>(lds, &r)       \
-                  : resident_workgroups_per_cu<RelinFused<LOGN, LOGR, kNttFusedMacAny>, RelinFusedArgs>(lds, &r);     \
+                  : resident_workgroups_per_cu<RelinFusedLong<LOGN, LOGR>, RelinFusedArgs>(lds, &r);                  \
   }
   switch (c->logn) {
     case 10: HCNN_OCC(10, 4) break;
@@ -1552,7 +1556,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
 #define HCNN_FUSED(LOGN, LOGR)                                                                                      \
   (k <= 8 ? run<RelinFused<LOGN, LOGR, kNttFusedMac>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMac>::kLdsBytes, fa, rows)             \
           : k <= 16 ? run<RelinFused<LOGN, LOGR, kNttFusedMac16>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMac16>::kLdsBytes, fa, rows) \
-                    : run<RelinFused<LOGN, LOGR, kNttFusedMacAny>>(c, grid, RelinFused<LOGN, LOGR, kNttFusedMacAny>::kLdsBytes, fa, rows))
+                    : run<RelinFusedLong<LOGN, LOGR>>(c, grid, RelinFusedLong<LOGN, LOGR>::kLdsBytes, fa, rows))
       switch (c->logn) {
         case 10: e = HCNN_FUSED(10, 4); break;
         case 11: e = HCNN_FUSED(11, 4); break;
