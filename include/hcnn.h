@@ -283,9 +283,11 @@ int hcnn_set_option(hcnn_ctx* ctx, int which, uint64_t value);
  * path (the classes follow the steps of HMult in Sec. 2.1 and the layer sum of Sec. 4.3).
  * `blocks` is the number of workgroups launched: one (polynomial, limb) row of n residues per
  * workgroup for the two NTT classes, 256 coefficient positions (1024 for RELIN_MAC and
- * SCALAR_MAC; RELIN_MAC through shared auxiliary primes counts three per tile of 64 coefficients
- * and eight ciphertexts, SCALAR_MAC's forms for many filters launch fewer or more) per workgroup for the others; for RELIN_FUSED it is the number of rows the launch
- * transforms (k forward + 2 inverse per workgroup).
+ * SCALAR_MAC) per workgroup for the others.  Other units: RELIN_MAC through shared auxiliary
+ * primes counts three quarters of its workgroups (three of four per tile of 64 coefficients and
+ * eight ciphertexts); SCALAR_MAC's matrix forms launch fewer or more than one per 1024 positions;
+ * TENSOR and RELIN_FUSED count the rows that the launch transforms (five per workgroup, or half a
+ * row each at n = 32768; k forward + 2 inverse).
  * hcnn_profile_read synchronises the stream; hcnn_reset_stats clears the accumulators. */
 enum {
   HCNN_PROF_NTT_FWD = 0,

@@ -1380,8 +1380,8 @@ static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* d
   if ((e = ntt_rows(c, r, false, kNttDigitTile))) return e;
   RelinSharedArgs sa{dig, c->d_evk_shared, acc, c->d_limbs + k, k, outs, n, (uint32_t)n_ct, (uint32_t)((n_ct + 7) / 8)};
   const size_t grid = (size_t)kSharedPrimes * (n / 64) * sa.n_grp;
-  // (the profile counts three per tile of 64 coefficients and eight ciphertexts)
-  const size_t units = (size_t)3 * (n / 64) * ((n_ct + 7) / 8);
+  // (the profile's unit is three for a tile of 64 coefficients and eight ciphertexts, whose workgroups are kSharedPrimes: counted from the grid)
+  const size_t units = grid * 3 / kSharedPrimes;
   switch ((outs + 7) / 8) {
 #define HCNN_SHARED_MAC(O) case O: e = run<RelinSharedMac<O>>(c, grid, RelinSharedMac<O>::lds_bytes(k), sa, units); break;
 #ifdef HCNN_SHARED_ALL
