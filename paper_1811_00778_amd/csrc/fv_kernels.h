@@ -199,8 +199,8 @@ struct ExtKernel {
     const int32_t v = untraced((int32_t)bconv_round(S, a.band, exact, a.fallback_counter));
     // (rows 0..K-1 of `out` are not written: the forward transform reads those limbs from the ciphertext itself)
     // rolled loop over the destination primes (three at a time for short bases, whose small launches wait for the tables: one squaring of 8 primes
-    // at n = 8192 34.4 / 34.1 us with the same in the scaling): row j of the transposed table is one contiguous scalar load
-#pragma unroll (K <= 8 ? 3 : 1)
+    // at n = 8192 34.4 / 34.1 us; the compiler does not unroll the like of it in the scaling): row j of the transposed table is one contiguous scalar load
+#pragma unroll K <= 8 ? 3 : 1
     for (uint32_t j = 0; j < kp; ++j) {
       const BConvDst d = ldc_at(a.bc.dst + j, 0u);
       dst[(size_t)(K + j) * n] = bconv_reduce(bconv_sum<K>((int64_t)v * d.v, z, a.bc.BT + (size_t)j * K, 1, d.rc), d);
@@ -304,7 +304,7 @@ struct ScaleKernel {
     for (int i = 0; i < K; ++i) out_acc[i] = 0;
     uint32_t S2 = 0, room = kSumRoom;
     Words dp_next = load(K);
-#pragma unroll (K <= 8 ? 3 : 1)
+#pragma unroll 1
     for (uint32_t j = 0; j < kp; ++j) {
       const Words dpj = dp_next;
       if (j + 1 < kp) dp_next = load(K + j + 1);
