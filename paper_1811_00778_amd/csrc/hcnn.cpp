@@ -1329,11 +1329,13 @@ static size_t relin_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_u
 static size_t tensor_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_units * c->tensor_fused_wgs; }
 
 // Workgroups (ciphertext, prime) from which the one-kernel relinearisation takes `n_ct` ciphertexts that are not whole rounds of it, by
-// themselves or (with_rounds) behind whole rounds.  1800 squarings of 1 to 700 ciphertexts timed with either form, 256 compute units; time of a
-// squaring with this form / with the separate kernels: n = 1024, 16 workgroups 0.84-0.95, n = 2048, 36 to 40 0.88-0.99, n = 4096, 64 to 128 0.90-1.05,
-// more 0.8-0.95.  From n = 8192 on it matters whether the fullest die has a compute unit for each of its workgroups (the primes of a ciphertext share
-// a die): n = 8192 190 0.99, 208 to 240 0.91-0.96 where it has, 198 to 260 1.01-1.17 where not, 297 to 340 0.89-0.97; n = 16384 128
-// 1.0-1.04, 140 to 256 0.83-0.98 and 216 to 288 0.99-1.19, 320 0.97.
+// themselves or (with_rounds) behind whole rounds.  1800 squarings of 1 to 700 ciphertexts timed with either form on 256 compute units (the lines are
+// counts on that device, not shares of another one); time of a squaring with this form / with the separate kernels: n = 1024, 16 workgroups 0.84-0.95, n =
+// 2048, 36 to 40 0.88-0.99, n = 4096, 64 to 128 0.90-1.05, more 0.8-0.95.  From n = 8192 on it matters whether the fullest die has a compute unit for each of
+// its workgroups: n = 8192 190 0.99, 208 to 240 0.91-0.96 where it has, 198 to 260 1.01-1.17 where not, 297 to 340 0.89-0.97; n = 16384 128 1.0-1.04, 140
+// to 256 0.83-0.98 and 216 to 288 0.99-1.19, 320 0.97.  That die is counted with all primes of a ciphertext on it, as they were when this was measured; where relin_share
+// puts half of them there, some calls fill it less than the rule has it (17 to 20 ciphertexts of 12 primes: 36 workgroups counted, 30 there are) and stay with the
+// separate kernels.
 constexpr uint32_t kRelinFusedMost = 288;
 static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds) {
   static constexpr uint32_t least[5] = {16, 40, 96, 192, 136};              // n = 1024 .. 16384
@@ -1437,7 +1439,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   // rows per ciphertext over the chip (relin_fused_least).
   const size_t shared_min = c->fusion == 0 && !static_ws && c->d_evk_shared ? shared_basis_min(c) : 0;
   const bool fused = c->fusion != 1 && (c->logn <= 13 || (c->logn == 14 && k <= 16));
-  // (the k workgroups of a ciphertext share a die, for its L2: a round is counted per die)
+  // (a round is counted in whole ciphertexts per die, also where half of a ciphertext's workgroups share one: relin_share)
   const size_t fused_round = fused ? relin_fused_slots(c) / kXcds / k * kXcds : 0;   // ciphertexts per round (0: never)
   const size_t words_main = (ext_rows + 3 * L + 3 * k) * rn;
   const size_t words_split = ((size_t)k * k + 2 * k) * rn, words_shared = (size_t)kSharedPrimes * (k + shared_outputs(k)) * rn;

@@ -1097,7 +1097,8 @@ struct TensorFused {
 // primes, plus y_b: one read of the sums, one write of the result.  (The largest ring does not hold three rows beside the one in
 // work in its registers: kNttBackRow and RelinCombine.)
 // Bound: one 1024-thread workgroup per compute unit, in step with itself.  A row's words are loaded during the last pass of the row before
-// (n = 16384, k = 16, 225 ciphertexts 690 -> 648 us; 397 by bytes).
+// (n = 16384, k = 16, 225 ciphertexts 690 -> 648 us; 397 by bytes); with three rows parked and the next one's words that takes all 128 registers and spills
+// 14 (60 bytes of scratch a lane).
 struct RelinBackArgs {
   const uint32_t* acc;      // [n_ct][4][n/64][outputs][64]
   const uint32_t* y;        // [n_ct][3][k][n]
