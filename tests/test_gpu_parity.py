@@ -166,7 +166,7 @@ def test_scalar_mac_over_the_union_of_two_rows(backend, c_in, side, f, stride, p
 @pytest.mark.parametrize("n,k,t", [(8192, 5, 65537), (8192, 6, pc.WIDE_T), (32768, 5, 65537), (32768, 6, pc.WIDE_T)])
 def test_decrypt_by_halves_with_every_comparison_exact(backend, n, k, t):
     say("decrypt, two workgroups per row, every comparison exact, n=%d k=%d" % (n, k))
-    assert emu.rules().rule_decrypts_by_halves(device_units(), n, k, 3)
+    assert emu.rules().rule_decrypts_by_halves(device_units(), n, k, 4)
     pc.check_decrypt_exact(backend, n, k, t)
 
 
