@@ -1078,13 +1078,13 @@ int secret_hat(hcnn_ctx* c, const int32_t* s, uint32_t* s_hat) {
 // Does every (ciphertext, limb) row find a compute unit of its own?  Then a workgroup's own transform of s is shorter than
 // a launch for it in front.
 bool decrypts_with_own_key(const hcnn_ctx* c, size_t n_ct) { return c->logn <= 14 && n_ct * c->k <= c->compute_units; }
-// Does a decryption take two workgroups per row, the rounding the last stage of their inverse transforms?  n = 8192 while both halves of every row
-// find a compute unit of their own (us, 8 primes, 10 ciphertexts 17.5 / 14.1); n = 32768 up to 4/9 of as many rows as compute units (12 primes, 1 ciphertext 48.2 /
-// 38.9, 4 49.9 / 40.8, 10 51.6 / 54.8; 16 primes, 7 54.1 / 46.4) and 16 primes (24, 1 52.7 / 56.2: the rounding waits for its loads).
+// Does a decryption take two workgroups per row, the rounding the last stage of their inverse transforms?  n = 8192 and 32768 while the fullest die, which has all
+// rows of an eighth of the ciphertexts, has a compute unit for each half (us, whole rows / halves: n = 8192, 8 primes, 10 ciphertexts 17.5 / 14.1; n = 32768, 12
+// primes, 4 49.9 / 40.8; 16 primes, 7 54.1 / 46.4).  Beyond, workgroups wait for each other: n = 8192, 10 primes, 12 ciphertexts (40 halves) 23.2 / 24.2, 26 primes, 2 (52)
+// 23.5 / 25.4, n = 32768, 10 primes, 11 (40) 51.6 / 53.8, 12 primes, 10 51.6 / 54.8, 24 primes, 1 52.7 / 56.2; at n = 8192 17 to 24 primes gain as much from whole rows.
 bool decrypts_by_halves(const hcnn_ctx* c, size_t n_ct) {
-  const size_t rows = n_ct * c->k;
-  if (c->logn == 13) return kSharedAll || 2 * rows <= c->compute_units;
-  return c->logn == 15 && c->k <= 16 && (kSharedAll || 9 * rows <= 4 * (size_t)c->compute_units);
+  const size_t fullest_die = 2 * ((n_ct + kXcds - 1) / kXcds) * c->k;
+  return (c->logn == 13 || c->logn == 15) && (kSharedAll || fullest_die * kXcds <= c->compute_units);
 }
 // Work buffer of a decryption or a noise read-out: x [C][k][n] of up to 256 MiB (C ciphertexts a piece), then s_hat [k][n]
 // unless the workgroups transform the secret themselves.

@@ -136,6 +136,15 @@ def test_smallest_batch_of_the_shared_basis_relinearisation(rules, n, k, least):
     assert rules.rule_shared_basis_min(n, k, 0) == 0           # no auxiliary primes: no squarings
 
 
+@pytest.mark.parametrize("n,k,n_ct,halves", [
+    (8192, 8, 16, True), (8192, 8, 17, False), (8192, 2, 64, True), (8192, 2, 65, False), (8192, 10, 8, True), (8192, 10, 9, False), (8192, 10, 12, False),
+    (8192, 16, 1, True), (8192, 17, 1, False), (8192, 26, 2, False), (32768, 4, 28, True), (32768, 6, 16, True), (32768, 6, 17, False), (32768, 6, 18, False),
+    (32768, 10, 11, False), (32768, 12, 8, True), (32768, 12, 9, False), (32768, 16, 8, True), (32768, 24, 1, False), (4096, 4, 1, False), (16384, 8, 1, False),
+])
+def test_decryptions_by_halves_fit_the_compute_units_of_every_die(rules, n, k, n_ct, halves):
+    assert bool(rules.rule_decrypts_by_halves(256, n, k, n_ct)) == halves
+
+
 def test_two_decryption_workgroups_of_the_second_largest_ring_fit_a_compute_unit(rules):
     assert 2 * rules.rule_decrypt_lds() <= 160 * 1024
 
