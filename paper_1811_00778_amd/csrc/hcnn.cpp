@@ -1340,13 +1340,12 @@ static size_t tensor_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_
 //   where not, 297 to 340 0.89-0.97; n = 16384 128 1.0-1.04, 140 to 256 0.83-0.98 and 216 to 288 0.99-1.19, 320 0.97.  That die is counted with all primes of a
 //   ciphertext on it, as they were when this was measured; where relin_share puts half of them there, some calls fill it less than the rule has it (17 to 20
 //   ciphertexts of 12 primes: 36 workgroups counted, 30 there are) and stay with the separate kernels.
-// - Behind whole rounds half as many do, whose workgroups end beside the last of those (1.0 or less in all rings); at n = 16384 with more than 8 primes, one
-//   1024-thread workgroup to a compute unit, 80 workgroups take 1.04-1.05, 110 1.01-1.03, 160 0.96.
+// - Behind whole rounds half as many do, whose workgroups end beside the last of those (1.0 or less; n = 16384: relin_fused_takes_rest).
 constexpr uint32_t kRelinFusedMost = 512, kRelinCts = 4;      // (ciphertexts that share the inner product's loads of the key)
 static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds) {
   static constexpr uint32_t least[5] = {16, 40, 96, 192, 136};              // n = 1024 .. 16384
   const uint32_t l = least[c->logn - 10], k = c->k;
-  if (with_rounds) return c->logn == 14 && k > 8 ? 112 : l / 2;
+  if (with_rounds) return l / 2;
   if (c->logn == 12) return std::max(l, std::min(2 * k * k, kRelinFusedMost));
   if (c->logn <= 11) return std::min(std::max(l, k * k * k / 2) * (n_ct % kRelinCts == 0 ? 2 : 1), kRelinFusedMost);
   return (n_ct + kXcds - 1) / kXcds * k > c->compute_units / kXcds ? 288 : l;
@@ -1378,6 +1377,20 @@ static bool takes_tensor_fused(const hcnn_ctx* c, size_t n_ct) {
 static uint32_t relin_share(const hcnn_ctx* c) {
   const bool outgrows_l2 = (size_t)2 * c->k * c->k * c->n * 4 >= ((size_t)4 << 20);
   return outgrows_l2 && c->k % 2 == 0 ? c->k / 2 : c->k;
+}
+
+// Does the one-kernel relinearisation take all n_ct ciphertexts of a batch, or the first `whole` of them, whole rounds by the count of ciphertexts?  At n =
+// 16384, where a compute unit holds one workgroup, the rest joins if the fullest die, with its share of the limbs, goes through no more rounds for it (0.94-0.95
+// of the time of the separate kernels for the rest) or fills the last one to half (0.93-0.96; less filled 1.02-1.09): 1060 squarings.  12 primes, 39 ciphertexts 473 /
+// 529 us, 23 281 / 266; 11 primes, 55 598 / 656.
+static bool relin_fused_takes_rest(const hcnn_ctx* c, size_t n_ct, size_t whole) {
+  if (whole && c->logn == 14) {
+    const size_t share = relin_share(c), slots = relin_fused_slots(c) / kXcds;
+    auto on_die = [&](size_t cts) { return (cts * (c->k / share) + kXcds - 1) / kXcds * share; };
+    const size_t last = (on_die(n_ct) - 1) % slots + 1;
+    return (on_die(n_ct) - 1) / slots == (on_die(whole) - 1) / slots || 2 * last >= slots;
+  }
+  return (n_ct - whole) * c->k >= relin_fused_least(c, n_ct - whole, whole != 0);
 }
 
 // Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 4k, acc 4 and (largest ring only) z 4 rows an output
@@ -1492,8 +1505,8 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   auto fused_count = [&](size_t cc) -> size_t {
     if (!fused || !fused_round) return 0;
     if (c->fusion == 2) return cc;
-    const size_t whole = cc / fused_round * fused_round, rest = cc - whole;
-    return rest * k >= relin_fused_least(c, rest, whole != 0) ? cc : whole;
+    const size_t whole = cc / fused_round * fused_round;
+    return relin_fused_takes_rest(c, cc, whole) ? cc : whole;
   };
   // One internal batch: ciphertexts [c0, c0 + cc) of the call, nf of
   // them through the one-kernel relinearisation.

@@ -87,6 +87,13 @@ size_t rule_relin_fused_least(uint32_t units, uint32_t n, uint32_t k, size_t n_c
   return relin_fused_least(&c, n_ct, with_rounds);
 }
 
+// Do n_ct ciphertexts take it to the last, `whole` of which fill its rounds, with per_unit workgroups on a compute unit?
+int rule_relin_fused_takes_rest(uint32_t units, uint32_t per_unit, uint32_t n, uint32_t k, size_t n_ct, size_t whole) {
+  hcnn_ctx c;
+  c.n = n; c.logn = (uint32_t)__builtin_ctz(n); c.k = k; c.compute_units = units; c.relin_fused_wgs = per_unit;
+  return relin_fused_takes_rest(&c, n_ct, whole);
+}
+
 // Pair (one workgroup of n <= 16384) or, n = 32768, place (half of a pair) that workgroup `bid` of the one-kernel tensor takes in the order of the limbs.
 uint32_t rule_tensor_place(uint32_t split, uint32_t n_ct, uint32_t L, uint32_t bid) {
   TensorFusedArgs a{};

@@ -191,12 +191,25 @@ def test_binding_reports_the_rule_of_the_one_kernel_tensor(rules, n, least):
     (1024, 3, 7, False, 16), (1024, 3, 8, False, 32), (1024, 4, 7, False, 32), (1024, 4, 8, False, 64), (1024, 6, 9, False, 108), (1024, 6, 12, False, 216),
     (1024, 16, 8, False, 512), (2048, 4, 7, False, 40), (2048, 4, 8, False, 80), (2048, 8, 7, False, 256), (2048, 8, 8, False, 512), (2048, 32, 8, False, 512),
     (4096, 6, 8, False, 96), (4096, 9, 8, False, 162), (4096, 12, 8, False, 288), (4096, 20, 8, False, 512),
-    (1024, 8, 8, True, 8), (2048, 8, 8, True, 20), (4096, 12, 8, True, 48), (8192, 8, 8, True, 96), (16384, 8, 8, True, 68), (16384, 9, 8, True, 112),
+    (1024, 8, 8, True, 8), (2048, 8, 8, True, 20), (4096, 12, 8, True, 48), (8192, 8, 8, True, 96), (16384, 8, 8, True, 68),
     # from n = 8192 on: does the fullest die have a compute unit for each of its workgroups?
     (8192, 8, 32, False, 192), (8192, 8, 33, False, 288), (8192, 10, 24, False, 192), (8192, 10, 25, False, 288), (16384, 16, 16, False, 136), (16384, 16, 17, False, 288),
 ])
 def test_workgroups_from_which_the_one_kernel_relinearisation_is_taken(rules, n, k, n_ct, rest, least):
     assert rules.rule_relin_fused_least(256, n, k, n_ct, rest) == least
+
+
+@pytest.mark.parametrize("per_unit,n,k,n_ct,whole,takes", [
+    # n = 16384: halves of 12 limbs on a die, 32 workgroups a round; 39 and 40 ciphertexts fill the second round, 23 put four into it, 28 ten, 29 sixteen
+    (1, 16384, 12, 39, 32, True), (1, 16384, 12, 40, 32, True), (1, 16384, 12, 41, 32, False), (1, 16384, 12, 23, 16, False), (1, 16384, 12, 28, 16, False),
+    (1, 16384, 12, 29, 16, True), (1, 16384, 12, 20, 16, True), (1, 16384, 12, 21, 16, False),
+    # all 11 limbs on a die: 55 ciphertexts end in the round that 48 begin, 17 put one workgroup into a new one
+    (1, 16384, 11, 55, 48, True), (1, 16384, 11, 17, 16, False), (1, 16384, 16, 17, 16, False), (1, 16384, 16, 24, 16, True),
+    # other rings count the rest's workgroups
+    (2, 8192, 8, 75, 64, False), (2, 8192, 8, 76, 64, True), (2, 8192, 8, 24, 0, True), (2, 8192, 8, 23, 0, False),
+])
+def test_rest_behind_whole_rounds_of_the_one_kernel_relinearisation(rules, per_unit, n, k, n_ct, whole, takes):
+    assert bool(rules.rule_relin_fused_takes_rest(256, per_unit, n, k, n_ct, whole)) == takes
 
 
 @pytest.mark.parametrize("n,k,share", [(8192, 7, 7), (8192, 8, 4), (8192, 9, 9), (8192, 12, 6), (16384, 6, 3), (16384, 16, 8), (4096, 6, 6), (4096, 12, 6)])
