@@ -270,8 +270,8 @@ enum {
                                    primes).  0 (default) = chosen per internal batch: the tensor kernel for
                                    batches that fill their rounds of its workgroups to at least 7/8 or have
                                    enough of them (320 to 640, none at n = 16384), the relinearisation kernel
-                                   for as many ciphertexts as fill whole rounds and for 16 to 288 workgroups
-                                   (by the ring) more, the separate kernels for less; n = 32768 with 12
+                                   for as many ciphertexts as fill whole rounds and for 16 to 512 workgroups
+                                   (by the ring and the number of primes) more, the separate kernels for less; n = 32768 with 12
                                    primes (batches of 16 or more), 13 (5) or 18 (4) and n = 16384 with 16 or
                                    more (64) relinearise through four auxiliary primes shared by all digits
                                    instead; 1 = always the separate kernels; 2 = always the one-kernel forms

@@ -230,7 +230,8 @@ struct ScaleArgs {
 // The number of ciphertext primes is a compile-time constant (see ExtKernel), the loop over the auxiliary primes is rolled:
 // y_j is produced, used at once for the p -> q conversion (k running 64-bit sums) and parked in the LDS column for the exact
 // path, so the register footprint is 3k + O(1) and the code size does not grow with k*k'.
-// Bound: memory up to k = 8 (3 L rows read, 3 k written: 4.7 TB/s), the multiply-adds and reductions beyond.
+// Bound: up to k = 8 4.7 TB/s (3 L rows read, 3 k written) at 0.61 of the issue slots, 0.525 us per ciphertext at 64, whose rows still lie in the memory-side cache, and 0.51
+// at 1024: neither by itself (one auxiliary row of a thread is in flight); the multiply-adds and reductions beyond.
 // HALVES (n = 8192, 32768): d holds rows without the last stage of their inverse transforms (n = 32768, and calls of one or two ciphertexts; n = 8192 keeps
 // whole rows otherwise: 720 squarings 1977 us, 1993 by halves; 30 of 16 primes 271, 277).  The stage is one more product of every residue: its
 // constants carry the factor that the residue is multiplied with here (z_i directly, or the sum's term of p_j), so that it needs no
