@@ -1397,6 +1397,9 @@ static bool relin_fused_takes_rest(const hcnn_ctx* c, size_t n_ct, size_t whole)
   return (n_ct - whole) * c->k >= relin_fused_least(c, n_ct - whole, whole != 0);
 }
 
+// Ciphertexts of a batch that go to the separate kernels at most, where the one-kernel form is there: what the work buffer has room for.
+static size_t relin_split_most(const hcnn_ctx* c, size_t fused_round) { return std::min(fused_round, (size_t)kRelinFusedMost / c->k + 1); }
+
 // Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 4k, acc 4 and (largest ring only) z 4 rows an output
 // per ciphertext.
 static int relin_shared(hcnn_ctx* c, const uint32_t* y, size_t n_ct, uint32_t* dig, uint32_t* acc, uint32_t* z, uint32_t* out) {
@@ -1491,7 +1494,7 @@ static int mul_relin_impl(hcnn_ctx* c, const uint32_t* in, const uint32_t* in_b,
   if (C < 1) C = 1;
   if (C > n_ct) C = n_ct;
   // ciphertexts of one internal batch that can take the separate kernels
-  const size_t C_split = shared_min ? std::min(C, shared_min - 1) : (fused && fused_round) ? std::min(C, std::min(fused_round, (size_t)kRelinFusedMost / k + 1)) : C;
+  const size_t C_split = shared_min ? std::min(C, shared_min - 1) : (fused && fused_round) ? std::min(C, relin_split_most(c, fused_round)) : C;
   int e;
   uint32_t* ext = c->static_scratch;
   e = static_ws ? 0 : work_buffer(c, (C * words_main + std::max(C_split * words_split, shared_min ? C * words_shared : 0)) * 4, &ext);

@@ -94,6 +94,13 @@ int rule_relin_fused_takes_rest(uint32_t units, uint32_t per_unit, uint32_t n, u
   return relin_fused_takes_rest(&c, n_ct, whole);
 }
 
+// Ciphertexts for whose separate kernels the work buffer has room.
+size_t rule_relin_split_most(uint32_t k, size_t fused_round) {
+  hcnn_ctx c;
+  c.k = k;
+  return relin_split_most(&c, fused_round);
+}
+
 // Pair (one workgroup of n <= 16384) or, n = 32768, place (half of a pair) that workgroup `bid` of the one-kernel tensor takes in the order of the limbs.
 uint32_t rule_tensor_place(uint32_t split, uint32_t n_ct, uint32_t L, uint32_t bid) {
   TensorFusedArgs a{};

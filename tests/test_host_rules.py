@@ -212,6 +212,18 @@ def test_rest_behind_whole_rounds_of_the_one_kernel_relinearisation(rules, per_u
     assert bool(rules.rule_relin_fused_takes_rest(256, per_unit, n, k, n_ct, whole)) == takes
 
 
+@pytest.mark.parametrize("n,per_units", [(1024, (4, 16, 32)), (2048, (4, 8, 16)), (4096, (2, 4, 8)), (8192, (2, 3)), (16384, (1,))])
+def test_work_buffer_holds_every_batch_that_the_separate_kernels_take(rules, n, per_units):
+    """Whatever the rules leave to the separate kernels, behind no, one or three whole rounds, fits what is allocated for them."""
+    for per_unit in per_units:
+        for k in range(1, 17 if n == 16384 else 33):
+            fused_round = 256 * per_unit // 8 // k * 8
+            most = rules.rule_relin_split_most(k, fused_round)
+            for whole in (0, fused_round, 3 * fused_round):
+                left = [rest for rest in range(1, fused_round) if not rules.rule_relin_fused_takes_rest(256, per_unit, n, k, whole + rest, whole)]
+                assert not left or max(left) <= most, (per_unit, k, whole)
+
+
 @pytest.mark.parametrize("n,k,share", [(8192, 7, 7), (8192, 8, 4), (8192, 9, 9), (8192, 12, 6), (16384, 6, 3), (16384, 16, 8), (4096, 6, 6), (4096, 12, 6)])
 def test_one_kernel_relinearisation_halves_the_limbs_of_a_die(rules, n, k, share):
     assert rules.rule_relin_share(n, k) == share
