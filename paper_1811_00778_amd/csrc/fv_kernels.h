@@ -1430,9 +1430,10 @@ struct DecRoundArgs {
   const uint32_t* tab;     // [k][3]: 16-bit pieces of b_i, least significant first
   const uint32_t* cts;     // HALVES: [count][2][k][n]
   const NttLimb* limbs;    // [k]
-  uint64_t t;
+  // (in this order the compiler loads the arguments in one turn: with t in front of n and band in two, 10 decryptions, n = 8192, k = 8 16.21 / 16.36 us)
   uint32_t n;
   uint32_t band;
+  uint64_t t;
   unsigned long long* fallback_counter;
 };
 // HALVES: x holds c1*s without the last stage of its inverse transforms and without c0, both taken while loading (positions as in ScaleKernel).
