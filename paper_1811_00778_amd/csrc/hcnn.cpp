@@ -1335,8 +1335,8 @@ static size_t tensor_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_
 //   workgroups 0.84-0.95 at up to 3 primes, but 1.2 at 5 and 6 until 24, 1.05 until 64; 7 and 8 primes 1.2 until 36, 1.05 until 160; n = 2048, 36 to 40 0.88-0.99 at up
 //   to 4, 5 and 6 primes 1.05 until 64, 7 and 8 1.08 until 64, 9 to 11 1.22 at 40, 1.07 at 80, 1.05 at 350; n = 4096, 64 to 128 0.90-1.05 at up to 6, 9 to 11 1.08 at 110, 1.0
 //   from 130 on, 12 to 14 1.14 at 110, 1.02 at 180, 0.96 at 300.  Ciphertexts in fours, which the separate inner product takes in one launch: n = 1024,
-//   4 primes 1.05 at 48 and 64, 5 1.10 at 60 to 120, 7 1.13 at 56, 1.08 at 140, 6 1.06 at 360; n = 2048, 4 primes 1.07 at 48, 7 1.09 at 84, 6 1.03 at 312; n = 4096, 8 primes 1.05 at
-//   128, 0.99 at 192.
+//   4 primes 1.05 at 48 and 64, 5 1.10 at 60 to 120, 7 1.13 at 56, 1.08 at 140, 6 1.06 at 360; n = 2048, 4 primes 1.07 at 48, 7 1.09 at 84, 6 1.03 at 312; n = 4096, 5 primes 1.08 at
+//   80, 8 1.05 at 128, 0.99 at 192, 9 1.0 at 180, 12 0.92 at 384.
 // - From n = 8192 on it matters whether the fullest die has a compute unit for each of its workgroups: n = 8192 190 0.99, 208 to 240 0.91-0.96 where it has, 198 to 260 1.01-1.17
 //   where not, 297 to 340 0.89-0.97; n = 16384 128 1.0-1.04, 140 to 256 0.83-0.98 and 216 to 288 0.99-1.19, 320 0.97.  That die is counted with all primes of a
 //   ciphertext on it, as they were when this was measured; where relin_share puts half of them there, some calls fill it less than the rule has it (17 to 20
@@ -1348,9 +1348,9 @@ static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds
   const uint32_t l = least[c->logn - 10], k = c->k;
   if (with_rounds) return l / 2;
   if (c->logn <= 12) {
-    const bool fours = n_ct % kRelinCts == 0;
     const uint32_t by_primes = std::max(l, c->logn == 12 ? 2 * k * k : k * k * k / 2);
-    return std::min(!fours ? by_primes : c->logn == 12 ? by_primes * 3 / 2 : by_primes * 4, kRelinFusedMost);
+    const uint32_t fours = c->logn == 12 ? std::max(by_primes, std::min(24 * k, 192u)) : 4 * by_primes;
+    return std::min(n_ct % kRelinCts == 0 ? fours : by_primes, kRelinFusedMost);
   }
   return (n_ct + kXcds - 1) / kXcds * k > c->compute_units / kXcds ? 288 : l;
 }

@@ -190,7 +190,8 @@ def test_binding_reports_the_rule_of_the_one_kernel_tensor(rules, n, least):
     # up to n = 4096: longer workgroups of more primes, later; ciphertexts in fours later still
     (1024, 3, 7, False, 16), (1024, 3, 8, False, 64), (1024, 4, 7, False, 32), (1024, 4, 8, False, 128), (1024, 6, 9, False, 108), (1024, 6, 12, False, 432),
     (1024, 16, 7, False, 512), (1024, 16, 8, False, 512), (2048, 4, 7, False, 40), (2048, 4, 8, False, 160), (2048, 8, 7, False, 256), (2048, 32, 8, False, 512),
-    (4096, 6, 7, False, 96), (4096, 6, 8, False, 144), (4096, 9, 9, False, 162), (4096, 8, 16, False, 192), (4096, 12, 7, False, 288), (4096, 20, 7, False, 512),
+    (4096, 6, 7, False, 96), (4096, 6, 8, False, 144), (4096, 9, 9, False, 162), (4096, 8, 16, False, 192), (4096, 10, 8, False, 200), (4096, 12, 32, False, 288),
+    (4096, 3, 8, False, 96), (4096, 20, 7, False, 512), (4096, 20, 8, False, 512),
     (1024, 8, 8, True, 8), (2048, 8, 8, True, 20), (4096, 12, 8, True, 48), (8192, 8, 8, True, 96), (16384, 8, 8, True, 68),
     # from n = 8192 on: does the fullest die have a compute unit for each of its workgroups?
     (8192, 8, 32, False, 192), (8192, 8, 33, False, 288), (8192, 10, 24, False, 192), (8192, 10, 25, False, 288), (16384, 16, 16, False, 136), (16384, 16, 17, False, 288),
