@@ -1348,9 +1348,9 @@ static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds
   const uint32_t l = least[c->logn - 10], k = c->k;
   if (with_rounds) return l / 2;
   if (c->logn <= 12) {
-    const uint32_t by_primes = std::max(l, c->logn == 12 ? 2 * k * k : k * k * k / 2);
+    const uint32_t by_primes = c->logn == 12 ? 2 * k * k : k * k * k / 2;
     const uint32_t fours = c->logn == 12 ? std::max(by_primes, std::min(24 * k, 192u)) : 4 * by_primes;
-    return std::min(n_ct % kRelinCts == 0 ? fours : by_primes, kRelinFusedMost);
+    return std::max(l, std::min(n_ct % kRelinCts == 0 ? fours : by_primes, kRelinFusedMost));
   }
   return (n_ct + kXcds - 1) / kXcds * k > c->compute_units / kXcds ? 288 : l;
 }

@@ -188,8 +188,9 @@ def test_binding_reports_the_rule_of_the_one_kernel_tensor(rules, n, least):
 
 @pytest.mark.parametrize("n,k,n_ct,rest,least", [
     # up to n = 4096: longer workgroups of more primes, later; ciphertexts in fours later still
-    (1024, 3, 7, False, 16), (1024, 3, 8, False, 64), (1024, 4, 7, False, 32), (1024, 4, 8, False, 128), (1024, 6, 9, False, 108), (1024, 6, 12, False, 432),
-    (1024, 16, 7, False, 512), (1024, 16, 8, False, 512), (2048, 4, 7, False, 40), (2048, 4, 8, False, 160), (2048, 8, 7, False, 256), (2048, 32, 8, False, 512),
+    (1024, 2, 8, False, 16), (1024, 3, 7, False, 16), (1024, 3, 8, False, 52), (1024, 4, 7, False, 32), (1024, 4, 8, False, 128), (1024, 6, 9, False, 108), (1024, 6, 12, False, 432),
+    (1024, 16, 7, False, 512), (1024, 16, 8, False, 512), (2048, 1, 148, False, 40), (2048, 3, 44, False, 52),
+    (2048, 4, 7, False, 40), (2048, 4, 8, False, 128), (2048, 8, 7, False, 256), (2048, 32, 8, False, 512),
     (4096, 6, 7, False, 96), (4096, 6, 8, False, 144), (4096, 9, 9, False, 162), (4096, 8, 16, False, 192), (4096, 10, 8, False, 200), (4096, 12, 32, False, 288),
     (4096, 3, 8, False, 96), (4096, 20, 7, False, 512), (4096, 20, 8, False, 512),
     (1024, 8, 8, True, 8), (2048, 8, 8, True, 20), (4096, 12, 8, True, 48), (8192, 8, 8, True, 96), (16384, 8, 8, True, 68),
