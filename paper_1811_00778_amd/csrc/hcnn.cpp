@@ -1342,7 +1342,8 @@ static size_t tensor_fused_slots(const hcnn_ctx* c) { return (size_t)c->compute_
 //   ciphertext on it, as they were when this was measured; where relin_share puts half of them there, some calls fill it less than the rule has it (17 to 20
 //   ciphertexts of 12 primes: 36 workgroups counted, 30 there are) and stay with the separate kernels.
 // - Behind whole rounds half as many do, whose workgroups end beside the last of those (1.0 or less; n = 16384: relin_fused_takes_rest).
-constexpr uint32_t kRelinFusedMost = 512, kRelinCts = 4;      // (ciphertexts that share the inner product's loads of the key)
+constexpr uint32_t kRelinFusedMostSmall = 512, kRelinFusedMost = 288;      // the largest lines up to n = 4096 and beyond
+constexpr uint32_t kRelinCts = 4;                                          // ciphertexts that share the inner product's loads of the key
 static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds) {
   static constexpr uint32_t least[5] = {16, 40, 96, 192, 136};              // n = 1024 .. 16384
   const uint32_t l = least[c->logn - 10], k = c->k;
@@ -1350,9 +1351,9 @@ static size_t relin_fused_least(const hcnn_ctx* c, size_t n_ct, bool with_rounds
   if (c->logn <= 12) {
     const uint32_t by_primes = c->logn == 12 ? 2 * k * k : k * k * k / 2;
     const uint32_t fours = c->logn == 12 ? std::max(by_primes, std::min(24 * k, 192u)) : 4 * by_primes;
-    return std::max(l, std::min(n_ct % kRelinCts == 0 ? fours : by_primes, kRelinFusedMost));
+    return std::max(l, std::min(n_ct % kRelinCts == 0 ? fours : by_primes, kRelinFusedMostSmall));
   }
-  return (n_ct + kXcds - 1) / kXcds * k > c->compute_units / kXcds ? 288 : l;
+  return (n_ct + kXcds - 1) / kXcds * k > c->compute_units / kXcds ? kRelinFusedMost : l;
 }
 // Workgroups from which the one-kernel tensor is taken however its rounds are filled (the same measurements: with it / with two kernels, n =
 // 1024 from 448 0.95-1.0, n = 2048 from 640 0.9-1.03, n = 4096 from 320 0.88-1.01, n = 8192 from 384 0.94-1.01, n = 32768 from 320 0.93-1.02; n = 16384, 0.95-1.05
@@ -1398,7 +1399,9 @@ static bool relin_fused_takes_rest(const hcnn_ctx* c, size_t n_ct, size_t whole)
 }
 
 // Ciphertexts of a batch that go to the separate kernels at most, where the one-kernel form is there: what the work buffer has room for.
-static size_t relin_split_most(const hcnn_ctx* c, size_t fused_round) { return std::min(fused_round, (size_t)kRelinFusedMost / c->k + 1); }
+static size_t relin_split_most(const hcnn_ctx* c, size_t fused_round) {
+  return std::min(fused_round, (size_t)(c->logn <= 12 ? kRelinFusedMostSmall : kRelinFusedMost) / c->k + 1);
+}
 
 // Steps 6-8 through the shared basis (fv_kernels.h): y [n_ct][3][k][n] -> out; dig 4k, acc 4 and (largest ring only) z 4 rows an output
 // per ciphertext.

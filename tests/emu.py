@@ -74,7 +74,7 @@ def rules():
         lib.rule_tensor_fused_least.argtypes, lib.rule_tensor_fused_least.restype = [ctypes.c_uint32], ctypes.c_size_t
         lib.rule_relin_fused_least.argtypes, lib.rule_relin_fused_least.restype = [ctypes.c_uint32] * 3 + [ctypes.c_size_t, ctypes.c_int], ctypes.c_size_t
         lib.rule_relin_fused_takes_rest.argtypes = [ctypes.c_uint32] * 4 + [ctypes.c_size_t] * 2
-        lib.rule_relin_split_most.argtypes, lib.rule_relin_split_most.restype = [ctypes.c_uint32, ctypes.c_size_t], ctypes.c_size_t
+        lib.rule_relin_split_most.argtypes, lib.rule_relin_split_most.restype = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_size_t], ctypes.c_size_t
         lib.rule_splits_tensor_rows.argtypes = [ctypes.c_uint32] * 2 + [ctypes.c_size_t]
         lib.rule_decrypts_by_halves.argtypes = [ctypes.c_uint32] * 3 + [ctypes.c_size_t]
         lib.rule_decrypt_lds.restype = ctypes.c_size_t

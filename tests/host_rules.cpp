@@ -95,9 +95,9 @@ int rule_relin_fused_takes_rest(uint32_t units, uint32_t per_unit, uint32_t n, u
 }
 
 // Ciphertexts for whose separate kernels the work buffer has room.
-size_t rule_relin_split_most(uint32_t k, size_t fused_round) {
+size_t rule_relin_split_most(uint32_t n, uint32_t k, size_t fused_round) {
   hcnn_ctx c;
-  c.k = k;
+  c.logn = (uint32_t)__builtin_ctz(n); c.k = k;
   return relin_split_most(&c, fused_round);
 }
 

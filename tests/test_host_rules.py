@@ -220,7 +220,7 @@ def test_work_buffer_holds_every_batch_that_the_separate_kernels_take(rules, n, 
     for per_unit in per_units:
         for k in range(1, 17 if n == 16384 else 33):
             fused_round = 256 * per_unit // 8 // k * 8
-            most = rules.rule_relin_split_most(k, fused_round)
+            most = rules.rule_relin_split_most(n, k, fused_round)
             for whole in (0, fused_round, 3 * fused_round):
                 left = [rest for rest in range(1, fused_round) if not rules.rule_relin_fused_takes_rest(256, per_unit, n, k, whole + rest, whole)]
                 assert not left or max(left) <= most, (per_unit, k, whole)
